@@ -73,6 +73,8 @@ struct DevSim {
     int32_t width, height, n_cams;
     int32_t road_color_uniform;   // 1 if every road strip has the colour road_color0
     int32_t road_color0;
+    const uint32_t *box_rgb;  // [A + S] palette colour of each box (byte 0 red)
+    uint32_t road_rgb, bg_rgb;    // colours of road_color0 and of the background
     float road_zmax;          // no pixel sample sees the road plane beyond this depth
     uint8_t *halted;          // [A] 1 once the agent committed an infraction (frozen in place)
     uint8_t *infr;            // [A] infractions found by the last check (bit 0 collision, 1 off-road)
@@ -108,7 +110,7 @@ struct LaunchCfg {
 // Settings of the wave-split rgb raster (gp_raster.hip).
 struct RgbCfg {
     int waves;        // wavefronts per view: 1, 2 or 4
-    int bcap;         // box triangles one view's list holds
+    int bcap;         // box faces one view's list holds: 64, 128 or 256
     int bins_cap;     // culling bins of the largest scene (surviving bins are listed in LDS)
 };
 

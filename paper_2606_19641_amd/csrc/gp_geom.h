@@ -537,9 +537,11 @@ __device__ __forceinline__ Prim prim_of(const TriGeo &t)
 // The quad of snapped corners X[k], Y[k] when it may replace its two fan
 // triangles (see above; also below 2^25 subpixels, the fp64 span range):
 // returns 1 with q set (positively oriented, rows [j0, j1] within [r0, r1)),
-// 0 if it covers no sample (bounding box without a sample), -1 when the
-// triangles must be used.
-__device__ __forceinline__ int make_quad(const Cam &c, const int32_t *X, const int32_t *Y, int r0, int r1, Prim &q)
+// 0 if it covers no sample (bounding box without a sample, or, one-sided, the
+// back of the face: a strictly convex quad turns the way both its triangles
+// do), -1 when the triangles must be used.
+__device__ __forceinline__ int make_quad(const Cam &c, bool one_sided, const int32_t *X, const int32_t *Y, int r0, int r1,
+                                         Prim &q)
 {
     const int32_t lim = 1 << 25;
     int32_t xmin = X[0], xmax = X[0], ymin = Y[0], ymax = Y[0];
@@ -564,6 +566,7 @@ __device__ __forceinline__ int make_quad(const Cam &c, const int32_t *X, const i
         nneg += cr < 0;
     }
     if (!(npos == 4 || nneg == 4)) return -1;
+    if (one_sided && npos == 4) return 0;      // front faces are negative in y-down screen space
     const int i0 = max((xmin - 128 + 255) >> 8, 0), i1 = min((xmax - 128) >> 8, c.W - 1);
     const int j0 = max((ymin - 128 + 255) >> 8, r0), j1 = min((ymax - 128) >> 8, r1 - 1);
     if (i0 > i1 || j0 > j1) return 0;
@@ -681,6 +684,48 @@ static_assert(kBinQuads < 128, "bin count packs into 7 bits");
 constexpr int kMaxVerts = 12;
 constexpr int kMaxTrisPerCand = kMaxVerts - 2;
 
+// One entry of a view's box list in the rgb rasters: a box face as one quad
+// where its quad covers exactly what its two fan triangles cover (above: the
+// fragments are the same too, since both triangles carry the face's plane and
+// key), else a triangle; its depth plane, key word and colour.
+struct FaceRec {
+    int32_t X0, Y0, X1, Y1, X2, Y2, X3, Y3;
+    float A, B, C;
+    uint32_t keylo;
+    int16_t j0, j1;
+    int16_t huge, nv;
+    uint32_t rgb;
+    int32_t pad;
+};
+static_assert(sizeof(FaceRec) == 64 && offsetof(FaceRec, A) == 32 && offsetof(FaceRec, j0) == 48, "FaceRec layout");
+
+__device__ __forceinline__ void face_geo(FaceRec &f, const Prim &p)
+{
+    f.X0 = p.X0; f.Y0 = p.Y0; f.X1 = p.X1; f.Y1 = p.Y1; f.X2 = p.X2; f.Y2 = p.Y2; f.X3 = p.X3; f.Y3 = p.Y3;
+    f.j0 = p.j0; f.j1 = p.j1; f.huge = p.huge; f.nv = p.nv;
+}
+
+__device__ __forceinline__ FaceRec face_of(const TriRec &t, uint32_t rgb)
+{
+    FaceRec f;
+    face_geo(f, prim_of(t.g));
+    f.A = t.A; f.B = t.B; f.C = t.C; f.keylo = t.keylo;
+    f.rgb = rgb;
+    f.pad = 0;
+    return f;
+}
+
+// the geometry of a listed face (the plane and key are read apart)
+__device__ __forceinline__ Prim lds_face_prim(lptr<const FaceRec> f)
+{
+    union { Prim p; gp_v4i v[3]; } u;
+    lptr<const gp_v4i> q = (lptr<const gp_v4i>)f;
+    u.v[0] = q[0];
+    u.v[1] = q[1];
+    u.v[2] = q[3];            // j0, j1, huge, nv lie at the same place of both records' last 16 bytes
+    return u.p;
+}
+
 // the low 16 bits of x moved to the even bit positions
 __device__ __forceinline__ uint32_t spread_bits(uint32_t x)
 {
@@ -738,6 +783,38 @@ __device__ __forceinline__ void fast_poly(const Cam &cam, const Poly &P, int r0,
         const Plane pl = face_plane(cam, P.n, d);
         t0.A = pl.A; t0.B = pl.B; t0.C = pl.C; t0.keylo = P.keylo;
         t1.A = pl.A; t1.B = pl.B; t1.C = pl.C; t1.keylo = P.keylo;
+    }
+}
+
+// The same for one box face of the rgb rasters: one entry (v0: f0) when the
+// quad may stand for its two triangles, else the triangles (v0: f0, v1: f1).
+__device__ __forceinline__ void fast_face(const Cam &cam, const Poly &P, uint32_t rgb, int r0, int r1, FaceRec &f0,
+                                          bool &v0, FaceRec &f1, bool &v1, bool &clip)
+{
+    if (outside(cam, P.v)) return;
+    const float d = plane_d(P.n, P.v[0]);
+    if (!(d < 0.0f)) return;
+    clip = needs_clip(cam, P.v);
+    if (clip) return;
+    int32_t X[4], Y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) snap(cam, P.v[k], X[k], Y[k]);
+    Prim p0 = {}, p1 = {};
+    const int qs = make_quad(cam, true, X, Y, r0, r1, p0);
+    v0 = qs > 0;
+    if (qs < 0) {
+        TriGeo t0, t1;
+        v0 = make_tri(cam, true, X[0], Y[0], X[1], Y[1], X[2], Y[2], r0, r1, t0);
+        v1 = make_tri(cam, true, X[0], Y[0], X[2], Y[2], X[3], Y[3], r0, r1, t1);
+        if (v0) p0 = prim_of(t0);
+        if (v1) p1 = prim_of(t1);
+    }
+    if (v0 || v1) {
+        const Plane pl = face_plane(cam, P.n, d);
+        face_geo(f0, p0);
+        face_geo(f1, p1);
+        f0.A = pl.A; f0.B = pl.B; f0.C = pl.C; f0.keylo = P.keylo; f0.rgb = rgb; f0.pad = 0;
+        f1.A = pl.A; f1.B = pl.B; f1.C = pl.C; f1.keylo = P.keylo; f1.rgb = rgb; f1.pad = 0;
     }
 }
 

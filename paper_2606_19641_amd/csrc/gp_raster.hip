@@ -61,15 +61,15 @@ constexpr int kBoxClip = 64;     // box faces waiting for the clipper (one setup
 
 struct RgbLds {
     lptr<int32_t> cnt;               // [R_NCNT]
-    lptr<uint32_t> pal;              // [256] RGB of each palette entry
     lptr<uint32_t> lut;              // [16][4] four-pixel road/background patterns, 3 packed dwords
     lptr<unsigned long long> bits;   // [H][nw] road coverage, bit i of word w: column 64 w + i
-    lptr<TriRec> btris;              // [bcap] the view's box triangles
+    lptr<FaceRec> faces;             // [bcap] the view's box faces
     lptr<int32_t> sbins;             // [bins_cap] surviving bins: start * 128 + count
     lptr<int32_t> cq;                // [kBoxClip] box faces to clip (box * 8 + face)
     lptr<int32_t> sring;             // [kSharedRing] strips that passed the cheap test (this round)
     lptr<unsigned char> waves;       // K regions of kWaveBytes
     int nw, bcap, krows;
+    int nmw;                         // 64-bit words of a face mask (bcap / 64)
     int region;                      // bytes from sbins to the end (free after the units)
 };
 
@@ -77,7 +77,7 @@ __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t
 
 // byte offsets of the LDS sections (shared by the carve and the size query)
 struct RgbLayout {
-    size_t cnt, pal, lut, bits, btris, sbins, cq, sring, waves, total;
+    size_t cnt, lut, bits, faces, sbins, cq, sring, waves, total;
 };
 
 __host__ __device__ inline RgbLayout rgb_layout(int W, int H, const RgbCfg &c)
@@ -86,14 +86,15 @@ __host__ __device__ inline RgbLayout rgb_layout(int W, int H, const RgbCfg &c)
     const size_t nw = (size_t)(W + 63) / 64;
     size_t o = 0;
     l.cnt = o; o = align16(o + 4 * R_NCNT);
-    l.pal = o; o = align16(o + 4 * 256);
     l.lut = o; o = align16(o + 4 * 64);
     l.bits = o; o = align16(o + 8 * nw * (size_t)H);
-    l.btris = o; o = align16(o + sizeof(TriRec) * (size_t)c.bcap);
+    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
     l.cq = o; o = align16(o + 4 * (size_t)kBoxClip);
     l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
     l.sring = o; o = align16(o + 4 * (size_t)kSharedRing);
     l.waves = o; o = align16(o + (size_t)kWaveBytes * (size_t)c.waves);
+    // the region from sbins on holds a row of keys, or of masks and spans
+    o = o > l.sbins + 8 * (size_t)W ? o : align16(l.sbins + 8 * (size_t)W);
     l.total = o;
     return l;
 }
@@ -244,7 +245,7 @@ __device__ __forceinline__ int road_setup(const DevSim &s, const Cam &cam, const
 #pragma unroll
         for (int k = 0; k < 4; ++k) snap(cam, v[k], X[k], Y[k]);
         // one quad where it covers exactly what the two fan triangles cover
-        const int qs = make_quad(cam, X, Y, 0, cam.H, p0);
+        const int qs = make_quad(cam, false, X, Y, 0, cam.H, p0);
         v0 = qs > 0;
         fan = qs < 0;
     }
@@ -335,11 +336,12 @@ __device__ __forceinline__ int box_reserve(const RgbLds &L, bool shared, int &nb
 
 // One setup pass over box face candidates [c0, c0 + P) (P <= 64): candidate c
 // is face c % 6 of box surv[c / 6] (use_surv), or of box c / 6 culled here.
-// Fast triangles and clipped faces (clip queue cq) are appended to the box
-// list (box_reserve); returns false as soon as the triangles would not fit
-// (the list is then incomplete: the view takes the overflow path, which
-// ignores it).  Eight candidates at a time never overflow a private list of
-// 96 (at most 10 triangles each).
+// Fast faces and the triangles of clipped faces (clip queue cq) are appended
+// to the box list (box_reserve), the low byte of each key word naming the
+// entry; returns false as soon as they would not fit (the list is then
+// incomplete: the view takes the overflow path, which ignores it).  Six
+// candidates at a time never overflow a private list of 64 (at most 10
+// triangles each).
 __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
                          lptr<const int32_t> surv, bool use_surv, int ncand, int c0, int P, lptr<int32_t> cq,
                          bool shared, int &nbt, int &bmin, int &bmax)
@@ -354,20 +356,30 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
         if (!use_surv) live = j != ego && !box_outside(s, sc, cam, j);
     }
     Poly Pf;
-    TriRec t0, t1;
+    FaceRec f0, f1;
     bool v0 = false, v1 = false, clip = false;
     if (live) {
         build_face(s, sc, cam, j, f, Pf);
-        fast_poly<true>(cam, Pf, 0, cam.H, t0, v0, t1, v1, clip);
+        fast_face(cam, Pf, s.box_rgb[box_slot(sc, j)], 0, cam.H, f0, v0, f1, v1, clip);
     }
     const unsigned long long b0 = __ballot(v0), b1 = __ballot(v1), bc = __ballot(clip);
     const int n0 = __popcll(b0), nf = n0 + __popcll(b1), ncl = __popcll(bc);
     const int at = box_reserve(L, shared, nbt, nf);
     if (at < 0) return false;
-    if (v0) lds_store(L.btris + at + lanes_below(b0), t0);
-    if (v1) lds_store(L.btris + at + n0 + lanes_below(b1), t1);
-    if (v0) { bmin = min(bmin, (int)t0.g.j0); bmax = max(bmax, (int)t0.g.j1); }
-    if (v1) { bmin = min(bmin, (int)t1.g.j0); bmax = max(bmax, (int)t1.g.j1); }
+    if (v0) {
+        const int t = at + lanes_below(b0);
+        f0.keylo = (f0.keylo & ~0xFFu) | (uint32_t)t;
+        lds_store(L.faces + t, f0);
+        bmin = min(bmin, (int)f0.j0);
+        bmax = max(bmax, (int)f0.j1);
+    }
+    if (v1) {
+        const int t = at + n0 + lanes_below(b1);
+        f1.keylo = (f1.keylo & ~0xFFu) | (uint32_t)t;
+        lds_store(L.faces + t, f1);
+        bmin = min(bmin, (int)f1.j0);
+        bmax = max(bmax, (int)f1.j1);
+    }
     if (clip) cq[lanes_below(bc)] = j * 8 + f;
     wave_lds_order();
     // the clipped faces, four per wavefront
@@ -375,9 +387,11 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
         const int q = q0 + (ln >> 4);
         const bool lv = q < ncl;
         Poly Q = {};
+        uint32_t rgb = 0u;
         if (lv) {
             const int code = cq[q];
             build_face(s, sc, cam, code >> 3, code & 7, Q);
+            rgb = s.box_rgb[box_slot(sc, code >> 3)];
         }
         TriRec t;
         const bool ok = clip_seg<true>(cam, Q, lv, 0, cam.H, t);
@@ -385,7 +399,9 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
         const int ato = box_reserve(L, shared, nbt, __popcll(bo));
         if (ato < 0) return false;
         if (ok) {
-            lds_store(L.btris + ato + lanes_below(bo), t);
+            const int e = ato + lanes_below(bo);
+            t.keylo = (t.keylo & ~0xFFu) | (uint32_t)e;
+            lds_store(L.faces + e, face_of(t, rgb));
             bmin = min(bmin, (int)t.g.j0);
             bmax = max(bmax, (int)t.g.j1);
         }
@@ -394,7 +410,7 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
 }
 
 // Box unit k: cull boxes [kBoxUnit k, kBoxUnit (k + 1)) of the scene, list
-// the survivors, set up their faces into the view's box triangle list
+// the survivors, set up their faces into the view's box list
 // (shared by the wavefronts; its row range kept with LDS min / max).  scr:
 // 128 ints of the wavefront's staging (survivors, then the clip queue).
 constexpr int kBoxUnit = 16;
@@ -420,8 +436,10 @@ __device__ __forceinline__ void do_boxes(const DevSim &s, const SceneRec &sc, co
     }
 }
 
-// Box fragments of the list's n triangles in rows [b0, b1) folded into the
-// key band.  The (triangle, row) items are dealt to the lanes by a prefix
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+// Box fragments of the list's n faces in rows [b0, b1) folded into the
+// key band.  The (face, row) items are dealt to the lanes by a prefix
 // over row counts, item passes shared out over the view's wavefronts (wave w
 // of nw takes passes w, w + nw, ...); each lane computes its item's exact
 // span; the spans are cut into pieces of up to 16 samples, which are dealt to
@@ -437,7 +455,7 @@ __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<u
         const int t = t0 + ln;
         int c = 0;
         if (t < n) {
-            const int32_t jj = ((lptr<const int32_t>)(L.btris + t))[6];
+            const int32_t jj = ((lptr<const int32_t>)(L.faces + t))[12];
             const int j0 = max((int)(int16_t)(jj & 0xFFFF), b0), j1 = min(jj >> 16, b1 - 1);
             c = max(0, j1 - j0 + 1);
         }
@@ -453,10 +471,11 @@ __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<u
             float A = 0.0f, B = 0.0f, Cc = 0.0f;
             uint32_t key = 0u;
             if (gi < total) {
-                const TriRec tr = lds_load(L.btris + t0 + o);
-                j = max((int)tr.g.j0, b0) + (gi - ex);
-                if (!row_span(tr.g, j, W, xl, xr)) { xl = 0; xr = -1; }
-                A = tr.A; B = tr.B; Cc = tr.C; key = tr.keylo;
+                const Prim pr = lds_face_prim((lptr<const FaceRec>)(L.faces + t0 + o));
+                j = max((int)pr.j0, b0) + (gi - ex);
+                if (!prim_span(pr, j, W, xl, xr)) { xl = 0; xr = -1; }
+                const f4v pk = ((lptr<const f4v>)(L.faces + t0 + o))[2];
+                A = pk.x; B = pk.y; Cc = pk.z; key = __float_as_uint(pk.w);
             }
             const int np = (xr - xl + 16) >> 4;            // pieces of up to 16 samples (0 if empty)
             const int inc2 = wave_incl_scan(np);
@@ -485,31 +504,29 @@ __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<u
 // ------------------------------------------------------------ box rows by group masks
 //
 // The box rows [c0, c1) without a key band: the exact span of every (box
-// triangle, row) item is computed once and stored, and every group of 16
-// samples of a row gets a mask of the triangles whose span meets it.  The
-// resolve then walks, for its 16 samples, the triangles of its group's mask
-// and keeps the largest key of each sample in registers.  Memory (the free
-// region): the masks M[c1 - c0][W / 16][2], then the spans S[t][c1 - c0].
-constexpr int kMaskTris = 128;     // triangles a mask holds (two 64-bit words)
-
-__host__ __device__ inline int mask_rows_fit(int region, int n, int W)
+// face, row) item is computed once and stored, and every group of 16 samples
+// of a row gets a mask of the faces whose span meets it.  The resolve then
+// walks, for its 16 samples, the faces of its group's mask and keeps the
+// largest key of each sample in registers.  Memory (the free region): the
+// masks M[c1 - c0][W / 16][nmw], then the spans S[t][c1 - c0].
+__host__ __device__ inline int mask_rows_fit(int region, int n, int W, int nmw)
 {
-    // rows per chunk so that the masks and a span of every triangle in every row fit
-    return region / (16 * (W / 16) + 4 * n);
+    // rows per chunk so that the masks and a span of every face in every row fit
+    return region / (8 * nmw * (W / 16) + 4 * n);
 }
 
 __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n, int c0, int c1, int wv, int nwv)
 {
     const int ln = (int)lane_id();
-    const int R = c1 - c0, G = cam.W >> 4;
+    const int R = c1 - c0, G = cam.W >> 4, nmw = L.nmw;
     lptr<unsigned long long> M = (lptr<unsigned long long>)L.sbins;
-    lptr<int32_t> S = (lptr<int32_t>)(M + 2 * G * R);
+    lptr<int32_t> S = (lptr<int32_t>)(M + nmw * G * R);
     int pass = 0;
     for (int t0 = 0; t0 < n; t0 += 64) {
         const int t = t0 + ln;
         int c = 0;
         if (t < n) {
-            const int32_t jj = ((lptr<const int32_t>)(L.btris + t))[6];
+            const int32_t jj = ((lptr<const int32_t>)(L.faces + t))[12];
             const int j0c = max((int)(int16_t)(jj & 0xFFFF), c0);
             c = max(0, min(jj >> 16, c1 - 1) - j0c + 1);
         }
@@ -523,14 +540,14 @@ __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n
             const int ex = __shfl(excl, o);
             if (gi < total) {
                 const int tt = t0 + o;
-                const TriGeo tg = lds_load((lptr<TriGeo>)(L.btris + tt));
-                const int j = max((int)tg.j0, c0) + (gi - ex);
+                const Prim pr = lds_face_prim((lptr<const FaceRec>)(L.faces + tt));
+                const int j = max((int)pr.j0, c0) + (gi - ex);
                 int xl, xr;
-                if (row_span(tg, j, cam.W, xl, xr)) {
+                if (prim_span(pr, j, cam.W, xl, xr)) {
                     S[tt * R + (j - c0)] = xl | (xr << 16);
-                    lptr<unsigned long long> mrow = M + 2 * G * (j - c0) + (tt >> 6);
+                    lptr<unsigned long long> mrow = M + nmw * G * (j - c0) + (tt >> 6);
                     const unsigned long long bit = 1ull << (tt & 63);
-                    for (int g = xl >> 4; g <= (xr >> 4); ++g) lds_or64(mrow + 2 * g, bit);
+                    for (int g = xl >> 4; g <= (xr >> 4); ++g) lds_or64(mrow + nmw * g, bit);
                 }
             }
         }
@@ -543,10 +560,9 @@ __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n
 __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, uint8_t *img, uint32_t road_rgb,
                                               uint32_t bg_rgb, int c0, int c1, int wv, int nwv)
 {
-    typedef float f4v __attribute__((ext_vector_type(4)));
-    const int R = c1 - c0, G = cam.W >> 4;
+    const int R = c1 - c0, G = cam.W >> 4, nmw = L.nmw;
     lptr<const unsigned long long> M = (lptr<const unsigned long long>)L.sbins;
-    lptr<const int32_t> S = (lptr<const int32_t>)(M + 2 * G * R);
+    lptr<const int32_t> S = (lptr<const int32_t>)(M + nmw * G * R);
     const int W = cam.W;
     const int n = R * G;
     const int ln = (int)lane_id();
@@ -564,15 +580,14 @@ __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, u
         unsigned long long best[16];
 #pragma unroll
         for (int m = 0; m < 16; ++m) best[m] = 0ull;
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            unsigned long long mk = M[2 * (G * r + g) + w];
+        for (int w = 0; w < nmw; ++w) {
+            unsigned long long mk = M[nmw * (G * r + g) + w];
             while (mk != 0ull) {
                 const int t = 64 * w + (__ffsll((long long)mk) - 1);
                 mk &= mk - 1ull;
                 // span and plane read together (both depend on t only)
                 const int sp = S[t * R + r];
-                const f4v pk = *(lptr<const f4v>)((lptr<const unsigned char>)(L.btris + t) + 32);   // A B C keylo
+                const f4v pk = ((lptr<const f4v>)(L.faces + t))[2];   // A B C keylo
                 // the span's samples within this group as a bit mask
                 const int lo = max((sp & 0xFFFF) - i, 0), hi = min((sp >> 16) - i, 15);
                 const uint32_t in = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
@@ -595,7 +610,8 @@ __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, u
             const unsigned long long kb = best[m];
             const bool road = (bits >> m) & 1u;
             const bool box = (kb != 0ull) & (!road | ((uint32_t)(kb >> 32) >= rzb));
-            const uint32_t boxc = L.pal[(uint32_t)kb & 0xFFu];   // any index is a palette entry
+            // the key's low byte names the list entry (entry 0 without a key: read, not used)
+            const uint32_t boxc = ((lptr<const uint32_t>)(L.faces + ((uint32_t)kb & 0xFFu)))[14];
             c[m] = box ? boxc : (road ? road_rgb : bg_rgb);
         }
         store16(img + 3 * ((int64_t)j * W + i), c);
@@ -647,8 +663,9 @@ __device__ __forceinline__ void resolve_lut(const RgbLds &L, const Cam &cam, uin
 // rows [b0, b1) of the key band: a box fragment wins where its 1/z is not
 // below the road's (agents rank above roads on equal depth); otherwise road
 // or background by the coverage bit
-__device__ __forceinline__ void resolve_band(const RgbLds &L, const Cam &cam, lptr<unsigned long long> keys, uint8_t *img,
-                             uint32_t road_rgb, uint32_t bg_rgb, int b0, int b1)
+__device__ __forceinline__ void resolve_band(const DevSim &s, const SceneRec &sc, const RgbLds &L, const Cam &cam,
+                                             lptr<unsigned long long> keys, uint8_t *img, uint32_t road_rgb,
+                                             uint32_t bg_rgb, int b0, int b1)
 {
     const int W = cam.W, gpr = W >> 4;
     const int n = (b1 - b0) * gpr;
@@ -666,8 +683,10 @@ __device__ __forceinline__ void resolve_band(const RgbLds &L, const Cam &cam, lp
             const unsigned long long kb = kp[m];
             const bool road = (bits >> m) & 1u;
             const bool box = (kb != 0ull) & (!road | ((uint32_t)(kb >> 32) >= rzb));
-            const uint32_t boxc = L.pal[(uint32_t)kb & 0xFFu];   // any index is a palette entry
-            c[m] = box ? boxc : (road ? road_rgb : bg_rgb);
+            uint32_t v = road ? road_rgb : bg_rgb;
+            // the box list was streamed: the colour comes from the key's box
+            if (box) v = s.box_rgb[box_slot(sc, ((kMaxPrims - 1) - (int)(((uint32_t)kb >> 8) & (uint32_t)(kMaxPrims - 1))) / 6)];
+            c[m] = v;
         }
         u4 *out = reinterpret_cast<u4 *>(img + 3 * ((int64_t)j * W + i));
 #pragma unroll
@@ -690,14 +709,13 @@ __device__ __forceinline__ void resolve_band(const RgbLds &L, const Cam &cam, lp
     }
 }
 
-// Box rows [kr0, kr1) through bands of 64-bit keys (the whole workgroup; the
-// region from the surviving-bin list on is free): the view's box triangle
-// list, or, if it overflowed (ovf), the box faces streamed through it eight
-// candidates at a time (at most 96 triangles per pass) with the boxes culled
-// again.  wv / nwv: this wavefront among the workgroup's.
+// Rows [kr0, kr1) of a view whose box list overflowed, through bands of
+// 64-bit keys (the whole workgroup; the region from the surviving-bin list on
+// is free): the box faces streamed through the list six candidates at a time
+// (at most 60 entries per pass) with the boxes culled again.  wv: this
+// wavefront among the workgroup's.
 __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                                              uint8_t *img, uint32_t road_rgb, uint32_t bg_rgb, int kr0, int kr1, bool ovf,
-                                              int nbt, int wv, int nwv)
+                                              uint8_t *img, uint32_t road_rgb, uint32_t bg_rgb, int kr0, int kr1, int wv)
 {
     const int W = cam.W;
     lptr<unsigned long long> keys = (lptr<unsigned long long>)L.sbins;
@@ -706,13 +724,11 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
         __syncthreads();
         for (int p = (int)threadIdx.x; p < (b1 - b0) * W; p += (int)blockDim.x) keys[p] = 0ull;
         __syncthreads();
-        if (!ovf) {
-            box_band(L, cam, keys, nbt, wv, nwv, b0, b1);
-        } else if (wv == 0) {
+        if (wv == 0) {
             const int ncand = 6 * (sc.n_agents + sc.n_static);
-            for (int c0 = 0; c0 < ncand; c0 += 8) {
+            for (int c0 = 0; c0 < ncand; c0 += 6) {
                 int n = 0, bmn = 0, bmx = 0;
-                (void)box_pass(s, sc, cam, ego, L, (lptr<const int32_t>)L.sbins, false, ncand, c0, 8, L.cq, false, n, bmn,
+                (void)box_pass(s, sc, cam, ego, L, (lptr<const int32_t>)L.sbins, false, ncand, c0, 6, L.cq, false, n, bmn,
                                bmx);
                 wave_lds_order();
                 box_band(L, cam, keys, n, 0, 1, b0, b1);
@@ -720,7 +736,7 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
             }
         }
         __syncthreads();
-        resolve_band(L, cam, keys, img, road_rgb, bg_rgb, b0, b1);
+        resolve_band(s, sc, L, cam, keys, img, road_rgb, bg_rgb, b0, b1);
     }
 }
 
@@ -896,9 +912,9 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
     }
     // the box rows are the costly part of the resolve (a mean view has about a dozen)
     view_priority(max(prio_b, kr1 - kr0 >= 64 ? 3 : (kr1 - kr0 >= 32 ? 2 : 0)));
-    const uint32_t road_rgb = L.pal[s.road_color0], bg_rgb = L.pal[0];
-    const int mrows = mask_rows_fit(L.region, nbt, W);
-    if (!ovf && nbt <= kMaskTris && mrows >= 1 && kr0 < kr1) {
+    const uint32_t road_rgb = s.road_rgb, bg_rgb = s.bg_rgb;
+    const int mrows = max(1, mask_rows_fit(L.region, nbt, W, L.nmw));
+    if (!ovf && kr0 < kr1) {
         // box rows through row masks, in chunks of rows whose items fit; the
         // rows outside them (the pattern table: coverage bits and table only)
         // go with the first chunk's spans (which write the free region only)
@@ -906,7 +922,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
             const int c1 = min(c0 + mrows, kr1);
             if (c0 != kr0) __syncthreads();
             lptr<unsigned long long> M = (lptr<unsigned long long>)L.sbins;
-            for (int p = tid; p < 2 * (W >> 4) * (c1 - c0); p += B) M[p] = 0ull;
+            for (int p = tid; p < L.nmw * (W >> 4) * (c1 - c0); p += B) M[p] = 0ull;
             __syncthreads();
             if (c0 == kr0) {
                 resolve_lut(L, cam, img, 0, kr0);
@@ -920,39 +936,34 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
     }
     resolve_lut(L, cam, img, 0, kr0);
     resolve_lut(L, cam, img, kr1, H);
-    if (kr0 < kr1) key_band_rows(s, sc, cam, ego, L, img, road_rgb, bg_rgb, kr0, kr1, ovf, nbt, wv, K);
+    if (ovf) key_band_rows(s, sc, cam, ego, L, img, road_rgb, bg_rgb, kr0, kr1, wv);
 }
 
 __device__ __forceinline__ void carve_rgb(unsigned char *smem, RgbLds &L, int W, int H, const RgbCfg &c)
 {
     const RgbLayout l = rgb_layout(W, H, c);
     L.cnt = (lptr<int32_t>)(smem + l.cnt);
-    L.pal = (lptr<uint32_t>)(smem + l.pal);
     L.lut = (lptr<uint32_t>)(smem + l.lut);
     L.bits = (lptr<unsigned long long>)(smem + l.bits);
-    L.btris = (lptr<TriRec>)(smem + l.btris);
+    L.faces = (lptr<FaceRec>)(smem + l.faces);
     L.sbins = (lptr<int32_t>)(smem + l.sbins);
     L.cq = (lptr<int32_t>)(smem + l.cq);
     L.sring = (lptr<int32_t>)(smem + l.sring);
     L.waves = (lptr<unsigned char>)(smem + l.waves);
     L.nw = (W + 63) >> 6;
     L.bcap = c.bcap;
+    L.nmw = c.bcap >> 6;
     // the key band takes the surviving-bin list, the box clip queue and the
     // waves' staging, all idle by then
     L.region = (int)(l.total - l.sbins);
     L.krows = max(1, L.region / (8 * W));
 }
 
-__device__ __forceinline__ void load_palette_rgb(const DevSim &s, const RgbLds &L)
+__device__ __forceinline__ void load_patterns(const DevSim &s, const RgbLds &L)
 {
-    auto rgb_of = [&](int idx) -> uint32_t {
-        return (uint32_t)s.palette[3 * idx] | ((uint32_t)s.palette[3 * idx + 1] << 8) |
-               ((uint32_t)s.palette[3 * idx + 2] << 16);
-    };
-    for (int p = threadIdx.x; p < 256; p += blockDim.x) L.pal[p] = rgb_of(p);
     if (threadIdx.x < 16) {
         // pattern b: pixel k is road where bit k of b is set, background elsewhere
-        const uint32_t road = rgb_of(s.road_color0), bg = rgb_of(0);
+        const uint32_t road = s.road_rgb, bg = s.bg_rgb;
         const int b = threadIdx.x;
         const uint32_t c0 = (b & 1) ? road : bg, c1 = (b & 2) ? road : bg;
         const uint32_t c2 = (b & 4) ? road : bg, c3 = (b & 8) ? road : bg;
@@ -971,7 +982,7 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(4))) voi
     extern __shared__ __align__(16) unsigned char smem[];
     RgbLds L;
     carve_rgb(smem, L, s.width, s.height, c);
-    load_palette_rgb(s, L);
+    load_patterns(s, L);
     __shared__ int s_item;
     if (mode != 2) {
         __syncthreads();

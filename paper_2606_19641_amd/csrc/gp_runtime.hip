@@ -49,7 +49,7 @@ constexpr float kBinExtent = 32.0f;   // metres
 
 struct Layout {
     int64_t halted, infr, actu, signals, signal_color;
-    int64_t scenes, views, state, cs, dims, agent_color, roads, road_index, road_color, bins, palette,
+    int64_t scenes, views, state, cs, dims, agent_color, box_rgb, roads, road_index, road_color, bins, palette,
         queue, order, counter;
     int64_t upload_end;   // the sections above are uploaded at creation
     // the chip-wide rgb raster's buffers (present when chip is true); ctl and
@@ -155,6 +155,7 @@ Layout make_layout(const gp_config *cfg, const gp_scene_desc *sc, int32_t n)
     L.cs = take(8 * n_box);
     L.dims = take(16 * n_box);
     L.agent_color = take(n_box);
+    L.box_rgb = take(4 * n_box);
     L.roads = take(32 * L.n_roads);
     L.road_index = take(4 * L.n_roads);
     L.road_color = take(L.n_roads);
@@ -319,6 +320,7 @@ struct gp_sim {
     gp::ChipBufs chip{};        // the chip-wide raster's buffers (lay.chip)
     int32_t road_uniform = 0;   // every road strip of every scene has one colour
     int32_t bins_cap = 1;       // culling bins of the largest scene
+    int32_t boxes_cap = 1;      // boxes (agents and obstacles) of the largest scene
 };
 
 namespace {
@@ -341,15 +343,23 @@ gp_status check_lds(const gp_sim *sim, const gp_launch &l)
     return GP_OK;
 }
 
-// box triangles one view's list holds in the split rasteriser (at least the
-// 96 that its streaming pass can need)
-constexpr int kSplitBoxTris = 96;
+// Box faces one view's list holds in the split rasteriser.  A box shows at
+// most three faces, one list entry each, and a view sees about a quarter of
+// its scene's boxes, so a list of twice the scene's boxes does not overflow in
+// practice; a view that overflows it all the same is rendered by the streaming
+// pass, several times slower (64 scenes of 4..128 agents with three cameras at
+// 128 x 128: 2,744 us per render with a fixed list of 96 triangles, most views
+// of the large scenes overflowing).
+int split_box_faces(const gp_sim *sim)
+{
+    return sim->boxes_cap <= 32 ? 64 : (sim->boxes_cap <= 64 ? 128 : 256);
+}
 
 gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l)
 {
     gp::RgbCfg c;
     c.waves = l.view_waves;
-    c.bcap = kSplitBoxTris;
+    c.bcap = split_box_faces(sim);
     c.bins_cap = sim->bins_cap;
     return c;
 }
@@ -557,9 +567,15 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
         rbase += d.n_roads;
         bbase += (int32_t)sb.size();
         sim->bins_cap = std::max<int32_t>(sim->bins_cap, (int32_t)sb.size());
+        sim->boxes_cap = std::max(sim->boxes_cap, d.n_agents + d.n_static);
     }
     std::memcpy(at(L.scenes), sim->scenes.data(), sizeof(gp::SceneRec) * n_scenes);
     std::memcpy(at(L.palette), cfg->palette, 768);
+    auto rgb_of = [&](int c) {
+        return (uint32_t)cfg->palette[c][0] | ((uint32_t)cfg->palette[c][1] << 8) | ((uint32_t)cfg->palette[c][2] << 16);
+    };
+    auto *brgb = reinterpret_cast<uint32_t *>(at(L.box_rgb));
+    for (int64_t b = 0; b < L.n_agents + L.n_static; ++b) brgb[b] = rgb_of(acol[b]);
     // persistent queue: kQueues segments, one per XCD, each holding whole
     // scenes so that a scene's geometry is read through one L2.  Scenes go to
     // the segment with the least work so far, heaviest first (work of a view
@@ -630,6 +646,7 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     D.cs = reinterpret_cast<float2 *>(base + L.cs);
     D.dims = reinterpret_cast<const float4 *>(base + L.dims);
     D.agent_color = base + L.agent_color;
+    D.box_rgb = reinterpret_cast<const uint32_t *>(base + L.box_rgb);
     D.roads = reinterpret_cast<const float4 *>(base + L.roads);
     D.road_index = reinterpret_cast<const int32_t *>(base + L.road_index);
     D.road_color = base + L.road_color;
@@ -673,6 +690,8 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     D.road_color_uniform = (sim->road_uniform && L.n_signals == 0) ? 1 : 0;
     D.shade = 0;
     D.road_color0 = color0 < 0 ? 0 : color0;
+    D.road_rgb = rgb_of(D.road_color0);
+    D.bg_rgb = rgb_of(0);
     for (int k = 0; k < gp::kMaxCams; ++k) {
         D.cam_dir[k][0] = cfg->cam_dir[k][0];
         D.cam_dir[k][1] = cfg->cam_dir[k][1];
