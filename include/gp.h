@@ -118,10 +118,10 @@ typedef enum {
 typedef enum {
     GP_RASTER_BANDED = 0,     /* one workgroup of block_threads per view; LDS key bands of
                                  band_rows rows; triangle lists of batch_tris             */
-    GP_RASTER_SPLIT = 1,      /* view_waves wavefronts per view sharing the view's work
-                                 through an LDS work counter; about 19 KB of LDS per view
-                                 at 128 x 128; needs width % 16 == 0 and a 16-byte aligned
-                                 image (else the banded rasteriser runs)                  */
+    GP_RASTER_SPLIT = 1,      /* one workgroup per view, its wavefronts (view_waves, more for
+                                 large images and for few views) sharing the view's work
+                                 through LDS work counters; needs width >= 16 (else, or where
+                                 its LDS does not fit, the banded rasteriser runs)        */
     GP_RASTER_CHIP = 2        /* three chip-wide passes: per-view setup (bin culling, box
                                  triangle lists), road items over the whole chip (coverage
                                  bitmasks in the workspace), resolve items of whole rows;
@@ -137,7 +137,9 @@ typedef struct {
     int32_t block_threads;    /* banded: threads per workgroup: 256, 512 or 1024       */
     int32_t blocks_per_cu;    /* persistent grid = blocks_per_cu * CUs (1..16)         */
     int32_t raster;           /* gp_raster                                            */
-    int32_t view_waves;       /* split: wavefronts per view: 1, 2 or 4                 */
+    int32_t view_waves;       /* split: wavefronts per view: 1, 2 or 4 (times 2 from 32K and 4
+                                 from 200K pixels, and doubled, up to 16, while every view's
+                                 wavefronts fit the chip at once)                       */
     int32_t road_wgs_per_cu;  /* chip: road-pass workgroups (4 wavefronts) per CU, 1..16 */
 } gp_launch;
 

@@ -109,7 +109,7 @@ struct LaunchCfg {
 
 // Settings of the wave-split rgb raster (gp_raster.hip).
 struct RgbCfg {
-    int waves;        // wavefronts per view: 1, 2 or 4
+    int waves;        // wavefronts per view: 1..16
     int bcap;         // box faces one view's list holds: 64, 128 or 256
     int bins_cap;     // culling bins of the largest scene (surviving bins are listed in LDS)
 };
@@ -155,10 +155,9 @@ size_t render_lds_bytes(int width, int height, const LaunchCfg &c, int fast);
 hipError_t launch_raycast(const DevSim &s, const RenderOut &o, int view_begin, int n_views, hipStream_t st);
 size_t raycast_lds_bytes();
 // wave-split rgb raster (gp_raster.hip) for uniform road colours, no depth /
-// primitive id, width a multiple of 16 and a 16-byte aligned image.
-// mode 0: workgroup b renders view view_begin + b; 1: view order[b]; 2: the
-// persistent work queue
-hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &c, int mode, int view_begin,
+// primitive id and width >= 16: workgroup b renders view order[b] (ordered) or
+// view_begin + b
+hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &c, int ordered, int view_begin,
                              int grid, hipStream_t st);
 size_t rgb_lds_bytes(int width, int height, const RgbCfg &c);
 // chip-wide rgb raster (gp_chip.hip), same conditions as the wave-split one

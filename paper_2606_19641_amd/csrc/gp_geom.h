@@ -1059,10 +1059,12 @@ __device__ __forceinline__ void road_corners(const DevSim &s, const Cam &cam, in
     v[0].y = y; v[1].y = y; v[2].y = y; v[3].y = y;
 }
 
-// 16 pixels' RGB (byte 0 red) packed into the 48 bytes of their samples
+// 16 pixels' RGB (byte 0 red) packed into the 48 bytes of their samples, at
+// any address (global stores need no alignment here)
 __device__ __forceinline__ void store16(uint8_t *dst, const uint32_t *c)
 {
     typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+    struct __attribute__((packed, aligned(1))) u4p { u4v v; };
     uint32_t w[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
@@ -1076,10 +1078,10 @@ __device__ __forceinline__ void store16(uint8_t *dst, const uint32_t *c)
         }
         w[k] = __builtin_amdgcn_perm(c[p + 1 < 16 ? p + 1 : 15], c[p], sel);
     }
-    u4v *out = reinterpret_cast<u4v *>(dst);
-    out[0] = u4v{w[0], w[1], w[2], w[3]};
-    out[1] = u4v{w[4], w[5], w[6], w[7]};
-    out[2] = u4v{w[8], w[9], w[10], w[11]};
+    u4p *out = reinterpret_cast<u4p *>(dst);
+    out[0].v = u4v{w[0], w[1], w[2], w[3]};
+    out[1].v = u4v{w[4], w[5], w[6], w[7]};
+    out[2].v = u4v{w[8], w[9], w[10], w[11]};
 }
 
 // ------------------------------------------------------------ work queue

@@ -7,33 +7,41 @@
 // banded kernel (k_render) and to the plain definition: the same clip, snap,
 // fill rule and winner order, only organised for throughput.
 //
-// One workgroup of K wavefronts (K = 1, 2 or 4) renders one view, with about
-// 19 KB of LDS at 128 x 128, so that a CU keeps eight views in flight:
+// One workgroup of K wavefronts (1..16) renders one view of any size from 16
+// samples a row on, with about 16 KB of LDS at 128 x 128 and two wavefronts:
 //   A  bins    the scene's road culling bins are tested against the view
 //              (frustum, road depth limit and the row-gap test below); the
 //              surviving bins are listed in LDS.
-//   B  units   the waves deal out work units through an LDS counter.  Unit 0
-//              is the boxes: cull, face setup and clipping into the view's
-//              box triangle list.  Every further unit is four surviving bins
-//              (64 strip slots).  A strip first meets a cheap test that can
-//              only reject strips covering no sample: the frustum, the road
-//              depth limit, and the row-gap test (every vertex a strip's clip
-//              can produce lies at camera height -h, so its snapped row
-//              coordinate is a non-increasing function of its depth; a strip
-//              whose depth range maps between two sample rows covers none).
-//              Survivors' camera-space corners go to the wave's ring; full
-//              setup (clip test, snap, a quad or the two fan triangles) runs 48 at a
-//              time, and each batch of triangles is rasterised at once: per
-//              (triangle, row) the exact span of covered samples is OR-ed
-//              into the view's road coverage bitmask.  Strips that need
-//              clipping are queued and clipped four per wavefront.
-//   C  resolve rows no box triangle touches are written from the table of the
-//              sixteen four-pixel road/background patterns, 16 pixels (48
-//              bytes) per lane; box rows go band by band through a band of
-//              64-bit keys that reuses the waves' staging memory: box
-//              fragments are dealt to lanes (span lengths prefix-summed over
-//              the wavefront) and folded in with LDS atomic max, and the band
-//              is resolved against the road coverage.
+//   B  units   the waves deal out work units through LDS counters.  A road
+//              unit is four surviving bins (64 strip slots).  A strip first
+//              meets a cheap test that can only reject strips covering no
+//              sample: the frustum, the road depth limit, and the row-gap test
+//              (every vertex a strip's clip can produce lies at camera height
+//              -h, so its snapped row coordinate is a non-increasing function
+//              of its depth; a strip whose depth range maps between two sample
+//              rows covers none).  Survivors join the view's ring.  Then the
+//              jobs: box units (cull, face set-up and clipping into the view's
+//              box list, a face as one quad where it covers what its triangles
+//              cover) and set-up jobs of up to 64 ring strips (clip test, snap,
+//              a quad or the two fan triangles, the clipper four strips per
+//              wavefront); per (primitive, row) the exact span of covered
+//              samples is OR-ed into the view's road coverage bits, which run
+//              on from row to row over the rows below the horizon.
+//   C  resolve rows no box face touches are written as one run of 16-byte
+//              pieces (1 KB per store instruction): the sky from three constant
+//              pieces, road rows from a table of the 64 patterns of six pixels
+//              at the three byte phases.  Box rows go in chunks: the span of
+//              every (face, row) once, masks of the faces per group of 16
+//              samples, each lane folding the 64-bit keys of its 16 samples in
+//              registers and writing 48 bytes.
+//
+// What bounds it: an image is a write stream, but the launch lasts as long as
+// its instruction issue and its slowest views, not its stores.  Measured on one
+// MI355X, render alone: 2,048 views at 128 x 128 54 us (1.9 TB/s; 60 us with
+// padded coverage rows and 48-byte stores), 8,192 views at 210 x 126 205 us
+// (3.2 TB/s; 464 us in the banded kernel, which took every width that is no
+// multiple of 16), at 434 x 252 563 us (4.8 TB/s; 1,478 us), 4,096 views at
+// 512 x 512 687 us (4.7 TB/s; 2,104 us in the chip-wide passes).
 //
 // Every float operation is written out (fmaf for fused operations) and the
 // file is compiled with -ffp-contract=off, correctly rounded division and
@@ -61,40 +69,50 @@ constexpr int kBoxClip = 64;     // box faces waiting for the clipper (one setup
 
 struct RgbLds {
     lptr<int32_t> cnt;               // [R_NCNT]
-    lptr<uint32_t> lut;              // [16][4] four-pixel road/background patterns, 3 packed dwords
-    lptr<unsigned long long> bits;   // [H][nw] road coverage, bit i of word w: column 64 w + i
+    lptr<unsigned long long> bits;   // road coverage: bit (j - hr0) * W + i is sample i of row j >= hr0
     lptr<FaceRec> faces;             // [bcap] the view's box faces
     lptr<int32_t> sbins;             // [bins_cap] surviving bins: start * 128 + count
     lptr<int32_t> cq;                // [kBoxClip] box faces to clip (box * 8 + face)
     lptr<int32_t> sring;             // [kSharedRing] strips that passed the cheap test (this round)
     lptr<unsigned char> waves;       // K regions of kWaveBytes
-    int nw, bcap, krows;
+    // after the units the memory from sbins on is free again: the pattern table, then masks and spans or keys
+    lptr<gp_v4i> pat;                // [3][64] the 16 bytes at byte phase p of a run of six pixels, by its coverage bits
+    lptr<unsigned long long> work;   // masks and spans, or rows of 64-bit keys
+    int bcap, krows;
+    int hr0;                         // first image row below the horizon
     int nmw;                         // 64-bit words of a face mask (bcap / 64)
-    int region;                      // bytes from sbins to the end (free after the units)
+    int region;                      // bytes from work to the end
 };
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 // byte offsets of the LDS sections (shared by the carve and the size query)
 struct RgbLayout {
-    size_t cnt, lut, bits, faces, sbins, cq, sring, waves, total;
+    size_t cnt, bits, faces, sbins, cq, sring, waves, total;
 };
+
+constexpr int kPatBytes = 3 * 64 * 16;
+
+// rows that can show road: below the principal point (the road's 1/z there is
+// positive only where (j + 0.5) - H / 2 is)
+__host__ __device__ inline int first_road_row(int H) { return (H + 1) >> 1; }
 
 __host__ __device__ inline RgbLayout rgb_layout(int W, int H, const RgbCfg &c)
 {
     RgbLayout l;
-    const size_t nw = (size_t)(W + 63) / 64;
+    // whole words of the flat coverage bits, and one more for reads across a word end
+    const size_t nbw = ((size_t)W * (size_t)(H - first_road_row(H)) + 63) / 64 + 1;
     size_t o = 0;
     l.cnt = o; o = align16(o + 4 * R_NCNT);
-    l.lut = o; o = align16(o + 4 * 64);
-    l.bits = o; o = align16(o + 8 * nw * (size_t)H);
+    l.bits = o; o = align16(o + 8 * nbw);
     l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
     l.cq = o; o = align16(o + 4 * (size_t)kBoxClip);
     l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
     l.sring = o; o = align16(o + 4 * (size_t)kSharedRing);
     l.waves = o; o = align16(o + (size_t)kWaveBytes * (size_t)c.waves);
-    // the region from sbins on holds a row of keys, or of masks and spans
-    o = o > l.sbins + 8 * (size_t)W ? o : align16(l.sbins + 8 * (size_t)W);
+    // the memory from sbins on holds the pattern table and a row of keys (or of masks and spans)
+    const size_t least = align16(l.sbins + kPatBytes + 8 * (size_t)W);
+    o = o > least ? o : least;
     l.total = o;
     return l;
 }
@@ -108,16 +126,23 @@ struct WaveSt {
     int nclip, nfan;         // queued strips
 };
 
-// OR the samples [xl, xr] of one row into its coverage words
-__device__ __forceinline__ void or_span(lptr<unsigned long long> row, int xl, int xr)
+// OR the coverage bits [b0, b1] into their words
+__device__ __forceinline__ void or_span(lptr<unsigned long long> bits, int b0, int b1)
 {
-    const int w0 = xl >> 6, w1 = xr >> 6;
+    const int w0 = b0 >> 6, w1 = b1 >> 6;
     for (int w = w0; w <= w1; ++w) {
-        const int lo = (w == w0) ? (xl & 63) : 0;
-        const int hi = (w == w1) ? (xr & 63) : 63;
-        const unsigned long long m = (hi == 63 ? ~0ull : ((1ull << (hi + 1)) - 1ull)) & (~0ull << lo);
-        lds_or64(row + w, m);
+        const int lo = (w == w0) ? (b0 & 63) : 0;
+        const int hi = (w == w1) ? (b1 & 63) : 63;
+        const unsigned long long m = (~0ull >> (63 - hi)) & (~0ull << lo);
+        lds_or64(bits + w, m);
     }
+}
+
+// the coverage bits from b on (at least 32 of them), bit 0 first
+__device__ __forceinline__ uint32_t bits_at(const RgbLds &L, int b)
+{
+    lptr<const uint32_t> w = (lptr<const uint32_t>)L.bits + (b >> 5);
+    return __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
 }
 
 // Rasterise the n staged road triangles into the coverage bitmask.  Lane t
@@ -153,7 +178,10 @@ __device__ __forceinline__ void road_spans(const RgbLds &L, const Cam &cam, cons
                 const Prim pr = lds_load(ws.tris + t0 + o);
                 const int j = pr.j0 + extra;
                 int xl, xr;
-                if (prim_span(pr, j, cam.W, xl, xr)) or_span(L.bits + (size_t)j * L.nw, xl, xr);
+                // (the row test holds for every row with road unless 1/z underflows)
+                const float rz = fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C);
+                const int b = (j - L.hr0) * cam.W;
+                if ((b >= 0) & (rz > 0.0f) & prim_span(pr, j, cam.W, xl, xr)) or_span(L.bits, b + xl, b + xr);
             }
         }
     }
@@ -409,18 +437,17 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
     return true;
 }
 
-// Box unit k: cull boxes [kBoxUnit k, kBoxUnit (k + 1)) of the scene, list
+// Box unit k: cull boxes [unit k, unit (k + 1)) of the scene (unit <= 64), list
 // the survivors, set up their faces into the view's box list
 // (shared by the wavefronts; its row range kept with LDS min / max).  scr:
 // 128 ints of the wavefront's staging (survivors, then the clip queue).
-constexpr int kBoxUnit = 16;
 __device__ __forceinline__ void do_boxes(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                                         int k, lptr<int32_t> scr)
+                                         int k, int unit, lptr<int32_t> scr)
 {
     const int ln = (int)lane_id();
     const int nbox = sc.n_agents + sc.n_static;
-    const int j = kBoxUnit * k + ln;
-    const bool keep = ln < kBoxUnit && j < nbox && j != ego && !box_outside(s, sc, cam, j);
+    const int j = unit * k + ln;
+    const bool keep = ln < unit && j < nbox && j != ego && !box_outside(s, sc, cam, j);
     const unsigned long long bm = __ballot(keep);
     if (keep) scr[lanes_below(bm)] = j;
     const int ns = __popcll(bm);
@@ -507,19 +534,22 @@ __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<u
 // face, row) item is computed once and stored, and every group of 16 samples
 // of a row gets a mask of the faces whose span meets it.  The resolve then
 // walks, for its 16 samples, the faces of its group's mask and keeps the
-// largest key of each sample in registers.  Memory (the free region): the
-// masks M[c1 - c0][W / 16][nmw], then the spans S[t][c1 - c0].
+// largest key of each sample in registers.  The G = ceil(W / 16) groups of a
+// row start at samples 0, 16, ...; where W is not a multiple of 16 the last
+// one starts at W - 16 and shares samples with the one before (both compute
+// and store the same pixels).  Memory (L.work): the masks M[c1 - c0][G][nmw],
+// then the spans S[t][c1 - c0].
 __host__ __device__ inline int mask_rows_fit(int region, int n, int W, int nmw)
 {
     // rows per chunk so that the masks and a span of every face in every row fit
-    return region / (8 * nmw * (W / 16) + 4 * n);
+    return region / (8 * nmw * ((W + 15) / 16) + 4 * n);
 }
 
 __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n, int c0, int c1, int wv, int nwv)
 {
     const int ln = (int)lane_id();
-    const int R = c1 - c0, G = cam.W >> 4, nmw = L.nmw;
-    lptr<unsigned long long> M = (lptr<unsigned long long>)L.sbins;
+    const int R = c1 - c0, G = (cam.W + 15) >> 4, nmw = L.nmw;
+    lptr<unsigned long long> M = L.work;
     lptr<int32_t> S = (lptr<int32_t>)(M + nmw * G * R);
     int pass = 0;
     for (int t0 = 0; t0 < n; t0 += 64) {
@@ -547,7 +577,8 @@ __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n
                     S[tt * R + (j - c0)] = xl | (xr << 16);
                     lptr<unsigned long long> mrow = M + nmw * G * (j - c0) + (tt >> 6);
                     const unsigned long long bit = 1ull << (tt & 63);
-                    for (int g = xl >> 4; g <= (xr >> 4); ++g) lds_or64(mrow + nmw * g, bit);
+                    const int gl = xr >= cam.W - 16 ? G - 1 : xr >> 4;
+                    for (int g = xl >> 4; g <= gl; ++g) lds_or64(mrow + nmw * g, bit);
                 }
             }
         }
@@ -560,8 +591,8 @@ __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n
 __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, uint8_t *img, uint32_t road_rgb,
                                               uint32_t bg_rgb, int c0, int c1, int wv, int nwv)
 {
-    const int R = c1 - c0, G = cam.W >> 4, nmw = L.nmw;
-    lptr<const unsigned long long> M = (lptr<const unsigned long long>)L.sbins;
+    const int R = c1 - c0, G = (cam.W + 15) >> 4, nmw = L.nmw;
+    lptr<const unsigned long long> M = (lptr<const unsigned long long>)L.work;
     lptr<const int32_t> S = (lptr<const int32_t>)(M + nmw * G * R);
     const int W = cam.W;
     const int n = R * G;
@@ -570,10 +601,10 @@ __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, u
     for (int blk = 2 * wv + half; 32 * blk < n; blk += 2 * nwv) {
         const int task = 32 * blk + sub;
         if (task >= n) continue;
-        const int r = task / G, g = task - r * G, i = g << 4, j = c0 + r;
+        const int r = task / G, g = task - r * G, i = min(g << 4, W - 16), j = c0 + r;
         const float dv = ((float)j + 0.5f) - cam.cy;
         const float rz = fmaf(cam.road.B, dv, cam.road.C);
-        const uint32_t bits = rz > 0.0f ? (uint32_t)(L.bits[(size_t)j * L.nw + (i >> 6)] >> (i & 63)) & 0xFFFFu : 0u;
+        const uint32_t bits = j >= L.hr0 ? bits_at(L, (j - L.hr0) * W + i) : 0u;
         const uint32_t rzb = __float_as_uint(rz);
         // sample offsets ((float)(i + m) + 0.5f) - cx are small exact values: du0 + m
         const float du0 = ((float)i + 0.5f) - cam.cx;
@@ -622,42 +653,99 @@ __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, u
 
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
-// rows [r0, r1) that no box fragment touches: 16 pixels (48 bytes) per lane
-// from the pattern table (road where the coverage bit is set and the row is
-// below the horizon, background elsewhere); two tasks per iteration so that
-// their LDS reads overlap
-__device__ __forceinline__ void resolve_lut(const RgbLds &L, const Cam &cam, uint8_t *img, int r0, int r1)
+// The rows that no box fragment touches are written as one run of bytes, in
+// 16-byte pieces at 16-byte aligned addresses whatever the width and the
+// image's address: piece q holds the bytes o .. o + 15 of the image, o = 16 q -
+// a (a: the image's address mod 16), which lie in the six pixels from f =
+// o / 3 on, at phase o mod 3 of their run.  Neighbouring lanes write
+// neighbouring pieces, so a store instruction writes 1 KB in one run.  (A lane
+// that wrote 16 pixels as three 16-byte stores 48 bytes apart reached 3.9 TB/s
+// in a kernel that only writes, pieces in one run 6.3 TB/s.)
+
+// byte b of a pixel's colour at channel c
+__device__ __forceinline__ uint8_t channel(uint32_t rgb, int c) { return (uint8_t)(rgb >> (8 * c)); }
+
+// bytes [b0, b1) of the background (the sky)
+__device__ __forceinline__ void write_sky(uint8_t *img, uint32_t bg, int b0, int b1)
 {
-    const int W = cam.W, gpr = W >> 4;
-    const int n = (r1 - r0) * gpr;
-    const lptr<u4> lut = (lptr<u4>)L.lut;
-    const int B = (int)blockDim.x;
-    for (int task = (int)threadIdx.x; task < n; task += 2 * B) {
-        uint32_t bits[2];
-        u4 *out[2];
-        bool act[2];
+    if (b0 >= b1) return;
+    const int a = (int)(reinterpret_cast<uintptr_t>(img) & 15), B = (int)blockDim.x, tid = (int)threadIdx.x;
+    const int q0 = (b0 + a + 15) >> 4, q1 = (b1 + a) >> 4;
+    const uint32_t w[3] = {bg | (bg << 24), (bg >> 8) | (bg << 16), (bg >> 16) | (bg << 8)};
+    // a thread's pieces are B apart: their phases repeat after three
+    u4 v[3];
+    int ph = (16 * (q0 + tid) - a + 48) % 3;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int tk = task + h * B;
-            act[h] = tk < n;
-            const int tc = act[h] ? tk : task;
-            const int r = tc / gpr, i = (tc - r * gpr) << 4, j = r0 + r;
-            const float dv = ((float)j + 0.5f) - cam.cy;
-            const float rz = fmaf(cam.road.B, dv, cam.road.C);
-            bits[h] = rz > 0.0f ? (uint32_t)(L.bits[(size_t)j * L.nw + (i >> 6)] >> (i & 63)) & 0xFFFFu : 0u;
-            out[h] = reinterpret_cast<u4 *>(img + 3 * ((int64_t)j * W + i));
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t b = bits[h];
-            const u4 a = lut[b & 15u], bb = lut[(b >> 4) & 15u], c = lut[(b >> 8) & 15u], d = lut[b >> 12];
-            if (act[h]) {
-                out[h][0] = u4{a.x, a.y, a.z, bb.x};
-                out[h][1] = u4{bb.y, bb.z, c.x, c.y};
-                out[h][2] = u4{c.z, d.x, d.y, d.z};
-            }
-        }
+    for (int k = 0; k < 3; ++k) {
+        v[k] = u4{__builtin_amdgcn_alignbyte(w[1], w[0], ph), __builtin_amdgcn_alignbyte(w[2], w[1], ph),
+                  __builtin_amdgcn_alignbyte(w[0], w[2], ph), __builtin_amdgcn_alignbyte(w[1], w[0], ph)};
+        ph = (ph + B) % 3;
     }
+    u4 *out = reinterpret_cast<u4 *>(img - a);
+    for (int q = q0 + tid; q < q1; q += 3 * B) {
+        out[q] = v[0];
+        if (q + B < q1) out[q + B] = v[1];
+        if (q + 2 * B < q1) out[q + 2 * B] = v[2];
+    }
+    // the partial pieces at the run's ends (a row has at least 48 bytes)
+    const int head = 16 * q0 - a - b0, tail = b1 - (16 * q1 - a);
+    if (tid < head) img[b0 + tid] = channel(bg, (b0 + tid) % 3);
+    if (tid >= 32 && tid < 32 + tail) img[b1 - tail + tid - 32] = channel(bg, (b1 - tail + tid - 32) % 3);
+}
+
+// the pattern table: entry (p, b) holds the 16 bytes at phase p of the run of
+// six pixels that are road where bit k of b is set and background elsewhere
+__device__ __forceinline__ void build_patterns(const RgbLds &L, uint32_t road, uint32_t bg)
+{
+    for (int e = (int)threadIdx.x; e < 3 * 64; e += (int)blockDim.x) {
+        const int ph = e >> 6;
+        uint32_t c[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) c[k] = (e >> k) & 1 ? road : bg;
+        const uint32_t w[5] = {c[0] | (c[1] << 24), (c[1] >> 8) | (c[2] << 16), (c[2] >> 16) | (c[3] << 8),
+                               c[4] | (c[5] << 24), c[5] >> 8};
+        gp_v4i v;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = (int)__builtin_amdgcn_alignbyte(w[d + 1], w[d], ph);
+        L.pat[e] = v;
+    }
+}
+
+// bytes [b0, b1) of rows below the horizon, road or background by the coverage bits
+__device__ __forceinline__ void write_road(const RgbLds &L, uint8_t *img, uint32_t road, uint32_t bg, int W, int b0,
+                                           int b1)
+{
+    if (b0 >= b1) return;
+    const int a = (int)(reinterpret_cast<uintptr_t>(img) & 15), B = (int)blockDim.x, tid = (int)threadIdx.x;
+    const int q0 = (b0 + a + 15) >> 4, q1 = (b1 + a) >> 4;
+    const int f0 = L.hr0 * W;            // pixel of coverage bit 0
+    gp_v4i *out = reinterpret_cast<gp_v4i *>(img - a);
+    auto piece = [&](int q) -> gp_v4i {
+        const uint32_t o = (uint32_t)(16 * q - a), f = o / 3u, ph = o - 3u * f;
+        return L.pat[(ph << 6) | (bits_at(L, (int)f - f0) & 63u)];
+    };
+    for (int q = q0 + tid; q < q1; q += 2 * B) {
+        const bool two = q + B < q1;
+        const gp_v4i v0 = piece(q), v1 = piece(two ? q + B : q);
+        out[q] = v0;
+        if (two) out[q + B] = v1;
+    }
+    const int head = 16 * q0 - a - b0, tail = b1 - (16 * q1 - a);
+    int o = -1;
+    if (tid < head) o = b0 + tid;
+    else if (tid >= 32 && tid < 32 + tail) o = b1 - tail + tid - 32;
+    if (o >= 0) {
+        const int f = o / 3;
+        img[o] = channel(bits_at(L, f - f0) & 1u ? road : bg, o - 3 * f);
+    }
+}
+
+// rows [r0, r1) that no box fragment touches: sky above the horizon, road or
+// background below it
+__device__ __forceinline__ void write_rows(const RgbLds &L, uint8_t *img, uint32_t road, uint32_t bg, int W, int r0, int r1)
+{
+    write_sky(img, bg, 3 * W * r0, 3 * W * min(r1, L.hr0));
+    write_road(L, img, road, bg, W, 3 * W * max(r0, L.hr0), 3 * W * r1);
 }
 
 // rows [b0, b1) of the key band: a box fragment wins where its 1/z is not
@@ -667,14 +755,13 @@ __device__ __forceinline__ void resolve_band(const DevSim &s, const SceneRec &sc
                                              lptr<unsigned long long> keys, uint8_t *img, uint32_t road_rgb,
                                              uint32_t bg_rgb, int b0, int b1)
 {
-    const int W = cam.W, gpr = W >> 4;
+    const int W = cam.W, gpr = (W + 15) >> 4;
     const int n = (b1 - b0) * gpr;
     for (int task = (int)threadIdx.x; task < n; task += (int)blockDim.x) {
-        const int r = task / gpr, i = (task - r * gpr) << 4, j = b0 + r;
+        const int r = task / gpr, i = min((task - r * gpr) << 4, W - 16), j = b0 + r;
         const float dv = ((float)j + 0.5f) - cam.cy;
         const float rz = fmaf(cam.road.B, dv, cam.road.C);
-        const bool rowok = rz > 0.0f;
-        const uint32_t bits = rowok ? (uint32_t)(L.bits[(size_t)j * L.nw + (i >> 6)] >> (i & 63)) & 0xFFFFu : 0u;
+        const uint32_t bits = j >= L.hr0 ? bits_at(L, (j - L.hr0) * W + i) : 0u;
         const uint32_t rzb = __float_as_uint(rz);
         lptr<unsigned long long> kp = keys + (size_t)r * W + i;
         uint32_t c[16];
@@ -688,24 +775,7 @@ __device__ __forceinline__ void resolve_band(const DevSim &s, const SceneRec &sc
             if (box) v = s.box_rgb[box_slot(sc, ((kMaxPrims - 1) - (int)(((uint32_t)kb >> 8) & (uint32_t)(kMaxPrims - 1))) / 6)];
             c[m] = v;
         }
-        u4 *out = reinterpret_cast<u4 *>(img + 3 * ((int64_t)j * W + i));
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            // 16 pixels = 48 bytes = 12 dwords; dword k holds bytes 4k .. 4k + 3
-            uint32_t w[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int k = 4 * q + d;     // dword index
-                uint32_t v = 0;
-#pragma unroll
-                for (int bb = 0; bb < 4; ++bb) {
-                    const int byte = 4 * k + bb, px = byte / 3, ch = byte - 3 * px;
-                    v |= ((c[px] >> (8 * ch)) & 0xFFu) << (8 * bb);
-                }
-                w[d] = v;
-            }
-            out[q] = u4{w[0], w[1], w[2], w[3]};
-        }
+        store16(img + 3 * ((int64_t)j * W + i), c);
     }
 }
 
@@ -718,7 +788,7 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
                                               uint8_t *img, uint32_t road_rgb, uint32_t bg_rgb, int kr0, int kr1, int wv)
 {
     const int W = cam.W;
-    lptr<unsigned long long> keys = (lptr<unsigned long long>)L.sbins;
+    lptr<unsigned long long> keys = L.work;
     for (int b0 = kr0; b0 < kr1; b0 += L.krows) {
         const int b1 = min(b0 + L.krows, kr1);
         __syncthreads();
@@ -728,7 +798,7 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
             const int ncand = 6 * (sc.n_agents + sc.n_static);
             for (int c0 = 0; c0 < ncand; c0 += 6) {
                 int n = 0, bmn = 0, bmx = 0;
-                (void)box_pass(s, sc, cam, ego, L, (lptr<const int32_t>)L.sbins, false, ncand, c0, 6, L.cq, false, n, bmn,
+                (void)box_pass(s, sc, cam, ego, L, (lptr<const int32_t>)L.cq, false, ncand, c0, 6, L.cq, false, n, bmn,
                                bmx);
                 wave_lds_order();
                 box_band(L, cam, keys, n, 0, 1, b0, b1);
@@ -786,10 +856,9 @@ __device__ __forceinline__ void cull_bins(const DevSim &s, const SceneRec &sc, c
     if (keep) L.sbins[base + lanes_below(bm)] = rec;
 }
 
-template <int K>
 __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut &o, const RgbLds &L, int view)
 {
-    constexpr int B = 64 * K;
+    const int B = (int)blockDim.x, K = B >> 6;
     const int tid = (int)threadIdx.x, ln = (int)lane_id(), wv = tid >> 6;
     const int scene = __builtin_amdgcn_readfirstlane(s.views[view].scene);
     const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
@@ -798,11 +867,16 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
     const Cam cam = make_cam(s, sc, ego, ego_cam & 3);
     const int W = cam.W, H = cam.H;
 
-    for (int p = tid; p < H * L.nw; p += B) L.bits[p] = 0ull;
+    const int nbits = ((W * (H - L.hr0) + 63) >> 6) + 1;
+    for (int p = tid; p < nbits; p += B) L.bits[p] = 0ull;
+    // boxes per box unit: a unit of 16 boxes sets up their faces in one or two
+    // passes; workgroups of many wavefronts take smaller units, so that the
+    // boxes are spread over them
+    const int ubox = K >= 8 ? 4 : 16;
+    const int nbu = (sc.n_agents + sc.n_static + ubox - 1) / ubox;
     // road units are numbered after the box units (dealt as jobs, below)
     if (tid < R_NCNT)
-        L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF
-                   : (tid == R_BMAX ? -1 : (tid == R_NEXT ? (sc.n_agents + sc.n_static + kBoxUnit - 1) / kBoxUnit : 0));
+        L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : (tid == R_NEXT ? nbu : 0));
     __syncthreads();
 
     // ---- A: road culling bins
@@ -814,7 +888,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
     // numbered from nbu on): the cheap test of the unit's strips with the
     // survivors appended to the view's ring (a unit is taken only with 64
     // free ring entries reserved).  B2: the jobs -- in the first round the box
-    // units first (boxes kBoxUnit k .. kBoxUnit k + kBoxUnit - 1: cull, face
+    // units first (boxes ubox k .. ubox k + ubox - 1: cull, face
     // set-up and clipping into the box list, which is needed only by the
     // resolve, so a long box unit overlaps the other wavefront's road jobs),
     // then set-up jobs of up to kSetupBatch ring strips: set-up, the fan
@@ -825,7 +899,6 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
     // road work ahead grows with the surviving bins (a mean view keeps about a dozen)
     const int prio_b = nsb >= 24 ? 2 : (nsb >= 16 ? 1 : 0);
     view_priority(prio_b);
-    const int nbu = (sc.n_agents + sc.n_static + kBoxUnit - 1) / kBoxUnit;
     const int n_units = nbu + (nsb + 3) / 4;
     lptr<unsigned char> wbase = L.waves + (size_t)wv * kWaveBytes;
     WaveSt ws;
@@ -881,7 +954,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
             if (ln == 0) j = lds_add(L.cnt + R_JOB, 1);
             j = __builtin_amdgcn_readfirstlane(__shfl(j, 0)) - box_jobs;
             if (j < 0) {
-                do_boxes(s, sc, cam, ego, L, j + box_jobs, (lptr<int32_t>)ws.tris);   // the staging is free here
+                do_boxes(s, sc, cam, ego, L, j + box_jobs, ubox, (lptr<int32_t>)ws.tris);   // the staging is free here
                 continue;
             }
             const int a = j * jsz;
@@ -914,28 +987,31 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, const RenderOut
     view_priority(max(prio_b, kr1 - kr0 >= 64 ? 3 : (kr1 - kr0 >= 32 ? 2 : 0)));
     const uint32_t road_rgb = s.road_rgb, bg_rgb = s.bg_rgb;
     const int mrows = max(1, mask_rows_fit(L.region, nbt, W, L.nmw));
-    if (!ovf && kr0 < kr1) {
-        // box rows through row masks, in chunks of rows whose items fit; the
-        // rows outside them (the pattern table: coverage bits and table only)
-        // go with the first chunk's spans (which write the free region only)
-        for (int c0 = kr0; c0 < kr1; c0 += mrows) {
-            const int c1 = min(c0 + mrows, kr1);
-            if (c0 != kr0) __syncthreads();
-            lptr<unsigned long long> M = (lptr<unsigned long long>)L.sbins;
-            for (int p = tid; p < L.nmw * (W >> 4) * (c1 - c0); p += B) M[p] = 0ull;
-            __syncthreads();
-            if (c0 == kr0) {
-                resolve_lut(L, cam, img, 0, kr0);
-                resolve_lut(L, cam, img, kr1, H);
-            }
+    // the pattern table, and the masks of the first chunk of box rows, in
+    // chunks of rows whose items fit; the rows without boxes go with the first
+    // chunk's spans
+    const bool masks = !ovf && kr0 < kr1;
+    int c1 = min(kr0 + mrows, kr1);
+    build_patterns(L, road_rgb, bg_rgb);
+    const int G = (W + 15) >> 4;
+    if (masks)
+        for (int p = tid; p < L.nmw * G * (c1 - kr0); p += B) L.work[p] = 0ull;
+    __syncthreads();
+    write_rows(L, img, road_rgb, bg_rgb, W, 0, kr0);
+    write_rows(L, img, road_rgb, bg_rgb, W, kr1, H);
+    if (masks) {
+        for (int c0 = kr0;;) {
             box_spans(L, cam, nbt, c0, c1, wv, K);
             __syncthreads();
             resolve_masks(L, cam, img, road_rgb, bg_rgb, c0, c1, wv, K);
+            if (c1 == kr1) return;
+            c0 = c1;
+            c1 = min(c0 + mrows, kr1);
+            __syncthreads();
+            for (int p = tid; p < L.nmw * G * (c1 - c0); p += B) L.work[p] = 0ull;
+            __syncthreads();
         }
-        return;
     }
-    resolve_lut(L, cam, img, 0, kr0);
-    resolve_lut(L, cam, img, kr1, H);
     if (ovf) key_band_rows(s, sc, cam, ego, L, img, road_rgb, bg_rgb, kr0, kr1, wv);
 }
 
@@ -943,80 +1019,44 @@ __device__ __forceinline__ void carve_rgb(unsigned char *smem, RgbLds &L, int W,
 {
     const RgbLayout l = rgb_layout(W, H, c);
     L.cnt = (lptr<int32_t>)(smem + l.cnt);
-    L.lut = (lptr<uint32_t>)(smem + l.lut);
     L.bits = (lptr<unsigned long long>)(smem + l.bits);
     L.faces = (lptr<FaceRec>)(smem + l.faces);
     L.sbins = (lptr<int32_t>)(smem + l.sbins);
     L.cq = (lptr<int32_t>)(smem + l.cq);
     L.sring = (lptr<int32_t>)(smem + l.sring);
     L.waves = (lptr<unsigned char>)(smem + l.waves);
-    L.nw = (W + 63) >> 6;
+    L.hr0 = first_road_row(H);
     L.bcap = c.bcap;
     L.nmw = c.bcap >> 6;
-    // the key band takes the surviving-bin list, the box clip queue and the
-    // waves' staging, all idle by then
-    L.region = (int)(l.total - l.sbins);
+    // the surviving-bin list, the ring and the waves' staging are idle by the resolve
+    L.pat = (lptr<gp_v4i>)(smem + l.sbins);
+    L.work = (lptr<unsigned long long>)(smem + l.sbins + kPatBytes);
+    L.region = (int)(l.total - l.sbins) - kPatBytes;
     L.krows = max(1, L.region / (8 * W));
 }
 
-__device__ __forceinline__ void load_patterns(const DevSim &s, const RgbLds &L)
-{
-    if (threadIdx.x < 16) {
-        // pattern b: pixel k is road where bit k of b is set, background elsewhere
-        const uint32_t road = s.road_rgb, bg = s.bg_rgb;
-        const int b = threadIdx.x;
-        const uint32_t c0 = (b & 1) ? road : bg, c1 = (b & 2) ? road : bg;
-        const uint32_t c2 = (b & 4) ? road : bg, c3 = (b & 8) ? road : bg;
-        L.lut[4 * b + 0] = c0 | (c1 << 24);
-        L.lut[4 * b + 1] = (c1 >> 8) | (c2 << 16);
-        L.lut[4 * b + 2] = (c2 >> 16) | (c3 << 8);
-        L.lut[4 * b + 3] = 0u;
-    }
-}
-
-// mode 0: view view_begin + blockIdx.x; 1: view order[blockIdx.x]; 2: the
-// persistent work queue
-template <int K>
-__global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(4))) void k_render_rgb(DevSim s, RenderOut o, RgbCfg c, int mode, int view_begin)
+// One workgroup per view: view view_begin + blockIdx.x (ordered 0), or
+// order[blockIdx.x].
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void k_render_rgb(DevSim s, RenderOut o, RgbCfg c,
+                                                                                            int ordered, int view_begin)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     RgbLds L;
     carve_rgb(smem, L, s.width, s.height, c);
-    load_patterns(s, L);
-    __shared__ int s_item;
-    if (mode != 2) {
-        __syncthreads();
-        const int view = mode == 0 ? view_begin + (int)blockIdx.x : s.order[blockIdx.x];
-        render_view_rgb<K>(s, o, L, view);
-        return;
-    }
-    int cur = (int)(blockIdx.x % kQueues);
-    for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) s_item = queue_take(s, cur);
-        __syncthreads();
-        const int it = __builtin_amdgcn_readfirstlane(s_item);
-        if (it >= s.n_views) break;
-        render_view_rgb<K>(s, o, L, s.queue[it]);
-    }
-    if (threadIdx.x == 0) queue_leave(s);
+    render_view_rgb(s, o, L, ordered ? s.order[blockIdx.x] : view_begin + (int)blockIdx.x);
 }
 
 }  // namespace
 
 size_t rgb_lds_bytes(int width, int height, const RgbCfg &c) { return rgb_layout(width, height, c).total; }
 
-hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &c, int mode, int view_begin,
+hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &c, int ordered, int view_begin,
                              int grid, hipStream_t st)
 {
     if (grid <= 0) return hipSuccess;
+    if (c.waves < 1 || c.waves > 16 || s.width < 16) return hipErrorInvalidValue;
     const size_t lds = rgb_lds_bytes(s.width, s.height, c);
-    switch (c.waves) {
-    case 1: hipLaunchKernelGGL(k_render_rgb<1>, dim3(grid), dim3(64), lds, st, s, o, c, mode, view_begin); break;
-    case 2: hipLaunchKernelGGL(k_render_rgb<2>, dim3(grid), dim3(128), lds, st, s, o, c, mode, view_begin); break;
-    case 4: hipLaunchKernelGGL(k_render_rgb<4>, dim3(grid), dim3(256), lds, st, s, o, c, mode, view_begin); break;
-    default: return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL(k_render_rgb, dim3(grid), dim3(64 * c.waves), lds, st, s, o, c, ordered, view_begin);
     return hipGetLastError();
 }
 

@@ -352,13 +352,34 @@ gp_status check_lds(const gp_sim *sim, const gp_launch &l)
 // of the large scenes overflowing).
 int split_box_faces(const gp_sim *sim)
 {
-    return sim->boxes_cap <= 32 ? 64 : (sim->boxes_cap <= 64 ? 128 : 256);
+    return std::min(256, (sim->boxes_cap * 3 / 2 + 63) / 64 * 64);
 }
 
-gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l)
+// Wavefronts per view in the split rasteriser: the launch's view_waves, times
+// 2 from 32K pixels on and 4 from 200K on (a view's rows are a serial loop of
+// its workgroup, and larger images leave room for fewer workgroups in LDS),
+// doubled while all wavefronts together still fit the chip at four per SIMD.
+// Render us by wavefronts per view, 2 / 4 / 8 / 16 (one MI355X):
+//   2,048 views 128 x 128 (32 agents, 2,000 strips)   54.2 /  65.7 / 102 / 167
+//   8,192 views 210 x 126                              214 /   257 / 411 / 687
+//   8,192 views 434 x 252                              762 /   563 / 659 / 953
+//   4,096 views 512 x 512 (64 agents, 4,000 strips)    886 /   742 / 687 / 822
+//   1,024 views 128 x 128                             49.8 /  40.4 / 58.4 / 82.2
+//     256 views 128 x 128                             38.4 /  31.7 / 28.6 / 27.7
+//       8 views  64 x 64  (8 agents, 200 strips)      26.9 /  22.2 / 18.4 / 19.0
+//      64 views 512 x 512                              256 /   143 / 94.2 / 72.4
+int split_waves(const gp_sim *sim, const gp_launch &l, int64_t n_views)
+{
+    const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
+    int k = l.view_waves * (px >= 200000 ? 4 : (px >= 32768 ? 2 : 1));
+    while (k < 16 && 2 * k * n_views <= 16 * (int64_t)sim->n_cu) k *= 2;
+    return std::min(k, 16);
+}
+
+gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
 {
     gp::RgbCfg c;
-    c.waves = l.view_waves;
+    c.waves = split_waves(sim, l, n_views);
     c.bcap = split_box_faces(sim);
     c.bins_cap = sim->bins_cap;
     return c;
@@ -372,11 +393,10 @@ bool chip_ok(const gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, int 
 }
 
 // can this render take the split rasteriser?
-bool split_ok(const gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, int kind)
+bool split_ok(const gp_sim *sim, const gp_launch &l, int kind)
 {
-    return l.raster == GP_RASTER_SPLIT && kind == 1 && sim->cfg.width % 16 == 0 &&
-           reinterpret_cast<uintptr_t>(o.rgb) % 16 == 0 && sim->cfg.cam_height > 0.0f &&
-           gp::rgb_lds_bytes(sim->cfg.width, sim->cfg.height, rgb_cfg(sim, l)) <= sim->max_lds;
+    return l.raster == GP_RASTER_SPLIT && kind == 1 && sim->cfg.width >= 16 && sim->cfg.cam_height > 0.0f &&
+           gp::rgb_lds_bytes(sim->cfg.width, sim->cfg.height, rgb_cfg(sim, l, sim->lay.n_views)) <= sim->max_lds;
 }
 
 gp_status render_impl(gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, hipStream_t st)
@@ -386,8 +406,8 @@ gp_status render_impl(gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, h
     // every road strip has the same colour; everything else takes the general one
     // (scenes with traffic lights take the general kernel's instances with lights)
     const int kind = sim->lay.n_signals > 0 ? 2 : (!o.depth && !o.primid && sim->dev.road_color_uniform) ? 1 : 0;
-    const bool split = split_ok(sim, o, l, kind);
-    const gp::RgbCfg rc = rgb_cfg(sim, l);
+    const bool split = split_ok(sim, l, kind);
+    const gp::RgbCfg rc = rgb_cfg(sim, l, sim->lay.n_views);
     hipError_t e;
     if (chip_ok(sim, o, l, kind)) {
         const int rg = l.road_wgs_per_cu * sim->n_cu;
@@ -728,20 +748,17 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     l.batch_tris = 256;
     l.block_threads = 256;
     l.blocks_per_cu = 3;
-    // rgb renders take the split rasteriser (two wavefronts per view, eight
-    // views per CU) where it can run
+    // rgb renders take the split rasteriser where its LDS fits, else the
+    // chip-wide passes where the image size allows them
     l.raster = GP_RASTER_BANDED;
     l.view_waves = 2;
     l.road_wgs_per_cu = 8;
     {
-        // rgb renders: the wave-split raster where eight views fit a CU, else
-        // the chip-wide passes where the image size allows them
         gp_launch t = l;
         t.raster = GP_RASTER_SPLIT;
-        if (cfg->width % 16 == 0 && cfg->cam_height > 0.0f &&
-            gp::rgb_lds_bytes(cfg->width, cfg->height, rgb_cfg(sim, t)) * 8 <= 160u * 1024u) {
+        if (split_ok(sim, t, 1)) {
             l.raster = GP_RASTER_SPLIT;
-            l.blocks_per_cu = 8;
+            if (cfg->width % 16 == 0 && (int64_t)cfg->width * cfg->height <= 128 * 128) l.blocks_per_cu = 8;
         } else if (L.chip && cfg->cam_height > 0.0f) {
             l.raster = GP_RASTER_CHIP;
         }

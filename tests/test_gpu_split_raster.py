@@ -59,3 +59,45 @@ def test_box_list_sizes(n_agents, waves):
     sim.set_launch(raster=1, view_waves=waves)
     picks = [(0, a, k) for a in range(0, n_agents, max(1, n_agents // 3)) for k in range(3)]
     _check(sim, scenes, cam, pal, picks, (n_agents, waves))
+
+
+@pytest.mark.parametrize("size", [(16, 16), (17, 9), (31, 33), (48, 1), (63, 40), (65, 64), (210, 126), (337, 100),
+                                  (434, 252), (250, 801)])
+def test_widths_and_alignments(size):
+    """Any width from 16 on (groups of 16 samples that overlap at the row end,
+    coverage bits that run on from row to row), images whose size and address
+    are no multiple of 16 bytes, every wavefront count, bytes around the image
+    left alone."""
+    print(f"split raster at {size}", flush=True)
+    W, H = size
+    scenes = [_crowd(60 + W, 9, n_roads=150), _crowd(61 + W, 3, n_roads=0)]
+    cam = g.Camera(width=W, height=H, focal_px=W / 2.0, cam_dirs=g.FRONT_AND_SIDES)
+    pal = g.mixed_palette()
+    pal[0] = (9, 70, 201)                       # every channel of sky and road differs
+    pal[1] = (150, 31, 4)
+    from paper_2606_19641_amd import gp
+    sim = gp.Sim(scenes, cam, pal)
+    picks = [(0, a, k) for a in (0, 4, 8) for k in range(3)] + [(1, 1, 0)]
+    for waves in (1, 2, 4):
+        sim.set_launch(raster=1, view_waves=waves)
+        _check(sim, scenes, cam, pal, picks, (size, waves))
+    ref, _, _ = sim.render()
+    for off in (4, 8, 12):
+        buf = torch.full((ref.numel() + 64,), 77, dtype=torch.uint8, device="cuda")
+        sim.render(rgb=buf[off:off + ref.numel()].view(ref.shape))
+        torch.cuda.synchronize()
+        assert torch.equal(buf[off:off + ref.numel()].view(ref.shape), ref), (size, off)
+        assert bool((buf[:off] == 77).all()) and bool((buf[off + ref.numel():] == 77).all()), (size, off)
+
+
+@pytest.mark.parametrize("scenes", [1, 3, 9])
+def test_wavefronts_for_few_views(scenes):
+    """Few views take up to 16 wavefronts each (small box units, many set-up jobs)."""
+    sc = [_crowd(300 + k, 12 + 31 * (k % 2), n_roads=90 + 400 * (k % 3)) for k in range(scenes)]
+    cam = g.camera_for(96)
+    pal = g.mixed_palette()
+    from paper_2606_19641_amd import gp
+    sim = gp.Sim(sc, cam, pal)
+    for waves in (1, 2, 4):
+        sim.set_launch(raster=1, view_waves=waves)
+        _check(sim, sc, cam, pal, [(0, a, 0) for a in range(4)], (scenes, waves))
