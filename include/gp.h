@@ -113,8 +113,8 @@ typedef enum {
  * launch gives every view a workgroup of its own and uses no queue. */
 
 /* Rasteriser of rgb-only renders (no depth / primitive id) of sims whose road
- * strips share one colour, without traffic lights or shading.  Other renders
- * always take the banded rasteriser. */
+ * strips share one colour (the chip-wide one without traffic lights or
+ * shading).  Other renders always take the banded rasteriser. */
 typedef enum {
     GP_RASTER_BANDED = 0,     /* one workgroup of block_threads per view; LDS key bands of
                                  band_rows rows; triangle lists of batch_tris             */
@@ -250,9 +250,8 @@ gp_status gp_sim_get_actuators(gp_sim *sim, float *d_dst, void *stream);
  * normal n shows each channel c of its palette colour as (c q + 127) / 255,
  * q = floor(255 (a + (1 - a) max(0, n . l)) + 0.5) in binary32; box faces
  * turn with the box heading, road strips face up, the background is unlit.
- * Lit frames are rendered by the general kernel.  Host-side only (takes
- * effect at the next render, drops a captured step + render graph); GP_EINVAL
- * on a bad light. */
+ * Host-side only (takes effect at the next render, drops a captured step +
+ * render graph); GP_EINVAL on a bad light. */
 gp_status gp_sim_set_light(gp_sim *sim, const float *h_light);
 
 /* Copy the agent state [total_agents][4] out of / into the sim (device to
@@ -272,7 +271,7 @@ gp_status gp_sim_set_state(gp_sim *sim, const float *d_src, void *stream);
  * gp_batch_step_render: for each sims[k], one kinematic step with the host
  * actions h_actions[k] (float [n_agents_k][2]) followed by an rgb render of
  * every view into d_rgb[k] (device uint8 [n_views_k][H][W][3], 4-byte
- * aligned), all sims in one step launch and at most two render launches.
+ * aligned), all sims in one step launch and at most three render launches.
  * Each sim's result is bit-identical to gp_sim_step + gp_sim_render on that
  * sim alone.  Every sim must have the same image size; a sim may appear once.
  * The library packs the batch into h_staging (host memory, pinned for an

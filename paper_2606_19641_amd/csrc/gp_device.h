@@ -112,6 +112,7 @@ struct RgbCfg {
     int waves;        // wavefronts per view: 1..16
     int bcap;         // box faces one view's list holds: 64, 128 or 256
     int bins_cap;     // culling bins of the largest scene (surviving bins are listed in LDS)
+    int appear;       // 1: the instances with the directional light and traffic lights
 };
 
 // Buffers of the chip-wide rgb raster (gp_chip.hip), all inside the
@@ -159,6 +160,9 @@ size_t raycast_lds_bytes();
 // view_begin + b
 hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &c, int ordered, int view_begin,
                              int grid, hipStream_t st);
+// the same over the (sim, view) items of a batch, every sim with width x height images
+hipError_t launch_render_rgb_multi(const SimEntry *tab, const int2 *items, int n_items, const RgbCfg &c, int width,
+                                   int height, hipStream_t st);
 size_t rgb_lds_bytes(int width, int height, const RgbCfg &c);
 // chip-wide rgb raster (gp_chip.hip), same conditions as the wave-split one
 // plus 64 <= width <= 1024: the setup pass over views [view_begin,

@@ -1084,6 +1084,101 @@ __device__ __forceinline__ void store16(uint8_t *dst, const uint32_t *c)
     out[2].v = u4v{w[8], w[9], w[10], w[11]};
 }
 
+// ------------------------------------------------------------ shading
+//
+// App. A: one directional light per world, a colour per instance.  With the
+// light on, a face with outward unit normal n is lit by
+// s = a + (1 - a) max(0, n . l) (l towards the light, world frame, a the
+// ambient term), quantised to the level q = floor(255 s + 0.5) in binary32,
+// and each channel c of its colour becomes (c q + 127) / 255.  Box normals
+// follow the heading cosines (front, left, back, right, top, bottom), road
+// strips face up; the background is not lit.
+
+__device__ __forceinline__ uint32_t shade_level(const DevSim &s, float nx, float ny, int face)
+{
+    // the light is read into scalars first: selecting between fields of the
+    // kernel-argument record would make the compiler keep it in memory
+    const float lx = s.light[0], ly = s.light[1], lz = s.light[2], amb = s.light[3];
+    const float side = fmaf(nx, lx, ny * ly);
+    const float d = face < 4 ? side : (face == 4 ? lz : -lz);
+    const float sh = fmaf(1.0f - amb, fmaxf(d, 0.0f), amb);
+    return (uint32_t)fmaf(sh, 255.0f, 0.5f);
+}
+
+__device__ __forceinline__ uint32_t shade_rgb(uint32_t c, uint32_t q)
+{
+    const uint32_t r = ((c & 0xFFu) * q + 127u) / 255u;
+    const uint32_t g = (((c >> 8) & 0xFFu) * q + 127u) / 255u;
+    const uint32_t b = (((c >> 16) & 0xFFu) * q + 127u) / 255u;
+    return r | (g << 8) | (b << 16);
+}
+
+// lit colour c of face f of box j
+__device__ __forceinline__ uint32_t lit_face(const DevSim &s, const SceneRec &sc, uint32_t c, int j, int f)
+{
+    const float2 cs = s.cs[box_slot(sc, j)];
+    const float nx = f == 0 ? cs.x : f == 1 ? -cs.y : f == 2 ? -cs.x : cs.y;
+    const float ny = f == 0 ? cs.y : f == 1 ? cs.x : f == 2 ? -cs.y : -cs.x;
+    return shade_rgb(c, shade_level(s, nx, ny, f));
+}
+
+// lit colour c of the box face that a winning key names (box and face from
+// the key's primitive index)
+__device__ __forceinline__ uint32_t lit_box(const DevSim &s, const SceneRec &sc, uint32_t c, unsigned long long key)
+{
+    const int prim = (kMaxPrims - 1) - (int)(((uint32_t)key >> 8) & (uint32_t)(kMaxPrims - 1));
+    const int j = prim / 6, f = prim - 6 * j;
+    return lit_face(s, sc, c, j, f);
+}
+
+// ------------------------------------------------------------ traffic lights
+//
+// Sec. 3.1: traffic lights are small spheres.  The sample of pixel (i, j)
+// casts the ray s D, D = (a, b, f), a = i + 0.5 - cx, b = cy - (j + 0.5); it
+// meets a sphere of camera-space centre c and radius r when, at the closest
+// approach s0 = (D . c) / (D . D), the miss w = c - s0 D has w . w < r^2; the
+// fragment is the near hit at planar depth z = (s0 - sqrt((r^2 - w . w) /
+// (D . D))) f, kept for z_near <= z <= z_far.  binary32 with fmaf and
+// correctly rounded division and square root.  Lights rank with the boxes on
+// depth ties, are numbered after the roads and are not lit (emissive).
+
+// Conservative pixel bounds of the sphere's part in [z_near, z_far]: the
+// projection of its bounding box, widened by a pixel; false if none.
+__device__ __forceinline__ bool signal_bounds(const Cam &cam, const V3 &c, float r, int &i0, int &i1, int &j0,
+                                              int &j1)
+{
+    if (c.z + r < cam.zn || c.z - r > cam.zf) return false;
+    const float zlo = fmaxf(c.z - r, cam.zn), zhi = fminf(c.z + r, cam.zf);
+    const float xm = c.x - r, xM = c.x + r, ym = c.y - r, yM = c.y + r;
+    const float xr0 = xm >= 0.0f ? xm / zhi : xm / zlo, xr1 = xM >= 0.0f ? xM / zlo : xM / zhi;
+    const float yr0 = ym >= 0.0f ? ym / zhi : ym / zlo, yr1 = yM >= 0.0f ? yM / zlo : yM / zhi;
+    const float u0 = fmaf(cam.f, xr0, cam.cx), u1 = fmaf(cam.f, xr1, cam.cx);
+    const float v0 = fmaf(-cam.f, yr1, cam.cy), v1 = fmaf(-cam.f, yr0, cam.cy);
+    const float Wf = (float)cam.W, Hf = (float)cam.H;
+    i0 = max((int)fminf(fmaxf(floorf(u0 - 0.5f) - 1.0f, -1.0f), Wf), 0);
+    i1 = min((int)fminf(fmaxf(ceilf(u1 - 0.5f) + 1.0f, -1.0f), Wf), cam.W - 1);
+    j0 = max((int)fminf(fmaxf(floorf(v0 - 0.5f) - 1.0f, -1.0f), Hf), 0);
+    j1 = min((int)fminf(fmaxf(ceilf(v1 - 0.5f) + 1.0f, -1.0f), Hf), cam.H - 1);
+    return i0 <= i1 && j0 <= j1;
+}
+
+// 1/z of the light (centre xc, yc, zc, squared radius r2, fz = f zc) at the
+// sample offsets a, b (ray (a, b, f)), or 0 where the sample does not show it
+__device__ __forceinline__ float signal_invz(const Cam &cam, float xc, float yc, float zc, float r2, float fz, float a,
+                                             float b)
+{
+    const float f = cam.f, ff = f * f;
+    const float dd = fmaf(a, a, fmaf(b, b, ff));
+    const float dc = fmaf(a, xc, fmaf(b, yc, fz));
+    const float s0 = dc / dd;
+    const float wx = fmaf(-s0, a, xc), wy = fmaf(-s0, b, yc), wz = fmaf(-s0, f, zc);
+    const float qq = r2 - fmaf(wx, wx, fmaf(wy, wy, wz * wz));
+    if (!(qq > 0.0f)) return 0.0f;
+    const float z = (s0 - sqrtf(qq / dd)) * f;
+    if (!(z >= cam.zn && z <= cam.zf)) return 0.0f;
+    return 1.0f / z;
+}
+
 // ------------------------------------------------------------ work queue
 
 // Take the next view of the persistent work queue: kQueues segments of the

@@ -321,6 +321,7 @@ struct gp_sim {
     int32_t road_uniform = 0;   // every road strip of every scene has one colour
     int32_t bins_cap = 1;       // culling bins of the largest scene
     int32_t boxes_cap = 1;      // boxes (agents and obstacles) of the largest scene
+    int32_t signals_cap = 0;    // traffic lights of the scene that has the most
 };
 
 namespace {
@@ -343,16 +344,17 @@ gp_status check_lds(const gp_sim *sim, const gp_launch &l)
     return GP_OK;
 }
 
-// Box faces one view's list holds in the split rasteriser.  A box shows at
-// most three faces, one list entry each, and a view sees about a quarter of
-// its scene's boxes, so a list of twice the scene's boxes does not overflow in
-// practice; a view that overflows it all the same is rendered by the streaming
-// pass, several times slower (64 scenes of 4..128 agents with three cameras at
-// 128 x 128: 2,744 us per render with a fixed list of 96 triangles, most views
-// of the large scenes overflowing).
+// Box faces (and traffic lights) one view's list holds in the split
+// rasteriser.  A box shows at most three faces, one list entry each, and a
+// view sees about a quarter of its scene's boxes, so 3/2 of the scene's boxes
+// do not overflow in practice; a view that overflows it all the same is
+// rendered by the streaming pass, several times slower (64 scenes of 4..128
+// agents with three cameras at 128 x 128: 2,744 us per render with a fixed list
+// of 96 triangles, most views of the large scenes overflowing; 523 us with
+// twice the scene's boxes and 454 us with 3/2, one more workgroup per CU).
 int split_box_faces(const gp_sim *sim)
 {
-    return std::min(256, (sim->boxes_cap * 3 / 2 + 63) / 64 * 64);
+    return (int)std::min<int64_t>(256, (sim->boxes_cap * 3LL / 2 + sim->signals_cap / 2 + 63) / 64 * 64);
 }
 
 // Wavefronts per view in the split rasteriser: the launch's view_waves, times
@@ -382,6 +384,7 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
     c.waves = split_waves(sim, l, n_views);
     c.bcap = split_box_faces(sim);
     c.bins_cap = sim->bins_cap;
+    c.appear = (sim->dev.shade || sim->lay.n_signals > 0) ? 1 : 0;
     return c;
 }
 
@@ -392,21 +395,22 @@ bool chip_ok(const gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, int 
            reinterpret_cast<uintptr_t>(o.rgb) % 16 == 0 && sim->bins_cap <= sim->lay.bins_stride;
 }
 
-// can this render take the split rasteriser?
-bool split_ok(const gp_sim *sim, const gp_launch &l, int kind)
+// can rgb-only renders take the split rasteriser?
+bool split_ok(const gp_sim *sim, const gp_launch &l)
 {
-    return l.raster == GP_RASTER_SPLIT && kind == 1 && sim->cfg.width >= 16 && sim->cfg.cam_height > 0.0f &&
+    return l.raster == GP_RASTER_SPLIT && sim->road_uniform && sim->cfg.width >= 16 && sim->cfg.cam_height > 0.0f &&
            gp::rgb_lds_bytes(sim->cfg.width, sim->cfg.height, rgb_cfg(sim, l, sim->lay.n_views)) <= sim->max_lds;
 }
 
 gp_status render_impl(gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, hipStream_t st)
 {
     const gp::LaunchCfg c = launch_cfg(l);
-    // the rgb-only kernels serve renders without depth / primitive id when
-    // every road strip has the same colour; everything else takes the general one
-    // (scenes with traffic lights take the general kernel's instances with lights)
+    // renders without depth / primitive id of sims whose road strips share one
+    // colour take the split rasteriser, lit or not, or the other rgb kernels
+    // where they have neither light nor traffic lights; everything else takes
+    // the general one (its instances with lights for scenes with traffic lights)
     const int kind = sim->lay.n_signals > 0 ? 2 : (!o.depth && !o.primid && sim->dev.road_color_uniform) ? 1 : 0;
-    const bool split = split_ok(sim, l, kind);
+    const bool split = !o.depth && !o.primid && split_ok(sim, l);
     const gp::RgbCfg rc = rgb_cfg(sim, l, sim->lay.n_views);
     hipError_t e;
     if (chip_ok(sim, o, l, kind)) {
@@ -588,6 +592,7 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
         bbase += (int32_t)sb.size();
         sim->bins_cap = std::max<int32_t>(sim->bins_cap, (int32_t)sb.size());
         sim->boxes_cap = std::max(sim->boxes_cap, d.n_agents + d.n_static);
+        sim->signals_cap = std::max(sim->signals_cap, d.n_signals);
     }
     std::memcpy(at(L.scenes), sim->scenes.data(), sizeof(gp::SceneRec) * n_scenes);
     std::memcpy(at(L.palette), cfg->palette, 768);
@@ -756,7 +761,7 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     {
         gp_launch t = l;
         t.raster = GP_RASTER_SPLIT;
-        if (split_ok(sim, t, 1)) {
+        if (split_ok(sim, t)) {
             l.raster = GP_RASTER_SPLIT;
             if (cfg->width % 16 == 0 && (int64_t)cfg->width * cfg->height <= 128 * 128) l.blocks_per_cu = 8;
         } else if (L.chip && cfg->cam_height > 0.0f) {
@@ -1002,15 +1007,42 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
         return fail(GP_ENOMEM, "batch needs %lld bytes of workspace and staging", (long long)B.total);
     if (n_views > INT32_MAX) return fail(GP_EINVAL, "too many views in one batch");
 
+    // The rgb renders of a batch go in up to three launches: the split raster
+    // for sims without light and traffic lights, its instances with them, and
+    // the banded kernels for the rest (mixed road colours; every sim where the
+    // first sim's launch setting asks for another rasteriser or the split
+    // raster's LDS does not fit), themselves in one launch per kind.
+    const gp_launch &l = sims[0]->launch;
+    const gp::LaunchCfg c = launch_cfg(l);
+    const int W = sims[0]->cfg.width, H = sims[0]->cfg.height;
+    gp::RgbCfg rc = rgb_cfg(sims[0], l, n_views);
+    for (int k = 1; k < n_sims; ++k) {
+        rc.bcap = std::max(rc.bcap, split_box_faces(sims[k]));
+        rc.bins_cap = std::max(rc.bins_cap, sims[k]->bins_cap);
+    }
+    const bool split = l.raster == GP_RASTER_SPLIT && W >= 16 && gp::rgb_lds_bytes(W, H, rc) <= sims[0]->max_lds;
+    enum { B_SPLIT = 0, B_APPEAR, B_FAST, B_GENERAL, B_N };
+    auto group_of = [&](const gp_sim *sim) {
+        if (split && sim->road_uniform) return sim->dev.road_color_uniform ? B_SPLIT : B_APPEAR;
+        return sim->dev.road_color_uniform ? B_FAST : B_GENERAL;
+    };
+    int64_t gn[B_N] = {}, g0[B_N + 1] = {};
+    for (int k = 0; k < n_sims; ++k) gn[group_of(sims[k])] += sims[k]->lay.n_views;
+    for (int g = 0; g < B_N; ++g) g0[g + 1] = g0[g] + gn[g];
+    for (int fast = 1; fast >= 0; --fast)
+        if (gn[fast ? B_FAST : B_GENERAL] > 0 && gp::render_lds_bytes(W, H, c, fast) > sims[0]->max_lds)
+            return fail(GP_EINVAL, "launch setting needs more LDS than the device has");
+
     // host image of the batch buffer: zeroed queue counters, the sim table,
-    // the (sim, view) items (rgb-kernel sims first), the packed actions
+    // the (sim, view) items group by group, the packed actions
     unsigned char *h = static_cast<unsigned char *>(h_staging);
     unsigned char *d = static_cast<unsigned char *>(d_ws);
     std::memset(h + B.ctl, 0, 16);
     auto *tab = reinterpret_cast<gp::SimEntry *>(h + B.table);
     auto *items = reinterpret_cast<int32_t *>(h + B.items);
     auto *act = reinterpret_cast<float *>(h + B.actions);
-    int64_t a0 = 0, n_fast = 0;
+    int64_t a0 = 0, at[B_N];
+    std::copy(g0, g0 + B_N, at);
     bool lights = false;          // the general launch takes the instances with traffic lights
     for (int k = 0; k < n_sims; ++k) {
         const gp_sim *sim = sims[k];
@@ -1021,17 +1053,12 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
         std::memcpy(&tab[k], &e, sizeof(e));
         std::memcpy(act + 2 * a0, h_actions[k], 8 * (size_t)sim->lay.n_agents);
         a0 += sim->lay.n_agents;
-        if (sim->dev.road_color_uniform) n_fast += sim->lay.n_views;
-        lights = lights || sim->lay.n_signals > 0;
-    }
-    int64_t qf = 0, qg = n_fast;
-    for (int k = 0; k < n_sims; ++k) {
-        const gp_sim *sim = sims[k];
-        int64_t &q = sim->dev.road_color_uniform ? qf : qg;
+        const int g = group_of(sim);
+        lights = lights || (g == B_GENERAL && sim->lay.n_signals > 0);
         for (int64_t v = 0; v < sim->lay.n_views; ++v) {
-            items[2 * q] = k;
-            items[2 * q + 1] = (int32_t)v;
-            ++q;
+            items[2 * at[g]] = k;
+            items[2 * at[g] + 1] = (int32_t)v;
+            ++at[g];
         }
     }
     hipStream_t hs = static_cast<hipStream_t>(stream);
@@ -1042,16 +1069,16 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
     auto *ctl = reinterpret_cast<uint32_t *>(d + B.ctl);
     e = gp::launch_step_multi(dtab, n_sims, max_agents, hs);
     if (e != hipSuccess) return hip_fail(e, "batch step launch");
-    const gp_launch &l = sims[0]->launch;
-    const gp::LaunchCfg c = launch_cfg(l);
-    const int W = sims[0]->cfg.width, H = sims[0]->cfg.height;
-    for (int fast = 1; fast >= 0; --fast) {
-        const int64_t n = fast ? n_fast : n_views - n_fast;
-        if (n == 0) continue;
-        if (gp::render_lds_bytes(W, H, c, fast) > sims[0]->max_lds)
-            return fail(GP_EINVAL, "launch setting needs more LDS than the device has");
-        const int grid = (int)std::min<int64_t>(n, (int64_t)l.blocks_per_cu * sims[0]->n_cu);
-        e = gp::launch_render_multi(dtab, ditems + (fast ? 0 : n_fast), (int)n, ctl + (fast ? 0 : 2), c,
+    for (int g = B_SPLIT; g <= B_APPEAR; ++g) {
+        rc.appear = g == B_APPEAR;
+        e = gp::launch_render_rgb_multi(dtab, ditems + g0[g], (int)gn[g], rc, W, H, hs);
+        if (e != hipSuccess) return hip_fail(e, "batch render launch");
+    }
+    for (int g = B_FAST; g <= B_GENERAL; ++g) {
+        const int fast = g == B_FAST;
+        if (gn[g] == 0) continue;
+        const int grid = (int)std::min<int64_t>(gn[g], (int64_t)l.blocks_per_cu * sims[0]->n_cu);
+        e = gp::launch_render_multi(dtab, ditems + g0[g], (int)gn[g], ctl + (fast ? 0 : 2), c,
                                     fast ? 1 : (lights ? 2 : 0), W, H, grid, hs);
         if (e != hipSuccess) return hip_fail(e, "batch render launch");
     }

@@ -101,3 +101,65 @@ def test_wavefronts_for_few_views(scenes):
     for waves in (1, 2, 4):
         sim.set_launch(raster=1, view_waves=waves)
         _check(sim, sc, cam, pal, [(0, a, 0) for a in range(4)], (scenes, waves))
+
+
+def _street(seed, n_agents, n_static, n_signals, radius=20.0):
+    """A crowd with obstacles and lights all around it, some of the lights close
+    to the cameras and cut by the near plane, one colour of road."""
+    s = _crowd(seed, n_agents, n_roads=60, radius=radius)
+    rng = np.random.default_rng(seed)
+    k = n_static
+    s.static_xyp = np.stack([rng.uniform(-radius, radius, k), rng.uniform(-radius, radius, k),
+                             rng.uniform(-3, 3, k)], 1).astype(np.float32)
+    s.static_dims = np.stack([rng.uniform(1, 6, k), rng.uniform(0.5, 2, k), rng.uniform(0.5, 2, k)], 1).astype(np.float32)
+    s.static_color = np.full(k, 4, np.uint8)
+    q = n_signals
+    s.signal_xyzr = np.stack([rng.uniform(-radius, radius, q), rng.uniform(-radius, radius, q), rng.uniform(0.5, 5, q),
+                              rng.uniform(0.1, 1.5, q)], 1).astype(np.float32)
+    s.signal_color = rng.integers(6, 9, q).astype(np.uint8)
+    return s
+
+
+@pytest.mark.parametrize("lit", [False, True])
+@pytest.mark.parametrize("counts", [(4, 0, 1), (6, 3, 64), (5, 2, 65), (30, 20, 0), (90, 100, 130)])
+def test_light_and_traffic_lights(counts, lit):
+    """The instances with the directional light and traffic lights: up to one
+    light unit and more, a list that overflows (boxes and lights streamed), the
+    state colours changing; alone and in a batch with a plain sim."""
+    print(f"appearance: {counts} lit {lit}", flush=True)
+    from paper_2606_19641_amd import gp
+    scenes = [_street(70 + sum(counts), *counts), _street(71, 3, 1, 2)]
+    cam = g.camera_for(80, 64, g.FRONT_AND_SIDES)
+    pal = g.mixed_palette()
+    pal[6:9] = ((255, 32, 32), (255, 200, 0), (32, 224, 64))
+    sims = [gp.Sim([s], cam, pal) for s in scenes] + [gp.Sim([_crowd(72, 6)], cam, pal)]
+    both = gp.Sim(scenes, cam, pal)
+    for s in sims[:2] + [both]:
+        s.set_light((0.6, -0.48, 0.64, 0.25) if lit else None)
+    n = counts[0]
+    for waves in (1, 2, 4):
+        for step in range(2):
+            if step and both.n_signals:
+                both.set_signal_colors(torch.from_numpy(np.roll(np.concatenate([s.signal_color for s in scenes]), 1)).cuda())
+            both.set_launch(raster=1, view_waves=waves)
+            rgb, _, _ = both.render()
+            ref, _, _ = both.render(depth=True, primid=True)
+            torch.cuda.synchronize()
+            assert torch.equal(rgb, ref), (counts, lit, waves, step)
+    # a batch: the plain sim and the two streets, each as alone
+    acts = [np.zeros((s.n_agents, 2), np.float32) for s in sims]
+    alone = []
+    for s, a in zip(sims, acts):
+        keep = s.get_state()
+        s.step(torch.from_numpy(a).cuda())
+        alone.append(s.render(depth=True, primid=True)[0])
+        s.set_state(keep)
+    nb = gp.batch_required_bytes(sims)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    st = torch.empty(nb, dtype=torch.uint8, pin_memory=True)
+    out = [s.new_rgb() for s in sims]
+    gp.batch_step_render(sims, acts, out, ws, st)
+    torch.cuda.synchronize()
+    for k in range(3):
+        assert torch.equal(out[k], alone[k]), (counts, lit, "batch", k)
+    assert n == sims[0].n_agents
