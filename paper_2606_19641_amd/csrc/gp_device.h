@@ -115,6 +115,15 @@ struct RgbCfg {
     int appear;       // 1: the instances with the directional light and traffic lights
 };
 
+// Settings of the ray caster (gp_raycast.hip).
+struct RcCfg {
+    int waves;        // wavefronts per view: 1..16
+    int bcap;         // boxes and lights the LDS list holds, a multiple of 64
+    int bins_cap;     // culling bins of the largest scene
+    int band_rows;    // rows of the key band (at least)
+    int cover;        // 1: roads as coverage bits
+};
+
 // Buffers of the chip-wide rgb raster (gp_chip.hip), all inside the
 // workspace.  The coverage words and the counters are zero between renders.
 enum { CHIP_NITEMS = 0, CHIP_NCTL = 8 };
@@ -152,9 +161,10 @@ hipError_t launch_render(const DevSim &s, const RenderOut &o, const LaunchCfg &c
                          int persistent, int view_begin, int grid, hipStream_t st);
 size_t render_lds_bytes(const DevSim &s, const LaunchCfg &c, int fast);
 size_t render_lds_bytes(int width, int height, const LaunchCfg &c, int fast);
-// ray-cast backend (gp_raycast.hip): one workgroup per view of [view_begin, view_begin + n_views)
-hipError_t launch_raycast(const DevSim &s, const RenderOut &o, int view_begin, int n_views, hipStream_t st);
-size_t raycast_lds_bytes();
+// ray-cast backend (gp_raycast.hip): one workgroup per view order[view_begin ..
+// view_begin + n_views); c.cover: rgb only, one road colour, width >= 16
+hipError_t launch_raycast(const DevSim &s, const RenderOut &o, const RcCfg &c, int view_begin, int n_views, hipStream_t st);
+size_t raycast_lds_bytes(int width, int height, const RcCfg &c);
 // wave-split rgb raster (gp_raster.hip) for uniform road colours, no depth /
 // primitive id and width >= 16: workgroup b renders view order[b] (ordered) or
 // view_begin + b

@@ -650,6 +650,11 @@ __device__ __forceinline__ void lds_or64(lptr<unsigned long long> p, unsigned lo
     __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+__device__ __forceinline__ void lds_or32(lptr<uint32_t> p, uint32_t v)
+{
+    __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 __device__ __forceinline__ unsigned lane_id() { return __lane_id(); }
 
 // Whole-record LDS copies as 16-byte vectors (the records' implicit copy

@@ -47,926 +47,11 @@
 // file is compiled with -ffp-contract=off, correctly rounded division and
 // IEEE denormals.
 
-#include "gp_device.h"
-#include "gp_geom.h"
+#include "gp_view.h"
 
 namespace gp {
 
 namespace {
-
-constexpr int kSharedRing = 768;   // strips passed by the cheap test, one ring per view (road slot indices)
-constexpr int kWTris = 64;      // road primitives (quads, triangles) staged for one span pass
-constexpr int kSetupBatch = kWTris;       // strips of one set-up job at most (one quad each; the rest are queued)
-constexpr int kWClip = kSetupBatch;       // strips of one job waiting for the clipper (from the front) or
-                                          // for their fan triangles (from the back)
-constexpr int kWaveBytes = kWTris * 48 + kWClip * 4;
-static_assert(kWaveBytes % 16 == 0, "wave regions stay 16-byte aligned");
-static_assert(sizeof(Prim) == 48, "staged primitive size");
-
-// LDS counters
-enum { R_NSB = 0, R_NEXT, R_NBT, R_BOVF, R_BMIN, R_BMAX, R_RING, R_RESV, R_JOB, R_NCNT = 12 };
-constexpr int kBoxClip = 64;     // box faces waiting for the clipper (one setup pass)
-
-struct RgbLds {
-    lptr<int32_t> cnt;               // [R_NCNT]
-    lptr<unsigned long long> bits;   // road coverage: bit (j - hr0) * W + i is sample i of row j >= hr0
-    lptr<FaceRec> faces;             // [bcap] the view's box faces
-    lptr<int32_t> sbins;             // [bins_cap] surviving bins: start * 128 + count
-    lptr<int32_t> cq;                // [kBoxClip] box faces to clip (box * 8 + face)
-    lptr<int32_t> sring;             // [kSharedRing] strips that passed the cheap test (this round)
-    lptr<unsigned char> waves;       // K regions of kWaveBytes
-    // after the units the memory from sbins on is free again: the pattern table, then masks and spans or keys
-    lptr<gp_v4i> pat;                // [3][64] the 16 bytes at byte phase p of a run of six pixels, by its coverage bits
-    lptr<unsigned long long> work;   // masks and spans, or rows of 64-bit keys
-    int bcap, krows;
-    int hr0;                         // first image row below the horizon
-    int nmw;                         // 64-bit words of a face mask (bcap / 64)
-    int region;                      // bytes from work to the end
-};
-
-__host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-
-// byte offsets of the LDS sections (shared by the carve and the size query)
-struct RgbLayout {
-    size_t cnt, bits, faces, sbins, cq, sring, waves, total;
-};
-
-constexpr int kPatBytes = 3 * 64 * 16;
-
-// rows that can show road: below the principal point (the road's 1/z there is
-// positive only where (j + 0.5) - H / 2 is)
-__host__ __device__ inline int first_road_row(int H) { return (H + 1) >> 1; }
-
-__host__ __device__ inline RgbLayout rgb_layout(int W, int H, const RgbCfg &c)
-{
-    RgbLayout l;
-    // whole words of the flat coverage bits, and one more for reads across a word end
-    const size_t nbw = ((size_t)W * (size_t)(H - first_road_row(H)) + 63) / 64 + 1;
-    size_t o = 0;
-    l.cnt = o; o = align16(o + 4 * R_NCNT);
-    l.bits = o; o = align16(o + 8 * nbw);
-    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
-    l.cq = o; o = align16(o + 4 * (size_t)kBoxClip);
-    l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
-    l.sring = o; o = align16(o + 4 * (size_t)kSharedRing);
-    l.waves = o; o = align16(o + (size_t)kWaveBytes * (size_t)c.waves);
-    // the memory from sbins on holds the pattern table and a row of keys (or of masks and spans)
-    const size_t least = align16(l.sbins + kPatBytes + 8 * (size_t)W);
-    o = o > least ? o : least;
-    l.total = o;
-    return l;
-}
-
-// ------------------------------------------------------------ per-wave state
-
-struct WaveSt {
-    lptr<Prim> tris;         // [kWTris] road primitives
-    lptr<int32_t> clipq;     // [kWClip] road slots (global): nclip for the clipper at the front,
-                             // nfan for their two fan triangles at the back
-    int nclip, nfan;         // queued strips
-};
-
-// OR the coverage bits [b0, b1] into their words
-__device__ __forceinline__ void or_span(lptr<unsigned long long> bits, int b0, int b1)
-{
-    const int w0 = b0 >> 6, w1 = b1 >> 6;
-    for (int w = w0; w <= w1; ++w) {
-        const int lo = (w == w0) ? (b0 & 63) : 0;
-        const int hi = (w == w1) ? (b1 & 63) : 63;
-        const unsigned long long m = (~0ull >> (63 - hi)) & (~0ull << lo);
-        lds_or64(bits + w, m);
-    }
-}
-
-// the coverage bits from b on (at least 32 of them), bit 0 first
-__device__ __forceinline__ uint32_t bits_at(const RgbLds &L, int b)
-{
-    lptr<const uint32_t> w = (lptr<const uint32_t>)L.bits + (b >> 5);
-    return __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
-}
-
-// Rasterise the n staged road triangles into the coverage bitmask.  Lane t
-// first takes the first row of triangle t; the further rows of triangles
-// that span several rows are then dealt to the lanes by a prefix over their
-// counts.  Per (triangle, row) the exact span of covered samples is OR-ed
-// into the row's coverage words.
-__device__ __forceinline__ void road_spans(const RgbLds &L, const Cam &cam, const WaveSt &ws, int n)
-{
-    const int ln = (int)lane_id();
-    wave_lds_order();
-    for (int t0 = 0; t0 < n; t0 += 64) {
-        const int t = t0 + ln;
-        int c = 0;
-        if (t < n) {
-            const int32_t jj = ((lptr<const int32_t>)(ws.tris + t))[8];     // j0 | j1 << 16
-            c = (jj >> 16) - (int)(int16_t)(jj & 0xFFFF);
-        }
-        const int incl = wave_incl_scan(c);
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        const int excl = incl - c;
-        for (int g0 = -64; g0 < total; g0 += 64) {
-            // g0 < 0: lane t's own first row; then the dealt further rows
-            const int gi = g0 + ln;
-            int o = ln, extra = 0;
-            bool act = t < n;
-            if (g0 >= 0) {
-                o = owner_of(incl, gi);
-                extra = 1 + gi - __shfl(excl, o);
-                act = gi < total;
-            }
-            if (act) {
-                const Prim pr = lds_load(ws.tris + t0 + o);
-                const int j = pr.j0 + extra;
-                int xl, xr;
-                // (the row test holds for every row with road unless 1/z underflows)
-                const float rz = fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C);
-                const int b = (j - L.hr0) * cam.W;
-                if ((b >= 0) & (rz > 0.0f) & prim_span(pr, j, cam.W, xl, xr)) or_span(L.bits, b + xl, b + xr);
-            }
-        }
-    }
-    wave_lds_order();
-}
-
-// Stage the triangles held by the lanes (v0: t0, v1: t1); returns how many.
-__device__ __forceinline__ int stage_tris(const WaveSt &ws, bool v0, const Prim &t0, bool v1, const Prim &t1)
-{
-    const unsigned long long b0 = __ballot(v0), b1 = __ballot(v1);
-    const int n0 = __popcll(b0);
-    if (v0) lds_store(ws.tris + lanes_below(b0), t0);
-    if (v1) lds_store(ws.tris + n0 + lanes_below(b1), t1);
-    return n0 + __popcll(b1);
-}
-
-// Clip up to four queued strips (the last ones of the queue), one per 16-lane
-// segment; stages their fan triangles and returns how many.
-__device__ __forceinline__ int road_clip(const DevSim &s, const Cam &cam, WaveSt &ws)
-{
-    const int m = min(ws.nclip, 4);
-    const int seg = (int)lane_id() >> 4;
-    const bool live = seg < m;
-    Poly P = {};
-    if (live) {
-        const int g = ws.clipq[ws.nclip - m + seg];
-        road_corners(s, cam, g, P.v);
-    }
-    P.n = dir_to_cam(cam, 0.0f, 0.0f, 1.0f);
-    P.one_sided = false;
-    P.keylo = 0u;
-    ws.nclip -= m;
-    TriRec t;
-    const bool ok = clip_seg<false>(cam, P, live, 0, cam.H, t);
-    Prim none = {};
-    return stage_tris(ws, ok, prim_of(t.g), false, none);
-}
-
-// The two fan triangles of up to 32 queued strips (the last ones queued at
-// the back of the queue); stages them and returns how many.  Their corners
-// and snap are computed again, as the set-up computed them.
-__device__ __forceinline__ int road_fan(const DevSim &s, const Cam &cam, WaveSt &ws)
-{
-    const int m = min(ws.nfan, 32);
-    const int ln = (int)lane_id();
-    Prim p0 = {}, p1 = {};
-    bool v0 = false, v1 = false;
-    if (ln < m) {
-        const int g = ws.clipq[kWClip - ws.nfan + ln];
-        V3 v[4];
-        road_corners(s, cam, g, v);
-        int32_t X[4], Y[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) snap(cam, v[k], X[k], Y[k]);
-        TriGeo t0, t1;
-        v0 = make_tri(cam, false, X[0], Y[0], X[1], Y[1], X[2], Y[2], 0, cam.H, t0);
-        v1 = make_tri(cam, false, X[0], Y[0], X[2], Y[2], X[3], Y[3], 0, cam.H, t1);
-        if (v0) p0 = prim_of(t0);
-        if (v1) p1 = prim_of(t1);
-    }
-    ws.nfan -= m;
-    return stage_tris(ws, v0, p0, v1, p1);
-}
-
-// Full setup of the n (<= kSetupBatch) strips ring[a .. a + n): clip test,
-// snap, and the quad of the strips whose quad covers exactly what their two
-// fan triangles cover (staged; returns how many); strips that need the
-// clipper join the front of the wave's queue, strips that need their fan
-// triangles its back (both empty when a job starts).
-__device__ __forceinline__ int road_setup(const DevSim &s, const Cam &cam, const RgbLds &L, WaveSt &ws, int a, int n)
-{
-    const int ln = (int)lane_id();
-    wave_lds_order();
-    const bool live = ln < n;
-    int g = 0;
-    V3 v[4] = {};
-    if (live) {
-        g = L.sring[a + ln];
-        road_corners(s, cam, g, v);
-    }
-    const bool clip = live && needs_clip(cam, v);
-    const unsigned long long cb = __ballot(clip);
-    if (clip) ws.clipq[ws.nclip + lanes_below(cb)] = g;
-    ws.nclip += __popcll(cb);
-    Prim p0 = {};
-    bool v0 = false, fan = false;
-    if (live && !clip) {
-        int32_t X[4], Y[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) snap(cam, v[k], X[k], Y[k]);
-        // one quad where it covers exactly what the two fan triangles cover
-        const int qs = make_quad(cam, false, X, Y, 0, cam.H, p0);
-        v0 = qs > 0;
-        fan = qs < 0;
-    }
-    const unsigned long long fb = __ballot(fan);
-    if (fan) ws.clipq[kWClip - 1 - (ws.nfan + lanes_below(fb))] = g;
-    ws.nfan += __popcll(fb);
-    Prim none = {};
-    return stage_tris(ws, v0, p0, false, none);
-}
-
-// One set-up job: the n ring strips from a set up, their primitives
-// rasterised into the coverage bitmask, then the strips that needed their fan
-// triangles (32 at a time) and those that needed the clipper (four at a time).
-__device__ __forceinline__ void setup_job(const DevSim &s, const Cam &cam, const RgbLds &L, WaveSt &ws, int a, int n)
-{
-    int ntri = road_setup(s, cam, L, ws, a, n);
-    for (;;) {
-        if (ntri > 0) road_spans(L, cam, ws, ntri);
-        if (ws.nfan > 0)
-            ntri = road_fan(s, cam, ws);
-        else if (ws.nclip > 0)
-            ntri = road_clip(s, cam, ws);
-        else
-            break;
-    }
-}
-
-// The cheap test of one unit's strips (loaded by load_unit into q0, q1); the
-// survivors' slots go to the view's ring (64 entries were reserved).
-__device__ __forceinline__ void road_unit(const Cam &cam, const RgbLds &L, bool live, int g, const float4 &q0,
-                                          const float4 &q1)
-{
-    float x[4], z[4];
-    ground_xz(cam, q0.x, q0.y, x[0], z[0]);
-    ground_xz(cam, q0.z, q0.w, x[1], z[1]);
-    ground_xz(cam, q1.x, q1.y, x[2], z[2]);
-    ground_xz(cam, q1.z, q1.w, x[3], z[3]);
-    const bool pass = live && !road_culled<false>(cam, x, z);
-    const unsigned long long bm = __ballot(pass);
-    int base = 0;
-    if (lane_id() == 0 && bm != 0ull) base = lds_add(L.cnt + R_RING, __popcll(bm));
-    base = __shfl(base, 0);
-    if (pass) L.sring[base + lanes_below(bm)] = g;
-}
-
-// strip data of unit u (lane l: strip l % 16 of surviving bin 4 u + l / 16)
-__device__ __forceinline__ bool load_unit(const DevSim &s, const SceneRec &sc, const RgbLds &L, int nsb, int u,
-                                          int &g, float4 &q0, float4 &q1)
-{
-    const int ln = (int)lane_id();
-    const int bi = 4 * u + (ln >> 4), k = ln & 15;
-    bool live = false;
-    if (u >= 0 && bi < nsb) {
-        const int pk = L.sbins[bi];
-        live = k < (pk & 127);
-        if (live) {
-            g = sc.road_base + (pk >> 7) + k;
-            q0 = s.roads[2 * g];
-            q1 = s.roads[2 * g + 1];
-        }
-    }
-    return live;
-}
-
-// ------------------------------------------------------------ boxes
-
-// Reserve n entries of the box list: at the wave's own count nbt (shared
-// false: the overflow path's private list), or through the view's LDS
-// counter (shared: several wavefronts append); returns the first entry, or
-// -1 (marking the view overflowed when shared) if they would not fit.
-__device__ __forceinline__ int box_reserve(const RgbLds &L, bool shared, int &nbt, int n)
-{
-    if (!shared) {
-        if (nbt + n > L.bcap) return -1;
-        const int at = nbt;
-        nbt += n;
-        return at;
-    }
-    int at = 0;
-    if (lane_id() == 0 && n > 0) at = lds_add(L.cnt + R_NBT, n);
-    at = __builtin_amdgcn_readfirstlane(__shfl(at, 0));
-    if (at + n > L.bcap) {
-        if (lane_id() == 0) L.cnt[R_BOVF] = 1;
-        return -1;
-    }
-    return at;
-}
-
-// the colour of face f of box j, lit where the sim has a light
-template <bool AP>
-__device__ __forceinline__ uint32_t face_rgb(const DevSim &s, const SceneRec &sc, int j, int f)
-{
-    const uint32_t c = s.box_rgb[box_slot(sc, j)];
-    return AP && s.shade ? lit_face(s, sc, c, j, f) : c;
-}
-
-// the colour of traffic light g's state (never lit)
-__device__ __forceinline__ uint32_t signal_rgb(const DevSim &s, const SceneRec &sc, int g)
-{
-    const int c = s.signal_color[sc.signal_base + g];
-    return (uint32_t)s.palette[3 * c] | ((uint32_t)s.palette[3 * c + 1] << 8) | ((uint32_t)s.palette[3 * c + 2] << 16);
-}
-
-// Traffic lights [g0, g0 + 64) of the scene into the view's list: an entry
-// holds the sphere test's terms (centre, squared radius, f zc) and the pixel
-// rectangle its image lies in (columns X3 .. Y3); nv = 0 tells it from a face.
-__device__ __forceinline__ bool light_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int g0,
-                                           bool shared, int &nbt, int &bmin, int &bmax)
-{
-    const int g = g0 + (int)lane_id();
-    bool keep = false;
-    FaceRec f = {};
-    if (g < sc.n_signals) {
-        const float4 q = s.signals[sc.signal_base + g];
-        const V3 c = to_cam(cam, q.x - cam.px, q.y - cam.py, q.z);
-        int i0, i1, j0, j1;
-        keep = signal_bounds(cam, c, q.w, i0, i1, j0, j1);
-        if (keep) {
-            f.X0 = __float_as_int(c.x); f.Y0 = __float_as_int(c.y); f.X1 = __float_as_int(c.z);
-            f.Y1 = __float_as_int(q.w * q.w); f.X2 = __float_as_int(cam.f * c.z);
-            f.X3 = i0; f.Y3 = i1;
-            f.j0 = (int16_t)j0; f.j1 = (int16_t)j1;
-            f.keylo = key_low(1u, 6 * (sc.n_agents + sc.n_static) + sc.n_roads + g, 0u);
-            f.rgb = signal_rgb(s, sc, g);
-        }
-    }
-    const unsigned long long bm = __ballot(keep);
-    const int at = box_reserve(L, shared, nbt, __popcll(bm));
-    if (at < 0) return false;
-    if (keep) {
-        const int t = at + lanes_below(bm);
-        f.keylo |= (uint32_t)t;
-        lds_store(L.faces + t, f);
-        bmin = min(bmin, (int)f.j0);
-        bmax = max(bmax, (int)f.j1);
-    }
-    return true;
-}
-
-// One setup pass over box face candidates [c0, c0 + P) (P <= 64): candidate c
-// is face c % 6 of box surv[c / 6] (use_surv), or of box c / 6 culled here.
-// Fast faces and the triangles of clipped faces (clip queue cq) are appended
-// to the box list (box_reserve), the low byte of each key word naming the
-// entry; returns false as soon as they would not fit (the list is then
-// incomplete: the view takes the overflow path, which ignores it).  Six
-// candidates at a time never overflow a private list of 64 (at most 10
-// triangles each).
-template <bool AP>
-__device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                         lptr<const int32_t> surv, bool use_surv, int ncand, int c0, int P, lptr<int32_t> cq,
-                         bool shared, int &nbt, int &bmin, int &bmax)
-{
-    const int ln = (int)lane_id();
-    const int c = c0 + ln;
-    bool live = ln < P && c < ncand;
-    int j = 0, f = 0;
-    if (live) {
-        j = use_surv ? surv[c / 6] : c / 6;
-        f = c - 6 * (c / 6);
-        if (!use_surv) live = j != ego && !box_outside(s, sc, cam, j);
-    }
-    Poly Pf;
-    FaceRec f0, f1;
-    bool v0 = false, v1 = false, clip = false;
-    if (live) {
-        build_face(s, sc, cam, j, f, Pf);
-        fast_face(cam, Pf, face_rgb<AP>(s, sc, j, f), 0, cam.H, f0, v0, f1, v1, clip);
-    }
-    const unsigned long long b0 = __ballot(v0), b1 = __ballot(v1), bc = __ballot(clip);
-    const int n0 = __popcll(b0), nf = n0 + __popcll(b1), ncl = __popcll(bc);
-    const int at = box_reserve(L, shared, nbt, nf);
-    if (at < 0) return false;
-    if (v0) {
-        const int t = at + lanes_below(b0);
-        f0.keylo = (f0.keylo & ~0xFFu) | (uint32_t)t;
-        lds_store(L.faces + t, f0);
-        bmin = min(bmin, (int)f0.j0);
-        bmax = max(bmax, (int)f0.j1);
-    }
-    if (v1) {
-        const int t = at + n0 + lanes_below(b1);
-        f1.keylo = (f1.keylo & ~0xFFu) | (uint32_t)t;
-        lds_store(L.faces + t, f1);
-        bmin = min(bmin, (int)f1.j0);
-        bmax = max(bmax, (int)f1.j1);
-    }
-    if (clip) cq[lanes_below(bc)] = j * 8 + f;
-    wave_lds_order();
-    // the clipped faces, four per wavefront
-    for (int q0 = 0; q0 < ncl; q0 += 4) {
-        const int q = q0 + (ln >> 4);
-        const bool lv = q < ncl;
-        Poly Q = {};
-        uint32_t rgb = 0u;
-        if (lv) {
-            const int code = cq[q];
-            build_face(s, sc, cam, code >> 3, code & 7, Q);
-            rgb = face_rgb<AP>(s, sc, code >> 3, code & 7);
-        }
-        TriRec t;
-        const bool ok = clip_seg<true>(cam, Q, lv, 0, cam.H, t);
-        const unsigned long long bo = __ballot(ok);
-        const int ato = box_reserve(L, shared, nbt, __popcll(bo));
-        if (ato < 0) return false;
-        if (ok) {
-            const int e = ato + lanes_below(bo);
-            t.keylo = (t.keylo & ~0xFFu) | (uint32_t)e;
-            lds_store(L.faces + e, face_of(t, rgb));
-            bmin = min(bmin, (int)t.g.j0);
-            bmax = max(bmax, (int)t.g.j1);
-        }
-    }
-    return true;
-}
-
-// the rows bmin .. bmax that the lanes' entries reach added to the view's box rows
-__device__ __forceinline__ void box_rows(const RgbLds &L, int bmin, int bmax)
-{
-    bmin = wave_min(bmin);
-    bmax = wave_max(bmax);
-    if (lane_id() == 0 && bmax >= 0) {
-        lds_min(L.cnt + R_BMIN, bmin);
-        lds_max(L.cnt + R_BMAX, bmax);
-    }
-}
-
-// Light unit k: traffic lights [64 k, 64 (k + 1)) of the scene.
-__device__ __forceinline__ void do_lights(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int k)
-{
-    int nbt = 0, bmin = 0x7FFFFFFF, bmax = -1;
-    if (light_pass(s, sc, cam, L, 64 * k, true, nbt, bmin, bmax)) box_rows(L, bmin, bmax);
-}
-
-// Box unit k: cull boxes [unit k, unit (k + 1)) of the scene (unit <= 64), list
-// the survivors, set up their faces into the view's box list
-// (shared by the wavefronts; its row range kept with LDS min / max).  scr:
-// 128 ints of the wavefront's staging (survivors, then the clip queue).
-template <bool AP>
-__device__ __forceinline__ void do_boxes(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                                         int k, int unit, lptr<int32_t> scr)
-{
-    const int ln = (int)lane_id();
-    const int nbox = sc.n_agents + sc.n_static;
-    const int j = unit * k + ln;
-    const bool keep = ln < unit && j < nbox && j != ego && !box_outside(s, sc, cam, j);
-    const unsigned long long bm = __ballot(keep);
-    if (keep) scr[lanes_below(bm)] = j;
-    const int ns = __popcll(bm);
-    wave_lds_order();
-    int nbt = 0, bmin = 0x7FFFFFFF, bmax = -1;
-    for (int c0 = 0; c0 < 6 * ns; c0 += 64)
-        if (!box_pass<AP>(s, sc, cam, ego, L, scr, true, 6 * ns, c0, 64, scr + 64, true, nbt, bmin, bmax)) break;
-    box_rows(L, bmin, bmax);
-}
-
-typedef float f4v __attribute__((ext_vector_type(4)));
-
-// the samples of row j that entry e may show: a face's exact span, or the
-// columns of a light's rectangle
-template <bool AP>
-__device__ __forceinline__ bool entry_span(const Prim &e, int j, int W, int &xl, int &xr)
-{
-    if (AP && e.nv == 0) {
-        xl = e.X3;
-        xr = e.Y3;
-        return true;
-    }
-    return prim_span(e, j, W, xl, xr);
-}
-
-// 1/z of the light entry at t for the sample offsets a, b (0: not shown)
-__device__ __forceinline__ float light_invz(const RgbLds &L, const Cam &cam, int t, float a, float b)
-{
-    const lptr<const f4v> e = (lptr<const f4v>)(L.faces + t);
-    const f4v p = e[0];
-    return signal_invz(cam, p.x, p.y, p.z, p.w, e[1].x, a, b);
-}
-
-// Fragments of the list's n entries in rows [b0, b1) folded into the key band
-// by one wavefront.  The (entry, row) items are dealt to the lanes by a prefix
-// over row counts; each lane computes its item's exact span; the spans are cut
-// into pieces of up to 16 samples, which are dealt to the lanes by a prefix
-// over piece counts, and each lane folds its piece's samples into the band
-// with LDS atomic max.
-template <bool AP>
-__device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<unsigned long long> keys, int n, int b0,
-                                         int b1)
-{
-    const int ln = (int)lane_id();
-    const int W = cam.W;
-    for (int t0 = 0; t0 < n; t0 += 64) {
-        const int t = t0 + ln;
-        int c = 0;
-        if (t < n) {
-            const int32_t jj = ((lptr<const int32_t>)(L.faces + t))[12];
-            const int j0 = max((int)(int16_t)(jj & 0xFFFF), b0), j1 = min(jj >> 16, b1 - 1);
-            c = max(0, j1 - j0 + 1);
-        }
-        const int incl = wave_incl_scan(c);
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        const int excl = incl - c;
-        for (int g0 = 0; g0 < total; g0 += 64) {
-            const int gi = g0 + ln;
-            const int o = owner_of(incl, gi);
-            const int ex = __shfl(excl, o);
-            int xl = 0, xr = -1, j = 0, light = 0;
-            if (gi < total) {
-                const Prim pr = lds_face_prim((lptr<const FaceRec>)(L.faces + t0 + o));
-                j = max((int)pr.j0, b0) + (gi - ex);
-                if (!entry_span<AP>(pr, j, W, xl, xr)) { xl = 0; xr = -1; }
-                light = AP && pr.nv == 0;
-            }
-            const int te = (t0 + o) | (light << 16);
-            const int np = (xr - xl + 16) >> 4;            // pieces of up to 16 samples (0 if empty)
-            const int inc2 = wave_incl_scan(np);
-            const int npt = __builtin_amdgcn_readlane(inc2, 63);
-            const int ex2 = inc2 - np;
-            for (int p0 = 0; p0 < npt; p0 += 64) {
-                const int pi = p0 + ln;
-                const int o2 = owner_of(inc2, pi);
-                const int k = pi - __shfl(ex2, o2);
-                const int sxl = __shfl(xl, o2), sxr = __shfl(xr, o2), sj = __shfl(j, o2), st = __shfl(te, o2);
-                if (pi >= npt) continue;
-                const f4v pk = ((lptr<const f4v>)(L.faces + (st & 0xFFFF)))[2];      // A B C keylo
-                const int i0 = sxl + 16 * k, i1 = min(i0 + 15, sxr);
-                const float dv = ((float)sj + 0.5f) - cam.cy, bdv = fmaf(pk.y, dv, pk.z);
-                lptr<unsigned long long> row = keys + (size_t)(sj - b0) * W;
-                for (int i = i0; i <= i1; ++i) {
-                    const float du = ((float)i + 0.5f) - cam.cx;
-                    float invz = fmaf(pk.x, du, bdv);
-                    if (AP && (st >> 16)) invz = light_invz(L, cam, st & 0xFFFF, du, -dv);
-                    if (invz > 0.0f) lds_max64(row + i, ((unsigned long long)__float_as_uint(invz) << 32) | __float_as_uint(pk.w));
-                }
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------ box rows by group masks
-//
-// The box rows [c0, c1) without a key band: the exact span of every (box
-// face, row) item is computed once and stored, and every group of 16 samples
-// of a row gets a mask of the faces whose span meets it.  The resolve then
-// walks, for its 16 samples, the faces of its group's mask and keeps the
-// largest key of each sample in registers.  The G = ceil(W / 16) groups of a
-// row start at samples 0, 16, ...; where W is not a multiple of 16 the last
-// one starts at W - 16 and shares samples with the one before (both compute
-// and store the same pixels).  Memory (L.work): the masks M[c1 - c0][G][nmw],
-// then the spans S[t][c1 - c0].
-__host__ __device__ inline int mask_rows_fit(int region, int n, int W, int nmw)
-{
-    // rows per chunk so that the masks and a span of every face in every row fit
-    return region / (8 * nmw * ((W + 15) / 16) + 4 * n);
-}
-
-template <bool AP>
-__device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n, int c0, int c1, int wv, int nwv)
-{
-    const int ln = (int)lane_id();
-    const int R = c1 - c0, G = (cam.W + 15) >> 4, nmw = L.nmw;
-    lptr<unsigned long long> M = L.work;
-    lptr<int32_t> S = (lptr<int32_t>)(M + nmw * G * R);
-    int pass = 0;
-    for (int t0 = 0; t0 < n; t0 += 64) {
-        const int t = t0 + ln;
-        int c = 0;
-        if (t < n) {
-            const int32_t jj = ((lptr<const int32_t>)(L.faces + t))[12];
-            const int j0c = max((int)(int16_t)(jj & 0xFFFF), c0);
-            c = max(0, min(jj >> 16, c1 - 1) - j0c + 1);
-        }
-        const int incl = wave_incl_scan(c);
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        const int excl = incl - c;
-        for (int g0 = 0; g0 < total; g0 += 64, ++pass) {
-            if (pass % nwv != wv) continue;
-            const int gi = g0 + ln;
-            const int o = owner_of(incl, gi);
-            const int ex = __shfl(excl, o);
-            if (gi < total) {
-                const int tt = t0 + o;
-                const Prim pr = lds_face_prim((lptr<const FaceRec>)(L.faces + tt));
-                const int j = max((int)pr.j0, c0) + (gi - ex);
-                int xl, xr;
-                if (entry_span<AP>(pr, j, cam.W, xl, xr)) {
-                    // bit 31 marks a light's columns
-                    S[tt * R + (j - c0)] = xl | (xr << 16) | (AP && pr.nv == 0 ? (int)0x80000000 : 0);
-                    lptr<unsigned long long> mrow = M + nmw * G * (j - c0) + (tt >> 6);
-                    const unsigned long long bit = 1ull << (tt & 63);
-                    const int gl = xr >= cam.W - 16 ? G - 1 : xr >> 4;
-                    for (int g = xl >> 4; g <= gl; ++g) lds_or64(mrow + nmw * g, bit);
-                }
-            }
-        }
-    }
-}
-
-// rows [c0, c1) from the group masks and spans: 16 samples (48 bytes) per
-// task; tasks alternate over the view's wavefronts in blocks of 32 lanes so
-// that a few box rows still keep every wavefront busy
-template <bool AP>
-__device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, uint8_t *img, uint32_t road_rgb,
-                                              uint32_t bg_rgb, int c0, int c1, int wv, int nwv)
-{
-    const int R = c1 - c0, G = (cam.W + 15) >> 4, nmw = L.nmw;
-    lptr<const unsigned long long> M = (lptr<const unsigned long long>)L.work;
-    lptr<const int32_t> S = (lptr<const int32_t>)(M + nmw * G * R);
-    const int W = cam.W;
-    const int n = R * G;
-    const int ln = (int)lane_id();
-    const int half = ln >> 5, sub = ln & 31;
-    for (int blk = 2 * wv + half; 32 * blk < n; blk += 2 * nwv) {
-        const int task = 32 * blk + sub;
-        if (task >= n) continue;
-        const int r = task / G, g = task - r * G, i = min(g << 4, W - 16), j = c0 + r;
-        const float dv = ((float)j + 0.5f) - cam.cy;
-        const float rz = fmaf(cam.road.B, dv, cam.road.C);
-        const uint32_t bits = j >= L.hr0 ? bits_at(L, (j - L.hr0) * W + i) : 0u;
-        const uint32_t rzb = __float_as_uint(rz);
-        // sample offsets ((float)(i + m) + 0.5f) - cx are small exact values: du0 + m
-        const float du0 = ((float)i + 0.5f) - cam.cx;
-        unsigned long long best[16];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) best[m] = 0ull;
-        for (int w = 0; w < nmw; ++w) {
-            unsigned long long mk = M[nmw * (G * r + g) + w];
-            while (mk != 0ull) {
-                const int t = 64 * w + (__ffsll((long long)mk) - 1);
-                mk &= mk - 1ull;
-                // span and plane read together (both depend on t only)
-                const int sp = S[t * R + r];
-                const f4v pk = ((lptr<const f4v>)(L.faces + t))[2];   // A B C keylo
-                // the span's samples within this group as a bit mask
-                const int lo = max((sp & 0xFFFF) - i, 0), hi = min(((sp >> 16) & 0x7FFF) - i, 15);
-                const uint32_t in = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
-                const float bdv = fmaf(pk.y, dv, pk.z);
-                const uint32_t keylo = __float_as_uint(pk.w);
-                if (AP && sp < 0) {
-                    // a light: few samples, each with its own sphere test
-#pragma unroll
-                    for (int m = 0; m < 16; ++m) {
-                        if (!((in >> m) & 1u)) continue;
-                        const float invz = light_invz(L, cam, t, du0 + (float)m, -dv);
-                        const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
-                        if (invz > 0.0f && key > best[m]) best[m] = key;
-                    }
-                    continue;
-                }
-                // branch-free: the three tests combined bitwise, so that each
-                // sample is a select and not a branch around the compare
-#pragma unroll
-                for (int m = 0; m < 16; ++m) {
-                    const float invz = fmaf(pk.x, du0 + (float)m, bdv);
-                    const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
-                    const bool take = (((in >> m) & 1u) != 0u) & (invz > 0.0f) & (key > best[m]);
-                    best[m] = take ? key : best[m];
-                }
-            }
-        }
-        uint32_t c[16];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const unsigned long long kb = best[m];
-            const bool road = (bits >> m) & 1u;
-            const bool box = (kb != 0ull) & (!road | ((uint32_t)(kb >> 32) >= rzb));
-            // the key's low byte names the list entry (entry 0 without a key: read, not used)
-            const uint32_t boxc = ((lptr<const uint32_t>)(L.faces + ((uint32_t)kb & 0xFFu)))[14];
-            c[m] = box ? boxc : (road ? road_rgb : bg_rgb);
-        }
-        store16(img + 3 * ((int64_t)j * W + i), c);
-    }
-}
-
-// ------------------------------------------------------------ resolve
-
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-// The rows that no box fragment touches are written as one run of bytes, in
-// 16-byte pieces at 16-byte aligned addresses whatever the width and the
-// image's address: piece q holds the bytes o .. o + 15 of the image, o = 16 q -
-// a (a: the image's address mod 16), which lie in the six pixels from f =
-// o / 3 on, at phase o mod 3 of their run.  Neighbouring lanes write
-// neighbouring pieces, so a store instruction writes 1 KB in one run.  (A lane
-// that wrote 16 pixels as three 16-byte stores 48 bytes apart reached 3.9 TB/s
-// in a kernel that only writes, pieces in one run 6.3 TB/s.)
-
-// byte b of a pixel's colour at channel c
-__device__ __forceinline__ uint8_t channel(uint32_t rgb, int c) { return (uint8_t)(rgb >> (8 * c)); }
-
-// bytes [b0, b1) of the background (the sky)
-__device__ __forceinline__ void write_sky(uint8_t *img, uint32_t bg, int b0, int b1)
-{
-    if (b0 >= b1) return;
-    const int a = (int)(reinterpret_cast<uintptr_t>(img) & 15), B = (int)blockDim.x, tid = (int)threadIdx.x;
-    const int q0 = (b0 + a + 15) >> 4, q1 = (b1 + a) >> 4;
-    const uint32_t w[3] = {bg | (bg << 24), (bg >> 8) | (bg << 16), (bg >> 16) | (bg << 8)};
-    // a thread's pieces are B apart: their phases repeat after three
-    u4 v[3];
-    int ph = (16 * (q0 + tid) - a + 48) % 3;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        v[k] = u4{__builtin_amdgcn_alignbyte(w[1], w[0], ph), __builtin_amdgcn_alignbyte(w[2], w[1], ph),
-                  __builtin_amdgcn_alignbyte(w[0], w[2], ph), __builtin_amdgcn_alignbyte(w[1], w[0], ph)};
-        ph = (ph + B) % 3;
-    }
-    u4 *out = reinterpret_cast<u4 *>(img - a);
-    for (int q = q0 + tid; q < q1; q += 3 * B) {
-        out[q] = v[0];
-        if (q + B < q1) out[q + B] = v[1];
-        if (q + 2 * B < q1) out[q + 2 * B] = v[2];
-    }
-    // the partial pieces at the run's ends (a row has at least 48 bytes)
-    const int head = 16 * q0 - a - b0, tail = b1 - (16 * q1 - a);
-    if (tid < head) img[b0 + tid] = channel(bg, (b0 + tid) % 3);
-    if (tid >= 32 && tid < 32 + tail) img[b1 - tail + tid - 32] = channel(bg, (b1 - tail + tid - 32) % 3);
-}
-
-// the pattern table: entry (p, b) holds the 16 bytes at phase p of the run of
-// six pixels that are road where bit k of b is set and background elsewhere
-__device__ __forceinline__ void build_patterns(const RgbLds &L, uint32_t road, uint32_t bg)
-{
-    for (int e = (int)threadIdx.x; e < 3 * 64; e += (int)blockDim.x) {
-        const int ph = e >> 6;
-        uint32_t c[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) c[k] = (e >> k) & 1 ? road : bg;
-        const uint32_t w[5] = {c[0] | (c[1] << 24), (c[1] >> 8) | (c[2] << 16), (c[2] >> 16) | (c[3] << 8),
-                               c[4] | (c[5] << 24), c[5] >> 8};
-        gp_v4i v;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) v[d] = (int)__builtin_amdgcn_alignbyte(w[d + 1], w[d], ph);
-        L.pat[e] = v;
-    }
-}
-
-// bytes [b0, b1) of rows below the horizon, road or background by the coverage bits
-__device__ __forceinline__ void write_road(const RgbLds &L, uint8_t *img, uint32_t road, uint32_t bg, int W, int b0,
-                                           int b1)
-{
-    if (b0 >= b1) return;
-    const int a = (int)(reinterpret_cast<uintptr_t>(img) & 15), B = (int)blockDim.x, tid = (int)threadIdx.x;
-    const int q0 = (b0 + a + 15) >> 4, q1 = (b1 + a) >> 4;
-    const int f0 = L.hr0 * W;            // pixel of coverage bit 0
-    gp_v4i *out = reinterpret_cast<gp_v4i *>(img - a);
-    auto piece = [&](int q) -> gp_v4i {
-        const uint32_t o = (uint32_t)(16 * q - a), f = o / 3u, ph = o - 3u * f;
-        return L.pat[(ph << 6) | (bits_at(L, (int)f - f0) & 63u)];
-    };
-    for (int q = q0 + tid; q < q1; q += 2 * B) {
-        const bool two = q + B < q1;
-        const gp_v4i v0 = piece(q), v1 = piece(two ? q + B : q);
-        out[q] = v0;
-        if (two) out[q + B] = v1;
-    }
-    const int head = 16 * q0 - a - b0, tail = b1 - (16 * q1 - a);
-    int o = -1;
-    if (tid < head) o = b0 + tid;
-    else if (tid >= 32 && tid < 32 + tail) o = b1 - tail + tid - 32;
-    if (o >= 0) {
-        const int f = o / 3;
-        img[o] = channel(bits_at(L, f - f0) & 1u ? road : bg, o - 3 * f);
-    }
-}
-
-// rows [r0, r1) that no box fragment touches: sky above the horizon, road or
-// background below it
-__device__ __forceinline__ void write_rows(const RgbLds &L, uint8_t *img, uint32_t road, uint32_t bg, int W, int r0, int r1)
-{
-    write_sky(img, bg, 3 * W * r0, 3 * W * min(r1, L.hr0));
-    write_road(L, img, road, bg, W, 3 * W * max(r0, L.hr0), 3 * W * r1);
-}
-
-// rows [b0, b1) of the key band: a box fragment wins where its 1/z is not
-// below the road's (agents rank above roads on equal depth); otherwise road
-// or background by the coverage bit
-template <bool AP>
-__device__ __forceinline__ void resolve_band(const DevSim &s, const SceneRec &sc, const RgbLds &L, const Cam &cam,
-                                             lptr<unsigned long long> keys, uint8_t *img, uint32_t road_rgb,
-                                             uint32_t bg_rgb, int b0, int b1)
-{
-    const int W = cam.W, gpr = (W + 15) >> 4;
-    const int n = (b1 - b0) * gpr;
-    for (int task = (int)threadIdx.x; task < n; task += (int)blockDim.x) {
-        const int r = task / gpr, i = min((task - r * gpr) << 4, W - 16), j = b0 + r;
-        const float dv = ((float)j + 0.5f) - cam.cy;
-        const float rz = fmaf(cam.road.B, dv, cam.road.C);
-        const uint32_t bits = j >= L.hr0 ? bits_at(L, (j - L.hr0) * W + i) : 0u;
-        const uint32_t rzb = __float_as_uint(rz);
-        lptr<unsigned long long> kp = keys + (size_t)r * W + i;
-        uint32_t c[16];
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const unsigned long long kb = kp[m];
-            const bool road = (bits >> m) & 1u;
-            const bool box = (kb != 0ull) & (!road | ((uint32_t)(kb >> 32) >= rzb));
-            uint32_t v = road ? road_rgb : bg_rgb;
-            // the box list was streamed: the colour comes from the key's primitive
-            if (box) {
-                const int prim = (kMaxPrims - 1) - (int)(((uint32_t)kb >> 8) & (uint32_t)(kMaxPrims - 1));
-                const int nbox = sc.n_agents + sc.n_static;
-                if (!AP || prim < 6 * nbox) v = face_rgb<AP>(s, sc, prim / 6, prim % 6);
-                else v = signal_rgb(s, sc, prim - 6 * nbox - sc.n_roads);
-            }
-            c[m] = v;
-        }
-        store16(img + 3 * ((int64_t)j * W + i), c);
-    }
-}
-
-// Rows [kr0, kr1) of a view whose box list overflowed, through bands of
-// 64-bit keys (the whole workgroup; the region from the surviving-bin list on
-// is free): the box faces streamed through the list six candidates at a time
-// (at most 60 entries per pass) with the boxes culled again.  wv: this
-// wavefront among the workgroup's.
-template <bool AP>
-__device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                                              uint8_t *img, uint32_t road_rgb, uint32_t bg_rgb, int kr0, int kr1, int wv)
-{
-    const int W = cam.W;
-    lptr<unsigned long long> keys = L.work;
-    for (int b0 = kr0; b0 < kr1; b0 += L.krows) {
-        const int b1 = min(b0 + L.krows, kr1);
-        __syncthreads();
-        for (int p = (int)threadIdx.x; p < (b1 - b0) * W; p += (int)blockDim.x) keys[p] = 0ull;
-        __syncthreads();
-        if (wv == 0) {
-            const int ncand = 6 * (sc.n_agents + sc.n_static);
-            for (int c0 = 0; c0 < ncand; c0 += 6) {
-                int n = 0, bmn = 0, bmx = 0;
-                (void)box_pass<AP>(s, sc, cam, ego, L, (lptr<const int32_t>)L.cq, false, ncand, c0, 6, L.cq, false, n, bmn,
-                                   bmx);
-                wave_lds_order();
-                box_band<AP>(L, cam, keys, n, b0, b1);
-                wave_lds_order();
-            }
-            for (int g0 = 0; AP && g0 < sc.n_signals; g0 += 64) {
-                int n = 0, bmn = 0, bmx = 0;
-                (void)light_pass(s, sc, cam, L, g0, false, n, bmn, bmx);
-                wave_lds_order();
-                box_band<AP>(L, cam, keys, n, b0, b1);
-                wave_lds_order();
-            }
-        }
-        __syncthreads();
-        resolve_band<AP>(s, sc, L, cam, keys, img, road_rgb, bg_rgb, b0, b1);
-    }
-}
-
-// ------------------------------------------------------------ per view
-
-// Issue priority of the view's wavefronts (0..3) against the other views'
-// on the same SIMDs.  Every view of a launch is resident at once, so the
-// launch lasts as long as its slowest view: a view with much work left
-// raises its priority and the views with little fill the gaps.  Only the
-// instruction issue order changes, never a result.
-__device__ __forceinline__ void view_priority(int p)
-{
-    p = __builtin_amdgcn_readfirstlane(p);
-    if (p >= 3) __builtin_amdgcn_s_setprio(3);
-    else if (p == 2) __builtin_amdgcn_s_setprio(2);
-    else if (p == 1) __builtin_amdgcn_s_setprio(1);
-    else __builtin_amdgcn_s_setprio(0);
-}
-
-// The scene's road culling bins [b0, b0 + 64) against the view (frustum, road
-// depth limit and row-gap test); the survivors are appended to the view's
-// list of surviving bins.
-__device__ __forceinline__ void cull_bins(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int b0)
-{
-    const int ln = (int)lane_id();
-    const int b = b0 + ln;
-    bool keep = false;
-    int rec = 0;
-    if (b < sc.n_bins) {
-        const RoadBin bn = s.bins[sc.bin_base + b];
-        float x[4], z[4];
-        ground_xz(cam, bn.xmin, bn.ymin, x[0], z[0]);
-        ground_xz(cam, bn.xmax, bn.ymin, x[1], z[1]);
-        ground_xz(cam, bn.xmax, bn.ymax, x[2], z[2]);
-        ground_xz(cam, bn.xmin, bn.ymax, x[3], z[3]);
-        keep = !road_culled<true>(cam, x, z);
-        rec = bn.start * 128 + bn.count;
-    }
-    const unsigned long long bm = __ballot(keep);
-    const int nk = __popcll(bm);
-    int base = 0;
-    if (nk > 0) {
-        const int leader = __ffsll((long long)bm) - 1;
-        if (ln == leader) base = lds_add(L.cnt + R_NSB, nk);
-        base = __shfl(base, leader);
-    }
-    if (keep) L.sbins[base + lanes_below(bm)] = rec;
-}
 
 // AP: the sim has a light or traffic lights (instances of their own, so that
 // they add nothing to the plain ones).  Lit streets used to take the general
@@ -978,7 +63,7 @@ template <bool AP>
 __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, const RgbLds &L, int view, bool one_cam)
 {
     const int B = (int)blockDim.x, K = B >> 6;
-    const int tid = (int)threadIdx.x, ln = (int)lane_id(), wv = tid >> 6;
+    const int tid = (int)threadIdx.x, wv = tid >> 6;
     const int scene = __builtin_amdgcn_readfirstlane(s.views[view].scene);
     const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
     const SceneRec sc = uniform_scene(s.scenes[scene]);
@@ -994,105 +79,40 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, c
     const int ubox = K >= 8 ? 4 : 16;
     const int nbu = (sc.n_agents + sc.n_static + ubox - 1) / ubox;
     const int nlu = AP ? (sc.n_signals + 63) / 64 : 0;
-    // road units are numbered after the box units (dealt as jobs, below)
-    if (tid < R_NCNT)
-        L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : (tid == R_NEXT ? nbu : 0));
+    if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();
 
     // ---- A: road culling bins
     for (int b0 = 64 * wv; b0 < sc.n_bins; b0 += B) cull_bins(s, sc, cam, L, b0);
     __syncthreads();
 
-    // ---- B: rounds of two steps, each dealt over the view's wavefronts
-    // through LDS counters.  B1: the road units (four surviving bins each,
-    // numbered from nbu on): the cheap test of the unit's strips with the
-    // survivors appended to the view's ring (a unit is taken only with 64
-    // free ring entries reserved).  B2: the jobs -- in the first round the box
-    // units first (boxes ubox k .. ubox k + ubox - 1: cull, face
-    // set-up and clipping into the box list, which is needed only by the
-    // resolve, so a long box unit overlaps the other wavefront's road jobs),
-    // then set-up jobs of up to kSetupBatch ring strips: set-up, the fan
-    // triangles and the clipper for the strips that need them, and the spans
-    // of every primitive.  A round ends when the ring is full or the units
-    // are used up.
+    // ---- B: the road and box units (boxes ubox k .. ubox k + ubox - 1: cull,
+    // face set-up and clipping into the box list)
     const int nsb = L.cnt[R_NSB];
     // road work ahead grows with the surviving bins (a mean view keeps about a dozen)
     const int prio_b = nsb >= 24 ? 2 : (nsb >= 16 ? 1 : 0);
     view_priority(prio_b);
-    const int n_units = nbu + (nsb + 3) / 4;
     lptr<unsigned char> wbase = L.waves + (size_t)wv * kWaveBytes;
     WaveSt ws;
     ws.tris = (lptr<Prim>)wbase;
     ws.clipq = (lptr<int32_t>)(wbase + kWTris * 48);
     ws.nclip = 0;
     ws.nfan = 0;
-    // the next unit with its ring entries reserved, or n_units (none left, or
-    // the ring cannot take another road unit this round)
-    auto take = [&]() -> int {
-        int u = n_units;
-        if (ln == 0) {
-            const int r = lds_add(L.cnt + R_RESV, 64);
-            if (r + 64 <= kSharedRing) {
-                u = min(lds_add(L.cnt + R_NEXT, 1), n_units);
-                if (u == n_units) lds_add(L.cnt + R_RESV, -64);   // no unit left
-            } else {
-                lds_add(L.cnt + R_RESV, -64);
-            }
-        }
-        return __builtin_amdgcn_readfirstlane(__shfl(u, 0));
-    };
-    int box_jobs = nbu + nlu;    // box and light units still to deal (first round)
-    for (;;) {
-        // B1, the next unit's strips loaded while the current one is tested
-        int u = take();
-        float4 q0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), q1 = q0;
-        int gq = 0;
-        bool live = u < n_units && load_unit(s, sc, L, nsb, u - nbu, gq, q0, q1);
-        while (u < n_units) {
-            const int un = take();
-            float4 n0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), n1 = n0;
-            int gn = 0;
-            const bool nlive = un < n_units && load_unit(s, sc, L, nsb, un - nbu, gn, n0, n1);
-            road_unit(cam, L, live, gq, q0, q1);
-            u = un;
-            q0 = n0;
-            q1 = n1;
-            gq = gn;
-            live = nlive;
-        }
-        __syncthreads();
-        const int nring = L.cnt[R_RING];
-        const bool more = L.cnt[R_NEXT] < n_units;
-        // the ring cut into jobs of at most kSetupBatch strips, as many as a
-        // multiple of the wavefronts, of equal size: a job's set-up takes about
-        // the same time for any number of strips up to a wavefront's width
-        const int njobs = (max(K, (nring + kSetupBatch - 1) / kSetupBatch) + K - 1) / K * K;
-        const int jsz = (nring + njobs - 1) / njobs;
-        // B2
-        for (;;) {
-            int j = 0;
-            if (ln == 0) j = lds_add(L.cnt + R_JOB, 1);
-            j = __builtin_amdgcn_readfirstlane(__shfl(j, 0)) - box_jobs;
-            if (j < 0) {
-                const int u = j + box_jobs;
-                if (AP && u >= nbu) do_lights(s, sc, cam, L, u - nbu);
-                else do_boxes<AP>(s, sc, cam, ego, L, u, ubox, (lptr<int32_t>)ws.tris);   // the staging is free here
-                continue;
-            }
-            const int a = j * jsz;
-            if (a >= nring) break;
-            setup_job(s, cam, L, ws, a, min(jsz, nring - a));
-        }
-        __syncthreads();
-        box_jobs = 0;
-        if (!more) break;
-        if (tid == 0) {
-            L.cnt[R_RING] = 0;
-            L.cnt[R_RESV] = 0;
-            L.cnt[R_JOB] = 0;
-        }
-        __syncthreads();
-    }
+    road_work(
+        s, sc, L, nsb, nbu + nlu, false,
+        [&](bool live, const float4 &q0, const float4 &q1) -> bool {
+            float x[4], z[4];
+            ground_xz(cam, q0.x, q0.y, x[0], z[0]);
+            ground_xz(cam, q0.z, q0.w, x[1], z[1]);
+            ground_xz(cam, q1.x, q1.y, x[2], z[2]);
+            ground_xz(cam, q1.z, q1.w, x[3], z[3]);
+            return live && !road_culled<false>(cam, x, z);
+        },
+        [&](int u) {
+            if (AP && u >= nbu) do_lights(s, sc, cam, L, u - nbu);
+            else do_boxes<AP>(s, sc, cam, ego, L, u, ubox, (lptr<int32_t>)ws.tris);   // the staging is free here
+        },
+        [&](int a, int n) { setup_job(s, cam, L, ws, a, n); });
 
     // ---- C: resolve
     uint8_t *img = rgb + 3 * ((int64_t)view * W * H);

@@ -22,447 +22,899 @@
 //            products fmaf(ex, wy, -(ey wx)) share one strict sign
 //   lights   the raster's sphere test in camera space
 //
-// Layout: one workgroup of 256 threads per view; the view is processed in
-// bands of about 4096 pixels whose keys live in LDS; between two barriers
-// each key is updated by one thread only (no atomics).  Boxes, road bins and
-// lights are culled against the view frustum in chunks of up to 256 and the
-// survivors staged in LDS; every pixel of the band then tests the staged
-// records (boxes only where their image rectangle holds the pixel, road bins
-// per sub-band of rows by the ground depths the rows see, their strips staged
-// in LDS sixteen bins at a time).  Colours come
-// from the keys as in the raster's general kernel.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include "gp_device.h"
+// The tests are dealt by primitive, not by pixel: every ray starts at the
+// camera, so a strip can only hold the ground points of the samples inside its
+// image.  Per (strip, row) the columns that the strip can reach are computed
+// with a margin (the slab of depths around the row's against the strip's
+// edges, no projection and no clipping), and those it holds for certain; the
+// exact test runs only for the samples between.  Boxes likewise by the
+// rectangle of their (near-clipped) image: where the hit of a side is certain
+// only its division is left.  Lights are tested inside their rectangle.
+// One workgroup per view.  Strips are culled by bins and one by one into the
+// view's ring (gp_view.h).  In rgb-only renders of scenes with one road
+// colour (COV) strips leave coverage bits, the rows without boxes are written
+// like the raster's, and keys are kept for box rows only, in bands of LDS; in
+// the others every fragment folds its key into a band of keys (LDS atomic max)
+// and the road work is done again for each band.
+//
+// Bound by VALU issue.  One MI355X: 2,048 views at 128 x 128 (32 agents, 2,000
+// strips) 116 us (1,100 us with the tests dealt by pixel; 218 us before the
+// certain runs of boxes and strips were taken without the full test), 16 scenes
+// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 475 us
+// (2,400 us).
+#include "gp_view.h"
 
 namespace gp {
 
 namespace {
 
-constexpr int kRcThreads = 256;
-constexpr int kRcBandPixels = 4096;
-constexpr int kRcRoadPixels = 512;        // pixels of a road sub-band
-constexpr int kRcStageWords = 10;         // words per staged record
-constexpr int kRcStripWords = 9;          // words per staged road strip: 8 corner coordinates, index and colour
-constexpr int kRcGroupBins = kRcThreads / kBinQuads;   // bins whose strips are staged together
-static_assert(kRcGroupBins * kBinQuads == kRcThreads, "one staged strip per thread");
+constexpr int kRcPiece = 8;               // samples of one lane's certain box hits
+constexpr int kRcTests = 4;               // samples of one lane's exact tests
+constexpr int kRcNarrow = 12;             // items of fewer columns are tested whole
+static_assert(kRcTests <= 16, "a piece's coverage bits fit the 32-bit pair below");
 
-#define GP_RC_LDS __attribute__((address_space(3)))
-
-struct RcCam {
-    float px, py, h, fx, fy, f, cx, cy, zn, zf, tx;   // tx: horizontal frustum slope bound
-    int W, H;
+struct RcLayout {
+    size_t cnt, bits, faces, sbins, sring, waves, pal, keys, total;
+    int krows, region;
 };
 
-// a value that is the same in every lane, kept in a scalar register
-__device__ __forceinline__ float uniform_float(float v)
+// LDS of one view: without COV the key band has its own memory (the ring is in
+// use beside it); with COV it takes the memory from sbins on, free by then,
+// behind the pattern table
+__host__ __device__ inline RcLayout rc_layout(int W, int H, const RcCfg &c)
 {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+    RcLayout l;
+    size_t o = 0;
+    l.cnt = o; o = align16(o + 4 * R_NCNT);
+    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
+    l.bits = o;
+    if (c.cover) o = align16(o + 8 * (((size_t)W * (size_t)(H - first_road_row(H)) + 63) / 64 + 1));
+    l.pal = o;
+    if (!c.cover) o = align16(o + 4 * 256);
+    l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
+    l.sring = o; o = align16(o + 4 * (size_t)kSharedRing);
+    l.waves = o; o = align16(o + (size_t)kWaveBytes * (size_t)c.waves);
+    const size_t band = 8 * (size_t)W * (size_t)c.band_rows;
+    if (c.cover) {
+        l.keys = l.sbins + kPatBytes;
+        const size_t least = align16(l.keys + band);
+        o = o > least ? o : least;
+        l.region = (int)(o - l.keys);
+    } else {
+        l.keys = o; o = align16(o + band);
+        l.region = (int)band;
+    }
+    l.krows = l.region / (8 * W) > 0 ? l.region / (8 * W) : 1;
+    l.total = o;
+    return l;
 }
 
-__device__ __forceinline__ uint32_t key_word(uint32_t cls, int prim, uint32_t color)
+// A staged strip (48 bytes): its world corners, its rows j0 | j1 << 16, key
+// word (class 0) and margin
+struct RcStrip {
+    float x0, y0, x1, y1, x2, y2, x3, y3;
+    int32_t rows;
+    uint32_t keylo;
+    float m;
+    int32_t pad;
+};
+static_assert(sizeof(RcStrip) == 48, "staged strip size");
+
+// What a row of samples sees of the ground: the ray parameter s = -h / b and
+// the planar depth z = s f (the per-sample arithmetic's own values), and
+// whether the depth is kept.
+struct RcRow {
+    float b, sp, z;
+    bool ok;
+};
+
+__device__ __forceinline__ RcRow rc_row(const Cam &c, int j)
 {
-    return (cls << 31) | ((uint32_t)(kMaxPrims - 1 - prim) << 8) | color;
+    RcRow r;
+    r.b = c.cy - ((float)j + 0.5f);
+    r.sp = -c.h / r.b;
+    r.z = r.sp * c.f;
+    r.ok = (r.b < 0.0f) & (r.z >= c.zn) & (r.z <= c.zf);
+    return r;
 }
 
-__device__ __forceinline__ unsigned long long make_key(float invz, uint32_t word)
+// Camera-space depth of the ground seen by a sample at planar depth z is s2 z
+// and its x is s2 s a, with s2 = fx^2 + fy^2 (1 for unit camera directions).
+__device__ __forceinline__ float rc_scale2(const Cam &c) { return fmaf(c.fx, c.fx, c.fy * c.fy); }
+
+// Rows [r0, r1) whose ground depth can lie within [zmin, zmax] (camera depth,
+// margins included by the caller): j + 0.5 - cy = h f s2 / z; the slack covers
+// the reciprocal's and the product's rounding (relative, 2^-20 of up to 1,024
+// rows, doubled).
+__device__ __forceinline__ bool rc_rows(const Cam &c, float hfs, float zmin, float zmax, int r0, int r1, int &j0, int &j1)
 {
-    return ((unsigned long long)__float_as_uint(invz) << 32) | word;
+    if (!(zmax > 0.0f)) return false;
+    const float lo = fmaf(hfs, __builtin_amdgcn_rcpf(zmax), c.cy) - 0.51f;
+    float hi = (float)(r1 - 1);
+    if (zmin > 0.0f) hi = fminf(hi, fmaf(hfs, __builtin_amdgcn_rcpf(zmin), c.cy) - 0.49f);
+    j0 = max(r0, (int)fminf(ceilf(lo), (float)r1));
+    j1 = (int)floorf(fmaxf(hi, -1.0f));
+    return j0 <= j1;
 }
 
-// lighting of the raster's general kernel: s = a + (1 - a) max(0, n . l),
-// level floor(255 s + 0.5), channel (c q + 127) / 255
-__device__ __forceinline__ uint32_t rc_level(const DevSim &s, float nx, float ny, int face)
+// Margin in metres that dominates the rounding of the exact test: the ground
+// point, its differences to the corners and the cross products are off by less
+// than 2^-21 of the coordinates and distances in play.
+__device__ __forceinline__ float rc_margin(const Cam &c, const float *x, const float *z)
 {
-    const float lx = s.light[0], ly = s.light[1], lz = s.light[2], amb = s.light[3];
-    const float side = fmaf(nx, lx, ny * ly);
-    const float d = face < 4 ? side : (face == 4 ? lz : -lz);
-    const float sh = fmaf(1.0f - amb, fmaxf(d, 0.0f), amb);
-    return (uint32_t)fmaf(sh, 255.0f, 0.5f);
+    float r = fabsf(c.px) + fabsf(c.py);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r += fabsf(x[k]) + fabsf(z[k]);
+    return fmaf(r, 0x1p-18f, 1e-4f);
 }
 
-__device__ __forceinline__ uint32_t rc_scale(uint32_t c, uint32_t q)
+// Conservative cull of a strip (or of a bin's box) with camera-space corners
+// x, z against rows [r0, r1): the depths and the sides of the frustum that its
+// ground points can lie in.
+__device__ __forceinline__ bool rc_outside(const Cam &c, float hfs, const float *x, const float *z, int r0, int r1,
+                                           int &j0, int &j1, float &m)
 {
-    const uint32_t r = ((c & 0xFFu) * q + 127u) / 255u;
-    const uint32_t g = (((c >> 8) & 0xFFu) * q + 127u) / 255u;
-    const uint32_t b = (((c >> 16) & 0xFFu) * q + 127u) / 255u;
-    return r | (g << 8) | (b << 16);
+    m = rc_margin(c, x, z);
+    bool l = true, r = true;
+    float zmin = INFINITY, zmax = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float mk = 1e-3f * (fabsf(x[k]) + fabsf(z[k])) + m;
+        r = r & (x[k] - c.t_right * z[k] > mk);
+        l = l & (-x[k] - c.t_left * z[k] > mk);
+        zmin = fminf(zmin, z[k]);
+        zmax = fmaxf(zmax, z[k]);
+    }
+    return l | r | !rc_rows(c, hfs, zmin - m, zmax + m, r0, r1, j0, j1);
 }
 
-__device__ __forceinline__ void rc_sample(const RcCam &c, int i, int j, float &a, float &b, float &dx, float &dy)
+__device__ __forceinline__ void rc_corners(const Cam &c, const float4 &q0, const float4 &q1, float *x, float *z)
 {
-    a = ((float)i + 0.5f) - c.cx;
-    b = c.cy - ((float)j + 0.5f);
-    dx = fmaf(a, c.fy, c.f * c.fx);
-    dy = fmaf(a, -c.fx, c.f * c.fy);
+    ground_xz(c, q0.x, q0.y, x[0], z[0]);
+    ground_xz(c, q0.z, q0.w, x[1], z[1]);
+    ground_xz(c, q1.x, q1.y, x[2], z[2]);
+    ground_xz(c, q1.z, q1.w, x[3], z[3]);
 }
 
-__global__ __launch_bounds__(kRcThreads) void k_raycast(DevSim s, RenderOut o, int view_begin)
+// Columns of row j whose samples the strip can hold: its extent in x over the
+// depths within m of the row's, edge by edge.  (A point with four cross
+// products of one strict sign lies inside the closed polygon, so between edge
+// crossings of the row, also when the quad is not convex.)
+__device__ __forceinline__ bool rc_columns(const Cam &c, const RcStrip &t, const RcRow &row, float s2, int &xl, int &xr)
+{
+    float x[4], z[4];
+    rc_corners(c, make_float4(t.x0, t.y0, t.x1, t.y1), make_float4(t.x2, t.y2, t.x3, t.y3), x, z);
+    const float zr = row.z * s2, m = fmaf(zr, 0x1p-18f, t.m);
+    const float zlo = zr - m, zhi = zr + m;
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int k1 = (k + 1) & 3;
+        const bool up = z[k] <= z[k1];
+        const float za = up ? z[k] : z[k1], zb = up ? z[k1] : z[k], xa = up ? x[k] : x[k1], xb = up ? x[k1] : x[k];
+        const float d = zb - za, inv = __builtin_amdgcn_rcpf(d);
+        // an edge along the row counts whole
+        const bool steep = d > m;
+        const float t0 = steep ? fminf(fmaxf((zlo - za) * inv, 0.0f), 1.0f) : 0.0f;
+        const float t1 = steep ? fminf(fmaxf((zhi - za) * inv, 0.0f), 1.0f) : 1.0f;
+        const float e0 = fmaf(t0, xb - xa, xa), e1 = fmaf(t1, xb - xa, xa);
+        const bool in = (zb >= zlo) & (za <= zhi);
+        lo = in ? fminf(lo, fminf(e0, e1)) : lo;
+        hi = in ? fmaxf(hi, fmaxf(e0, e1)) : hi;
+    }
+    const float ia = __builtin_amdgcn_rcpf(row.sp * s2);            // columns per metre
+    const float al = fmaf(lo - m, ia, c.cx) - 0.52f, ar = fmaf(hi + m, ia, c.cx) - 0.48f;
+    const float Wf = (float)c.W;
+    xl = (int)ceilf(fminf(fmaxf(al, 0.0f), Wf));
+    xr = (int)floorf(fminf(fmaxf(ar, -1.0f), Wf - 1.0f));
+    return lo <= hi && xl <= xr;
+}
+
+// Columns [xl, xr] of a row cut down to those whose samples the strip holds
+// for certain: along a row each cross product is affine in the column, and
+// beyond the margin (in metres from each edge) its sign is the exact test's.
+__device__ __forceinline__ void rc_inside(const Cam &c, const RcStrip &t, const RcRow &row, int &xl, int &xr)
+{
+    const float qx[4] = {t.x0, t.x1, t.x2, t.x3}, qy[4] = {t.y0, t.y1, t.y2, t.y3};
+    // ground point of column offset a relative to the camera: P + a D
+    const float Px = row.z * c.fx, Py = row.z * c.fy, Dx = row.sp * c.fy, Dy = -(row.sp * c.fx);
+    const float area = (qx[2] - qx[0]) * (qy[3] - qy[1]) - (qy[2] - qy[0]) * (qx[3] - qx[1]);
+    const float m = fmaf(row.z, 0x1p-18f, t.m);
+    float al = -INFINITY, ar = INFINITY;
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float ux = qx[(e + 1) & 3] - qx[e], uy = qy[(e + 1) & 3] - qy[e];
+        const float ex = area < 0.0f ? -ux : ux, ey = area < 0.0f ? -uy : uy;
+        const float C = ex * (Py + (c.py - qy[e])) - ey * (Px + (c.px - qx[e])) - m * (fabsf(ex) + fabsf(ey));
+        const float G = ex * Dy - ey * Dx;
+        const float r = -C * __builtin_amdgcn_rcpf(G);
+        al = G > 0.0f ? fmaxf(al, r) : al;
+        ar = G < 0.0f ? fminf(ar, r) : ar;
+        ok = ok & ((G != 0.0f) | (C > 0.0f));
+    }
+    const int l = max(xl, (int)ceilf(fminf(fmaxf(al + c.cx - 0.48f, -1.0f), 2048.0f)));
+    const int r = min(xr, (int)floorf(fminf(fmaxf(ar + c.cx - 0.52f, -2.0f), 2048.0f)));
+    xl = l;
+    xr = ok ? r : -1;
+}
+
+// One set-up job: the n ring strips from a staged, their (strip, row) items on
+// rows [b0, b1) (of a key band that starts at row band0) dealt to the lanes by
+// a prefix over row counts, the items'
+// columns cut into pieces of up to kRcPiece samples, dealt again, and the exact
+// test run per sample.
+template <bool COV>
+__device__ __forceinline__ void rc_strips(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L,
+                                          lptr<RcStrip> st, float hfs, float s2, int a, int n, int b0, int b1,
+                                          int band0)
+{
+    const int ln = (int)lane_id(), W = cam.W;
+    wave_lds_order();
+    int rows = 0;
+    if (ln < n) {
+        const int g = L.sring[a + ln];
+        const float4 q0 = s.roads[2 * g], q1 = s.roads[2 * g + 1];
+        float x[4], z[4];
+        rc_corners(cam, q0, q1, x, z);
+        int j0, j1;
+        RcStrip t;
+        if (!rc_outside(cam, hfs, x, z, b0, b1, j0, j1, t.m)) rows = j1 - j0 + 1;
+        t.x0 = q0.x; t.y0 = q0.y; t.x1 = q0.z; t.y1 = q0.w; t.x2 = q1.x; t.y2 = q1.y; t.x3 = q1.z; t.y3 = q1.w;
+        t.rows = j0 | (j1 << 16);
+        t.keylo = COV ? 0u : key_low(0u, 6 * (sc.n_agents + sc.n_static) + s.road_index[g], s.road_color[g]);
+        t.pad = 0;
+        lds_store(st + ln, t);
+    }
+    const int incl = wave_incl_scan(rows);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int excl = incl - rows;
+    wave_lds_order();
+    for (int g0 = 0; g0 < total; g0 += 64) {
+        const int gi = g0 + ln;
+        const int o = owner_of(incl, gi);
+        const int ex = __shfl(excl, o);
+        int xl = 0, xr = -1, yl = W, yr = -1, j = 0;
+        if (gi < total) {
+            const RcStrip t = lds_load(st + o);
+            j = (t.rows & 0xFFFF) + (gi - ex);
+            const RcRow row = rc_row(cam, j);
+            if (!(row.ok && rc_columns(cam, t, row, s2, xl, xr))) { xl = 0; xr = -1; }
+            if (xr - xl >= kRcNarrow) {
+                yl = xl;
+                yr = xr;
+                rc_inside(cam, t, row, yl, yr);
+            }
+            if (yl > yr) {                                  // no certain column: all lie left of xr + 1
+                yl = xr + 1;
+                yr = xr;
+            }
+            if (COV && yl <= yr) or_span(L.bits, (j - L.hr0) * W + yl, (j - L.hr0) * W + yr);
+        }
+        if (!COV) {
+            // the certain columns' keys
+            const int nc = yl <= yr ? (yr - yl + 16) >> 4 : 0;
+            const int inc2 = wave_incl_scan(nc);
+            const int npt = __builtin_amdgcn_readlane(inc2, 63);
+            const int ex2 = inc2 - nc;
+            for (int p0 = 0; p0 < npt; p0 += 64) {
+                const int pi = p0 + ln;
+                const int o2 = owner_of(inc2, pi);
+                const int k = pi - __shfl(ex2, o2);
+                const int syl = __shfl(yl, o2), syr = __shfl(yr, o2), sj = __shfl(j, o2), so = __shfl(o, o2);
+                if (pi >= npt) continue;
+                const int i0 = syl + 16 * k, i1 = min(i0 + 15, syr);
+                const unsigned long long key = ((unsigned long long)__float_as_uint(1.0f / rc_row(cam, sj).z) << 32) |
+                                               ((lptr<const uint32_t>)(st + so))[9];
+                lptr<unsigned long long> kp = L.work + (sj - band0) * W;
+                for (int i = i0; i <= i1; ++i) lds_max64(kp + i, key);
+            }
+        }
+        const int nl = (yl - xl + kRcTests - 1) / kRcTests;
+        const int np = xl <= xr ? nl + (xr - yr + kRcTests - 1) / kRcTests : 0;
+        const int inc2 = wave_incl_scan(np);
+        const int npt = __builtin_amdgcn_readlane(inc2, 63);
+        const int ex2 = inc2 - np;
+        const int x2 = xl | (xr << 16), y2 = yl | (yr << 16);
+        for (int p0 = 0; p0 < npt; p0 += 64) {
+            const int pi = p0 + ln;
+            const int o2 = owner_of(inc2, pi);
+            const int k = pi - __shfl(ex2, o2);
+            const int sx = __shfl(x2, o2), sy = __shfl(y2, o2), sj = __shfl(j, o2), so = __shfl(o, o2);
+            if (pi >= npt) continue;
+            const int sxl = sx & 0xFFFF, sxr = sx >> 16, syl = sy & 0xFFFF, syr = sy >> 16;
+            const int snl = (syl - sxl + kRcTests - 1) / kRcTests;
+            const int i0 = k < snl ? sxl + kRcTests * k : syr + 1 + kRcTests * (k - snl);
+            const int i1 = min(i0 + kRcTests, k < snl ? syl : sxr + 1) - 1;
+            const RcStrip t = lds_load(st + so);
+            const RcRow row = rc_row(cam, sj);
+            const float qx[4] = {t.x0, t.x1, t.x2, t.x3}, qy[4] = {t.y0, t.y1, t.y2, t.y3};
+            float ex4[4], ey4[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ex4[e] = qx[(e + 1) & 3] - qx[e];
+                ey4[e] = qy[(e + 1) & 3] - qy[e];
+            }
+            uint32_t in = 0u;
+            for (int i = i0; i <= i1; ++i) {
+                const float av = ((float)i + 0.5f) - cam.cx;
+                const float dx = fmaf(av, cam.fy, cam.f * cam.fx), dy = fmaf(av, -cam.fx, cam.f * cam.fy);
+                const float x = fmaf(row.sp, dx, cam.px), y = fmaf(row.sp, dy, cam.py);
+                bool pos = true, neg = true;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float c = fmaf(ex4[e], y - qy[e], -(ey4[e] * (x - qx[e])));
+                    pos = pos & (c > 0.0f);
+                    neg = neg & (c < 0.0f);
+                }
+                in |= (uint32_t)(pos | neg) << (i - i0);
+            }
+            if (in == 0u) continue;
+            if (COV) {
+                const int b = (sj - L.hr0) * W + i0;
+                const unsigned long long m = (unsigned long long)in << (b & 31);
+                lptr<uint32_t> w = (lptr<uint32_t>)L.bits + (b >> 5);
+                lds_or32(w, (uint32_t)m);
+                if ((uint32_t)(m >> 32)) lds_or32(w + 1, (uint32_t)(m >> 32));
+            } else {
+                const unsigned long long key = ((unsigned long long)__float_as_uint(1.0f / row.z) << 32) | t.keylo;
+                lptr<unsigned long long> kp = L.work + (sj - band0) * W + i0;
+                for (; in != 0u; in &= in - 1u) lds_max64(kp + (__ffs((int)in) - 1), key);
+            }
+        }
+    }
+    wave_lds_order();
+}
+
+// store entry t of the list, named by its key word's low byte
+__device__ __forceinline__ void list_entry(const RgbLds &L, bool has, int t, FaceRec f)
+{
+    f.keylo |= (uint32_t)t & 0xFFu;
+    if (has) lds_store(L.faces + t, f);
+}
+
+// Colour of a winning box or light key: of its list entry's side, or (the list
+// was filled in chunks) from the scene.
+__device__ __forceinline__ uint32_t rc_color(const DevSim &s, const SceneRec &sc, const RgbLds &L, bool chunked, uint32_t keylo)
+{
+    const int prim = (kMaxPrims - 1) - (int)((keylo >> 8) & (uint32_t)(kMaxPrims - 1));
+    const int nbox = sc.n_agents + sc.n_static;
+    const int face = prim < 6 * nbox ? prim % 6 : 4;
+    if (chunked) return prim < 6 * nbox ? face_rgb<true>(s, sc, prim / 6, face) : signal_rgb(s, sc, prim - 6 * nbox - sc.n_roads);
+    const int word = face >= 4 ? 14 : ((face & 1) ? 10 : 9);
+    return ((lptr<const uint32_t>)(L.faces + (keylo & 0xFFu)))[word];
+}
+
+// Box unit: boxes [u0, u0 + n) of the scene (n <= 64) against the view: an
+// entry holds the box (centre, heading cosines, half sizes, height) and the
+// pixel rectangle that every sample whose ray can hit it lies in: the hull of
+// the images of its footprint's corners, clipped just before the near plane,
+// at the ground and at its top (a pixel of margin for rounding).
+__device__ __forceinline__ void rc_boxes(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
+                                         float s2, int u0, int n)
+{
+    const int ln = (int)lane_id();
+    const int u = u0 + ln;
+    bool keep = false;
+    FaceRec f = {};
+    if (ln < n && u < sc.n_agents + sc.n_static && u != ego) {
+        const int g = box_slot(sc, u);
+        const float4 st = s.state[g], dm = s.dims[g];
+        const float2 cs = s.cs[g];
+        const float ox = st.x - cam.px, oy = st.y - cam.py;
+        const float ax = 0.5f * dm.x * cs.x, ay = 0.5f * dm.x * cs.y, bx = -(0.5f * dm.y * cs.y), by = 0.5f * dm.y * cs.x;
+        float x[4], z[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float sa = k == 0 || k == 1 ? 1.0f : -1.0f, sb = k == 0 || k == 3 ? -1.0f : 1.0f;
+            const float wx = ox + sa * ax + sb * bx, wy = oy + sa * ay + sb * by;
+            z[k] = fmaf(wx, cam.fx, wy * cam.fy);
+            x[k] = fmaf(wx, cam.fy, -(wy * cam.fx));
+        }
+        // hits lie at planar depth >= z_near, camera depth >= s2 z_near
+        const float zc = 0.99f * (cam.zn * s2);
+        const float vt = (dm.z - cam.h) * cam.f * s2, vg = -cam.h * cam.f * s2;
+        float umin = INFINITY, umax = -INFINITY, vmin = INFINITY, vmax = -INFINITY, zmin = INFINITY;
+        auto point = [&](float px, float pz) {
+            const float iz = 1.0f / pz;
+            const float uu = fmaf(cam.f * px, iz, cam.cx);
+            umin = fminf(umin, uu);
+            umax = fmaxf(umax, uu);
+            const float v0 = fmaf(-vg, iz, cam.cy), v1 = fmaf(-vt, iz, cam.cy);
+            vmin = fminf(vmin, fminf(v0, v1));
+            vmax = fmaxf(vmax, fmaxf(v0, v1));
+        };
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int k1 = (k + 1) & 3;
+            zmin = fminf(zmin, z[k]);
+            if (z[k] >= zc) point(x[k], z[k]);
+            if ((z[k] >= zc) != (z[k1] >= zc)) point(fmaf((zc - z[k]) / (z[k1] - z[k]), x[k1] - x[k], x[k]), zc);
+        }
+        const float Wf = (float)cam.W, Hf = (float)cam.H;
+        const int i0 = max(0, (int)fminf(fmaxf(floorf(umin - 0.5f) - 1.0f, -1.0f), Wf));
+        const int i1 = min(cam.W - 1, (int)fminf(fmaxf(ceilf(umax - 0.5f) + 1.0f, -1.0f), Wf));
+        const int j0 = max(0, (int)fminf(fmaxf(floorf(vmin - 0.5f) - 1.0f, -1.0f), Hf));
+        const int j1 = min(cam.H - 1, (int)fminf(fmaxf(ceilf(vmax - 0.5f) + 1.0f, -1.0f), Hf));
+        keep = (umin <= umax) & !(zmin > 1.01f * (cam.zf * s2)) & (i0 <= i1) & (j0 <= j1);
+        f.X0 = __float_as_int(st.x); f.Y0 = __float_as_int(st.y);
+        f.X1 = __float_as_int(cs.x); f.Y1 = __float_as_int(cs.y);
+        f.X2 = __float_as_int(0.5f * dm.x); f.Y2 = __float_as_int(0.5f * dm.y);
+        f.X3 = i0; f.Y3 = i1;
+        f.A = dm.z;
+        // colours of the sides facing the camera: across the length, across the
+        // width, the top
+        const float px = cam.px - st.x, py = cam.py - st.y;
+        const bool front = fmaf(px, cs.x, py * cs.y) > 0.0f, left = fmaf(py, cs.x, -(px * cs.y)) > 0.0f;
+        const uint32_t c = s.box_rgb[g];
+        f.B = __uint_as_float(s.shade ? lit_face(s, sc, c, u, front ? 0 : 2) : c);
+        f.C = __uint_as_float(s.shade ? lit_face(s, sc, c, u, left ? 1 : 3) : c);
+        f.rgb = s.shade ? lit_face(s, sc, c, u, 4) : c;
+        f.keylo = key_low(1u, 6 * u, 0u);
+        f.j0 = (int16_t)j0; f.j1 = (int16_t)j1;
+        f.nv = 1;
+    }
+    const unsigned long long bm = __ballot(keep);
+    int nbt = 0;
+    const int at = box_reserve(L, true, nbt, __popcll(bm));
+    list_entry(L, keep && at >= 0, at + lanes_below(bm), f);
+    int bmin = keep ? (int)f.j0 : 0x7FFFFFFF, bmax = keep ? (int)f.j1 : -1;
+    box_rows(L, bmin, bmax);
+}
+
+// Traffic lights [u0, u0 + 64): light_pass's entries.
+__device__ __forceinline__ void rc_lights(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int u0)
+{
+    const int u = u0 + (int)lane_id();
+    bool keep = false;
+    FaceRec f = {};
+    if (u < sc.n_signals) {
+        const float4 q = s.signals[sc.signal_base + u];
+        const V3 c = to_cam(cam, q.x - cam.px, q.y - cam.py, q.z);
+        int i0, i1, j0, j1;
+        keep = signal_bounds(cam, c, q.w, i0, i1, j0, j1);
+        f.X0 = __float_as_int(c.x); f.Y0 = __float_as_int(c.y); f.X1 = __float_as_int(c.z);
+        f.Y1 = __float_as_int(q.w * q.w); f.X2 = __float_as_int(cam.f * c.z);
+        f.X3 = i0; f.Y3 = i1;
+        f.j0 = (int16_t)j0; f.j1 = (int16_t)j1;
+        f.keylo = key_low(1u, 6 * (sc.n_agents + sc.n_static) + sc.n_roads + u, 0u);
+        f.rgb = signal_rgb(s, sc, u);
+    }
+    const unsigned long long bm = __ballot(keep);
+    int nbt = 0;
+    const int at = box_reserve(L, true, nbt, __popcll(bm));
+    list_entry(L, keep && at >= 0, at + lanes_below(bm), f);
+    box_rows(L, keep ? (int)f.j0 : 0x7FFFFFFF, keep ? (int)f.j1 : -1);
+}
+
+// the key of the box entry's hit at the sample offsets a, b, or 0
+__device__ __forceinline__ unsigned long long rc_box_key(const Cam &cam, const float *o, const float *half, float cb,
+                                                         float sb, float Hb, uint32_t keylo, float a, float b)
+{
+    const float dx = fmaf(a, cam.fy, cam.f * cam.fx), dy = fmaf(a, -cam.fx, cam.f * cam.fy);
+    const float e0 = fmaf(dx, cb, dy * sb), e1 = fmaf(dy, cb, -(dx * sb)), e2 = b;
+    float t_in = -INFINITY, t_out = INFINITY;
+    int face = -1;
+    // the slab lo .. hi of an axis: entry and exit, the side entered (flo for a
+    // positive direction, fhi for a negative one)
+    auto axis = [&](float e, float p, float lo, float hi, int flo, int fhi) {
+        float en, lv;
+        int fk;
+        if (e != 0.0f) {
+            const bool up = e > 0.0f;
+            en = ((up ? lo : hi) - p) / e;
+            lv = ((up ? hi : lo) - p) / e;
+            fk = up ? flo : fhi;
+        } else {
+            const bool in = lo < p && p < hi;
+            en = in ? -INFINITY : INFINITY;
+            lv = in ? INFINITY : -INFINITY;
+            fk = -1;
+        }
+        if (en > t_in) {
+            t_in = en;
+            face = fk;
+        }
+        t_out = fminf(t_out, lv);
+    };
+    axis(e0, o[0], -half[0], half[0], 2, 0);
+    axis(e1, o[1], -half[1], half[1], 3, 1);
+    axis(e2, cam.h, 0.0f, Hb, 5, 4);
+    if (!((t_in <= t_out) & (t_in > 0.0f) & (t_in < INFINITY))) return 0ull;
+    const float z = t_in * cam.f;
+    if (!((z >= cam.zn) & (z <= cam.zf))) return 0ull;
+    return ((unsigned long long)__float_as_uint(1.0f / z) << 32) | (keylo - ((uint32_t)face << 8));
+}
+
+// The columns of row offset b on which a box's hit is certain, by the side
+// entered: segs[] holds up to three disjoint runs l << 16 | r << 2 | axis in
+// column order (unused ones last, l = W).  Along a row the ray's direction in
+// the box frame is affine in the column offset a, e_k = A_k + B_k a, so the hit
+// at t = N / e_k of the side facing the camera on axis k lies inside the other
+// two slabs, and within [z_near, z_far], where seven affine functions of a are
+// positive.  The margin (2^-16 of the distances in play) dominates the rounding
+// of the exact test, so on these columns that test takes this side and
+// accepts the hit: only its division is left to do.
+__device__ __forceinline__ void rc_certain(const Cam &cam, const FaceRec &f, float b, int xl, int xr, int *segs)
+{
+    const float cb = __int_as_float(f.X1), sb = __int_as_float(f.Y1);
+    const float ox = cam.px - __int_as_float(f.X0), oy = cam.py - __int_as_float(f.Y0);
+    const float p[3] = {fmaf(ox, cb, oy * sb), fmaf(oy, cb, -(ox * sb)), cam.h};
+    const float lo[3] = {-__int_as_float(f.X2), -__int_as_float(f.Y2), 0.0f};
+    const float hi[3] = {-lo[0], -lo[1], f.A};
+    const float ca = cam.fx * cb + cam.fy * sb, sa = cam.fy * cb - cam.fx * sb;     // forward in the box frame
+    const float A[3] = {cam.f * ca, cam.f * sa, b}, B[3] = {sa, -ca, 0.0f};
+    const float mu = fmaf(fabsf(ox) + fabsf(oy) + cam.h + hi[0] + hi[1] + hi[2], 0x1p-16f, 1e-5f);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        segs[k] = (cam.W << 16) | (int)((uint32_t)(cam.W - 1) << 2);
+        // the side facing the camera, and the direction's sign towards it
+        const bool above = p[k] > hi[k], below = p[k] < lo[k];
+        const float sg = above ? -1.0f : 1.0f;
+        const float M = above ? p[k] - hi[k] : lo[k] - p[k];
+        const float E0 = sg * A[k], E1 = sg * B[k];
+        float al = -INFINITY, ar = INFINITY;
+        bool ok = above | below;
+        auto positive = [&](float F0, float F1) {            // F0 + F1 a > 0
+            const float r = -F0 * __builtin_amdgcn_rcpf(F1);
+            al = F1 > 0.0f ? fmaxf(al, r) : al;
+            ar = F1 < 0.0f ? fminf(ar, r) : ar;
+            ok = ok & ((F1 != 0.0f) | (F0 > 0.0f));
+        };
+        positive(E0 - 1e-6f * cam.f, E1);
+        positive(M * cam.f - 1.0001f * (cam.zn * E0), -1.0001f * (cam.zn * E1));
+        positive(0.9999f * (cam.zf * E0) - M * cam.f, 0.9999f * (cam.zf * E1));
+#pragma unroll
+        for (int q = 1; q < 3; ++q) {
+            const int m = (k + q) % 3;
+            const float u = hi[m] - mu - p[m], v = p[m] - lo[m] - mu;
+            positive(fmaf(u, E0, -(M * A[m])), fmaf(u, E1, -(M * B[m])));
+            positive(fmaf(v, E0, M * A[m]), fmaf(v, E1, M * B[m]));
+        }
+        // whole columns, 2% of a column inside
+        const int l = max(xl, (int)ceilf(fminf(fmaxf(al + cam.cx - 0.48f, -1.0f), 2048.0f)));
+        const int r = min(xr, (int)floorf(fminf(fmaxf(ar + cam.cx - 0.52f, -2.0f), 2048.0f)));
+        if (ok & (l <= r)) segs[k] = (l << 16) | (r << 2) | k;
+    }
+    // column order
+    const int s01 = min(segs[0], segs[1]), l01 = max(segs[0], segs[1]);
+    segs[0] = min(s01, segs[2]);
+    const int t = max(s01, segs[2]);
+    segs[1] = min(l01, t);
+    segs[2] = max(l01, t);
+}
+
+// Fragments of the list's n entries in rows [b0, b1) folded into the key band.
+// The (entry, row) items are dealt to the lanes; an item's columns are the
+// certain runs above and what is left between them, cut into pieces that are
+// dealt again: certain pieces take one division a sample for the hit, the
+// others the full test.  Many items are shared out over the wavefronts by
+// passes of 64; few are set up by every wavefront, which then share the pieces
+// (one box near the camera can hold most of a view's samples).
+__device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, int b0, int b1, int wv, int nwv)
+{
+    const int ln = (int)lane_id(), W = cam.W;
+    int pass = 0;
+    for (int t0 = 0; t0 < n; t0 += 64) {
+        const int t = t0 + ln;
+        int c = 0, first = 0;
+        if (t < n) {
+            const int32_t jj = ((lptr<const int32_t>)(L.faces + t))[12];
+            first = max((int)(int16_t)(jj & 0xFFFF), b0);
+            c = max(0, min(jj >> 16, b1 - 1) - first + 1);
+        }
+        const int incl = wave_incl_scan(c);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        const int excl = incl - c;
+        const bool split = total <= 128 * nwv;              // pieces shared out, not passes
+        for (int g0 = 0; g0 < total; g0 += 64, ++pass) {
+            if (!split && pass % nwv != wv) continue;
+            const int gi = g0 + ln;
+            const int o = owner_of(incl, gi);
+            const int j = __shfl(first, o) + (gi - __shfl(excl, o));
+            int xl = 0, xr = -1;
+            const int none = (W << 16) | ((W - 1) << 2);
+            int segs[3] = {none, none, none};
+            int nq = 0, nu = 0;
+            if (gi < total) {
+                const FaceRec f = lds_load(L.faces + t0 + o);
+                xl = f.X3;
+                xr = f.Y3;
+                if (f.nv != 0) rc_certain(cam, f, cam.cy - ((float)j + 0.5f), xl, xr, segs);
+                int at = xl;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int l = segs[k] >> 16, r = (segs[k] >> 2) & 0x3FFF;
+                    if (l > r) continue;
+                    nq += (r - l + kRcPiece) / kRcPiece;
+                    nu += (l - at + kRcTests - 1) / kRcTests;
+                    at = r + 1;
+                }
+                nu += (xr - at + kRcTests) / kRcTests;
+            }
+            // ---- certain pieces
+            {
+                const int inc2 = wave_incl_scan(nq);
+                const int npt = __builtin_amdgcn_readlane(inc2, 63);
+                const int ex2 = inc2 - nq;
+                for (int p0 = split ? 64 * wv : 0; p0 < npt; p0 += split ? 64 * nwv : 64) {
+                    const int pi = p0 + ln;
+                    const int o2 = owner_of(inc2, pi);
+                    int k = pi - __shfl(ex2, o2);
+                    const int sj = __shfl(j, o2), so = t0 + __shfl(o, o2);
+                    const int g[3] = {__shfl(segs[0], o2), __shfl(segs[1], o2), __shfl(segs[2], o2)};
+                    if (pi >= npt) continue;
+                    int i0 = 0, i1 = -1, axis = 0;
+                    bool found = false;
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const int l = g[q] >> 16, r = (g[q] >> 2) & 0x3FFF;
+                        const int np = l <= r ? (r - l + kRcPiece) / kRcPiece : 0;
+                        if (!found && k < np) {
+                            i0 = l + kRcPiece * k;
+                            i1 = min(i0 + kRcPiece - 1, r);
+                            axis = g[q] & 3;
+                            found = true;
+                        }
+                        k -= np;
+                    }
+                    const float b = cam.cy - ((float)sj + 0.5f);
+                    lptr<unsigned long long> kp = L.work + (sj - b0) * W;
+                    const FaceRec f = lds_load(L.faces + so);
+                    const float cb = __int_as_float(f.X1), sb = __int_as_float(f.Y1);
+                    const float ox = cam.px - __int_as_float(f.X0), oy = cam.py - __int_as_float(f.Y0);
+                    const float pk = axis == 0 ? fmaf(ox, cb, oy * sb) : (axis == 1 ? fmaf(oy, cb, -(ox * sb)) : cam.h);
+                    const float hk = axis == 0 ? __int_as_float(f.X2) : (axis == 1 ? __int_as_float(f.Y2) : f.A);
+                    const bool above = pk > 0.0f;            // the camera is beyond the side hk (else beyond -hk)
+                    const float num = (above ? hk : -hk) - pk;
+                    const int face = axis == 2 ? 4 : (axis == 0 ? (above ? 0 : 2) : (above ? 1 : 3));
+                    const uint32_t keylo = f.keylo - ((uint32_t)face << 8);
+                    const float s1 = axis == 0 ? sb : -sb;
+                    for (int i = i0; i <= i1; ++i) {
+                        const float a = ((float)i + 0.5f) - cam.cx;
+                        const float dx = fmaf(a, cam.fy, cam.f * cam.fx), dy = fmaf(a, -cam.fx, cam.f * cam.fy);
+                        float e = axis == 0 ? fmaf(dx, cb, dy * s1) : fmaf(dy, cb, dx * s1);
+                        e = axis == 2 ? b : e;
+                        const float z = (num / e) * cam.f;
+                        lds_max64(kp + i, ((unsigned long long)__float_as_uint(1.0f / z) << 32) | keylo);
+                    }
+                }
+            }
+            // ---- the rest
+            const int inc2 = wave_incl_scan(nu);
+            const int npt = __builtin_amdgcn_readlane(inc2, 63);
+            const int ex2 = inc2 - nu;
+            for (int p0 = split ? 64 * wv : 0; p0 < npt; p0 += split ? 64 * nwv : 64) {
+                const int pi = p0 + ln;
+                const int o2 = owner_of(inc2, pi);
+                int k = pi - __shfl(ex2, o2);
+                const int sj = __shfl(j, o2), so = t0 + __shfl(o, o2);
+                const int sxl = __shfl(xl, o2), sxr = __shfl(xr, o2);
+                const int g[3] = {__shfl(segs[0], o2), __shfl(segs[1], o2), __shfl(segs[2], o2)};
+                if (pi >= npt) continue;
+                int i0 = 0, i1 = -1, at = sxl;
+                bool found = false;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    // the gap before run q, or after the last one
+                    const int l = q < 3 ? g[q < 3 ? q : 0] >> 16 : sxr + 1, r = q < 3 ? (g[q < 3 ? q : 0] >> 2) & 0x3FFF : sxr;
+                    if (q < 3 && l > r) continue;
+                    const int np = (l - at + kRcTests - 1) / kRcTests;
+                    if (!found && k < np) {
+                        i0 = at + kRcTests * k;
+                        i1 = min(i0 + kRcTests, l) - 1;
+                        found = true;
+                    }
+                    k -= np;
+                    at = r + 1;
+                }
+                const float b = cam.cy - ((float)sj + 0.5f);
+                lptr<unsigned long long> kp = L.work + (sj - b0) * W;
+                const FaceRec f = lds_load(L.faces + so);
+                if (f.nv == 0) {
+                    for (int i = i0; i <= i1; ++i) {
+                        const float invz = light_invz(L, cam, so, ((float)i + 0.5f) - cam.cx, b);
+                        if (invz > 0.0f) lds_max64(kp + i, ((unsigned long long)__float_as_uint(invz) << 32) | f.keylo);
+                    }
+                    continue;
+                }
+                const float cb = __int_as_float(f.X1), sb = __int_as_float(f.Y1);
+                const float ox = cam.px - __int_as_float(f.X0), oy = cam.py - __int_as_float(f.Y0);
+                const float og[2] = {fmaf(ox, cb, oy * sb), fmaf(oy, cb, -(ox * sb))};
+                const float half[2] = {__int_as_float(f.X2), __int_as_float(f.Y2)};
+                for (int i = i0; i <= i1; ++i) {
+                    const unsigned long long key = rc_box_key(cam, og, half, cb, sb, f.A, f.keylo, ((float)i + 0.5f) - cam.cx, b);
+                    if (key != 0ull) lds_max64(kp + i, key);
+                }
+            }
+        }
+    }
+}
+
+template <bool COV>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_raycast(DevSim s, RenderOut o, RcCfg c,
+                                                                                         int view_begin)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    GP_RC_LDS unsigned long long *keys = (GP_RC_LDS unsigned long long *)smem;
-    GP_RC_LDS float *stg = (GP_RC_LDS float *)(smem + 8 * kRcBandPixels);       // [kRcStageWords][256]
-    GP_RC_LDS int32_t *cnt = (GP_RC_LDS int32_t *)(smem + 8 * kRcBandPixels + 4 * kRcStageWords * kRcThreads);
-    GP_RC_LDS uint32_t *pal = (GP_RC_LDS uint32_t *)(cnt + 4);
-    GP_RC_LDS float *sst = (GP_RC_LDS float *)(pal + 256);                         // [kRcStripWords][256]
-    GP_RC_LDS int32_t *isst = (GP_RC_LDS int32_t *)sst;
-    GP_RC_LDS int32_t *istg = (GP_RC_LDS int32_t *)stg;
-    const int tid = threadIdx.x, B = kRcThreads;
-    const int view = view_begin + blockIdx.x;
+    const int B = (int)blockDim.x, K = B >> 6, tid = (int)threadIdx.x, wv = tid >> 6;
+    const int W = s.width, H = s.height;
+    const RcLayout l = rc_layout(W, H, c);
+    RgbLds L;
+    L.cnt = (lptr<int32_t>)(smem + l.cnt);
+    L.bits = (lptr<unsigned long long>)(smem + l.bits);
+    L.faces = (lptr<FaceRec>)(smem + l.faces);
+    L.sbins = (lptr<int32_t>)(smem + l.sbins);
+    L.cq = nullptr;
+    L.sring = (lptr<int32_t>)(smem + l.sring);
+    L.waves = (lptr<unsigned char>)(smem + l.waves);
+    L.pat = (lptr<gp_v4i>)(smem + l.sbins);
+    L.work = (lptr<unsigned long long>)(smem + l.keys);
+    L.bcap = c.bcap;
+    L.krows = l.krows;
+    L.hr0 = first_road_row(H);
+    L.nmw = 0;
+    L.region = l.region;
+    lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
+
+    const int view = s.order[view_begin + (int)blockIdx.x];
     const int scene = __builtin_amdgcn_readfirstlane(s.views[view].scene);
     const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
-    const SceneRec sc = s.scenes[scene];
-    const int ego = ego_cam >> 2, k = ego_cam & 3;
-    const int n_box = sc.n_agents + sc.n_static;
-    RcCam cam;
-    {
-        const int ga = sc.agent_base + ego;
-        const float4 st = s.state[ga];
-        const float2 cs = s.cs[ga];
-        const float ck = s.cam_dir[k][0], sk = s.cam_dir[k][1];
-        cam.px = uniform_float(st.x);
-        cam.py = uniform_float(st.y);
-        cam.fx = uniform_float(fmaf(cs.x, ck, -(cs.y * sk)));
-        cam.fy = uniform_float(fmaf(cs.y, ck, cs.x * sk));
-        cam.h = s.cam_height;
-        cam.f = s.focal;
-        cam.W = s.width;
-        cam.H = s.height;
-        cam.cx = 0.5f * (float)s.width;
-        cam.cy = 0.5f * (float)s.height;
-        cam.zn = s.z_near;
-        cam.zf = s.z_far;
-        cam.tx = (0.5f * (float)s.width / s.focal) * 1.001f + 1e-3f;
+    const SceneRec sc = uniform_scene(s.scenes[scene]);
+    const int ego = ego_cam >> 2;
+    const Cam cam = make_cam(s, sc, ego, ego_cam & 3);
+    const float s2 = uniform_f(rc_scale2(cam));
+    const float hfs = uniform_f(cam.h * cam.f * s2);
+
+    if (COV) {
+        const int nbits = ((W * (H - L.hr0) + 63) >> 6) + 1;
+        for (int p = tid; p < nbits; p += B) L.bits[p] = 0ull;
+    } else {
+        for (int p = tid; p < 256; p += B)
+            pal[p] = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) |
+                     ((uint32_t)s.palette[3 * p + 2] << 16);
     }
-    for (int p = tid; p < 256; p += B)
-        pal[p] = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) |
-                 ((uint32_t)s.palette[3 * p + 2] << 16);
-    const int W = cam.W, H = cam.H;
-    const int rows = max(1, kRcBandPixels / W);
-    const int rrows = max(1, kRcRoadPixels / W);      // rows of a road sub-band
-    const int64_t img0 = (int64_t)view * W * H;
-    const int sig0 = 6 * n_box + sc.n_roads;
-    for (int j0 = 0; j0 < H; j0 += rows) {
-        const int j1 = min(H, j0 + rows), npix = (j1 - j0) * W;
-        for (int p = tid; p < npix; p += B) keys[p] = 0ull;
+    if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
+    __syncthreads();
 
-        // ---- boxes: cull a chunk, stage the survivors, test every pixel
-        for (int u0 = 0; u0 < n_box; u0 += B) {
-            __syncthreads();
-            if (tid == 0) cnt[0] = 0;
-            __syncthreads();
-            const int u = u0 + tid;
-            if (u < n_box && u != ego) {
-                const int g = box_slot(sc, u);
-                const float4 st = s.state[g];
-                const float4 dm = s.dims[g];
-                const float ox = st.x - cam.px, oy = st.y - cam.py;
-                const float z = fmaf(ox, cam.fx, oy * cam.fy), x = fmaf(ox, cam.fy, -(oy * cam.fx));
-                const float R = 0.5f * (dm.x + dm.y) + 1e-3f;      // bounds the footprint's reach from its centre
-                const bool keep = !(z + R < cam.zn) && !(z - R > cam.zf) && !(fabsf(x) - R > (z + R) * cam.tx);
-                if (keep) {
-                    const int q = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    const float2 cs = s.cs[g];
-                    // pixel rectangle that holds every sample whose ray can hit the
-                    // box: with every corner in front of the camera, the box's
-                    // image is the hull of its corners' images (a pixel of margin
-                    // for rounding); otherwise the whole image
-                    int i0 = 0, i1 = cam.W - 1, jr0 = 0, jr1 = cam.H - 1;
-                    {
-                        const float ax = 0.5f * dm.x * cs.x, ay = 0.5f * dm.x * cs.y;
-                        const float bx = -(0.5f * dm.y * cs.y), by = 0.5f * dm.y * cs.x;
-                        float umin = INFINITY, umax = -INFINITY, vmin = INFINITY, vmax = -INFINITY, zmin = INFINITY;
-#pragma unroll
-                        for (int c4 = 0; c4 < 4; ++c4) {
-                            const float sa = (c4 & 1) ? -1.0f : 1.0f, sb = (c4 & 2) ? -1.0f : 1.0f;
-                            const float wx = ox + sa * ax + sb * bx, wy = oy + sa * ay + sb * by;
-                            const float zc = fmaf(wx, cam.fx, wy * cam.fy), xc = fmaf(wx, cam.fy, -(wy * cam.fx));
-                            zmin = fminf(zmin, zc);
-                            const float iz = 1.0f / zc;
-                            const float u = fmaf(cam.f * xc, iz, cam.cx);
-                            const float v0 = fmaf(-cam.f * (0.0f - cam.h), iz, cam.cy), v1 = fmaf(-cam.f * (dm.z - cam.h), iz, cam.cy);
-                            umin = fminf(umin, u);
-                            umax = fmaxf(umax, u);
-                            vmin = fminf(vmin, fminf(v0, v1));
-                            vmax = fmaxf(vmax, fmaxf(v0, v1));
-                        }
-                        if (zmin > 0.05f) {
-                            i0 = max(0, (int)fminf(fmaxf(floorf(umin - 0.5f) - 1.0f, -1.0f), (float)cam.W));
-                            i1 = min(cam.W - 1, (int)fminf(fmaxf(ceilf(umax - 0.5f) + 1.0f, -1.0f), (float)cam.W));
-                            jr0 = max(0, (int)fminf(fmaxf(floorf(vmin - 0.5f) - 1.0f, -1.0f), (float)cam.H));
-                            jr1 = min(cam.H - 1, (int)fminf(fmaxf(ceilf(vmax - 0.5f) + 1.0f, -1.0f), (float)cam.H));
-                        }
-                    }
-                    istg[8 * B + q] = i0 | (jr0 << 16);
-                    istg[9 * B + q] = i1 | (jr1 << 16);
-                    stg[0 * B + q] = st.x;
-                    stg[1 * B + q] = st.y;
-                    stg[2 * B + q] = cs.x;
-                    stg[3 * B + q] = cs.y;
-                    stg[4 * B + q] = 0.5f * dm.x;
-                    stg[5 * B + q] = 0.5f * dm.y;
-                    stg[6 * B + q] = dm.z;
-                    istg[7 * B + q] = (u << 8) | s.agent_color[g];
-                }
-            }
-            __syncthreads();
-            const int nb = cnt[0];
-            for (int p = tid; p < npix; p += B) {
-                const int j = j0 + p / W, i = p - (p / W) * W;
-                float a, b, dx, dy;
-                rc_sample(cam, i, j, a, b, dx, dy);
-                unsigned long long best = keys[p];
-                for (int r = 0; r < nb; ++r) {
-                    const int lo = istg[8 * B + r], hi = istg[9 * B + r];
-                    if (i < (lo & 0xFFFF) || j < (lo >> 16) || i > (hi & 0xFFFF) || j > (hi >> 16)) continue;
-                    const float bxr = stg[r], byr = stg[B + r], cb = stg[2 * B + r], sb = stg[3 * B + r];
-                    const float hl = stg[4 * B + r], hw = stg[5 * B + r], Hb = stg[6 * B + r];
-                    const int tag = istg[7 * B + r];
-                    const float ox = cam.px - bxr, oy = cam.py - byr;
-                    const float o0 = fmaf(ox, cb, oy * sb), o1 = fmaf(oy, cb, -(ox * sb)), o2 = cam.h;
-                    const float e0 = fmaf(dx, cb, dy * sb), e1 = fmaf(dy, cb, -(dx * sb)), e2 = b;
-                    float t_in = -INFINITY, t_out = INFINITY;
-                    int face = -1;
-                    // axis 0: [-hl, hl], faces back (2) / front (0)
-                    {
-                        float en, lv;
-                        int fk;
-                        if (e0 > 0.0f) { en = (-hl - o0) / e0; lv = (hl - o0) / e0; fk = 2; }
-                        else if (e0 < 0.0f) { en = (hl - o0) / e0; lv = (-hl - o0) / e0; fk = 0; }
-                        else { const bool in = -hl < o0 && o0 < hl; en = in ? -INFINITY : INFINITY; lv = in ? INFINITY : -INFINITY; fk = -1; }
-                        if (en > t_in) { t_in = en; face = fk; }
-                        t_out = fminf(t_out, lv);
-                    }
-                    {
-                        float en, lv;
-                        int fk;
-                        if (e1 > 0.0f) { en = (-hw - o1) / e1; lv = (hw - o1) / e1; fk = 3; }
-                        else if (e1 < 0.0f) { en = (hw - o1) / e1; lv = (-hw - o1) / e1; fk = 1; }
-                        else { const bool in = -hw < o1 && o1 < hw; en = in ? -INFINITY : INFINITY; lv = in ? INFINITY : -INFINITY; fk = -1; }
-                        if (en > t_in) { t_in = en; face = fk; }
-                        t_out = fminf(t_out, lv);
-                    }
-                    {
-                        float en, lv;
-                        int fk;
-                        if (e2 > 0.0f) { en = (0.0f - o2) / e2; lv = (Hb - o2) / e2; fk = 5; }
-                        else if (e2 < 0.0f) { en = (Hb - o2) / e2; lv = (0.0f - o2) / e2; fk = 4; }
-                        else { const bool in = 0.0f < o2 && o2 < Hb; en = in ? -INFINITY : INFINITY; lv = in ? INFINITY : -INFINITY; fk = -1; }
-                        if (en > t_in) { t_in = en; face = fk; }
-                        t_out = fminf(t_out, lv);
-                    }
-                    if (!(t_in <= t_out && t_in > 0.0f && t_in < INFINITY)) continue;
-                    const float z = t_in * cam.f;
-                    if (!(z >= cam.zn && z <= cam.zf)) continue;
-                    const unsigned long long key =
-                        make_key(1.0f / z, key_word(1u, 6 * (tag >> 8) + face, (uint32_t)tag & 0xFFu));
-                    best = key > best ? key : best;
-                }
-                keys[p] = best;
-            }
+    // ---- bins of the scene whose strips some row can see
+    for (int b0 = 64 * wv; b0 < sc.n_bins; b0 += B) {
+        const int b = b0 + (int)lane_id();
+        bool keep = false;
+        int rec = 0;
+        if (b < sc.n_bins) {
+            const RoadBin bn = s.bins[sc.bin_base + b];
+            float x[4], z[4], m;
+            int j0, j1;
+            rc_corners(cam, make_float4(bn.xmin, bn.ymin, bn.xmax, bn.ymin), make_float4(bn.xmax, bn.ymax, bn.xmin, bn.ymax),
+                       x, z);
+            keep = !rc_outside(cam, hfs, x, z, L.hr0, H, j0, j1, m);
+            rec = bn.start * 128 + bn.count;
         }
+        list_bins(L, keep, rec);
+    }
+    __syncthreads();
+    const int nsb = L.cnt[R_NSB];
+    lptr<RcStrip> st = (lptr<RcStrip>)(L.waves + (size_t)wv * kWaveBytes);
 
-        // ---- road strips by culling bin: the ground point of each pixel, in
-        // sub-bands of rows.  A row's ground points share the depth -h f / b,
-        // so a sub-band sees the ground only between the depths of its lowest
-        // row and of its highest row below the horizon; bins outside that
-        // range are culled as well
-        for (int r0 = j0; r0 < j1; r0 += rrows) {
-            const int r1 = min(j1, r0 + rrows);
-            const float b_low = cam.cy - ((float)(r1 - 1) + 0.5f);
-            const int j_top = max(r0, (int)floorf(cam.cy - 0.5f) + 1);
-            const float b_top = cam.cy - ((float)j_top + 0.5f);
-            const float gz_lo = b_low < 0.0f ? fmaxf(cam.zn, -(cam.h * cam.f) / b_low) : cam.zf;
-            const float gz_hi = b_top < 0.0f ? fminf(cam.zf, -(cam.h * cam.f) / b_top) : cam.zf;
-            for (int u0 = 0; b_low < 0.0f && u0 < sc.n_bins; u0 += B) {
-                __syncthreads();
-                if (tid == 0) cnt[0] = 0;
-                __syncthreads();
-                const int u = u0 + tid;
-                if (u < sc.n_bins) {
-                    const RoadBin bn = s.bins[sc.bin_base + u];
-                    // ground points a sample can show lie at depth [zn, zf] inside the
-                    // horizontal frustum; reject bins whose corners are all out on one side
-                    const float xs[4] = {bn.xmin, bn.xmax, bn.xmax, bn.xmin}, ys[4] = {bn.ymin, bn.ymin, bn.ymax, bn.ymax};
-                    bool nz = true, fz = true, lft = true, rgt = true;
-    #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float ox = xs[q] - cam.px, oy = ys[q] - cam.py;
-                        const float z = fmaf(ox, cam.fx, oy * cam.fy), x = fmaf(ox, cam.fy, -(oy * cam.fx));
-                        const float m = 1e-3f * (fabsf(x) + fabsf(z)) + 1e-3f;
-                        nz = nz && (z < gz_lo - m);
-                        fz = fz && (z > gz_hi + m);
-                        rgt = rgt && (x - cam.tx * z > m);
-                        lft = lft && (-x - cam.tx * z > m);
-                    }
-                    if (!(nz || fz || lft || rgt)) {
-                        const int q = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        stg[0 * B + q] = bn.xmin - 1e-2f;
-                        stg[1 * B + q] = bn.ymin - 1e-2f;
-                        stg[2 * B + q] = bn.xmax + 1e-2f;
-                        stg[3 * B + q] = bn.ymax + 1e-2f;
-                        istg[4 * B + q] = bn.start;
-                        istg[5 * B + q] = bn.count;
-                    }
-                }
-                __syncthreads();
-                const int nb = cnt[0];
-                if (nb == 0) continue;
-                // the staged bins in groups of kRcGroupBins: a group's strips go
-                // to LDS (thread k holds strip k mod kBinQuads of bin k / kBinQuads),
-                // then every pixel tests them and folds its best road into its
-                // key; the largest key over the groups is the lowest road index
-                for (int g0 = 0; g0 < nb; g0 += kRcGroupBins) {
-                    const int g1 = min(nb, g0 + kRcGroupBins);
-                    {
-                        const int r = g0 + tid / kBinQuads, q = tid % kBinQuads;
-                        if (r < g1 && q < istg[5 * B + r]) {
-                            const int g = sc.road_base + istg[4 * B + r] + q;
-                            const float4 q0 = s.roads[2 * g], q1 = s.roads[2 * g + 1];
-                            sst[0 * B + tid] = q0.x;
-                            sst[1 * B + tid] = q0.y;
-                            sst[2 * B + tid] = q0.z;
-                            sst[3 * B + tid] = q0.w;
-                            sst[4 * B + tid] = q1.x;
-                            sst[5 * B + tid] = q1.y;
-                            sst[6 * B + tid] = q1.z;
-                            sst[7 * B + tid] = q1.w;
-                            isst[8 * B + tid] = (s.road_index[g] << 8) | (int)s.road_color[g];
-                        }
-                    }
-                    __syncthreads();
-                    for (int p = (r0 - j0) * W + tid; p < (r1 - j0) * W; p += B) {
-                        const int j = j0 + p / W, i = p - (p / W) * W;
-                        float a, b, dx, dy;
-                        rc_sample(cam, i, j, a, b, dx, dy);
-                        if (!(b < 0.0f)) continue;
-                        const float sp = -cam.h / b;
-                        const float z = sp * cam.f;
-                        if (!(z >= cam.zn && z <= cam.zf)) continue;
-                        const float x = fmaf(sp, dx, cam.px), y = fmaf(sp, dy, cam.py);
-                        int best = INT32_MAX;          // (road index << 8) | colour of the best strip
-                        for (int r = g0; r < g1; ++r) {
-                            if (x < stg[r] || y < stg[B + r] || x > stg[2 * B + r] || y > stg[3 * B + r]) continue;
-                            const int n = istg[5 * B + r], base = (r - g0) * kBinQuads;
-                            for (int q = 0; q < n; ++q) {
-                                const int k = base + q;
-                                const float qx[4] = {sst[k], sst[2 * B + k], sst[4 * B + k], sst[6 * B + k]};
-                                const float qy[4] = {sst[B + k], sst[3 * B + k], sst[5 * B + k], sst[7 * B + k]};
-                                int pos = 0, neg = 0;
-    #pragma unroll
-                                for (int e = 0; e < 4; ++e) {
-                                    const int e1 = (e + 1) & 3;
-                                    const float ex = qx[e1] - qx[e], ey = qy[e1] - qy[e];
-                                    const float wx = x - qx[e], wy = y - qy[e];
-                                    const float c = fmaf(ex, wy, -(ey * wx));
-                                    pos += c > 0.0f;
-                                    neg += c < 0.0f;
-                                }
-                                const int rc = isst[8 * B + k];
-                                if ((pos == 4 || neg == 4) && rc < best) best = rc;
-                            }
-                        }
-                        if (best != INT32_MAX) {
-                            const unsigned long long key =
-                                make_key(1.0f / z, key_word(0u, 6 * n_box + (best >> 8), (uint32_t)best & 0xFFu));
-                            if (key > keys[p]) keys[p] = key;
-                        }
-                    }
-                    __syncthreads();                   // the next group overwrites the strips
-                }
-            }
+    // The list holds every box and light of the scene, or (c.chunk) is filled
+    // and folded in chunks of candidates per band.
+    const int nbox = sc.n_agents + sc.n_static, ncand = nbox + sc.n_signals;
+    const bool chunked = ncand > c.bcap;
+    const int ub = K >= 8 ? 16 : 64;
+    const int nbu = (nbox + ub - 1) / ub, nlu = (sc.n_signals + 63) / 64;
+    auto box_job = [&](int u) {
+        if (u < nbu) rc_boxes(s, sc, cam, ego, L, s2, ub * u, ub);
+        else rc_lights(s, sc, cam, L, 64 * (u - nbu));
+    };
+    auto roads = [&](int jobs, bool reuse, int b0, int b1, int band0) -> bool {
+        return road_work(
+            s, sc, L, nsb, jobs, reuse,
+            [&](bool live, const float4 &q0, const float4 &q1) -> bool {
+                float x[4], z[4], m;
+                int j0, j1;
+                rc_corners(cam, q0, q1, x, z);
+                return live && !rc_outside(cam, hfs, x, z, L.hr0, H, j0, j1, m);
+            },
+            box_job, [&](int a, int n) { rc_strips<COV>(s, sc, cam, L, st, hfs, s2, a, n, b0, b1, band0); });
+    };
+    // the entries of rows [b0, b1) folded into the (cleared) key band; ends with a barrier
+    auto boxes = [&](int b0, int b1) {
+        if (!chunked) {
+            rc_band(L, cam, L.cnt[R_NBT], b0, b1, wv, K);
+            __syncthreads();
+            return;
         }
-
-        // ---- traffic lights: the raster's sphere test
-        for (int u0 = 0; u0 < sc.n_signals; u0 += B) {
+        for (int c0 = 0; c0 < nbox; c0 += c.bcap) {
+            if (tid == 0) L.cnt[R_NBT] = 0;
             __syncthreads();
-            if (tid == 0) cnt[0] = 0;
+            for (int u = c0 + 64 * wv; u < min(nbox, c0 + c.bcap); u += B)
+                rc_boxes(s, sc, cam, ego, L, s2, u, min(64, c0 + c.bcap - u));
             __syncthreads();
-            const int u = u0 + tid;
-            if (u < sc.n_signals) {
-                const int g = sc.signal_base + u;
-                const float4 q = s.signals[g];
-                const float dxw = q.x - cam.px, dyw = q.y - cam.py;
-                const float cz = fmaf(dxw, cam.fx, dyw * cam.fy), cxx = fmaf(dxw, cam.fy, -(dyw * cam.fx));
-                const float cy = q.z - cam.h;
-                const bool keep = !(cz + q.w < cam.zn) && !(cz - q.w > cam.zf) &&
-                                  !(fabsf(cxx) - q.w > (cz + q.w) * cam.tx);
-                if (keep) {
-                    const int k2 = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    stg[0 * B + k2] = cxx;
-                    stg[1 * B + k2] = cy;
-                    stg[2 * B + k2] = cz;
-                    stg[3 * B + k2] = q.w * q.w;
-                    stg[4 * B + k2] = cam.f * cz;
-                    istg[5 * B + k2] = (int)key_word(1u, sig0 + u, s.signal_color[g]);
-                }
+            rc_band(L, cam, L.cnt[R_NBT], b0, b1, wv, K);
+            __syncthreads();
+        }
+        for (int c0 = 0; c0 < sc.n_signals; c0 += 64) {
+            if (tid == 0) L.cnt[R_NBT] = 0;
+            __syncthreads();
+            if (wv == 0) rc_lights(s, sc, cam, L, c0);
+            __syncthreads();
+            rc_band(L, cam, L.cnt[R_NBT], b0, b1, wv, K);
+            __syncthreads();
+        }
+    };
+    auto clear = [&](int npix) {
+        for (int p = tid; p < npix; p += B) L.work[p] = 0ull;
+    };
+    if (COV) {
+        (void)roads(chunked ? 0 : nbu + nlu, false, L.hr0, H, 0);
+        uint8_t *img = o.rgb + 3 * ((int64_t)view * W * H);
+        int kr0 = H, kr1 = H;
+        if (chunked) {
+            kr0 = 0;
+        } else if (L.cnt[R_NBT] > 0) {
+            kr0 = L.cnt[R_BMIN];
+            kr1 = L.cnt[R_BMAX] + 1;
+        }
+        const uint32_t bg_rgb = s.bg_rgb;
+        const uint32_t road_rgb = s.shade ? shade_rgb(s.road_rgb, shade_level(s, 0.0f, 0.0f, 4)) : s.road_rgb;
+        build_patterns(L, road_rgb, bg_rgb);
+        clear((min(kr0 + L.krows, kr1) - kr0) * W);
+        __syncthreads();
+        write_rows(L, img, road_rgb, bg_rgb, W, 0, kr0);
+        write_rows(L, img, road_rgb, bg_rgb, W, kr1, H);
+        for (int b0 = kr0; b0 < kr1; b0 += L.krows) {
+            const int b1 = min(b0 + L.krows, kr1);
+            if (b0 != kr0) {
+                __syncthreads();
+                clear((b1 - b0) * W);
+                __syncthreads();
             }
-            __syncthreads();
-            const int nb = cnt[0];
-            const float f = cam.f, ff = f * f;
-            for (int p = tid; p < npix; p += B) {
-                const int j = j0 + p / W, i = p - (p / W) * W;
-                const float a = ((float)i + 0.5f) - cam.cx;
-                const float b = cam.cy - ((float)j + 0.5f);
-                unsigned long long best = keys[p];
-                for (int r = 0; r < nb; ++r) {
-                    const float xc = stg[r], yc = stg[B + r], zc = stg[2 * B + r], r2 = stg[3 * B + r], fz = stg[4 * B + r];
-                    const float dd = fmaf(a, a, fmaf(b, b, ff));
-                    const float dc = fmaf(a, xc, fmaf(b, yc, fz));
-                    const float s0 = dc / dd;
-                    const float wx = fmaf(-s0, a, xc), wy = fmaf(-s0, b, yc), wz = fmaf(-s0, f, zc);
-                    const float qq = r2 - fmaf(wx, wx, fmaf(wy, wy, wz * wz));
-                    if (!(qq > 0.0f)) continue;
-                    const float z = (s0 - sqrtf(qq / dd)) * f;
-                    if (!(z >= cam.zn && z <= cam.zf)) continue;
-                    const unsigned long long key = make_key(1.0f / z, (uint32_t)istg[5 * B + r]);
-                    best = key > best ? key : best;
-                }
-                keys[p] = best;
-            }
+            boxes(b0, b1);
+            resolve_band(
+                L, W,
+                [&](int j) {
+                    const RcRow r = rc_row(cam, j);
+                    return r.ok ? 1.0f / r.z : 0.0f;
+                },
+                [&](uint32_t keylo) { return rc_color(s, sc, L, chunked, keylo); }, L.work, img, road_rgb, bg_rgb, b0, b1);
+        }
+        return;
+    }
+    bool first = true, whole = false;            // whole: the ring holds every strip of the view
+    for (int b0 = 0; b0 < H; b0 += L.krows) {
+        const int b1 = min(b0 + L.krows, H);
+        if (!first) __syncthreads();                 // the last band's keys are read
+        clear((b1 - b0) * W);
+        if (!first && tid == 0) {
+            L.cnt[R_JOB] = 0;
+            if (!whole) L.cnt[R_NEXT] = L.cnt[R_RING] = L.cnt[R_RESV] = 0;
         }
         __syncthreads();
-
-        // ---- resolve the band (as the raster's general kernel)
-        const uint32_t q_road = s.shade ? rc_level(s, 0.0f, 0.0f, 4) : 255u;
-        for (int p = tid; p < npix; p += B) {
-            const unsigned long long key = keys[p];
-            const int64_t px = img0 + (int64_t)j0 * W + p;
-            uint32_t c = pal[key ? ((uint32_t)key & 0xFFu) : 0u];
-            const int prim = key ? (kMaxPrims - 1) - (int)(((uint32_t)key >> 8) & (uint32_t)(kMaxPrims - 1)) : -1;
-            if (s.shade && key) {
-                if (prim < 6 * n_box) {
-                    const int bi = prim / 6, fc = prim - 6 * bi;
-                    const float2 cs = s.cs[box_slot(sc, bi)];
-                    const float nx = fc == 0 ? cs.x : fc == 1 ? -cs.y : fc == 2 ? -cs.x : cs.y;
-                    const float ny = fc == 0 ? cs.y : fc == 1 ? cs.x : fc == 2 ? -cs.y : -cs.x;
-                    c = rc_scale(c, rc_level(s, nx, ny, fc));
-                } else if (prim < sig0) {
-                    c = rc_scale(c, q_road);
-                }
-            }
-            o.rgb[3 * px] = (uint8_t)c;
-            o.rgb[3 * px + 1] = (uint8_t)(c >> 8);
-            o.rgb[3 * px + 2] = (uint8_t)(c >> 16);
-            if (o.depth) o.depth[px] = key ? 1.0f / __uint_as_float((uint32_t)(key >> 32)) : __int_as_float(0x7F800000);
-            if (o.primid) o.primid[px] = prim;
-        }
-        __syncthreads();
+        // the first band's road work lists the boxes too, whether or not the band shows road
+        if (first || b1 > L.hr0)
+            whole = roads(first && !chunked ? nbu + nlu : 0, whole, max(b0, L.hr0), max(b1, L.hr0), b0) | whole;
+        first = false;
+        boxes(b0, b1);
+        resolve_full(s, (lptr<const uint32_t>)pal,
+                     [&](uint32_t keylo) { return rc_color(s, sc, L, chunked, keylo); },
+                     (lptr<const unsigned long long>)L.work, o,
+                     ((int64_t)view * H + b0) * W, (b1 - b0) * W);
     }
 }
 
 }  // namespace
 
-size_t raycast_lds_bytes()
-{
-    return 8 * kRcBandPixels + 4 * kRcStageWords * kRcThreads + 16 + 1024 + 4 * kRcStripWords * kRcThreads;
-}
+size_t raycast_lds_bytes(int width, int height, const RcCfg &c) { return rc_layout(width, height, c).total; }
 
-hipError_t launch_raycast(const DevSim &s, const RenderOut &o, int view_begin, int n_views, hipStream_t st)
+hipError_t launch_raycast(const DevSim &s, const RenderOut &o, const RcCfg &c, int view_begin, int n_views, hipStream_t st)
 {
     if (n_views <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_raycast, dim3(n_views), dim3(kRcThreads), raycast_lds_bytes(), st, s, o, view_begin);
+    if (c.waves < 1 || c.waves > 16 || c.band_rows < 1 || c.bcap < 64 || c.bcap % 64 != 0 || (c.cover && s.width < 16))
+        return hipErrorInvalidValue;
+    const size_t lds = raycast_lds_bytes(s.width, s.height, c);
+    const dim3 block(64 * c.waves);
+    if (c.cover) hipLaunchKernelGGL(k_raycast<true>, dim3(n_views), block, lds, st, s, o, c, view_begin);
+    else hipLaunchKernelGGL(k_raycast<false>, dim3(n_views), block, lds, st, s, o, c, view_begin);
     return hipGetLastError();
 }
 

@@ -388,6 +388,31 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
     return c;
 }
 
+// Settings of the ray caster.  The list holds every box and light of the
+// largest scene up to 256 (scenes with more are cast in chunks).  Wavefronts per
+// view: 4, with coverage bits 8 from 200K pixels on, without them (depth,
+// primitive ids, mixed road colours) 8 from 24K on; doubled while every view's
+// wavefronts fit the chip.  The key band holds 4,096 samples with coverage bits
+// and 512 per wavefront without: a larger band leaves room for fewer
+// workgroups, a smaller one repeats the road work more often.  Us by
+// wavefronts and samples (one MI355X): 2,048 views 128 x 128 rgb 4/4,096 116,
+// 4/2,048 124, 2/2,048 136, 8/4,096 129; with depth and ids 4/2,048 209, 8/4,096
+// 227, 4/4,096 259; 1,024 views 512 x 512 rgb 8/4,096 819, 4/4,096 1,054; 16
+// scenes, four cameras 210 x 126, depth and ids 8/4,096 475, 4/2,048 527; 128
+// views 128 x 128 rgb 8/4,096 45, 4/4,096 56.
+gp::RcCfg rc_cfg(const gp_sim *sim, bool rgb_only)
+{
+    const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
+    gp::RcCfg c;
+    c.cover = rgb_only && sim->road_uniform && sim->cfg.width >= 16;
+    c.waves = px >= (c.cover ? 200000 : 24000) ? 8 : 4;
+    while (c.waves < 16 && 2 * c.waves * sim->lay.n_views <= 16 * (int64_t)sim->n_cu) c.waves *= 2;
+    c.bcap = (int)std::min<int64_t>(256, ((int64_t)sim->boxes_cap + sim->signals_cap + 63) / 64 * 64);
+    c.bins_cap = sim->bins_cap;
+    c.band_rows = std::min(sim->cfg.height, std::max(1, (c.cover ? 4096 : 512 * c.waves) / sim->cfg.width));
+    return c;
+}
+
 // can this render take the chip-wide rasteriser?
 bool chip_ok(const gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, int kind)
 {
@@ -1126,9 +1151,11 @@ gp_status gp_sim_set_light(gp_sim *sim, const float *h_light)
 gp_status gp_sim_render_raycast(gp_sim *sim, uint8_t *d_rgb, float *d_depth, int32_t *d_primid, void *stream)
 {
     if (!sim || !d_rgb) return fail(GP_EINVAL, "NULL argument");
-    if (gp::raycast_lds_bytes() > sim->max_lds) return fail(GP_EINVAL, "ray caster needs more LDS than the device has");
-    gp::RenderOut o{d_rgb, d_depth, d_primid};
-    hipError_t e = gp::launch_raycast(sim->dev, o, 0, (int)sim->lay.n_views, static_cast<hipStream_t>(stream));
+    const gp::RenderOut o{d_rgb, d_depth, d_primid};
+    const gp::RcCfg c = rc_cfg(sim, !d_depth && !d_primid);
+    if (gp::raycast_lds_bytes(sim->cfg.width, sim->cfg.height, c) > sim->max_lds)
+        return fail(GP_EINVAL, "ray caster needs more LDS than the device has");
+    hipError_t e = gp::launch_raycast(sim->dev, o, c, 0, (int)sim->lay.n_views, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? GP_OK : hip_fail(e, "ray-cast launch");
 }
 
