@@ -114,7 +114,8 @@ typedef enum {
 
 /* Rasteriser of rgb-only renders (no depth / primitive id) of sims whose road
  * strips share one colour (the chip-wide one without traffic lights or
- * shading).  Other renders always take the banded rasteriser. */
+ * shading).  Other renders take the general raster, which divides a view's work
+ * as the split one does, or the banded one where that is asked for. */
 typedef enum {
     GP_RASTER_BANDED = 0,     /* one workgroup of block_threads per view; LDS key bands of
                                  band_rows rows; triangle lists of batch_tris             */

@@ -77,7 +77,7 @@ __device__ __forceinline__ int setup_bins(const DevSim &s, const ChipBufs &cb, c
             ground_xz(cam, bn.xmax, bn.ymin, x[1], z[1]);
             ground_xz(cam, bn.xmax, bn.ymax, x[2], z[2]);
             ground_xz(cam, bn.xmin, bn.ymax, x[3], z[3]);
-            keep = !road_culled<true>(cam, x, z);
+            keep = !road_culled<true>(cam, x, z, 0, cam.H);
             rec = bn.start * 128 + bn.count;
         }
         const unsigned long long bm = __ballot(keep);
@@ -349,7 +349,7 @@ __device__ __forceinline__ void road_item(const DevSim &s, const ChipBufs &cb, i
         x[q] = v[q].x;
         z[q] = v[q].z;
     }
-    const bool pass = live && !road_culled<false>(cam, x, z);
+    const bool pass = live && !road_culled<false>(cam, x, z, 0, cam.H);
     const bool clip = pass && needs_clip(cam, v);
     TriGeo t0 = {}, t1 = {};
     bool v0 = false, v1 = false;

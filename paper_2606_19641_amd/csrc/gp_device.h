@@ -115,6 +115,14 @@ struct RgbCfg {
     int appear;       // 1: the instances with the directional light and traffic lights
 };
 
+// Settings of the general raster (gp_full.hip).
+struct FullCfg {
+    int waves;        // wavefronts per view: 1..16
+    int bcap;         // box faces and lights one view's list holds: 64, 128, 192 or 256
+    int bins_cap;     // culling bins of the largest scene
+    int band_rows;    // rows of the key band
+};
+
 // Settings of the ray caster (gp_raycast.hip).
 struct RcCfg {
     int waves;        // wavefronts per view: 1..16
@@ -165,6 +173,11 @@ size_t render_lds_bytes(int width, int height, const LaunchCfg &c, int fast);
 // view_begin + n_views); c.cover: rgb only, one road colour, width >= 16
 hipError_t launch_raycast(const DevSim &s, const RenderOut &o, const RcCfg &c, int view_begin, int n_views, hipStream_t st);
 size_t raycast_lds_bytes(int width, int height, const RcCfg &c);
+// general raster (gp_full.hip): any outputs, road colours, light and traffic
+// lights; workgroup b renders view order[b] (ordered) or view_begin + b
+hipError_t launch_render_full(const DevSim &s, const RenderOut &o, const FullCfg &c, int ordered, int view_begin, int grid,
+                              hipStream_t st);
+size_t full_lds_bytes(int width, const FullCfg &c);
 // wave-split rgb raster (gp_raster.hip) for uniform road colours, no depth /
 // primitive id and width >= 16: workgroup b renders view order[b] (ordered) or
 // view_begin + b

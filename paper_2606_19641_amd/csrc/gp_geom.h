@@ -298,7 +298,10 @@ struct TriRec {
 static_assert(sizeof(TriRec) == 48, "TriRec layout");
 
 // Orient and bound one fan triangle.  Returns false if it is culled or its
-// bounding box holds no sample within rows [r0, r1).
+// bounding box holds no sample within rows [r0, r1).  A row whose samples lie
+// exactly at the lowest vertex holds none (a bottom edge is exclusive, and so
+// is the right edge through a single lowest vertex): the last row is the last
+// one strictly above it.
 __device__ __forceinline__ bool make_tri(const Cam &c, bool one_sided, int32_t X0, int32_t Y0,
                                          int32_t X1, int32_t Y1, int32_t X2, int32_t Y2, int r0,
                                          int r1, TriGeo &t)
@@ -316,7 +319,7 @@ __device__ __forceinline__ bool make_tri(const Cam &c, bool one_sided, int32_t X
     const int32_t xmin = min(X0, min(X1, X2)), xmax = max(X0, max(X1, X2));
     const int32_t ymin = min(Y0, min(Y1, Y2)), ymax = max(Y0, max(Y1, Y2));
     const int i0 = max((xmin - 128 + 255) >> 8, 0), i1 = min((xmax - 128) >> 8, c.W - 1);
-    const int j0 = max((ymin - 128 + 255) >> 8, r0), j1 = min((ymax - 128) >> 8, r1 - 1);
+    const int j0 = max((ymin - 128 + 255) >> 8, r0), j1 = min((ymax - 129) >> 8, r1 - 1);
     if (i0 > i1 || j0 > j1) return false;
     t.X0 = X0; t.Y0 = Y0; t.X1 = X1; t.Y1 = Y1; t.X2 = X2; t.Y2 = Y2;
     t.j0 = (int16_t)j0;
@@ -513,9 +516,9 @@ __device__ __forceinline__ bool row_span_banded(const TriGeo &t, int j, int W, i
 // Coverage is all a road strip contributes in the rgb rasters (strips share
 // one plane and colour), so such a strip is rasterised as one quad.
 
-// A road primitive: a positively oriented triangle (nv 3, vertices 0..2) or
-// convex quad (nv 4), its sample rows [j0, j1], and whether it needs the
-// int64 span path (triangles only).
+// A road primitive: a positively oriented triangle (nv 3, vertices 0..2, and 3 =
+// 0) or convex quad (nv 4), a topmost vertex first, its sample rows [j0, j1],
+// and whether it needs the int64 span path (triangles only).
 struct Prim {
     int32_t X0, Y0, X1, Y1, X2, Y2, X3, Y3;
     int16_t j0, j1;
@@ -527,8 +530,11 @@ static_assert(sizeof(Prim) == 48, "Prim layout");
 __device__ __forceinline__ Prim prim_of(const TriGeo &t)
 {
     Prim p;
-    p.X0 = t.X0; p.Y0 = t.Y0; p.X1 = t.X1; p.Y1 = t.Y1; p.X2 = t.X2; p.Y2 = t.Y2;
-    p.X3 = t.X0; p.Y3 = t.Y0;
+    const bool m1 = (t.Y1 < t.Y0) & (t.Y1 <= t.Y2), m2 = !m1 & (t.Y2 < t.Y0);
+    p.X0 = m1 ? t.X1 : (m2 ? t.X2 : t.X0); p.Y0 = m1 ? t.Y1 : (m2 ? t.Y2 : t.Y0);
+    p.X1 = m1 ? t.X2 : (m2 ? t.X0 : t.X1); p.Y1 = m1 ? t.Y2 : (m2 ? t.Y0 : t.Y1);
+    p.X2 = m1 ? t.X0 : (m2 ? t.X1 : t.X2); p.Y2 = m1 ? t.Y0 : (m2 ? t.Y1 : t.Y2);
+    p.X3 = p.X0; p.Y3 = p.Y0;
     p.j0 = t.j0; p.j1 = t.j1; p.huge = t.huge; p.nv = 3;
     p.pad0 = 0; p.pad1 = 0;
     return p;
@@ -568,55 +574,76 @@ __device__ __forceinline__ int make_quad(const Cam &c, bool one_sided, const int
     if (!(npos == 4 || nneg == 4)) return -1;
     if (one_sided && npos == 4) return 0;      // front faces are negative in y-down screen space
     const int i0 = max((xmin - 128 + 255) >> 8, 0), i1 = min((xmax - 128) >> 8, c.W - 1);
-    const int j0 = max((ymin - 128 + 255) >> 8, r0), j1 = min((ymax - 128) >> 8, r1 - 1);
+    const int j0 = max((ymin - 128 + 255) >> 8, r0), j1 = min((ymax - 129) >> 8, r1 - 1);
     if (i0 > i1 || j0 > j1) return 0;
     // positive orientation (every corner turn > 0, the orientation make_tri
     // gives road triangles after its swap): reverse a quad turning the other
     // way, keeping corner 0 and the diagonal 0-2 (its fan triangles are then
     // the two swapped ones)
-    if (npos == 4) {
-        q.X0 = X[0]; q.Y0 = Y[0]; q.X1 = X[1]; q.Y1 = Y[1]; q.X2 = X[2]; q.Y2 = Y[2]; q.X3 = X[3]; q.Y3 = Y[3];
-    } else {
-        q.X0 = X[0]; q.Y0 = Y[0]; q.X1 = X[3]; q.Y1 = Y[3]; q.X2 = X[2]; q.Y2 = Y[2]; q.X3 = X[1]; q.Y3 = Y[1];
-    }
+    int32_t x0 = X[0], y0 = Y[0], x1 = npos == 4 ? X[1] : X[3], y1 = npos == 4 ? Y[1] : Y[3];
+    int32_t x2 = X[2], y2 = Y[2], x3 = npos == 4 ? X[3] : X[1], y3 = npos == 4 ? Y[3] : Y[1];
+    // a topmost vertex first: turned by two corners, then by one
+    const bool t2 = min(y2, y3) < min(y0, y1);
+    const int32_t a0 = t2 ? x2 : x0, b0 = t2 ? y2 : y0, a1 = t2 ? x3 : x1, b1 = t2 ? y3 : y1;
+    const int32_t a2 = t2 ? x0 : x2, b2 = t2 ? y0 : y2, a3 = t2 ? x1 : x3, b3 = t2 ? y1 : y3;
+    const bool t1 = b1 < b0;
+    q.X0 = t1 ? a1 : a0; q.Y0 = t1 ? b1 : b0; q.X1 = t1 ? a2 : a1; q.Y1 = t1 ? b2 : b1;
+    q.X2 = t1 ? a3 : a2; q.Y2 = t1 ? b3 : b2; q.X3 = t1 ? a0 : a3; q.Y3 = t1 ? b0 : b3;
     q.j0 = (int16_t)j0; q.j1 = (int16_t)j1;
     q.huge = 0; q.nv = 4;
     q.pad0 = 0; q.pad1 = 0;
     return 1;
 }
 
-// Samples [xl, xr] of row j covered by a primitive (row_span for triangles;
-// the same exact per-edge bounds over the quad's four edges).
+// The first sample at or right of the crossing of the edge from (x, y) down to
+// (x + dX, y + dY), dY > 0, with row Sy = 256 j + 128, y <= Sy < y + dY: the
+// ceiling of v, where 256 v + 128 is the crossing's x.  v comes from a binary32
+// reciprocal; its error is below eps (2^-22 of |dX|, 2^-24 of |x| subpixels, and
+// the rounding of v itself inside the image), so only a v within eps of an
+// integer k is in doubt, and there the two sides of dX (Sy - y) > (256 k + 128 -
+// x) dY, integers below 2^53, decide exactly.  Results beyond the image are
+// clamped to [-1, 2048].
+__device__ __forceinline__ int edge_ceil(int32_t x, int32_t y, int32_t dX, int32_t dY, int32_t Sy)
+{
+    const float dXf = (float)dX, xf = (float)x;
+    const float t = (float)(Sy - y) * __builtin_amdgcn_rcpf((float)dY);
+    const float v = fmaf(fmaf(dXf, t, xf), 1.0f / 256.0f, -0.5f);
+    const float eps = fmaf(fabsf(dXf), 0x1p-29f, fmaf(fabsf(xf), 0x1p-30f, 0x1p-11f));
+    const float k = rintf(v);
+    float c = ceilf(v);
+    if (fabsf(v - k) <= eps) {
+        const double side = (double)dX * (double)(Sy - y), at = fma(256.0, (double)k, 128.0) - (double)x;
+        c = fma(-at, (double)dY, side) > 0.0 ? k + 1.0f : k;
+    }
+    return (int)fminf(fmaxf(c, -1.0f), 2048.0f);
+}
+
+// Samples [xl, xr] of row j covered by a primitive.  Of a convex polygon only
+// the left and the right edge that cross the row bound its samples (row_span's
+// per-edge bounds of the others are no tighter): right edges run down from the
+// topmost vertex 0 in vertex order, left edges in the other direction, and a
+// row is crossed by the first whose lower end lies below it (rows at the lowest
+// vertex are not listed).  Samples on the left edge count, on the right edge
+// they don't, as in the top-left rule.
+// About a third of the instructions of all four edges in fp64: step + render of
+// 2,048 views at 128 x 128 70.3 -> 67.0 us, of 64 uneven scenes with three
+// cameras 463 -> 435 us.
 __device__ __forceinline__ bool prim_span(const Prim &p, int j, int W, int &xl_out, int &xr_out)
 {
-    if (p.nv == 3) {
-        TriGeo t;
-        t.X0 = p.X0; t.Y0 = p.Y0; t.X1 = p.X1; t.Y1 = p.Y1; t.X2 = p.X2; t.Y2 = p.Y2;
-        t.j0 = p.j0; t.j1 = p.j1; t.huge = p.huge; t.pad = 0;
-        return row_span(t, j, W, xl_out, xr_out);
+    if (p.huge) {
+        const int2 r = row_span_int64(p.X0, p.Y0, p.X1, p.Y1, p.X2, p.Y2, j, W);
+        xl_out = r.x;
+        xr_out = r.y;
+        return r.x <= r.y;
     }
-    const int32_t X[4] = {p.X0, p.X1, p.X2, p.X3}, Y[4] = {p.Y0, p.Y1, p.Y2, p.Y3};
-    const double Sy = 256.0 * (double)j + 128.0;
-    const double Wd = (double)W;
-    double lo = 0.0, hi = Wd - 1.0;
-    bool empty = false;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int k1 = (k + 1) & 3;
-        const int32_t dX = X[k1] - X[k], dY = Y[k1] - Y[k];
-        const double tk = (dY < 0 || (dY == 0 && dX > 0)) ? 0.0 : 1.0;
-        const double P = fma((double)dX, Sy - (double)Y[k], (double)dY * ((double)X[k] - 128.0));
-        const double N = P - tk;
-        empty = empty | ((dY == 0) & (N < 0.0));
-        const double D = 256.0 * (double)abs(dY);
-        const double qe = (double)((float)N * __builtin_amdgcn_rcpf((float)D));
-        double f = fmin(fmax(floor(qe), -Wd - 1.0), Wd + 1.0);
-        const double r = fma(-D, f, N);
-        f = r < 0.0 ? f - 1.0 : (r >= D ? f + 1.0 : f);
-        hi = dY > 0 ? fmin(hi, f) : hi;
-        lo = dY < 0 ? fmax(lo, -f) : lo;
-    }
-    const int xl = (int)lo, xr = empty ? -1 : (int)hi;
+    const int32_t Sy = 256 * j + 128;
+    const bool r1 = Sy < p.Y1, r2 = Sy < p.Y2, l3 = Sy < p.Y3;
+    const int32_t ax = r1 ? p.X0 : (r2 ? p.X1 : p.X2), ay = r1 ? p.Y0 : (r2 ? p.Y1 : p.Y2);
+    const int32_t bx = r1 ? p.X1 : (r2 ? p.X2 : p.X3), by = r1 ? p.Y1 : (r2 ? p.Y2 : p.Y3);
+    const int32_t cx = l3 ? p.X0 : (r2 ? p.X3 : p.X2), cy = l3 ? p.Y0 : (r2 ? p.Y3 : p.Y2);
+    const int32_t dx = l3 ? p.X3 : (r2 ? p.X2 : p.X1), dy = l3 ? p.Y3 : (r2 ? p.Y2 : p.Y1);
+    const int xl = max(edge_ceil(cx, cy, dx - cx, dy - cy, Sy), 0);
+    const int xr = min(edge_ceil(ax, ay, bx - ax, by - ay, Sy) - 1, W - 1);
     xl_out = xl;
     xr_out = xr;
     return xl <= xr;
@@ -997,9 +1024,10 @@ __device__ __forceinline__ void wave_lds_order() { __asm__ __volatile__("" ::: "
 // crossings, so its triangles' sample rows lie among the rows whose sample
 // 256 j + 128 falls within [Y(zhi), Y(zlo)].  The estimate below uses the
 // hardware reciprocal; its error (below 2^-20 relative on the quotient term)
-// and the rounding of rint are covered by the margins.  True if no image row
-// has its sample in the widened range: then the set covers no sample.
-__device__ __forceinline__ bool road_rows_empty(const Cam &c, float zmin, float zmax)
+// and the rounding of rint are covered by the margins.  True if no row of
+// [r0, r1) has its sample in the widened range: then the set covers no sample
+// there.
+__device__ __forceinline__ bool road_rows_empty(const Cam &c, float zmin, float zmax, int r0, int r1)
 {
     const float zlo = fmaxf(zmin, c.zn) * (1.0f - 0x1p-20f);
     const float zhi = fminf(zmax, c.zf) * (1.0f + 0x1p-20f);
@@ -1008,8 +1036,8 @@ __device__ __forceinline__ bool road_rows_empty(const Cam &c, float zmin, float 
     const float yhi = fmaf(hF, __builtin_amdgcn_rcpf(zlo), c.CY256);
     const float a = fmaf(-fabsf(ylo), 0x1p-18f, ylo) - 4.0f;
     const float b = fmaf(fabsf(yhi), 0x1p-18f, yhi) + 4.0f;
-    const float j0 = fmaxf(ceilf((a - 128.0f) * (1.0f / 256.0f)), 0.0f);
-    const float j1 = fminf(floorf((b - 128.0f) * (1.0f / 256.0f)), (float)(c.H - 1));
+    const float j0 = fmaxf(ceilf((a - 128.0f) * (1.0f / 256.0f)), (float)r0);
+    const float j1 = fminf(floorf((b - 128.0f) * (1.0f / 256.0f)), (float)(r1 - 1));
     return !(j0 <= j1);
 }
 
@@ -1023,7 +1051,7 @@ __device__ __forceinline__ bool road_rows_empty(const Cam &c, float zmin, float 
 // depths can differ from the box corners' by rounding (below 2^-22 of
 // |x| + |z|), so a bin's depth tests carry that margin.
 template <bool BIN>
-__device__ __forceinline__ bool road_culled(const Cam &c, const float *x, const float *z)
+__device__ __forceinline__ bool road_culled(const Cam &c, const float *x, const float *z, int r0, int r1)
 {
     bool n = true, fa = true, l = true, r = true;
     float zmin = INFINITY, zmax = -INFINITY;
@@ -1041,7 +1069,7 @@ __device__ __forceinline__ bool road_culled(const Cam &c, const float *x, const 
         zmax = fmaxf(zmax, z[k] + dz);
     }
     // combined bitwise (no branch; the row test is cheap next to a divergent exit)
-    return n | fa | l | r | road_rows_empty(c, zmin, zmax);
+    return n | fa | l | r | road_rows_empty(c, zmin, zmax, r0, r1);
 }
 
 // camera-space x and z of a ground point (world x, y)

@@ -106,13 +106,15 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, c
             ground_xz(cam, q0.z, q0.w, x[1], z[1]);
             ground_xz(cam, q1.x, q1.y, x[2], z[2]);
             ground_xz(cam, q1.z, q1.w, x[3], z[3]);
-            return live && !road_culled<false>(cam, x, z);
+            return live && !road_culled<false>(cam, x, z, 0, cam.H);
         },
         [&](int u) {
             if (AP && u >= nbu) do_lights(s, sc, cam, L, u - nbu);
             else do_boxes<AP>(s, sc, cam, ego, L, u, ubox, (lptr<int32_t>)ws.tris);   // the staging is free here
         },
-        [&](int a, int n) { setup_job(s, cam, L, ws, a, n); });
+        [&](int a, int n) {
+            setup_job<false>(s, sc, cam, L, ws, a, n, [&](int t) { road_spans(L, cam, ws, t); });
+        });
 
     // ---- C: resolve
     uint8_t *img = rgb + 3 * ((int64_t)view * W * H);

@@ -380,7 +380,7 @@ __device__ __forceinline__ uint32_t rc_color(const DevSim &s, const SceneRec &sc
     const int prim = (kMaxPrims - 1) - (int)((keylo >> 8) & (uint32_t)(kMaxPrims - 1));
     const int nbox = sc.n_agents + sc.n_static;
     const int face = prim < 6 * nbox ? prim % 6 : 4;
-    if (chunked) return prim < 6 * nbox ? face_rgb<true>(s, sc, prim / 6, face) : signal_rgb(s, sc, prim - 6 * nbox - sc.n_roads);
+    if (chunked) return streamed_rgb<true>(s, sc, keylo);
     const int word = face >= 4 ? 14 : ((face & 1) ? 10 : 9);
     return ((lptr<const uint32_t>)(L.faces + (keylo & 0xFFu)))[word];
 }

@@ -388,6 +388,27 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
     return c;
 }
 
+// Settings of the general raster: wavefronts per view and samples of the key
+// band.  A larger band leaves room for fewer workgroups in LDS, a smaller one
+// repeats the set-up of the strips that reach it more often.  Us by wavefronts
+// and samples, depth and ids (one MI355X): 2,048 views 128 x 128 4/2,048 180,
+// 4/1,024 265, 4/4,096 223, 8/4,096 199; 4,096 views 210 x 126 4/2,048 574, 8/4,096
+// 597, 4/4,096 681; 4,096 views 434 x 252 4/4,096 1,836, 8/4,096 2,037, 4/2,048
+// 2,361; 1,024 views 512 x 512 8/4,096 1,552, 4/4,096 1,805; 128 views 128 x 128
+// 8/4,096 48, 4/2,048 73.
+gp::FullCfg full_cfg(const gp_sim *sim)
+{
+    const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
+    gp::FullCfg c;
+    c.waves = px >= 200000 ? 8 : 4;
+    while (c.waves < 16 && 2 * c.waves * sim->lay.n_views <= 16 * (int64_t)sim->n_cu) c.waves *= 2;
+    c.bcap = split_box_faces(sim);
+    c.bins_cap = sim->bins_cap;
+    const int samples = std::max(512 * c.waves, px >= 60000 ? 4096 : 2048);
+    c.band_rows = std::min(sim->cfg.height, std::max(1, samples / sim->cfg.width));
+    return c;
+}
+
 // Settings of the ray caster.  The list holds every box and light of the
 // largest scene up to 256 (scenes with more are cast in chunks).  Wavefronts per
 // view: 4, with coverage bits 8 from 200K pixels on, without them (depth,
@@ -433,10 +454,15 @@ gp_status render_impl(gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, h
     // renders without depth / primitive id of sims whose road strips share one
     // colour take the split rasteriser, lit or not, or the other rgb kernels
     // where they have neither light nor traffic lights; everything else takes
-    // the general one (its instances with lights for scenes with traffic lights)
+    // the general raster (or the banded kernels of that kind)
     const int kind = sim->lay.n_signals > 0 ? 2 : (!o.depth && !o.primid && sim->dev.road_color_uniform) ? 1 : 0;
     const bool split = !o.depth && !o.primid && split_ok(sim, l);
     const gp::RgbCfg rc = rgb_cfg(sim, l, sim->lay.n_views);
+    const gp::FullCfg fc = full_cfg(sim);
+    // renders that take neither rgb-only rasteriser: the general raster, or the
+    // banded kernels where they are asked for
+    const bool full = !split && (kind != 1) && l.raster != GP_RASTER_BANDED &&
+                      gp::full_lds_bytes(sim->cfg.width, fc) <= sim->max_lds;
     hipError_t e;
     if (chip_ok(sim, o, l, kind)) {
         const int rg = l.road_wgs_per_cu * sim->n_cu;
@@ -457,14 +483,17 @@ gp_status render_impl(gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, h
         for (int s = 0; s < sim->n_scenes; ++s) {
             const gp::SceneRec &r = sim->scenes[s];
             const int nv = r.n_agents * sim->cfg.n_cams;
-            e = split ? gp::launch_render_rgb(sim->dev, o, rc, 0, r.view_base, nv, st)
-                      : gp::launch_render(sim->dev, o, c, kind, 0, r.view_base, nv, st);
+            e = split  ? gp::launch_render_rgb(sim->dev, o, rc, 0, r.view_base, nv, st)
+                : full ? gp::launch_render_full(sim->dev, o, fc, 0, r.view_base, nv, st)
+                       : gp::launch_render(sim->dev, o, c, kind, 0, r.view_base, nv, st);
             if (e != hipSuccess) return hip_fail(e, "render launch");
         }
         return GP_OK;
     }
     const int64_t resident = (int64_t)l.blocks_per_cu * sim->n_cu;
-    if (sim->lay.n_views <= resident || split) {
+    if (full) {
+        e = gp::launch_render_full(sim->dev, o, fc, 1, 0, (int)sim->lay.n_views, st);
+    } else if (sim->lay.n_views <= resident || split) {
         // every view gets a workgroup of its own: one launch over all views,
         // without the queue (whose empty segments would cost each workgroup a
         // chain of device-scope atomics before it finds its view).  The

@@ -145,6 +145,61 @@ __device__ __forceinline__ void road_spans(const RgbLds &L, const Cam &cam, cons
     wave_lds_order();
 }
 
+// Fragments of the n staged road primitives in rows [b0, b1) folded into the
+// key band (first row band0): (primitive, row) items dealt to the lanes, their
+// exact spans cut into pieces of up to 16 samples, dealt again.  Every strip
+// lies in one plane, so 1/z is the row's.
+__device__ __forceinline__ void road_fold(const RgbLds &L, const Cam &cam, const WaveSt &ws, int n, int b0, int b1, int band0)
+{
+    const int ln = (int)lane_id(), W = cam.W;
+    wave_lds_order();
+    int c = 0, first = 0;
+    if (ln < n) {
+        const int32_t jj = ((lptr<const int32_t>)(ws.tris + ln))[8];     // j0 | j1 << 16
+        first = max((int)(int16_t)(jj & 0xFFFF), b0);
+        c = max(0, min(jj >> 16, b1 - 1) - first + 1);
+    }
+    const int incl = wave_incl_scan(c);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int excl = incl - c;
+    for (int g0 = 0; g0 < total; g0 += 64) {
+        const int gi = g0 + ln;
+        const int o = owner_of(incl, gi);
+        const int j = __shfl(first, o) + (gi - __shfl(excl, o));
+        int xl = 0, xr = -1, key = 0;
+        if (gi < total) {
+            const Prim pr = lds_load(ws.tris + o);
+            key = pr.pad0;
+            const float rz = fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C);
+            if (!((rz > 0.0f) & prim_span(pr, j, W, xl, xr))) { xl = 0; xr = -1; }
+        }
+        const int np = (xr - xl + 16) >> 4;
+        const int inc2 = wave_incl_scan(np);
+        const int npt = __builtin_amdgcn_readlane(inc2, 63);
+        const int ex2 = inc2 - np;
+        const int x2 = xl | (xr << 16);
+        for (int p0 = 0; p0 < npt; p0 += 64) {
+            const int pi = p0 + ln;
+            const int o2 = owner_of(inc2, pi);
+            const int k = pi - __shfl(ex2, o2);
+            const int sx = __shfl(x2, o2), sj = __shfl(j, o2), sk = __shfl(key, o2);
+            if (pi >= npt) continue;
+            const int i0 = (sx & 0xFFFF) + 16 * k, i1 = min(i0 + 15, sx >> 16);
+            const float rz = fmaf(cam.road.B, ((float)sj + 0.5f) - cam.cy, cam.road.C);
+            const unsigned long long kv = ((unsigned long long)__float_as_uint(rz) << 32) | (uint32_t)sk;
+            lptr<unsigned long long> row = L.work + (sj - band0) * W;
+            for (int i = i0; i <= i1; ++i) lds_max64(row + i, kv);
+        }
+    }
+    wave_lds_order();
+}
+
+// the key word of the strip in road slot g (global)
+__device__ __forceinline__ int road_key(const DevSim &s, const SceneRec &sc, int g)
+{
+    return (int)key_low(0u, 6 * (sc.n_agents + sc.n_static) + s.road_index[g], s.road_color[g]);
+}
+
 // Stage the triangles held by the lanes (v0: t0, v1: t1); returns how many.
 __device__ __forceinline__ int stage_tris(const WaveSt &ws, bool v0, const Prim &t0, bool v1, const Prim &t1)
 {
@@ -157,15 +212,18 @@ __device__ __forceinline__ int stage_tris(const WaveSt &ws, bool v0, const Prim 
 
 // Clip up to four queued strips (the last ones of the queue), one per 16-lane
 // segment; stages their fan triangles and returns how many.
-__device__ __forceinline__ int road_clip(const DevSim &s, const Cam &cam, WaveSt &ws)
+template <bool KEY>
+__device__ __forceinline__ int road_clip(const DevSim &s, const SceneRec &sc, const Cam &cam, WaveSt &ws)
 {
     const int m = min(ws.nclip, 4);
     const int seg = (int)lane_id() >> 4;
     const bool live = seg < m;
     Poly P = {};
+    int key = 0;
     if (live) {
         const int g = ws.clipq[ws.nclip - m + seg];
         road_corners(s, cam, g, P.v);
+        if (KEY) key = road_key(s, sc, g);
     }
     P.n = dir_to_cam(cam, 0.0f, 0.0f, 1.0f);
     P.one_sided = false;
@@ -173,14 +231,16 @@ __device__ __forceinline__ int road_clip(const DevSim &s, const Cam &cam, WaveSt
     ws.nclip -= m;
     TriRec t;
     const bool ok = clip_seg<false>(cam, P, live, 0, cam.H, t);
-    Prim none = {};
-    return stage_tris(ws, ok, prim_of(t.g), false, none);
+    Prim p = prim_of(t.g), none = {};
+    p.pad0 = key;
+    return stage_tris(ws, ok, p, false, none);
 }
 
 // The two fan triangles of up to 32 queued strips (the last ones queued at
 // the back of the queue); stages them and returns how many.  Their corners
 // and snap are computed again, as the set-up computed them.
-__device__ __forceinline__ int road_fan(const DevSim &s, const Cam &cam, WaveSt &ws)
+template <bool KEY>
+__device__ __forceinline__ int road_fan(const DevSim &s, const SceneRec &sc, const Cam &cam, WaveSt &ws)
 {
     const int m = min(ws.nfan, 32);
     const int ln = (int)lane_id();
@@ -198,6 +258,7 @@ __device__ __forceinline__ int road_fan(const DevSim &s, const Cam &cam, WaveSt 
         v1 = make_tri(cam, false, X[0], Y[0], X[2], Y[2], X[3], Y[3], 0, cam.H, t1);
         if (v0) p0 = prim_of(t0);
         if (v1) p1 = prim_of(t1);
+        if (KEY) p0.pad0 = p1.pad0 = road_key(s, sc, g);
     }
     ws.nfan -= m;
     return stage_tris(ws, v0, p0, v1, p1);
@@ -208,7 +269,9 @@ __device__ __forceinline__ int road_fan(const DevSim &s, const Cam &cam, WaveSt 
 // fan triangles cover (staged; returns how many); strips that need the
 // clipper join the front of the wave's queue, strips that need their fan
 // triangles its back (both empty when a job starts).
-__device__ __forceinline__ int road_setup(const DevSim &s, const Cam &cam, const RgbLds &L, WaveSt &ws, int a, int n)
+template <bool KEY>
+__device__ __forceinline__ int road_setup(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, WaveSt &ws,
+                                          int a, int n)
 {
     const int ln = (int)lane_id();
     wave_lds_order();
@@ -233,6 +296,7 @@ __device__ __forceinline__ int road_setup(const DevSim &s, const Cam &cam, const
         const int qs = make_quad(cam, false, X, Y, 0, cam.H, p0);
         v0 = qs > 0;
         fan = qs < 0;
+        if (KEY) p0.pad0 = road_key(s, sc, g);
     }
     const unsigned long long fb = __ballot(fan);
     if (fan) ws.clipq[kWClip - 1 - (ws.nfan + lanes_below(fb))] = g;
@@ -242,17 +306,20 @@ __device__ __forceinline__ int road_setup(const DevSim &s, const Cam &cam, const
 }
 
 // One set-up job: the n ring strips from a set up, their primitives
-// rasterised into the coverage bitmask, then the strips that needed their fan
-// triangles (32 at a time) and those that needed the clipper (four at a time).
-__device__ __forceinline__ void setup_job(const DevSim &s, const Cam &cam, const RgbLds &L, WaveSt &ws, int a, int n)
+// rasterised (spans(n): the n staged ones), then the strips that needed their
+// fan triangles (32 at a time) and those that needed the clipper (four at a
+// time).  KEY: a staged primitive carries its strip's key word in pad0.
+template <bool KEY, class Spans>
+__device__ __forceinline__ void setup_job(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, WaveSt &ws,
+                                          int a, int n, Spans spans)
 {
-    int ntri = road_setup(s, cam, L, ws, a, n);
+    int ntri = road_setup<KEY>(s, sc, cam, L, ws, a, n);
     for (;;) {
-        if (ntri > 0) road_spans(L, cam, ws, ntri);
+        if (ntri > 0) spans(ntri);
         if (ws.nfan > 0)
-            ntri = road_fan(s, cam, ws);
+            ntri = road_fan<KEY>(s, sc, cam, ws);
         else if (ws.nclip > 0)
-            ntri = road_clip(s, cam, ws);
+            ntri = road_clip<KEY>(s, sc, cam, ws);
         else
             break;
     }
@@ -587,17 +654,19 @@ __device__ __forceinline__ float light_invz(const RgbLds &L, const Cam &cam, int
 }
 
 // Fragments of the list's n entries in rows [b0, b1) folded into the key band
-// by one wavefront.  The (entry, row) items are dealt to the lanes by a prefix
+// by wavefronts wv of nwv (passes of many items shared out, of few their
+// pieces).  The (entry, row) items are dealt to the lanes by a prefix
 // over row counts; each lane computes its item's exact span; the spans are cut
 // into pieces of up to 16 samples, which are dealt to the lanes by a prefix
 // over piece counts, and each lane folds its piece's samples into the band
 // with LDS atomic max.
 template <bool AP>
 __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<unsigned long long> keys, int n, int b0,
-                                         int b1)
+                                         int b1, int wv, int nwv)
 {
     const int ln = (int)lane_id();
     const int W = cam.W;
+    int pass = 0;
     for (int t0 = 0; t0 < n; t0 += 64) {
         const int t = t0 + ln;
         int c = 0;
@@ -609,7 +678,9 @@ __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<u
         const int incl = wave_incl_scan(c);
         const int total = __builtin_amdgcn_readlane(incl, 63);
         const int excl = incl - c;
-        for (int g0 = 0; g0 < total; g0 += 64) {
+        const bool split = total <= 128 * nwv;
+        for (int g0 = 0; g0 < total; g0 += 64, ++pass) {
+            if (!split && pass % nwv != wv) continue;
             const int gi = g0 + ln;
             const int o = owner_of(incl, gi);
             const int ex = __shfl(excl, o);
@@ -625,7 +696,7 @@ __device__ __forceinline__ void box_band(const RgbLds &L, const Cam &cam, lptr<u
             const int inc2 = wave_incl_scan(np);
             const int npt = __builtin_amdgcn_readlane(inc2, 63);
             const int ex2 = inc2 - np;
-            for (int p0 = 0; p0 < npt; p0 += 64) {
+            for (int p0 = split ? 64 * wv : 0; p0 < npt; p0 += split ? 64 * nwv : 64) {
                 const int pi = p0 + ln;
                 const int o2 = owner_of(inc2, pi);
                 const int k = pi - __shfl(ex2, o2);
@@ -788,41 +859,92 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 // The rows that no box fragment touches are written as one run of bytes, in
 // 16-byte pieces at 16-byte aligned addresses whatever the width and the
 // image's address: piece q holds the bytes o .. o + 15 of the image, o = 16 q -
-// a (a: the image's address mod 16), which lie in the six pixels from f =
-// o / 3 on, at phase o mod 3 of their run.  Neighbouring lanes write
-// neighbouring pieces, so a store instruction writes 1 KB in one run.  (A lane
-// that wrote 16 pixels as three 16-byte stores 48 bytes apart reached 3.9 TB/s
-// in a kernel that only writes, pieces in one run 6.3 TB/s.)
+// a (a: the image's address mod 1024), which lie in the six pixels from f =
+// o / 3 on, at phase o mod 3 of their run.  A store instruction writes one
+// aligned KB (64 pieces), whole cache lines but at the run's ends; the
+// wavefronts take turns.  A kernel that only writes images, one per workgroup,
+// reaches 5.5..6.1 TB/s so, 3.6 TB/s where the KBs of 128 threads start within a
+// cache line (images of 328,104 bytes), 3.9 TB/s where a lane writes 16 pixels
+// as three pieces 48 bytes apart; a plain fill of the same memory reaches 6.9.
+// Blocks of 3 to 30 KB per wavefront in turn are no faster than single KBs.
 
 // byte b of a pixel's colour at channel c
 __device__ __forceinline__ uint8_t channel(uint32_t rgb, int c) { return (uint8_t)(rgb >> (8 * c)); }
+
+// The pieces of bytes [b0, b1) of an image: pieces [q0, q1) whole, in chunks of
+// 64; chunks [f0, f1) are whole too.  This wavefront takes chunks c0, c0 + step, ...
+struct Run {
+    gp_v4i *out;         // piece 0
+    int a, q0, q1, f0, f1, c0, step;
+};
+
+__device__ __forceinline__ Run run_of(uint8_t *img, int b0, int b1)
+{
+    Run r;
+    r.a = (int)(reinterpret_cast<uintptr_t>(img) & 1023);
+    r.out = reinterpret_cast<gp_v4i *>(img - r.a);
+    r.q0 = (b0 + r.a + 15) >> 4;
+    r.q1 = (b1 + r.a) >> 4;
+    r.f0 = (r.q0 + 63) >> 6;
+    r.f1 = max(r.q1 >> 6, r.f0);
+    const int K = (int)blockDim.x >> 6, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    r.step = K;
+    r.c0 = r.f0 + w;
+    return r;
+}
+
+// the whole piece of the run's first or last, partial chunk that this lane
+// writes, or -1: by the first wavefront, the last chunk by the last one
+__device__ __forceinline__ int run_end_piece(const Run &r, bool last)
+{
+    const int K = (int)blockDim.x >> 6, w = (int)threadIdx.x >> 6, ln = (int)lane_id();
+    if (w != (last ? K - 1 : 0)) return -1;
+    const int q = last ? 64 * r.f1 + ln : 64 * (r.f0 - 1) + ln;
+    return q >= r.q0 && q < (last ? r.q1 : min(r.q1, 64 * r.f0)) ? q : -1;
+}
+
+// the byte offset of a partial piece at the run's ends that this thread writes, or -1
+__device__ __forceinline__ int run_end_byte(const Run &r, int b0, int b1)
+{
+    const int tid = (int)threadIdx.x;
+    const int head = min(16 * r.q0 - r.a, b1) - b0, tail = b1 - max(16 * r.q1 - r.a, b0);
+    if (tid < head) return b0 + tid;
+    if (tid >= 32 && tid < 32 + tail && r.q0 <= r.q1) return b1 - tail + tid - 32;
+    return -1;
+}
 
 // bytes [b0, b1) of the background (the sky)
 __device__ __forceinline__ void write_sky(uint8_t *img, uint32_t bg, int b0, int b1)
 {
     if (b0 >= b1) return;
-    const int a = (int)(reinterpret_cast<uintptr_t>(img) & 15), B = (int)blockDim.x, tid = (int)threadIdx.x;
-    const int q0 = (b0 + a + 15) >> 4, q1 = (b1 + a) >> 4;
+    const Run r = run_of(img, b0, b1);
+    const int ln = (int)lane_id();
     const uint32_t w[3] = {bg | (bg << 24), (bg >> 8) | (bg << 16), (bg >> 16) | (bg << 8)};
-    // a thread's pieces are B apart: their phases repeat after three
-    u4 v[3];
-    int ph = (16 * (q0 + tid) - a + 48) % 3;
+    auto piece = [&](int ph) -> gp_v4i {
+        return gp_v4i{(int)__builtin_amdgcn_alignbyte(w[1], w[0], ph), (int)__builtin_amdgcn_alignbyte(w[2], w[1], ph),
+                      (int)__builtin_amdgcn_alignbyte(w[0], w[2], ph), (int)__builtin_amdgcn_alignbyte(w[1], w[0], ph)};
+    };
+    auto phase = [&](int q) -> int { return (16 * q - r.a + 3072) % 3; };
+    // a lane's pieces are 64 step apart: their phases repeat after three
+    const gp_v4i v0 = piece(phase(64 * r.c0 + ln)), v1 = piece(phase(64 * (r.c0 + r.step) + ln)),
+                 v2 = piece(phase(64 * (r.c0 + 2 * r.step) + ln));
+    int c = r.c0;
+    gp_v4i *p = r.out + (size_t)64 * c + ln;
+    const size_t st = (size_t)64 * r.step;
+    for (; c + 2 * r.step < r.f1; c += 3 * r.step, p += 3 * st) {
+        p[0] = v0;
+        p[st] = v1;
+        p[2 * st] = v2;
+    }
+    if (c < r.f1) p[0] = v0;
+    if (c + r.step < r.f1) p[st] = v1;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        v[k] = u4{__builtin_amdgcn_alignbyte(w[1], w[0], ph), __builtin_amdgcn_alignbyte(w[2], w[1], ph),
-                  __builtin_amdgcn_alignbyte(w[0], w[2], ph), __builtin_amdgcn_alignbyte(w[1], w[0], ph)};
-        ph = (ph + B) % 3;
+    for (int t = 0; t < 2; ++t) {
+        const int q = run_end_piece(r, t != 0);
+        if (q >= 0) r.out[q] = piece(phase(q));
     }
-    u4 *out = reinterpret_cast<u4 *>(img - a);
-    for (int q = q0 + tid; q < q1; q += 3 * B) {
-        out[q] = v[0];
-        if (q + B < q1) out[q + B] = v[1];
-        if (q + 2 * B < q1) out[q + 2 * B] = v[2];
-    }
-    // the partial pieces at the run's ends (a row has at least 48 bytes)
-    const int head = 16 * q0 - a - b0, tail = b1 - (16 * q1 - a);
-    if (tid < head) img[b0 + tid] = channel(bg, (b0 + tid) % 3);
-    if (tid >= 32 && tid < 32 + tail) img[b1 - tail + tid - 32] = channel(bg, (b1 - tail + tid - 32) % 3);
+    const int o = run_end_byte(r, b0, b1);
+    if (o >= 0) img[o] = channel(bg, o % 3);
 }
 
 // the pattern table: entry (p, b) holds the 16 bytes at phase p of the run of
@@ -848,24 +970,53 @@ __device__ __forceinline__ void write_road(const RgbLds &L, uint8_t *img, uint32
                                            int b1)
 {
     if (b0 >= b1) return;
-    const int a = (int)(reinterpret_cast<uintptr_t>(img) & 15), B = (int)blockDim.x, tid = (int)threadIdx.x;
-    const int q0 = (b0 + a + 15) >> 4, q1 = (b1 + a) >> 4;
+    const Run r = run_of(img, b0, b1);
+    const int ln = (int)lane_id();
     const int f0 = L.hr0 * W;            // pixel of coverage bit 0
-    gp_v4i *out = reinterpret_cast<gp_v4i *>(img - a);
-    auto piece = [&](int q) -> gp_v4i {
-        const uint32_t o = (uint32_t)(16 * q - a), f = o / 3u, ph = o - 3u * f;
-        return L.pat[(ph << 6) | (bits_at(L, (int)f - f0) & 63u)];
+    // the coverage bit of the first pixel of piece q, and its phase
+    auto pixel = [&](int q, int &ph) -> int {
+        const uint32_t o = (uint32_t)(16 * q - r.a), f = o / 3u;
+        ph = (int)(o - 3u * f);
+        return (int)f - f0;
     };
-    for (int q = q0 + tid; q < q1; q += 2 * B) {
-        const bool two = q + B < q1;
-        const gp_v4i v0 = piece(q), v1 = piece(two ? q + B : q);
-        out[q] = v0;
-        if (two) out[q + B] = v1;
+    // three of a lane's pieces are 1,024 step pixels, whole words of coverage:
+    // word addresses advance, shifts and phases stay
+    const lptr<const uint32_t> bits = (lptr<const uint32_t>)L.bits;
+    lptr<const uint32_t> wd[3];
+    lptr<const gp_v4i> tab[3];
+    int sh[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        int ph;
+        const int f = pixel(64 * (r.c0 + k * r.step) + ln, ph);
+        wd[k] = bits + (f >> 5);
+        sh[k] = f & 31;
+        tab[k] = (lptr<const gp_v4i>)L.pat + (ph << 6);
     }
-    const int head = 16 * q0 - a - b0, tail = b1 - (16 * q1 - a);
-    int o = -1;
-    if (tid < head) o = b0 + tid;
-    else if (tid >= 32 && tid < 32 + tail) o = b1 - tail + tid - 32;
+    int c = r.c0, at = 0;
+    gp_v4i *p = r.out + (size_t)64 * c + ln;
+    const size_t st = (size_t)64 * r.step;
+    for (; c + 2 * r.step < r.f1; c += 3 * r.step, p += 3 * st, at += 32 * r.step) {
+        gp_v4i v[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] = tab[k][__builtin_amdgcn_alignbit(wd[k][at + 1], wd[k][at], sh[k]) & 63u];
+        p[0] = v[0];
+        p[st] = v[1];
+        p[2 * st] = v[2];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (c + k * r.step < r.f1) p[k * st] = tab[k][__builtin_amdgcn_alignbit(wd[k][at + 1], wd[k][at], sh[k]) & 63u];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int q = run_end_piece(r, t != 0);
+        if (q >= 0) {
+            int ph;
+            const int f = pixel(q, ph);
+            r.out[q] = L.pat[(ph << 6) | (int)(bits_at(L, f) & 63u)];
+        }
+    }
+    const int o = run_end_byte(r, b0, b1);
     if (o >= 0) {
         const int f = o / 3;
         img[o] = channel(bits_at(L, f - f0) & 1u ? road : bg, o - 3 * f);
@@ -953,11 +1104,44 @@ __device__ __forceinline__ void resolve_full(const DevSim &s, lptr<const uint32_
     }
 }
 
+// The fragments of every box and light in rows [b0, b1) folded into the key
+// band by one wavefront through its own use of the list: the faces six
+// candidates at a time (at most 60 entries per pass), the boxes culled again.
+template <bool AP>
+__device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
+                                               lptr<unsigned long long> keys, int b0, int b1)
+{
+    const int ncand = 6 * (sc.n_agents + sc.n_static);
+    for (int c0 = 0; c0 < ncand; c0 += 6) {
+        int n = 0, bmn = 0, bmx = 0;
+        (void)box_pass<AP>(s, sc, cam, ego, L, (lptr<const int32_t>)L.cq, false, ncand, c0, 6, L.cq, false, n, bmn, bmx);
+        wave_lds_order();
+        box_band<AP>(L, cam, keys, n, b0, b1, 0, 1);
+        wave_lds_order();
+    }
+    for (int g0 = 0; AP && g0 < sc.n_signals; g0 += 64) {
+        int n = 0, bmn = 0, bmx = 0;
+        (void)light_pass(s, sc, cam, L, g0, false, n, bmn, bmx);
+        wave_lds_order();
+        box_band<AP>(L, cam, keys, n, b0, b1, 0, 1);
+        wave_lds_order();
+    }
+}
+
+// Colour of a streamed box or light key: from its primitive (the list's
+// entries are gone).
+template <bool AP>
+__device__ __forceinline__ uint32_t streamed_rgb(const DevSim &s, const SceneRec &sc, uint32_t keylo)
+{
+    const int prim = (kMaxPrims - 1) - (int)((keylo >> 8) & (uint32_t)(kMaxPrims - 1));
+    const int nbox = sc.n_agents + sc.n_static;
+    if (!AP || prim < 6 * nbox) return face_rgb<AP>(s, sc, prim / 6, prim % 6);
+    return signal_rgb(s, sc, prim - 6 * nbox - sc.n_roads);
+}
+
 // Rows [kr0, kr1) of a view whose box list overflowed, through bands of
 // 64-bit keys (the whole workgroup; the region from the surviving-bin list on
-// is free): the box faces streamed through the list six candidates at a time
-// (at most 60 entries per pass) with the boxes culled again.  wv: this
-// wavefront among the workgroup's.
+// is free).  wv: this wavefront among the workgroup's.
 template <bool AP>
 __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
                                               uint8_t *img, uint32_t road_rgb, uint32_t bg_rgb, int kr0, int kr1, int wv)
@@ -969,34 +1153,11 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
         __syncthreads();
         for (int p = (int)threadIdx.x; p < (b1 - b0) * W; p += (int)blockDim.x) keys[p] = 0ull;
         __syncthreads();
-        if (wv == 0) {
-            const int ncand = 6 * (sc.n_agents + sc.n_static);
-            for (int c0 = 0; c0 < ncand; c0 += 6) {
-                int n = 0, bmn = 0, bmx = 0;
-                (void)box_pass<AP>(s, sc, cam, ego, L, (lptr<const int32_t>)L.cq, false, ncand, c0, 6, L.cq, false, n, bmn,
-                                   bmx);
-                wave_lds_order();
-                box_band<AP>(L, cam, keys, n, b0, b1);
-                wave_lds_order();
-            }
-            for (int g0 = 0; AP && g0 < sc.n_signals; g0 += 64) {
-                int n = 0, bmn = 0, bmx = 0;
-                (void)light_pass(s, sc, cam, L, g0, false, n, bmn, bmx);
-                wave_lds_order();
-                box_band<AP>(L, cam, keys, n, b0, b1);
-                wave_lds_order();
-            }
-        }
+        if (wv == 0) stream_entries<AP>(s, sc, cam, ego, L, keys, b0, b1);
         __syncthreads();
         resolve_band(
             L, W, [&](int j) { return fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C); },
-            [&](uint32_t keylo) -> uint32_t {
-                // the box list was streamed: the colour comes from the key's primitive
-                const int prim = (kMaxPrims - 1) - (int)((keylo >> 8) & (uint32_t)(kMaxPrims - 1));
-                const int nbox = sc.n_agents + sc.n_static;
-                if (!AP || prim < 6 * nbox) return face_rgb<AP>(s, sc, prim / 6, prim % 6);
-                return signal_rgb(s, sc, prim - 6 * nbox - sc.n_roads);
-            },
+            [&](uint32_t keylo) { return streamed_rgb<AP>(s, sc, keylo); },
             keys, img, road_rgb, bg_rgb, b0, b1);
     }
 }
@@ -1047,7 +1208,7 @@ __device__ __forceinline__ void cull_bins(const DevSim &s, const SceneRec &sc, c
         ground_xz(cam, bn.xmax, bn.ymin, x[1], z[1]);
         ground_xz(cam, bn.xmax, bn.ymax, x[2], z[2]);
         ground_xz(cam, bn.xmin, bn.ymax, x[3], z[3]);
-        keep = !road_culled<true>(cam, x, z);
+        keep = !road_culled<true>(cam, x, z, 0, cam.H);
         rec = bn.start * 128 + bn.count;
     }
     list_bins(L, keep, rec);
