@@ -110,15 +110,18 @@ struct LaunchCfg {
 // Settings of the wave-split rgb raster (gp_raster.hip).
 struct RgbCfg {
     int waves;        // wavefronts per view: 1..16
-    int bcap;         // box faces one view's list holds: 64, 128 or 256
-    int bins_cap;     // culling bins of the largest scene (surviving bins are listed in LDS)
+    int bcap;         // box faces and lights one view's list holds: 64..256
+    int recs;         // boxes one view's records hold: 1..64
+    int bins_cap;     // surviving culling bins one view's list holds (more are taken in segments): multiple of 64
+                      // where it is below the bins of the largest scene
     int appear;       // 1: the instances with the directional light and traffic lights
 };
 
 // Settings of the general raster (gp_full.hip).
 struct FullCfg {
     int waves;        // wavefronts per view: 1..16
-    int bcap;         // box faces and lights one view's list holds: 64, 128, 192 or 256
+    int bcap;         // box faces and lights one view's list holds: 64..256
+    int recs;         // boxes one view's records hold: 1..64
     int bins_cap;     // culling bins of the largest scene
     int band_rows;    // rows of the key band
 };

@@ -23,7 +23,7 @@ namespace gp {
 namespace {
 
 struct FullLayout {
-    size_t cnt, faces, cq, pal, sbins, sring, waves, keys, total;
+    size_t cnt, faces, recs, cq, pal, sbins, sring, waves, keys, total;
 };
 
 __host__ __device__ inline FullLayout full_layout(int W, const FullCfg &c)
@@ -32,6 +32,7 @@ __host__ __device__ inline FullLayout full_layout(int W, const FullCfg &c)
     size_t o = 0;
     l.cnt = o; o = align16(o + 4 * R_NCNT);
     l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
+    l.recs = o; o = align16(o + sizeof(BoxRec) * (size_t)c.recs);
     l.cq = o; o = align16(o + 4 * (size_t)kBoxClip);
     l.pal = o; o = align16(o + 4 * 256);
     l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
@@ -54,12 +55,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     RgbLds L = {};
     L.cnt = (lptr<int32_t>)(smem + l.cnt);
     L.faces = (lptr<FaceRec>)(smem + l.faces);
+    L.recs = (lptr<BoxRec>)(smem + l.recs);
     L.cq = (lptr<int32_t>)(smem + l.cq);
     L.sbins = (lptr<int32_t>)(smem + l.sbins);
     L.sring = (lptr<int32_t>)(smem + l.sring);
     L.waves = (lptr<unsigned char>)(smem + l.waves);
     L.work = (lptr<unsigned long long>)(smem + l.keys);
     L.bcap = c.bcap;
+    L.batch = kBatch;
+    L.ring = kSharedRing;
+    L.bins = c.bins_cap;
+    L.nrec = c.recs;
     L.krows = c.band_rows;
     L.hr0 = first_road_row(H);
     lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
@@ -74,23 +80,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         pal[p] = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) | ((uint32_t)s.palette[3 * p + 2] << 16);
     if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();
-    for (int b0 = 64 * wv; b0 < sc.n_bins; b0 += B) cull_bins(s, sc, cam, L, b0);
+    const int nbox = sc.n_agents + sc.n_static;
+    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
     __syncthreads();
-    const int nsb = L.cnt[R_NSB];
-    const int ubox = K >= 8 ? 4 : 16;
-    const int nbu = (sc.n_agents + sc.n_static + ubox - 1) / ubox, nlu = (sc.n_signals + 63) / 64;
-    lptr<unsigned char> wbase = L.waves + (size_t)wv * kWaveBytes;
-    WaveSt ws;
-    ws.tris = (lptr<Prim>)wbase;
-    ws.clipq = (lptr<int32_t>)(wbase + kWTris * 48);
-    ws.nclip = 0;
-    ws.nfan = 0;
+    const int nsb = L.cnt[R_NSB], nsv = L.cnt[R_NSV];
+    const int ubox = box_unit(K);
+    const int nbu = nsv <= L.nrec ? (nsv + ubox - 1) / ubox : 0, nlu = (sc.n_signals + 63) / 64;
+    WaveSt ws = wave_state(L, wv);
     for (int b0 = 0; b0 < H; b0 += L.krows) {
         const int b1 = min(b0 + L.krows, H);
         const int r0 = max(b0, L.hr0), r1 = max(b1, L.hr0);        // rows that can show road
         if (b0 > 0) __syncthreads();                               // the last band's keys are read
         for (int p = tid; p < (b1 - b0) * W; p += B) L.work[p] = 0ull;
-        if (b0 > 0 && tid == 0) L.cnt[R_NEXT] = L.cnt[R_RING] = L.cnt[R_RESV] = L.cnt[R_JOB] = 0;
+        if (b0 > 0 && tid == 0) L.cnt[R_RING] = L.cnt[R_JOB] = 0;
         __syncthreads();
         // the first band's road work lists the boxes and lights too
         if (b0 == 0 || r0 < r1)
@@ -106,14 +108,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
                 },
                 [&](int u) {
                     if (u >= nbu) do_lights(s, sc, cam, L, u - nbu);
-                    else do_boxes<true>(s, sc, cam, ego, L, u, ubox, (lptr<int32_t>)ws.tris);   // the staging is free here
+                    else do_boxes<true>(s, sc, cam, L, u, ubox, nsv, (lptr<int32_t>)ws.tris);   // the staging is free here
                 },
                 [&](int a, int n) {
                     setup_job<true>(s, sc, cam, L, ws, a, n, [&](int t) { road_fold(L, cam, ws, t, r0, r1, b0); });
                 });
-        const bool ovf = L.cnt[R_BOVF] != 0;
+        const bool ovf = L.cnt[R_BOVF] != 0 || nsv > L.nrec;
         if (!ovf) box_band<true>(L, cam, L.work, L.cnt[R_NBT], b0, b1, wv, K);
-        else if (wv == 0) stream_entries<true>(s, sc, cam, ego, L, L.work, b0, b1);
+        else stream_entries<true>(s, sc, cam, ego, L, L.work, b0, b1, wv, K);
         __syncthreads();
         resolve_full(
             s, (lptr<const uint32_t>)pal,
@@ -133,7 +135,7 @@ hipError_t launch_render_full(const DevSim &s, const RenderOut &o, const FullCfg
                               hipStream_t st)
 {
     if (grid <= 0) return hipSuccess;
-    if (c.waves < 1 || c.waves > 16 || c.band_rows < 1 || c.bcap < 64 || c.bcap > 256 || c.bcap % 64 != 0)
+    if (c.waves < 1 || c.waves > 16 || c.band_rows < 1 || c.bcap < 64 || c.bcap > 256 || c.recs < 1 || c.recs > 64 || c.bins_cap < 1)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_render_full, dim3(grid), dim3(64 * c.waves), full_lds_bytes(s.width, c), st, s, o, c, ordered,
                        view_begin);

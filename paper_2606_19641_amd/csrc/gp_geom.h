@@ -125,18 +125,13 @@ __device__ __forceinline__ uint32_t key_low(uint32_t cls, int prim, uint32_t col
     return (cls << 31) | ((uint32_t)(kMaxPrims - 1 - prim) << 8) | color;
 }
 
-// face f (0 front, 1 left, 2 back, 3 right, 4 top, 5 bottom) of box j (an
-// agent, or a static obstacle for j >= n_agents)
-__device__ __forceinline__ void build_face(const DevSim &s, const SceneRec &sc, const Cam &cam, int j,
-                                           int f, Poly &P)
+// face f (0 front, 1 left, 2 back, 3 right, 4 top, 5 bottom) of the box at
+// (px, py), heading (cj, sj), of size dx x dy x Hb
+__device__ __forceinline__ void face_corners(const Cam &cam, float px, float py, float cj, float sj, float dx, float dy,
+                                             float Hb, int f, Poly &P)
 {
-    const int ga = box_slot(sc, j);
-    const float4 st = s.state[ga];
-    const float2 csj = s.cs[ga];
-    const float4 dm = s.dims[ga];
-    const float cj = csj.x, sj = csj.y;
-    const float ox = st.x - cam.px, oy = st.y - cam.py;
-    const float hl = 0.5f * dm.x, hw = 0.5f * dm.y, Hb = dm.z;
+    const float ox = px - cam.px, oy = py - cam.py;
+    const float hl = 0.5f * dx, hw = 0.5f * dy;
     const float ax = hl * cj, ay = hl * sj;
     const float bx = -(hw * sj), by = hw * cj;
     // footprint corners, counter-clockwise from above:
@@ -166,8 +161,19 @@ __device__ __forceinline__ void build_face(const DevSim &s, const SceneRec &sc, 
         nx = 0.0f; ny = 0.0f; nz = -1.0f;
     }
     P.n = dir_to_cam(cam, nx, ny, nz);
-    P.keylo = key_low(1u, 6 * j + f, s.agent_color[ga]);
     P.one_sided = true;
+}
+
+// face f of box j (an agent, or a static obstacle for j >= n_agents)
+__device__ __forceinline__ void build_face(const DevSim &s, const SceneRec &sc, const Cam &cam, int j,
+                                           int f, Poly &P)
+{
+    const int ga = box_slot(sc, j);
+    const float4 st = s.state[ga];
+    const float2 csj = s.cs[ga];
+    const float4 dm = s.dims[ga];
+    face_corners(cam, st.x, st.y, csj.x, csj.y, dm.x, dm.y, dm.z, f, P);
+    P.keylo = key_low(1u, 6 * j + f, s.agent_color[ga]);
 }
 
 // road slot `slot` (relative to the scene's road_base) with corners q0, q1
@@ -209,11 +215,8 @@ __device__ __forceinline__ bool outside(const Cam &c, const V3 *v)
 
 // Whole-box rejection by the box's bounding cylinder (radius hl + hw >= half
 // diagonal, height H) with the same margins as outside().
-__device__ __forceinline__ bool box_outside(const DevSim &s, const SceneRec &sc, const Cam &c, int j)
+__device__ __forceinline__ bool box_outside_at(const Cam &c, const float4 &st, const float4 &dm)
 {
-    const int ga = box_slot(sc, j);
-    const float4 st = s.state[ga];
-    const float4 dm = s.dims[ga];
     const float ox = st.x - c.px, oy = st.y - c.py;
     const float r = 0.5f * (dm.x + dm.y);
     const float z = fmaf(ox, c.fx, oy * c.fy);
@@ -224,6 +227,12 @@ __device__ __forceinline__ bool box_outside(const DevSim &s, const SceneRec &sc,
     return (zmax < c.zn - m) | (zmin > c.zf + m) | (x - c.t_right * z - r * (1.0f + c.t_right) > m) |
            (-x - c.t_left * z - r * (1.0f + c.t_left) > m) | (-(dm.z - c.h) - c.t_bottom * zmax > m) |
            (-c.h - c.t_top * zmax > m);
+}
+
+__device__ __forceinline__ bool box_outside(const DevSim &s, const SceneRec &sc, const Cam &c, int j)
+{
+    const int ga = box_slot(sc, j);
+    return box_outside_at(c, s.state[ga], s.dims[ga]);
 }
 
 // Road geometry lies at camera height -h, so a road point at depth z projects
@@ -618,6 +627,39 @@ __device__ __forceinline__ int edge_ceil(int32_t x, int32_t y, int32_t dX, int32
     return (int)fminf(fmaxf(c, -1.0f), 2048.0f);
 }
 
+// The span of a triangle with a coordinate of 2^25 subpixels or more, in exact
+// int64 arithmetic: per edge the samples of the row that it excludes (a left
+// edge) or holds (a right edge) are a run from sample 0, counted by bisection.
+// Rare, and without a division short enough to stand in line: a call would
+// cost the kernel its scalar registers (every one live across it is spilled).
+__device__ __forceinline__ bool prim_span_int64(const Prim &p, int j, int W, int &xl_out, int &xr_out)
+{
+    int xl = 0, xr = W - 1;
+    const auto sel = [](int k, int32_t a, int32_t b, int32_t c) -> int32_t { return k == 0 ? a : (k == 1 ? b : c); };
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        const int32_t xa = sel(k, p.X0, p.X1, p.X2), ya = sel(k, p.Y0, p.Y1, p.Y2);
+        const int32_t xb = sel(k, p.X1, p.X2, p.X0), yb = sel(k, p.Y1, p.Y2, p.Y0);
+        const int64_t dX = (int64_t)xb - xa, dY = (int64_t)yb - ya;
+        const int64_t tk = (dY < 0 || (dY == 0 && dX > 0)) ? 0 : 1;
+        const int64_t N = dX * (256 * (int64_t)j + 128 - ya) + dY * ((int64_t)xa - 128) - tk;
+        if (dY == 0) {
+            if (N < 0) xr = -1;
+            continue;
+        }
+        // sample i is inside the edge iff N - 256 dY i >= 0
+        int c = 0;
+#pragma unroll 1
+        for (int b = 1024; b > 0; b >>= 1)
+            if (c + b <= W && (N - 256 * dY * (int64_t)(c + b - 1) >= 0) == (dY > 0)) c += b;
+        if (dY > 0) xr = min(xr, c - 1);
+        else xl = max(xl, c);
+    }
+    xl_out = xl;
+    xr_out = xr;
+    return xl <= xr;
+}
+
 // Samples [xl, xr] of row j covered by a primitive.  Of a convex polygon only
 // the left and the right edge that cross the row bound its samples (row_span's
 // per-edge bounds of the others are no tighter): right edges run down from the
@@ -630,18 +672,16 @@ __device__ __forceinline__ int edge_ceil(int32_t x, int32_t y, int32_t dX, int32
 // cameras 463 -> 435 us.
 __device__ __forceinline__ bool prim_span(const Prim &p, int j, int W, int &xl_out, int &xr_out)
 {
-    if (p.huge) {
-        const int2 r = row_span_int64(p.X0, p.Y0, p.X1, p.Y1, p.X2, p.Y2, j, W);
-        xl_out = r.x;
-        xr_out = r.y;
-        return r.x <= r.y;
-    }
+    if (p.huge) return prim_span_int64(p, j, W, xl_out, xr_out);
     const int32_t Sy = 256 * j + 128;
     const bool r1 = Sy < p.Y1, r2 = Sy < p.Y2, l3 = Sy < p.Y3;
-    const int32_t ax = r1 ? p.X0 : (r2 ? p.X1 : p.X2), ay = r1 ? p.Y0 : (r2 ? p.Y1 : p.Y2);
-    const int32_t bx = r1 ? p.X1 : (r2 ? p.X2 : p.X3), by = r1 ? p.Y1 : (r2 ? p.Y2 : p.Y3);
-    const int32_t cx = l3 ? p.X0 : (r2 ? p.X3 : p.X2), cy = l3 ? p.Y0 : (r2 ? p.Y3 : p.Y2);
-    const int32_t dx = l3 ? p.X3 : (r2 ? p.X2 : p.X1), dy = l3 ? p.Y3 : (r2 ? p.Y2 : p.Y1);
+    // the choices are made between values: ?: between the record's fields is one
+    // between addresses, which puts the record into scratch memory
+    const auto sel = [](bool c, int32_t a, int32_t b) -> int32_t { return c ? a : b; };
+    const int32_t ax = sel(r1, p.X0, sel(r2, p.X1, p.X2)), ay = sel(r1, p.Y0, sel(r2, p.Y1, p.Y2));
+    const int32_t bx = sel(r1, p.X1, sel(r2, p.X2, p.X3)), by = sel(r1, p.Y1, sel(r2, p.Y2, p.Y3));
+    const int32_t cx = sel(l3, p.X0, sel(r2, p.X3, p.X2)), cy = sel(l3, p.Y0, sel(r2, p.Y3, p.Y2));
+    const int32_t dx = sel(l3, p.X3, sel(r2, p.X2, p.X1)), dy = sel(l3, p.Y3, sel(r2, p.Y2, p.Y1));
     const int xl = max(edge_ceil(cx, cy, dx - cx, dy - cy, Sy), 0);
     const int xr = min(edge_ceil(ax, ay, bx - ax, by - ay, Sy) - 1, W - 1);
     xl_out = xl;
@@ -883,12 +923,14 @@ __device__ __forceinline__ bool clip_seg(const Cam &cam, const Poly &P, bool liv
     const int l4 = sl & 3;
     V3 v = sel_v3(l4 == 0, P.v[0], sel_v3(l4 == 1, P.v[1], sel_v3(l4 == 2, P.v[2], P.v[3])));
     for (int pl = 0; pl < 6; ++pl) {
-        const V3 b = shfl_v3(v, base + (sl + 1 >= n ? 0 : sl + 1));
-        const float da = plane_dist(pl, cam, v), db = plane_dist(pl, cam, b);
+        const float da = plane_dist(pl, cam, v);
         const bool act = sl < n;
-        const bool ia = da >= 0.0f, ib = db >= 0.0f;
+        const bool ia = da >= 0.0f;
         // every vertex of every segment inside: the walks emit the polygons unchanged
         if (__ballot(act && !ia) == 0ull) continue;
+        const V3 b = shfl_v3(v, base + (sl + 1 >= n ? 0 : sl + 1));
+        const float db = plane_dist(pl, cam, b);
+        const bool ib = db >= 0.0f;
         const bool e0 = act & ia, e1 = act & (ia != ib);
         V3 r = v;
         if (e1) {
@@ -1146,13 +1188,18 @@ __device__ __forceinline__ uint32_t shade_rgb(uint32_t c, uint32_t q)
     return r | (g << 8) | (b << 16);
 }
 
-// lit colour c of face f of box j
-__device__ __forceinline__ uint32_t lit_face(const DevSim &s, const SceneRec &sc, uint32_t c, int j, int f)
+// lit colour c of face f of a box with heading cs
+__device__ __forceinline__ uint32_t lit_heading(const DevSim &s, uint32_t c, float2 cs, int f)
 {
-    const float2 cs = s.cs[box_slot(sc, j)];
     const float nx = f == 0 ? cs.x : f == 1 ? -cs.y : f == 2 ? -cs.x : cs.y;
     const float ny = f == 0 ? cs.y : f == 1 ? cs.x : f == 2 ? -cs.y : -cs.x;
     return shade_rgb(c, shade_level(s, nx, ny, f));
+}
+
+// lit colour c of face f of box j
+__device__ __forceinline__ uint32_t lit_face(const DevSim &s, const SceneRec &sc, uint32_t c, int j, int f)
+{
+    return lit_heading(s, c, s.cs[box_slot(sc, j)], f);
 }
 
 // lit colour c of the box face that a winning key names (box and face from

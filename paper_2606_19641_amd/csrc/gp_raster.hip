@@ -9,19 +9,20 @@
 //
 // One workgroup of K wavefronts (1..16) renders one view of any size from 16
 // samples a row on, with about 16 KB of LDS at 128 x 128 and two wavefronts:
-//   A  bins    the scene's road culling bins are tested against the view
-//              (frustum, road depth limit and the row-gap test below); the
-//              surviving bins are listed in LDS.
-//   B  units   the waves deal out work units through LDS counters.  A road
-//              unit is four surviving bins (64 strip slots).  A strip first
+//   A  cull    the scene's road culling bins are tested against the view
+//              (frustum, road depth limit and the row-gap test below) and its
+//              boxes against the frustum; the surviving bins are listed in
+//              LDS, the surviving boxes with what their faces are built from.
+//   B  units   the waves share the work units.  A road unit is four surviving
+//              bins (64 strip slots).  A strip first
 //              meets a cheap test that can only reject strips covering no
 //              sample: the frustum, the road depth limit, and the row-gap test
 //              (every vertex a strip's clip can produce lies at camera height
 //              -h, so its snapped row coordinate is a non-increasing function
 //              of its depth; a strip whose depth range maps between two sample
 //              rows covers none).  Survivors join the view's ring.  Then the
-//              jobs: box units (cull, face set-up and clipping into the view's
-//              box list, a face as one quad where it covers what its triangles
+//              jobs: box units (face set-up and clipping of ten boxes into the
+//              view's box list, a face as one quad where it covers what its triangles
 //              cover) and set-up jobs of up to 64 ring strips (clip test, snap,
 //              a quad or the two fan triangles, the clipper four strips per
 //              wavefront); per (primitive, row) the exact span of covered
@@ -60,7 +61,7 @@ namespace {
 // a scene 326 us, here 77 us.  one_cam: the sim's record holds the
 // view's camera direction only (a batch's copy of it), as camera 0.
 template <bool AP>
-__device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, const RgbLds &L, int view, bool one_cam)
+__device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, RgbLds L, int view, bool one_cam)
 {
     const int B = (int)blockDim.x, K = B >> 6;
     const int tid = (int)threadIdx.x, wv = tid >> 6;
@@ -73,53 +74,72 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, c
 
     const int nbits = ((W * (H - L.hr0) + 63) >> 6) + 1;
     for (int p = tid; p < nbits; p += B) L.bits[p] = 0ull;
-    // boxes per box unit: a unit of 16 boxes sets up their faces in one or two
-    // passes; workgroups of many wavefronts take smaller units, so that the
-    // boxes are spread over them
-    const int ubox = K >= 8 ? 4 : 16;
-    const int nbu = (sc.n_agents + sc.n_static + ubox - 1) / ubox;
     const int nlu = AP ? (sc.n_signals + 63) / 64 : 0;
     if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();
 
-    // ---- A: road culling bins
-    for (int b0 = 64 * wv; b0 < sc.n_bins; b0 += B) cull_bins(s, sc, cam, L, b0);
+    // ---- A: road culling bins and boxes
+    const int nbox = sc.n_agents + sc.n_static;
+    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
     __syncthreads();
 
-    // ---- B: the road and box units (boxes ubox k .. ubox k + ubox - 1: cull,
-    // face set-up and clipping into the box list)
-    const int nsb = L.cnt[R_NSB];
+    // ---- B: the road and box units (set-up and clipping of the faces into the
+    // box list)
+    const int nsb = L.cnt[R_NSB], nsv = L.cnt[R_NSV];
+    const int ubox = box_unit(K);
+    const int nbu = nsv <= L.nrec ? (nsv + ubox - 1) / ubox : 0;
     // road work ahead grows with the surviving bins (a mean view keeps about a dozen)
     const int prio_b = nsb >= 24 ? 2 : (nsb >= 16 ? 1 : 0);
     view_priority(prio_b);
-    lptr<unsigned char> wbase = L.waves + (size_t)wv * kWaveBytes;
-    WaveSt ws;
-    ws.tris = (lptr<Prim>)wbase;
-    ws.clipq = (lptr<int32_t>)(wbase + kWTris * 48);
-    ws.nclip = 0;
-    ws.nfan = 0;
-    road_work(
-        s, sc, L, nsb, nbu + nlu, false,
-        [&](bool live, const float4 &q0, const float4 &q1) -> bool {
-            float x[4], z[4];
-            ground_xz(cam, q0.x, q0.y, x[0], z[0]);
-            ground_xz(cam, q0.z, q0.w, x[1], z[1]);
-            ground_xz(cam, q1.x, q1.y, x[2], z[2]);
-            ground_xz(cam, q1.z, q1.w, x[3], z[3]);
-            return live && !road_culled<false>(cam, x, z, 0, cam.H);
-        },
-        [&](int u) {
-            if (AP && u >= nbu) do_lights(s, sc, cam, L, u - nbu);
-            else do_boxes<AP>(s, sc, cam, ego, L, u, ubox, (lptr<int32_t>)ws.tris);   // the staging is free here
-        },
-        [&](int a, int n) {
-            setup_job<false>(s, sc, cam, L, ws, a, n, [&](int t) { road_spans(L, cam, ws, t); });
-        });
+    // a view that may list more faces (three a box) than its list holds gives it
+    // the memory of a smaller ring and smaller set-up jobs
+    if (3 * nsv + (AP ? sc.n_signals : 0) > L.bcap && nsv <= L.nrec) {
+        L.ring = kSmallRing;
+        L.batch = kSmallBatch;
+        const int tail = 4 * kSmallRing + K * wave_bytes(kSmallBatch);
+        const int cap = min(256, (L.tail - max(tail, resolve_bytes(W))) / (int)sizeof(FaceRec));
+        if (cap > L.bcap) L.bcap = cap;
+        L.sring = (lptr<int32_t>)((lptr<unsigned char>)L.faces + L.tail - tail);
+        L.waves = (lptr<unsigned char>)(L.sring + kSmallRing);
+    }
+    WaveSt ws = wave_state(L, wv);
+    // more surviving bins than the list holds: the scene's bins in segments that
+    // it does hold
+    const bool over = nsb > L.bins;
+    for (int s0 = 0;;) {
+        if (over) {
+            __syncthreads();                       // the counters are read
+            if (tid == 0) L.cnt[R_NSB] = L.cnt[R_RING] = L.cnt[R_JOB] = 0;
+            __syncthreads();
+            const int s1 = min(s0 + L.bins, sc.n_bins);
+            for (int b0 = s0 + 64 * wv; b0 < s1; b0 += B) cull_pass(s, sc, cam, ego, L, b0, s1, 0);
+            __syncthreads();
+        }
+        road_work(
+            s, sc, L, over ? L.cnt[R_NSB] : nsb, s0 == 0 ? nbu + nlu : 0, false,
+            [&](bool live, const float4 &q0, const float4 &q1) -> bool {
+                float x[4], z[4];
+                ground_xz(cam, q0.x, q0.y, x[0], z[0]);
+                ground_xz(cam, q0.z, q0.w, x[1], z[1]);
+                ground_xz(cam, q1.x, q1.y, x[2], z[2]);
+                ground_xz(cam, q1.z, q1.w, x[3], z[3]);
+                return live && !road_culled<false>(cam, x, z, 0, cam.H);
+            },
+            [&](int u) {
+                if (AP && u >= nbu) do_lights(s, sc, cam, L, u - nbu);
+                else do_boxes<AP>(s, sc, cam, L, u, ubox, nsv, (lptr<int32_t>)ws.tris);   // the staging is free here
+            },
+            [&](int a, int n) {
+                setup_job<false>(s, sc, cam, L, ws, a, n, [&](int t) { road_spans(L, cam, ws, t); });
+            });
+        s0 += L.bins;
+        if (!over || s0 >= sc.n_bins) break;
+    }
 
     // ---- C: resolve
     uint8_t *img = rgb + 3 * ((int64_t)view * W * H);
     const int nbt = L.cnt[R_NBT];
-    const bool ovf = L.cnt[R_BOVF] != 0;
+    const bool ovf = L.cnt[R_BOVF] != 0 || nsv > L.nrec;
     int kr0 = H, kr1 = H;          // rows that need the key band
     if (ovf) {
         kr0 = 0;
@@ -131,6 +151,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, c
     view_priority(max(prio_b, kr1 - kr0 >= 64 ? 3 : (kr1 - kr0 >= 32 ? 2 : 0)));
     const uint32_t bg_rgb = s.bg_rgb;
     const uint32_t road_rgb = AP && s.shade ? shade_rgb(s.road_rgb, shade_level(s, 0.0f, 0.0f, 4)) : s.road_rgb;
+    free_region(L, ovf ? L.bcap : nbt, W);
     const int mrows = max(1, mask_rows_fit(L.region, nbt, W, L.nmw));
     // the pattern table, and the masks of the first chunk of box rows, in
     // chunks of rows whose items fit; the rows without boxes go with the first
@@ -166,18 +187,17 @@ __device__ __forceinline__ void carve_rgb(unsigned char *smem, RgbLds &L, int W,
     L.cnt = (lptr<int32_t>)(smem + l.cnt);
     L.bits = (lptr<unsigned long long>)(smem + l.bits);
     L.faces = (lptr<FaceRec>)(smem + l.faces);
+    L.recs = (lptr<BoxRec>)(smem + l.recs);
     L.sbins = (lptr<int32_t>)(smem + l.sbins);
-    L.cq = (lptr<int32_t>)(smem + l.cq);
     L.sring = (lptr<int32_t>)(smem + l.sring);
     L.waves = (lptr<unsigned char>)(smem + l.waves);
     L.hr0 = first_road_row(H);
     L.bcap = c.bcap;
-    L.nmw = c.bcap >> 6;
-    // the surviving-bin list, the ring and the waves' staging are idle by the resolve
-    L.pat = (lptr<gp_v4i>)(smem + l.sbins);
-    L.work = (lptr<unsigned long long>)(smem + l.sbins + kPatBytes);
-    L.region = (int)(l.total - l.sbins) - kPatBytes;
-    L.krows = max(1, L.region / (8 * W));
+    L.bins = c.bins_cap;
+    L.nrec = c.recs;
+    L.tail = (int)(l.total - l.faces);
+    L.batch = kBatch;
+    L.ring = kSharedRing;
 }
 
 // One workgroup per view: view view_begin + blockIdx.x (ordered 0), or
@@ -250,7 +270,7 @@ hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &
                              int grid, hipStream_t st)
 {
     if (grid <= 0) return hipSuccess;
-    if (c.waves < 1 || c.waves > 16 || s.width < 16) return hipErrorInvalidValue;
+    if (c.waves < 1 || c.waves > 16 || s.width < 16 || c.bcap < 64 || c.bcap > 256 || c.recs < 1 || c.recs > 64) return hipErrorInvalidValue;
     const size_t lds = rgb_lds_bytes(s.width, s.height, c);
     const dim3 block(64 * c.waves);
     if (c.appear) hipLaunchKernelGGL(k_render_rgb<true>, dim3(grid), block, lds, st, s, o, c, ordered, view_begin);
@@ -262,7 +282,7 @@ hipError_t launch_render_rgb_multi(const SimEntry *tab, const int2 *items, int n
                                    int height, hipStream_t st)
 {
     if (n_items <= 0) return hipSuccess;
-    if (c.waves < 1 || c.waves > 16 || width < 16) return hipErrorInvalidValue;
+    if (c.waves < 1 || c.waves > 16 || width < 16 || c.bcap < 64 || c.bcap > 256 || c.recs < 1 || c.recs > 64) return hipErrorInvalidValue;
     const size_t lds = rgb_lds_bytes(width, height, c);
     const dim3 block(64 * c.waves);
     if (c.appear) hipLaunchKernelGGL(k_render_rgb_multi<true>, dim3(n_items), block, lds, st, tab, items, c);

@@ -752,6 +752,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     L.bcap = c.bcap;
     L.krows = l.krows;
     L.hr0 = first_road_row(H);
+    L.batch = kBatch;
+    L.ring = kSharedRing;
+    L.bins = c.bins_cap;
+    L.nrec = 0;
     L.nmw = 0;
     L.region = l.region;
     lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
@@ -790,7 +794,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
             keep = !rc_outside(cam, hfs, x, z, L.hr0, H, j0, j1, m);
             rec = bn.start * 128 + bn.count;
         }
-        list_bins(L, keep, rec);
+        const unsigned long long bm = __ballot(keep);
+        if (bm == 0ull) continue;
+        int at = 0;
+        if (lane_id() == 0) at = lds_add(L.cnt + R_NSB, __popcll(bm));
+        at = __builtin_amdgcn_readlane(at, 0) + lanes_below(bm);
+        if (keep) L.sbins[at] = rec;
     }
     __syncthreads();
     const int nsb = L.cnt[R_NSB];
@@ -887,7 +896,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         clear((b1 - b0) * W);
         if (!first && tid == 0) {
             L.cnt[R_JOB] = 0;
-            if (!whole) L.cnt[R_NEXT] = L.cnt[R_RING] = L.cnt[R_RESV] = 0;
+            if (!whole) L.cnt[R_RING] = 0;
         }
         __syncthreads();
         // the first band's road work lists the boxes too, whether or not the band shows road

@@ -344,18 +344,25 @@ gp_status check_lds(const gp_sim *sim, const gp_launch &l)
     return GP_OK;
 }
 
-// Box faces (and traffic lights) one view's list holds in the split
-// rasteriser.  A box shows at most three faces, one list entry each, and a
-// view sees about a quarter of its scene's boxes, so 3/2 of the scene's boxes
-// do not overflow in practice; a view that overflows it all the same is
-// rendered by the streaming pass, several times slower (64 scenes of 4..128
-// agents with three cameras at 128 x 128: 2,744 us per render with a fixed list
-// of 96 triangles, most views of the large scenes overflowing; 523 us with
-// twice the scene's boxes and 454 us with 3/2, one more workgroup per CU).
-int split_box_faces(const gp_sim *sim)
+// Box faces (and traffic lights) one view's list holds in the split rasteriser.
+// A view of the largest scenes lists about twenty; one that may list more than
+// 64 takes memory of its road work for them (LDS of 27 KB instead, a list for
+// 3/2 of 128 boxes, left five workgroups to a CU: 64 scenes of 4..128 agents
+// with three cameras at 128 x 128 428 us per step, here 310).  A view that
+// overflows its list all the same is rendered by the streaming pass, several
+// times slower.
+constexpr int kListFaces = 64;
+
+// The same in the general raster: a box shows at most three faces, one entry
+// each, and a view sees about a quarter of its scene's boxes.
+int full_box_faces(const gp_sim *sim)
 {
     return (int)std::min<int64_t>(256, (sim->boxes_cap * 3LL / 2 + sim->signals_cap / 2 + 63) / 64 * 64);
 }
+
+// boxes of one view kept in LDS after their culling: every box of a small
+// scene, 64 of a large one (a view with more is streamed)
+int box_recs(const gp_sim *sim) { return (int)std::min<int64_t>(64, sim->boxes_cap); }
 
 // Wavefronts per view in the split rasteriser: the launch's view_waves, times
 // 2 from 32K pixels on and 4 from 200K on (a view's rows are a serial loop of
@@ -382,8 +389,9 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
 {
     gp::RgbCfg c;
     c.waves = split_waves(sim, l, n_views);
-    c.bcap = split_box_faces(sim);
-    c.bins_cap = sim->bins_cap;
+    c.bcap = kListFaces;
+    c.recs = box_recs(sim);
+    c.bins_cap = std::min(sim->bins_cap, 256);
     c.appear = (sim->dev.shade || sim->lay.n_signals > 0) ? 1 : 0;
     return c;
 }
@@ -402,7 +410,8 @@ gp::FullCfg full_cfg(const gp_sim *sim)
     gp::FullCfg c;
     c.waves = px >= 200000 ? 8 : 4;
     while (c.waves < 16 && 2 * c.waves * sim->lay.n_views <= 16 * (int64_t)sim->n_cu) c.waves *= 2;
-    c.bcap = split_box_faces(sim);
+    c.bcap = full_box_faces(sim);
+    c.recs = box_recs(sim);
     c.bins_cap = sim->bins_cap;
     const int samples = std::max(512 * c.waves, px >= 60000 ? 4096 : 2048);
     c.band_rows = std::min(sim->cfg.height, std::max(1, samples / sim->cfg.width));
@@ -1071,8 +1080,8 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
     const int W = sims[0]->cfg.width, H = sims[0]->cfg.height;
     gp::RgbCfg rc = rgb_cfg(sims[0], l, n_views);
     for (int k = 1; k < n_sims; ++k) {
-        rc.bcap = std::max(rc.bcap, split_box_faces(sims[k]));
-        rc.bins_cap = std::max(rc.bins_cap, sims[k]->bins_cap);
+        rc.recs = std::max(rc.recs, box_recs(sims[k]));
+        rc.bins_cap = std::max(rc.bins_cap, std::min(sims[k]->bins_cap, 256));
     }
     const bool split = l.raster == GP_RASTER_SPLIT && W >= 16 && gp::rgb_lds_bytes(W, H, rc) <= sims[0]->max_lds;
     enum { B_SPLIT = 0, B_APPEAR, B_FAST, B_GENERAL, B_N };

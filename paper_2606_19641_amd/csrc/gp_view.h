@@ -12,43 +12,66 @@ namespace gp {
 namespace {
 
 constexpr int kSharedRing = 768;   // strips passed by the cheap test, one ring per view (road slot indices)
-constexpr int kWTris = 64;      // road primitives (quads, triangles) staged for one span pass
-constexpr int kSetupBatch = kWTris;       // strips of one set-up job at most (one quad each; the rest are queued)
-constexpr int kWClip = kSetupBatch;       // strips of one job waiting for the clipper (from the front) or
-                                          // for their fan triangles (from the back)
-constexpr int kWaveBytes = kWTris * 48 + kWClip * 4;
-static_assert(kWaveBytes % 16 == 0, "wave regions stay 16-byte aligned");
+constexpr int kBatch = 64;      // road primitives (quads, triangles) a wavefront stages for one span pass, strips
+                                // of one set-up job at most (one quad each; the rest are queued), and entries
+                                // of its queue: strips waiting for the clipper (from the front) or for their fan
+                                // triangles (from the back)
+constexpr int kSmallBatch = 32, kSmallRing = 256;    // the same, and the ring, in a crowded view
+__host__ __device__ constexpr int wave_bytes(int batch) { return batch * (48 + 4); }
+constexpr int kWaveBytes = wave_bytes(kBatch);
+static_assert(kWaveBytes % 16 == 0 && wave_bytes(kSmallBatch) % 16 == 0, "wave regions stay 16-byte aligned");
 static_assert(sizeof(Prim) == 48, "staged primitive size");
 
 // LDS counters
-enum { R_NSB = 0, R_NEXT, R_NBT, R_BOVF, R_BMIN, R_BMAX, R_RING, R_RESV, R_JOB, R_NCNT = 12 };
+enum { R_NSB = 0, R_NBT, R_BOVF, R_BMIN, R_BMAX, R_RING, R_JOB, R_NSV, R_AT, R_NCNT = 12 };
 constexpr int kBoxClip = 64;     // box faces waiting for the clipper (one setup pass)
+constexpr int kBoxRecs = 64;     // boxes of one view kept in LDS after their culling, at most
+
+// A box that may be seen by the view: what its faces are built from.  (Box
+// units that culled 16 boxes each and read the survivors' state again took 7,000
+// cycles apiece, 40% of the set-up of scenes with 128 agents.)
+struct BoxRec {
+    float x, y, c, s;            // centre, cosine and sine of the heading
+    float dx, dy, dz;            // size
+    int32_t j;                   // box of the scene
+};
+static_assert(sizeof(BoxRec) == 32, "BoxRec layout");
 
 struct RgbLds {
     lptr<int32_t> cnt;               // [R_NCNT]
     lptr<unsigned long long> bits;   // road coverage: bit (j - hr0) * W + i is sample i of row j >= hr0
     lptr<FaceRec> faces;             // [bcap] the view's box faces
     lptr<int32_t> sbins;             // [bins_cap] surviving bins: start * 128 + count
-    lptr<int32_t> cq;                // [kBoxClip] box faces to clip (box * 8 + face)
-    lptr<int32_t> sring;             // [kSharedRing] strips that passed the cheap test (this round)
-    lptr<unsigned char> waves;       // K regions of kWaveBytes
-    // after the units the memory from sbins on is free again: the pattern table, then masks and spans or keys
+    lptr<BoxRec> recs;               // [nrec] the boxes that survived their culling
+    lptr<int32_t> cq;                // [kBoxClip] box faces to clip (record * 8 + face)
+    lptr<int32_t> sring;             // [ring] strips that passed the cheap test (this round)
+    lptr<unsigned char> waves;       // K regions of wave_bytes(batch)
+    // after the units the memory behind the listed faces is free again: the pattern table, then masks and
+    // spans or keys
     lptr<gp_v4i> pat;                // [3][64] the 16 bytes at byte phase p of a run of six pixels, by its coverage bits
     lptr<unsigned long long> work;   // masks and spans, or rows of 64-bit keys
     int bcap, krows;
+    int batch, ring;                 // primitives a wavefront stages, strips the ring holds
+    int bins;                        // surviving bins the list holds
+    int nrec;                        // boxes the records hold
     int hr0;                         // first image row below the horizon
-    int nmw;                         // 64-bit words of a face mask (bcap / 64)
+    int nmw;                         // 64-bit words of a face mask
     int region;                      // bytes from work to the end
+    int tail;                        // bytes from faces to the end
 };
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 // byte offsets of the LDS sections (shared by the carve and the size query)
 struct RgbLayout {
-    size_t cnt, bits, faces, sbins, cq, sring, waves, total;
+    size_t cnt, bits, recs, sbins, faces, sring, waves, total;
 };
 
 constexpr int kPatBytes = 3 * 64 * 16;
+
+// the resolve's memory behind the listed faces: the pattern table, and a row of
+// keys or a row of masks and spans of up to 256 faces
+__host__ __device__ inline int resolve_bytes(int W) { return kPatBytes + 8 * W + 1280; }
 
 // rows that can show road: below the principal point (the road's 1/z there is
 // positive only where (j + 0.5) - H / 2 is)
@@ -62,13 +85,12 @@ __host__ __device__ inline RgbLayout rgb_layout(int W, int H, const RgbCfg &c)
     size_t o = 0;
     l.cnt = o; o = align16(o + 4 * R_NCNT);
     l.bits = o; o = align16(o + 8 * nbw);
-    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
-    l.cq = o; o = align16(o + 4 * (size_t)kBoxClip);
+    l.recs = o; o = align16(o + sizeof(BoxRec) * (size_t)c.recs);
     l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
+    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
+    const size_t least = align16(o + (size_t)resolve_bytes(W));
     l.sring = o; o = align16(o + 4 * (size_t)kSharedRing);
     l.waves = o; o = align16(o + (size_t)kWaveBytes * (size_t)c.waves);
-    // the memory from sbins on holds the pattern table and a row of keys (or of masks and spans)
-    const size_t least = align16(l.sbins + kPatBytes + 8 * (size_t)W);
     o = o > least ? o : least;
     l.total = o;
     return l;
@@ -77,11 +99,38 @@ __host__ __device__ inline RgbLayout rgb_layout(int W, int H, const RgbCfg &c)
 // ------------------------------------------------------------ per-wave state
 
 struct WaveSt {
-    lptr<Prim> tris;         // [kWTris] road primitives
-    lptr<int32_t> clipq;     // [kWClip] road slots (global): nclip for the clipper at the front,
+    lptr<Prim> tris;         // [batch] road primitives
+    lptr<int32_t> clipq;     // [batch] road slots (global): nclip for the clipper at the front,
                              // nfan for their two fan triangles at the back
     int nclip, nfan;         // queued strips
+    int batch;
 };
+
+__device__ __forceinline__ WaveSt wave_state(const RgbLds &L, int wv)
+{
+    lptr<unsigned char> base = L.waves + (size_t)wv * wave_bytes(L.batch);
+    WaveSt ws;
+    ws.tris = (lptr<Prim>)base;
+    ws.clipq = (lptr<int32_t>)(base + L.batch * 48);
+    ws.nclip = 0;
+    ws.nfan = 0;
+    ws.batch = L.batch;
+    return ws;
+}
+
+// The memory behind the list's n faces for the resolve (the ring and the
+// wavefronts' staging are idle by then); after the pattern table's use its
+// place holds the streaming pass's clip queue.
+__device__ __forceinline__ void free_region(RgbLds &L, int n, int W)
+{
+    lptr<unsigned char> p = (lptr<unsigned char>)(L.faces + n);
+    L.pat = (lptr<gp_v4i>)p;
+    L.cq = (lptr<int32_t>)p;
+    L.work = (lptr<unsigned long long>)(p + kPatBytes);
+    L.region = L.tail - n * (int)sizeof(FaceRec) - kPatBytes;
+    L.krows = max(1, L.region / (8 * W));
+    L.nmw = max(1, (n + 63) >> 6);
+}
 
 // OR the coverage bits [b0, b1] into their words
 __device__ __forceinline__ void or_span(lptr<unsigned long long> bits, int b0, int b1)
@@ -200,22 +249,23 @@ __device__ __forceinline__ int road_key(const DevSim &s, const SceneRec &sc, int
     return (int)key_low(0u, 6 * (sc.n_agents + sc.n_static) + s.road_index[g], s.road_color[g]);
 }
 
-// Stage the triangles held by the lanes (v0: t0, v1: t1); returns how many.
-__device__ __forceinline__ int stage_tris(const WaveSt &ws, bool v0, const Prim &t0, bool v1, const Prim &t1)
+// Stage the triangles held by the lanes (v) behind the n staged ones; returns
+// how many are staged then.
+__device__ __forceinline__ int stage_tris(const WaveSt &ws, int n, bool v, const Prim &t)
 {
-    const unsigned long long b0 = __ballot(v0), b1 = __ballot(v1);
-    const int n0 = __popcll(b0);
-    if (v0) lds_store(ws.tris + lanes_below(b0), t0);
-    if (v1) lds_store(ws.tris + n0 + lanes_below(b1), t1);
-    return n0 + __popcll(b1);
+    const unsigned long long b = __ballot(v);
+    if (v) lds_store(ws.tris + n + lanes_below(b), t);
+    return n + __popcll(b);
 }
 
 // Clip up to four queued strips (the last ones of the queue), one per 16-lane
-// segment; stages their fan triangles and returns how many.
+// segment; stages their fan triangles behind the n staged primitives and
+// returns how many are staged then, or -1 (the strips stay queued) where they
+// do not fit.  They always fit an empty stage.
 template <bool KEY>
-__device__ __forceinline__ int road_clip(const DevSim &s, const SceneRec &sc, const Cam &cam, WaveSt &ws)
+__device__ __forceinline__ int road_clip(const DevSim &s, const SceneRec &sc, const Cam &cam, WaveSt &ws, int n)
 {
-    const int m = min(ws.nclip, 4);
+    const int m = min(ws.nclip, min(4, ws.batch / kMaxTrisPerCand));
     const int seg = (int)lane_id() >> 4;
     const bool live = seg < m;
     Poly P = {};
@@ -228,26 +278,28 @@ __device__ __forceinline__ int road_clip(const DevSim &s, const SceneRec &sc, co
     P.n = dir_to_cam(cam, 0.0f, 0.0f, 1.0f);
     P.one_sided = false;
     P.keylo = 0u;
-    ws.nclip -= m;
     TriRec t;
     const bool ok = clip_seg<false>(cam, P, live, 0, cam.H, t);
-    Prim p = prim_of(t.g), none = {};
+    if (n + __popcll(__ballot(ok)) > ws.batch) return -1;
+    ws.nclip -= m;
+    Prim p = prim_of(t.g);
     p.pad0 = key;
-    return stage_tris(ws, ok, p, false, none);
+    return stage_tris(ws, n, ok, p);
 }
 
-// The two fan triangles of up to 32 queued strips (the last ones queued at
-// the back of the queue); stages them and returns how many.  Their corners
+// The two fan triangles of up to batch / 2 queued strips (the last ones queued
+// at the back of the queue); stages them behind the n staged primitives and
+// returns how many are staged then.  Their corners
 // and snap are computed again, as the set-up computed them.
 template <bool KEY>
-__device__ __forceinline__ int road_fan(const DevSim &s, const SceneRec &sc, const Cam &cam, WaveSt &ws)
+__device__ __forceinline__ int road_fan(const DevSim &s, const SceneRec &sc, const Cam &cam, WaveSt &ws, int n)
 {
-    const int m = min(ws.nfan, 32);
+    const int m = min(ws.nfan, ws.batch / 2);
     const int ln = (int)lane_id();
     Prim p0 = {}, p1 = {};
     bool v0 = false, v1 = false;
     if (ln < m) {
-        const int g = ws.clipq[kWClip - ws.nfan + ln];
+        const int g = ws.clipq[ws.batch - ws.nfan + ln];
         V3 v[4];
         road_corners(s, cam, g, v);
         int32_t X[4], Y[4];
@@ -261,10 +313,11 @@ __device__ __forceinline__ int road_fan(const DevSim &s, const SceneRec &sc, con
         if (KEY) p0.pad0 = p1.pad0 = road_key(s, sc, g);
     }
     ws.nfan -= m;
-    return stage_tris(ws, v0, p0, v1, p1);
+    n = stage_tris(ws, n, v0, p0);
+    return stage_tris(ws, n, v1, p1);
 }
 
-// Full setup of the n (<= kSetupBatch) strips ring[a .. a + n): clip test,
+// Full setup of the n (<= batch) strips ring[a .. a + n): clip test,
 // snap, and the quad of the strips whose quad covers exactly what their two
 // fan triangles cover (staged; returns how many); strips that need the
 // clipper join the front of the wave's queue, strips that need their fan
@@ -299,40 +352,44 @@ __device__ __forceinline__ int road_setup(const DevSim &s, const SceneRec &sc, c
         if (KEY) p0.pad0 = road_key(s, sc, g);
     }
     const unsigned long long fb = __ballot(fan);
-    if (fan) ws.clipq[kWClip - 1 - (ws.nfan + lanes_below(fb))] = g;
+    if (fan) ws.clipq[ws.batch - 1 - (ws.nfan + lanes_below(fb))] = g;
     ws.nfan += __popcll(fb);
-    Prim none = {};
-    return stage_tris(ws, v0, p0, false, none);
+    return stage_tris(ws, 0, v0, p0);
 }
 
-// One set-up job: the n ring strips from a set up, their primitives
-// rasterised (spans(n): the n staged ones), then the strips that needed their
-// fan triangles (32 at a time) and those that needed the clipper (four at a
-// time).  KEY: a staged primitive carries its strip's key word in pad0.
+// One set-up job: the n ring strips from a set up and their primitives
+// rasterised (spans(n): the n staged ones): the quads, with the triangles of
+// the strips that need the clipper (four at a time) and of those that need
+// their fan triangles where they fit behind them, else in passes of their own
+// (four strips cut by one plane have sixteen triangles at most).  KEY: a staged primitive carries its
+// strip's key word in pad0.
 template <bool KEY, class Spans>
 __device__ __forceinline__ void setup_job(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, WaveSt &ws,
                                           int a, int n, Spans spans)
 {
-    int ntri = road_setup<KEY>(s, sc, cam, L, ws, a, n);
+    int staged = road_setup<KEY>(s, sc, cam, L, ws, a, n);
     for (;;) {
-        if (ntri > 0) spans(ntri);
-        if (ws.nfan > 0)
-            ntri = road_fan<KEY>(s, sc, cam, ws);
-        else if (ws.nclip > 0)
-            ntri = road_clip<KEY>(s, sc, cam, ws);
-        else
-            break;
+        while (ws.nclip > 0 && (staged == 0 || staged + 16 <= ws.batch)) {
+            const int t = road_clip<KEY>(s, sc, cam, ws, staged);
+            if (t < 0) break;
+            staged = t;
+        }
+        if (ws.nfan > 0 && staged + 2 * min(ws.nfan, ws.batch / 2) <= ws.batch) staged = road_fan<KEY>(s, sc, cam, ws, staged);
+        if (staged > 0) spans(staged);
+        else if (ws.nclip + ws.nfan == 0) break;
+        staged = 0;
     }
 }
 
 // The survivors of one unit's strips (pass; slot g) appended to the view's
-// ring (64 entries were reserved).
+// ring (a round has no more units than the ring takes 64 strips of).
 __device__ __forceinline__ void ring_append(const RgbLds &L, bool pass, int g)
 {
     const unsigned long long bm = __ballot(pass);
+    if (bm == 0ull) return;
     int base = 0;
-    if (lane_id() == 0 && bm != 0ull) base = lds_add(L.cnt + R_RING, __popcll(bm));
-    base = __shfl(base, 0);
+    if (lane_id() == 0) base = lds_add(L.cnt + R_RING, __popcll(bm));
+    base = __builtin_amdgcn_readlane(base, 0);
     if (pass) L.sring[base + lanes_below(bm)] = g;
 }
 
@@ -356,69 +413,56 @@ __device__ __forceinline__ bool load_unit(const DevSim &s, const SceneRec &sc, c
 }
 
 // The road work of a view (and, as its first jobs, the box and light units),
-// dealt over the wavefronts through LDS counters in rounds of two steps.  B1:
-// the road units (four surviving bins each): test(live, q0, q1) is the cheap
-// test of the unit's strips, whose survivors join the view's ring (a unit is
-// taken only with 64 free ring entries reserved).  B2: the jobs -- in the first
-// round box(u) for u < box_jobs (their lists are needed only by the resolve, so
-// a long box unit overlaps the other wavefronts' road jobs), then road(a, n)
-// for up to kSetupBatch ring strips at a time.  A round ends when the ring is
-// full or the units are used up.  R_NEXT, R_RING, R_RESV and R_JOB are zero at
-// the start (published by a barrier); ends with a barrier.  Returns whether one
-// round sufficed: the ring then still holds every strip, and a further call
+// shared by the wavefronts in rounds of two steps.  B1: the road units (four
+// surviving bins each), as many as the ring has 64 entries for, in turn:
+// test(live, q0, q1) is the cheap test of the unit's strips, whose survivors
+// join the view's ring.  B2: the jobs, dealt through an LDS counter -- in the
+// first round box(u) for u < box_jobs (their lists are needed only by the
+// resolve, so a long box unit overlaps the other wavefronts' road jobs), then
+// road(a, n) for up to batch ring strips at a time.  R_RING and R_JOB are zero
+// at the start (published by a barrier); ends with a barrier.  Returns whether
+// one round sufficed: the ring then still holds every strip, and a further call
 // with reuse set (R_JOB zero) only deals its jobs again.
+// (The units were dealt through LDS counters too, with ring entries reserved:
+// four dependent LDS operations before a unit's loads, and units cost the same.)
 template <class Test, class Box, class Road>
 __device__ __forceinline__ bool road_work(const DevSim &s, const SceneRec &sc, const RgbLds &L, int nsb, int box_jobs,
                                           bool reuse, Test test, Box box, Road road)
 {
     const int ln = (int)lane_id(), K = (int)blockDim.x >> 6;
-    const int n_units = (nsb + 3) / 4;
-    // the next unit with its ring entries reserved, or n_units (none left, or
-    // the ring cannot take another road unit this round)
-    auto take = [&]() -> int {
-        int u = n_units;
-        if (ln == 0) {
-            const int r = lds_add(L.cnt + R_RESV, 64);
-            if (r + 64 <= kSharedRing) {
-                u = min(lds_add(L.cnt + R_NEXT, 1), n_units);
-                if (u == n_units) lds_add(L.cnt + R_RESV, -64);   // no unit left
-            } else {
-                lds_add(L.cnt + R_RESV, -64);
-            }
-        }
-        return __builtin_amdgcn_readfirstlane(__shfl(u, 0));
-    };
-    for (bool one = true;; one = false) {
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n_units = (nsb + 3) / 4, per = L.ring / 64;
+    for (int u0 = 0;; u0 += per) {
         // B1, the next unit's strips loaded while the current one is tested
-        int u = reuse ? n_units : take();
-        float4 q0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), q1 = q0;
-        int gq = 0;
-        bool live = u < n_units && load_unit(s, sc, L, nsb, u, gq, q0, q1);
-        while (u < n_units) {
-            const int un = take();
-            float4 n0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), n1 = n0;
-            int gn = 0;
-            const bool nlive = un < n_units && load_unit(s, sc, L, nsb, un, gn, n0, n1);
-            ring_append(L, test(live, q0, q1), gq);
-            u = un;
-            q0 = n0;
-            q1 = n1;
-            gq = gn;
-            live = nlive;
+        const int u1 = min(u0 + per, n_units);
+        if (!reuse) {
+            float4 q0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), q1 = q0;
+            int gq = 0;
+            bool live = u0 + wv < u1 && load_unit(s, sc, L, nsb, u0 + wv, gq, q0, q1);
+            for (int u = u0 + wv; u < u1; u += K) {
+                float4 n0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), n1 = n0;
+                int gn = 0;
+                const bool nlive = u + K < u1 && load_unit(s, sc, L, nsb, u + K, gn, n0, n1);
+                ring_append(L, test(live, q0, q1), gq);
+                q0 = n0;
+                q1 = n1;
+                gq = gn;
+                live = nlive;
+            }
+            __syncthreads();
         }
-        if (!reuse) __syncthreads();
         const int nring = L.cnt[R_RING];
-        const bool more = L.cnt[R_NEXT] < n_units;
-        // the ring cut into jobs of at most kSetupBatch strips, as many as a
+        const bool more = u1 < n_units;
+        // the ring cut into jobs of at most batch strips, as many as a
         // multiple of the wavefronts, of equal size: a job's set-up takes about
         // the same time for any number of strips up to a wavefront's width
-        const int njobs = (max(K, (nring + kSetupBatch - 1) / kSetupBatch) + K - 1) / K * K;
+        const int njobs = (max(K, (nring + L.batch - 1) / L.batch) + K - 1) / K * K;
         const int jsz = (nring + njobs - 1) / njobs;
         // B2
         for (;;) {
             int j = 0;
             if (ln == 0) j = lds_add(L.cnt + R_JOB, 1);
-            j = __builtin_amdgcn_readfirstlane(__shfl(j, 0)) - box_jobs;
+            j = __builtin_amdgcn_readlane(j, 0) - box_jobs;
             if (j < 0) {
                 box(j + box_jobs);
                 continue;
@@ -429,12 +473,8 @@ __device__ __forceinline__ bool road_work(const DevSim &s, const SceneRec &sc, c
         }
         __syncthreads();
         box_jobs = 0;
-        if (!more) return one;
-        if (threadIdx.x == 0) {
-            L.cnt[R_RING] = 0;
-            L.cnt[R_RESV] = 0;
-            L.cnt[R_JOB] = 0;
-        }
+        if (!more) return u0 == 0;
+        if (threadIdx.x == 0) L.cnt[R_RING] = L.cnt[R_JOB] = 0;
         __syncthreads();
     }
 }
@@ -455,7 +495,7 @@ __device__ __forceinline__ int box_reserve(const RgbLds &L, bool shared, int &nb
     }
     int at = 0;
     if (lane_id() == 0 && n > 0) at = lds_add(L.cnt + R_NBT, n);
-    at = __builtin_amdgcn_readfirstlane(__shfl(at, 0));
+    at = __builtin_amdgcn_readlane(at, 0);
     if (at + n > L.bcap) {
         if (lane_id() == 0) L.cnt[R_BOVF] = 1;
         return -1;
@@ -469,6 +509,14 @@ __device__ __forceinline__ uint32_t face_rgb(const DevSim &s, const SceneRec &sc
 {
     const uint32_t c = s.box_rgb[box_slot(sc, j)];
     return AP && s.shade ? lit_face(s, sc, c, j, f) : c;
+}
+
+// the same from the box's record
+template <bool AP>
+__device__ __forceinline__ uint32_t rec_rgb(const DevSim &s, const SceneRec &sc, const BoxRec &b, int f)
+{
+    const uint32_t c = s.box_rgb[box_slot(sc, b.j)];
+    return AP && s.shade ? lit_heading(s, c, make_float2(b.c, b.s), f) : c;
 }
 
 // the colour of traffic light g's state (never lit)
@@ -514,34 +562,33 @@ __device__ __forceinline__ bool light_pass(const DevSim &s, const SceneRec &sc, 
     return true;
 }
 
-// One setup pass over box face candidates [c0, c0 + P) (P <= 64): candidate c
-// is face c % 6 of box surv[c / 6] (use_surv), or of box c / 6 culled here.
-// Fast faces and the triangles of clipped faces (clip queue cq) are appended
-// to the box list (box_reserve), the low byte of each key word naming the
-// entry; returns false as soon as they would not fit (the list is then
-// incomplete: the view takes the overflow path, which ignores it).  Six
-// candidates at a time never overflow a private list of 64 (at most 10
-// triangles each).
+// face f of the box in a record; the key word without its low byte
+__device__ __forceinline__ void rec_face(const Cam &cam, const BoxRec &b, int f, Poly &P)
+{
+    face_corners(cam, b.x, b.y, b.c, b.s, b.dx, b.dy, b.dz, f, P);
+    P.keylo = key_low(1u, 6 * b.j + f, 0u);
+}
+
+// One setup pass over the faces of box records [r0, r0 + n) (n <= 10): fast
+// faces and the triangles of clipped faces (clip queue cq) are appended to the
+// box list (box_reserve), the low byte of each key word naming the entry;
+// returns false as soon as they would not fit (the list is then incomplete).
+// One record never overflows a private list of 64 (its six faces have at most
+// 10 triangles each).
 template <bool AP>
-__device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                         lptr<const int32_t> surv, bool use_surv, int ncand, int c0, int P, lptr<int32_t> cq,
-                         bool shared, int &nbt, int &bmin, int &bmax)
+__device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int r0, int n,
+                                         lptr<int32_t> cq, bool shared, int &nbt, int &bmin, int &bmax)
 {
     const int ln = (int)lane_id();
-    const int c = c0 + ln;
-    bool live = ln < P && c < ncand;
-    int j = 0, f = 0;
-    if (live) {
-        j = use_surv ? surv[c / 6] : c / 6;
-        f = c - 6 * (c / 6);
-        if (!use_surv) live = j != ego && !box_outside(s, sc, cam, j);
-    }
+    const bool live = ln < 6 * n;
+    const int r = r0 + ln / 6, f = ln % 6;
     Poly Pf;
     FaceRec f0, f1;
     bool v0 = false, v1 = false, clip = false;
     if (live) {
-        build_face(s, sc, cam, j, f, Pf);
-        fast_face(cam, Pf, face_rgb<AP>(s, sc, j, f), 0, cam.H, f0, v0, f1, v1, clip);
+        const BoxRec b = lds_load(L.recs + r);
+        rec_face(cam, b, f, Pf);
+        fast_face(cam, Pf, rec_rgb<AP>(s, sc, b, f), 0, cam.H, f0, v0, f1, v1, clip);
     }
     const unsigned long long b0 = __ballot(v0), b1 = __ballot(v1), bc = __ballot(clip);
     const int n0 = __popcll(b0), nf = n0 + __popcll(b1), ncl = __popcll(bc);
@@ -561,7 +608,7 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
         bmin = min(bmin, (int)f1.j0);
         bmax = max(bmax, (int)f1.j1);
     }
-    if (clip) cq[lanes_below(bc)] = j * 8 + f;
+    if (clip) cq[lanes_below(bc)] = r * 8 + f;
     wave_lds_order();
     // the clipped faces, four per wavefront
     for (int q0 = 0; q0 < ncl; q0 += 4) {
@@ -571,8 +618,9 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
         uint32_t rgb = 0u;
         if (lv) {
             const int code = cq[q];
-            build_face(s, sc, cam, code >> 3, code & 7, Q);
-            rgb = face_rgb<AP>(s, sc, code >> 3, code & 7);
+            const BoxRec b = lds_load(L.recs + (code >> 3));
+            rec_face(cam, b, code & 7, Q);
+            rgb = rec_rgb<AP>(s, sc, b, code & 7);
         }
         TriRec t;
         const bool ok = clip_seg<true>(cam, Q, lv, 0, cam.H, t);
@@ -608,26 +656,64 @@ __device__ __forceinline__ void do_lights(const DevSim &s, const SceneRec &sc, c
     if (light_pass(s, sc, cam, L, 64 * k, true, nbt, bmin, bmax)) box_rows(L, bmin, bmax);
 }
 
-// Box unit k: cull boxes [unit k, unit (k + 1)) of the scene (unit <= 64), list
-// the survivors, set up their faces into the view's box list
-// (shared by the wavefronts; its row range kept with LDS min / max).  scr:
-// 128 ints of the wavefront's staging (survivors, then the clip queue).
-template <bool AP>
-__device__ __forceinline__ void do_boxes(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                                         int k, int unit, lptr<int32_t> scr)
+// Road culling bins [b0, min(b0 + 64, n_bins)) (frustum, road depth limit and
+// row-gap test) and boxes [b0, min(b0 + 64, nbox)) of the scene against the
+// view: the survivors join the view's bin list and box records (R_NSB and R_NSV
+// count them all, also those that the lists cannot hold).  The loads of both
+// are under way together.
+__device__ __forceinline__ void cull_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L, int b0,
+                                          int n_bins, int nbox)
 {
-    const int ln = (int)lane_id();
-    const int nbox = sc.n_agents + sc.n_static;
-    const int j = unit * k + ln;
-    const bool keep = ln < unit && j < nbox && j != ego && !box_outside(s, sc, cam, j);
-    const unsigned long long bm = __ballot(keep);
-    if (keep) scr[lanes_below(bm)] = j;
-    const int ns = __popcll(bm);
-    wave_lds_order();
+    const int b = b0 + (int)lane_id();
+    const bool bin = b < n_bins, box = b < nbox && b != ego;
+    RoadBin bn = {};
+    float4 st = make_float4(0.0f, 0.0f, 0.0f, 0.0f), dm = st;
+    float2 cs = make_float2(0.0f, 0.0f);
+    if (bin) bn = s.bins[sc.bin_base + b];
+    if (box) {
+        const int ga = box_slot(sc, b);
+        st = s.state[ga];
+        dm = s.dims[ga];
+        cs = s.cs[ga];
+    }
+    bool kbin = false, kbox = false;
+    if (b0 < n_bins) {
+        float x[4], z[4];
+        ground_xz(cam, bn.xmin, bn.ymin, x[0], z[0]);
+        ground_xz(cam, bn.xmax, bn.ymin, x[1], z[1]);
+        ground_xz(cam, bn.xmax, bn.ymax, x[2], z[2]);
+        ground_xz(cam, bn.xmin, bn.ymax, x[3], z[3]);
+        kbin = bin & !road_culled<true>(cam, x, z, 0, cam.H);
+    }
+    if (b0 < nbox) kbox = box & !box_outside_at(cam, st, dm);
+    // the counters of both lists are advanced together
+    const unsigned long long mbin = __ballot(kbin), mbox = __ballot(kbox);
+    int abin = 0, abox = 0;
+    if (lane_id() == 0) {
+        if (mbin != 0ull) abin = lds_add(L.cnt + R_NSB, __popcll(mbin));
+        if (mbox != 0ull) abox = lds_add(L.cnt + R_NSV, __popcll(mbox));
+    }
+    abin = __builtin_amdgcn_readlane(abin, 0) + lanes_below(mbin);
+    abox = __builtin_amdgcn_readlane(abox, 0) + lanes_below(mbox);
+    if (kbin && abin < L.bins) L.sbins[abin] = bn.start * 128 + bn.count;
+    if (kbox && abox < L.nrec) lds_store(L.recs + abox, BoxRec{st.x, st.y, cs.x, cs.y, dm.x, dm.y, dm.z, b});
+}
+
+// records a box unit sets up: ten fill a pass's lanes with their six faces;
+// workgroups of many wavefronts take smaller units, so that clipped faces are
+// spread over them
+__device__ __forceinline__ int box_unit(int K) { return K >= 8 ? 4 : 10; }
+
+// Box unit k: the faces of records [unit k, unit (k + 1)) into the view's box
+// list (shared by the wavefronts; its row range kept with LDS min / max).
+// scr: 64 ints of the wavefront's staging (the clip queue).
+template <bool AP>
+__device__ __forceinline__ void do_boxes(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int k, int unit,
+                                         int n_recs, lptr<int32_t> scr)
+{
     int nbt = 0, bmin = 0x7FFFFFFF, bmax = -1;
-    for (int c0 = 0; c0 < 6 * ns; c0 += 64)
-        if (!box_pass<AP>(s, sc, cam, ego, L, scr, true, 6 * ns, c0, 64, scr + 64, true, nbt, bmin, bmax)) break;
-    box_rows(L, bmin, bmax);
+    if (box_pass<AP>(s, sc, cam, L, unit * k, min(unit, n_recs - unit * k), scr, true, nbt, bmin, bmax))
+        box_rows(L, bmin, bmax);
 }
 
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -1105,26 +1191,56 @@ __device__ __forceinline__ void resolve_full(const DevSim &s, lptr<const uint32_
 }
 
 // The fragments of every box and light in rows [b0, b1) folded into the key
-// band by one wavefront through its own use of the list: the faces six
-// candidates at a time (at most 60 entries per pass), the boxes culled again.
+// band, for views with more boxes than the records or entries than the list
+// hold: as many boxes at a time are culled as there are records, the first wavefront
+// lists the faces of as many as fit, every wavefront folds them (ends with a
+// barrier).
 template <bool AP>
 __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
-                                               lptr<unsigned long long> keys, int b0, int b1)
+                                               lptr<unsigned long long> keys, int b0, int b1, int wv, int K)
 {
-    const int ncand = 6 * (sc.n_agents + sc.n_static);
-    for (int c0 = 0; c0 < ncand; c0 += 6) {
-        int n = 0, bmn = 0, bmx = 0;
-        (void)box_pass<AP>(s, sc, cam, ego, L, (lptr<const int32_t>)L.cq, false, ncand, c0, 6, L.cq, false, n, bmn, bmx);
-        wave_lds_order();
-        box_band<AP>(L, cam, keys, n, b0, b1, 0, 1);
-        wave_lds_order();
+    const int nbox = sc.n_agents + sc.n_static;
+    for (int j0 = 0; j0 < nbox; j0 += L.nrec) {
+        if (threadIdx.x == 0) L.cnt[R_NSV] = L.cnt[R_AT] = 0;
+        __syncthreads();
+        if (wv == 0) cull_pass(s, sc, cam, ego, L, j0, 0, min(j0 + L.nrec, nbox));
+        __syncthreads();
+        const int ns = L.cnt[R_NSV];
+        for (int q = 0; q < ns;) {
+            if (wv == 0) {
+                int n = 0, bmn = 0, bmx = 0, step = 10;
+                while (q < ns) {
+                    int m = n;
+                    wave_lds_order();
+                    if (box_pass<AP>(s, sc, cam, L, q, min(step, ns - q), L.cq, false, m, bmn, bmx)) {
+                        n = m;
+                        q += min(step, ns - q);
+                    } else if (n > 0 || step == 1) {
+                        break;
+                    } else {
+                        step = 1;      // clipped faces: one record always fits an empty list
+                    }
+                }
+                if (lane_id() == 0) {
+                    L.cnt[R_NBT] = n;
+                    L.cnt[R_AT] = q;
+                }
+            }
+            __syncthreads();
+            q = L.cnt[R_AT];
+            box_band<AP>(L, cam, keys, L.cnt[R_NBT], b0, b1, wv, K);
+            __syncthreads();
+        }
     }
     for (int g0 = 0; AP && g0 < sc.n_signals; g0 += 64) {
-        int n = 0, bmn = 0, bmx = 0;
-        (void)light_pass(s, sc, cam, L, g0, false, n, bmn, bmx);
-        wave_lds_order();
-        box_band<AP>(L, cam, keys, n, b0, b1, 0, 1);
-        wave_lds_order();
+        if (wv == 0) {
+            int n = 0, bmn = 0, bmx = 0;
+            (void)light_pass(s, sc, cam, L, g0, false, n, bmn, bmx);
+            if (lane_id() == 0) L.cnt[R_NBT] = n;
+        }
+        __syncthreads();
+        box_band<AP>(L, cam, keys, L.cnt[R_NBT], b0, b1, wv, K);
+        __syncthreads();
     }
 }
 
@@ -1153,7 +1269,7 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
         __syncthreads();
         for (int p = (int)threadIdx.x; p < (b1 - b0) * W; p += (int)blockDim.x) keys[p] = 0ull;
         __syncthreads();
-        if (wv == 0) stream_entries<AP>(s, sc, cam, ego, L, keys, b0, b1);
+        stream_entries<AP>(s, sc, cam, ego, L, keys, b0, b1, wv, (int)blockDim.x >> 6);
         __syncthreads();
         resolve_band(
             L, W, [&](int j) { return fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C); },
@@ -1176,42 +1292,6 @@ __device__ __forceinline__ void view_priority(int p)
     else if (p == 2) __builtin_amdgcn_s_setprio(2);
     else if (p == 1) __builtin_amdgcn_s_setprio(1);
     else __builtin_amdgcn_s_setprio(0);
-}
-
-// the lanes' surviving bins appended to the view's list
-__device__ __forceinline__ void list_bins(const RgbLds &L, bool keep, int rec)
-{
-    const unsigned long long bm = __ballot(keep);
-    const int nk = __popcll(bm);
-    int base = 0;
-    if (nk > 0) {
-        const int leader = __ffsll((long long)bm) - 1;
-        if ((int)lane_id() == leader) base = lds_add(L.cnt + R_NSB, nk);
-        base = __shfl(base, leader);
-    }
-    if (keep) L.sbins[base + lanes_below(bm)] = rec;
-}
-
-// The scene's road culling bins [b0, b0 + 64) against the view (frustum, road
-// depth limit and row-gap test); the survivors are appended to the view's
-// list of surviving bins.
-__device__ __forceinline__ void cull_bins(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int b0)
-{
-    const int ln = (int)lane_id();
-    const int b = b0 + ln;
-    bool keep = false;
-    int rec = 0;
-    if (b < sc.n_bins) {
-        const RoadBin bn = s.bins[sc.bin_base + b];
-        float x[4], z[4];
-        ground_xz(cam, bn.xmin, bn.ymin, x[0], z[0]);
-        ground_xz(cam, bn.xmax, bn.ymin, x[1], z[1]);
-        ground_xz(cam, bn.xmax, bn.ymax, x[2], z[2]);
-        ground_xz(cam, bn.xmin, bn.ymax, x[3], z[3]);
-        keep = !road_culled<true>(cam, x, z, 0, cam.H);
-        rec = bn.start * 128 + bn.count;
-    }
-    list_bins(L, keep, rec);
 }
 
 }  // namespace

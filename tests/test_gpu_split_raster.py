@@ -163,3 +163,37 @@ def test_light_and_traffic_lights(counts, lit):
     for k in range(3):
         assert torch.equal(out[k], alone[k]), (counts, lit, "batch", k)
     assert n == sims[0].n_agents
+
+
+@pytest.mark.parametrize("n_roads", [4090, 4112, 9000])
+@pytest.mark.parametrize("waves", [1, 4])
+def test_more_culling_bins_than_the_list_holds(n_roads, waves):
+    """Views that keep about as many culling bins as their list holds (256) and
+    more: the bins are then taken in segments."""
+    print(f"bins: {n_roads} strips, {waves} wavefronts", flush=True)
+    scenes = [_crowd(41, 6, n_roads=n_roads, radius=20.0), _crowd(42, 2, n_roads=30)]
+    cam = g.camera_for(64, cams=g.FRONT_AND_SIDES)
+    pal = g.mixed_palette()
+    from paper_2606_19641_amd import gp
+    sim = gp.Sim(scenes, cam, pal)
+    sim.set_launch(raster=1, view_waves=waves)
+    _check(sim, scenes, cam, pal, [(0, a, k) for a in (0, 5) for k in range(3)], (n_roads, waves))
+
+
+@pytest.mark.parametrize("z_near", [0.01, 0.2])
+def test_spans_beyond_the_fp64_range(z_near):
+    """Strips and boxes that reach 2^25 subpixels and more (long ones cut by a
+    close near plane, a long focal length): their spans are counted in int64."""
+    print(f"int64 spans: near {z_near}", flush=True)
+    rng = np.random.default_rng(5)
+    s = _crowd(43, 7, n_roads=160, radius=6.0)
+    a = rng.uniform(0, 2 * np.pi, 160)
+    c = rng.uniform(-4, 4, (160, 2))
+    u, v = np.stack([np.cos(a), np.sin(a)], 1) * 150.0, np.stack([-np.sin(a), np.cos(a)], 1) * rng.uniform(0.05, 3, (160, 1))
+    s.road_xy[:] = np.stack([c - u - v, c + u - v, c + u + v, c - u + v], 1).astype(np.float32)
+    s.agent_dims[:, 0] = 12.0
+    cam = g.Camera(width=96, height=70, focal_px=900.0, z_near=z_near, cam_dirs=g.FRONT_AND_SIDES)
+    pal = g.mixed_palette()
+    from paper_2606_19641_amd import gp
+    sim = gp.Sim([s], cam, pal)
+    _check(sim, [s], cam, pal, [(0, a, k) for a in range(7) for k in range(3)], z_near)
