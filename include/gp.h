@@ -204,7 +204,9 @@ gp_status gp_sim_render_raycast(gp_sim *sim, uint8_t *d_rgb, float *d_depth, int
  * images are bit-identical to gp_sim_render's. */
 gp_status gp_sim_render_noalloc(gp_sim *sim, uint8_t *d_rgb, void *stream);
 
-/* Step then render (rgb only) as one hipGraph replay.  The graph is built on
+/* Step then render (rgb only).  Where the launch setting and the sim take the
+ * wave-split raster this is one kernel launch: the raster steps the agents
+ * itself.  Else it is one hipGraph replay.  The graph is built on
  * first use and rebuilt when the image pointer or the launch settings change;
  * a new d_actions pointer only updates the step node's arguments, so callers
  * may pass each step's own action buffer without a copy.  Uses the persistent

@@ -17,6 +17,9 @@ constexpr int kQueues = 8;               // work-queue segments, one per XCD of 
 // MI355X), on distinct lines they proceed in parallel.
 constexpr int kCtrStride = 64;
 
+// Spacing of the scenes' view counters, a cache line each, for the same reason.
+constexpr int kDoneStride = 32;
+
 // Per-scene record.
 struct SceneRec {
     int32_t agent_base, n_agents;   // agents [agent_base, agent_base + n_agents)
@@ -76,6 +79,10 @@ struct DevSim {
     const uint32_t *box_rgb;  // [A + S] palette colour of each box (byte 0 red)
     uint32_t road_rgb, bg_rgb;    // colours of road_color0 and of the background
     float road_zmax;          // no pixel sample sees the road plane beyond this depth
+    // a render that steps the agents first (the rgb raster only; else act is null)
+    const float2 *act;        // [A] actions (accel, steer)
+    uint32_t *scene_done;     // [n_scenes * kDoneStride] views of each scene that have read its agents' states
+                              // in this launch (zero between launches)
     uint8_t *halted;          // [A] 1 once the agent committed an infraction (frozen in place)
     uint8_t *infr;            // [A] infractions found by the last check (bit 0 collision, 1 off-road)
     float4 *actu;             // [A] jerk actuators: a_lon, a_lat, steering angle, 0

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();
     const int nbox = sc.n_agents + sc.n_static;
-    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
+    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass<false>(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
     __syncthreads();
     const int nsb = L.cnt[R_NSB], nsv = L.cnt[R_NSV];
     const int ubox = box_unit(K);
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
                 });
         const bool ovf = L.cnt[R_BOVF] != 0 || nsv > L.nrec;
         if (!ovf) box_band<true>(L, cam, L.work, L.cnt[R_NBT], b0, b1, wv, K);
-        else stream_entries<true>(s, sc, cam, ego, L, L.work, b0, b1, wv, K);
+        else stream_entries<true, false>(s, sc, cam, ego, L, L.work, b0, b1, wv, K);
         __syncthreads();
         resolve_full(
             s, (lptr<const uint32_t>)pal,

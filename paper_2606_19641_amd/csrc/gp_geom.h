@@ -11,6 +11,91 @@
 
 namespace gp {
 
+// ------------------------------------------------------------ agent step
+
+#define GP_PIO2_HI 1.57079637e+00f
+#define GP_PIO2_LO -4.37113883e-08f
+#define GP_2_OVER_PI 0.636619747f
+#define GP_PI 3.14159274f
+#define GP_2PI 6.28318548f
+
+__device__ __forceinline__ void dev_sincos(float t, float &s, float &c)
+{
+    // Cody-Waite reduction by pi/2 (two binary32 parts), Taylor polynomials
+    // of sin (to r^9) and cos (to r^10) on the reduced argument, quadrant swap.
+    const float k = rintf(t * GP_2_OVER_PI);
+    float r = fmaf(-k, GP_PIO2_HI, t);
+    r = fmaf(-k, GP_PIO2_LO, r);
+    const float r2 = r * r;
+    float p = fmaf(r2, 2.75573188e-06f, -1.98412701e-04f);
+    p = fmaf(r2, p, 8.33333377e-03f);
+    p = fmaf(r2, p, -1.66666672e-01f);
+    const float sr = fmaf(r * r2, p, r);
+    float q = fmaf(r2, -2.75573200e-07f, 2.48015876e-05f);
+    q = fmaf(r2, q, -1.38888892e-03f);
+    q = fmaf(r2, q, 4.16666679e-02f);
+    q = fmaf(r2, q, -0.5f);
+    const float cr = fmaf(r2, q, 1.0f);
+    const int quad = ((int)k) & 3;
+    s = (quad == 0) ? sr : (quad == 1) ? cr : (quad == 2) ? -sr : -cr;
+    c = (quad == 0) ? cr : (quad == 1) ? -sr : (quad == 2) ? -cr : sr;
+}
+
+// One bicycle update of an agent of length L in state st: its next state n and
+// heading cosines cs (App. A: wheelbase 60% of the length; acceleration, speed
+// and steering clipped); returns the curvature.
+__device__ __forceinline__ float bicycle(float dt, float4 st, float L, float accel, float steer, float4 &n, float2 &cs)
+{
+    const float a = fminf(fmaxf(accel, -6.0f), 3.0f);
+    const float delta = fminf(fmaxf(steer, -0.5f), 0.5f);
+    const float v1 = fminf(fmaxf(fmaf(a, dt, st.w), 0.0f), 30.0f);
+    float sd, cd;
+    dev_sincos(delta, sd, cd);
+    const float kappa = sd / (cd * (0.6f * L));      // wheelbase = 60% of the length
+    const float vdt = v1 * dt;
+    float psi = fmaf(vdt, kappa, st.z);
+    if (psi > GP_PI)
+        psi = psi - GP_2PI;
+    else if (psi <= -GP_PI)
+        psi = psi + GP_2PI;
+    float sp, cp;
+    dev_sincos(psi, sp, cp);
+    n = make_float4(fmaf(vdt, cp, st.x), fmaf(vdt, sp, st.y), psi, v1);
+    cs = make_float2(cp, sp);
+    return kappa;
+}
+
+__device__ __forceinline__ void step_agent(const DevSim &s, const float2 *act, int i)
+{
+    if (s.halted[i]) return;                      // halted in place (App. A): state unchanged
+    const float2 u = act[i];
+    float4 n;
+    float2 cs;
+    (void)bicycle(s.dt, s.state[i], s.dims[i].x, u.x, u.y, n, cs);
+    s.state[i] = n;
+    s.cs[i] = cs;
+}
+
+// State and heading cosines of box slot i, whose size is dm, as the render sees
+// them: after the step where the render steps the agents itself (as step_agent
+// does; obstacles lie behind the agents).
+__device__ __forceinline__ void box_pose(const DevSim &s, int i, const float4 &dm, float4 &st, float2 &cs)
+{
+    st = s.state[i];
+    cs = s.cs[i];
+    if (s.act && i < s.n_agents) {
+        const float2 u = s.act[i];
+        const uint8_t halted = s.halted[i];
+        float4 n;
+        float2 c;
+        (void)bicycle(s.dt, st, dm.x, u.x, u.y, n, c);
+        if (!halted) {
+            st = n;
+            cs = c;
+        }
+    }
+}
+
 // ------------------------------------------------------------ geometry
 
 struct V3 { float x, y, z; };
@@ -67,12 +152,20 @@ __device__ __forceinline__ Plane face_plane(const Cam &c, const V3 &n, float d)
     return pl;
 }
 
+// STEP: the kernel may step the agents itself (box_pose)
+template <bool STEP = false>
 __device__ __forceinline__ Cam make_cam(const DevSim &s, const SceneRec &sc, int ego, int k)
 {
     Cam c;
     const int ga = sc.agent_base + ego;
-    const float4 st = s.state[ga];
-    const float2 cs = s.cs[ga];
+    float4 st;
+    float2 cs;
+    if (STEP) {
+        box_pose(s, ga, s.dims[ga], st, cs);
+    } else {
+        st = s.state[ga];
+        cs = s.cs[ga];
+    }
     const float ce = cs.x, se = cs.y;
     const float ck = s.cam_dir[k][0], sk = s.cam_dir[k][1];
     c.px = st.x;

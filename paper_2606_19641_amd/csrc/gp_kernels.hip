@@ -44,66 +44,7 @@
 
 namespace gp {
 
-// ------------------------------------------------------------ constants
-#define GP_PIO2_HI 1.57079637e+00f
-#define GP_PIO2_LO -4.37113883e-08f
-#define GP_2_OVER_PI 0.636619747f
-#define GP_PI 3.14159274f
-#define GP_2PI 6.28318548f
-
-__device__ __forceinline__ void dev_sincos(float t, float &s, float &c)
-{
-    // Cody-Waite reduction by pi/2 (two binary32 parts), Taylor polynomials
-    // of sin (to r^9) and cos (to r^10) on the reduced argument, quadrant swap.
-    const float k = rintf(t * GP_2_OVER_PI);
-    float r = fmaf(-k, GP_PIO2_HI, t);
-    r = fmaf(-k, GP_PIO2_LO, r);
-    const float r2 = r * r;
-    float p = fmaf(r2, 2.75573188e-06f, -1.98412701e-04f);
-    p = fmaf(r2, p, 8.33333377e-03f);
-    p = fmaf(r2, p, -1.66666672e-01f);
-    const float sr = fmaf(r * r2, p, r);
-    float q = fmaf(r2, -2.75573200e-07f, 2.48015876e-05f);
-    q = fmaf(r2, q, -1.38888892e-03f);
-    q = fmaf(r2, q, 4.16666679e-02f);
-    q = fmaf(r2, q, -0.5f);
-    const float cr = fmaf(r2, q, 1.0f);
-    const int quad = ((int)k) & 3;
-    s = (quad == 0) ? sr : (quad == 1) ? cr : (quad == 2) ? -sr : -cr;
-    c = (quad == 0) ? cr : (quad == 1) ? -sr : (quad == 2) ? -cr : sr;
-}
-
 // ------------------------------------------------------------ agent step
-
-// One bicycle update of agent i from state st (App. A: wheelbase 60% of the
-// length; acceleration, speed and steering clipped); returns the curvature.
-__device__ __forceinline__ float bicycle(const DevSim &s, int i, float4 st, float L, float accel, float steer)
-{
-    const float a = fminf(fmaxf(accel, -6.0f), 3.0f);
-    const float delta = fminf(fmaxf(steer, -0.5f), 0.5f);
-    const float v1 = fminf(fmaxf(fmaf(a, s.dt, st.w), 0.0f), 30.0f);
-    float sd, cd;
-    dev_sincos(delta, sd, cd);
-    const float kappa = sd / (cd * (0.6f * L));      // wheelbase = 60% of the length
-    const float vdt = v1 * s.dt;
-    float psi = fmaf(vdt, kappa, st.z);
-    if (psi > GP_PI)
-        psi = psi - GP_2PI;
-    else if (psi <= -GP_PI)
-        psi = psi + GP_2PI;
-    float sp, cp;
-    dev_sincos(psi, sp, cp);
-    s.state[i] = make_float4(fmaf(vdt, cp, st.x), fmaf(vdt, sp, st.y), psi, v1);
-    s.cs[i] = make_float2(cp, sp);
-    return kappa;
-}
-
-__device__ __forceinline__ void step_agent(const DevSim &s, const float2 *act, int i)
-{
-    if (s.halted[i]) return;                      // halted in place (App. A): state unchanged
-    const float2 u = act[i];
-    (void)bicycle(s, i, s.state[i], s.dims[i].x, u.x, u.y);
-}
 
 __global__ void k_step(DevSim s, const float2 *__restrict__ act, int begin, int count)
 {
@@ -118,7 +59,7 @@ __global__ void k_step_multi(const SimEntry *__restrict__ tab)
     const SimEntry &e = tab[blockIdx.y];
     const DevSim s = e.s;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= s.n_agents) return;
+    if (s.act || i >= s.n_agents) return;         // (its render steps a sim with act)
     step_agent(s, e.act, i);
 }
 
@@ -177,7 +118,11 @@ __global__ void k_step_jerk(DevSim s, const uint8_t *__restrict__ act)
     const float tau = fminf(fmaxf((a_lat * l) / fmaxf(v1 * v1, 1.0f), -tan_max), tan_max);
     float d1 = fminf(fmaxf(atan_small(tau), fmaf(-0.6f, s.dt, ac.z)), fmaf(0.6f, s.dt, ac.z));
     d1 = fminf(fmaxf(d1, -0.5f), 0.5f);
-    const float kappa = bicycle(s, i, st, L, a_lon, d1);
+    float4 n;
+    float2 cs;
+    const float kappa = bicycle(s.dt, st, L, a_lon, d1, n, cs);
+    s.state[i] = n;
+    s.cs[i] = cs;
     s.actu[i] = make_float4(v1 == v_free ? a_lon : 0.0f, (v1 * v1) * kappa, d1, 0.0f);
 }
 

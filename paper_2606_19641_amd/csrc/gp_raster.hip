@@ -54,6 +54,31 @@ namespace gp {
 
 namespace {
 
+// A render that steps the agents first (s.act): every view computes the states
+// after the step of the boxes it culls by itself, and the state arrays are
+// advanced in place by the last view of a scene to have read them: views count
+// themselves in once their reads are done (the barrier before has every
+// wavefront past them), and the one that completes the count steps the scene's
+// agents and clears it.  A step kernel of its own before the render costs 5 us
+// of start and drain: step + render of 2,048 views at 128 x 128 60.0 us, here
+// 52.3 us.
+__device__ __forceinline__ int view_arrives(const DevSim &s, int scene)
+{
+    int n = 0;
+    if (s.act && threadIdx.x == 0)
+        n = (int)__hip_atomic_fetch_add(s.scene_done + (size_t)scene * kDoneStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return n;
+}
+
+// by the first wavefront: arrived is lane 0's view_arrives
+__device__ __forceinline__ void step_scene(const DevSim &s, const SceneRec &sc, int scene, int arrived)
+{
+    if (!s.act || threadIdx.x >= 64) return;
+    if (__builtin_amdgcn_readlane(arrived, 0) != sc.n_agents * s.n_cams - 1) return;
+    for (int a = (int)lane_id(); a < sc.n_agents; a += 64) step_agent(s, s.act, sc.agent_base + a);
+    if (threadIdx.x == 0) __hip_atomic_store(s.scene_done + (size_t)scene * kDoneStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // AP: the sim has a light or traffic lights (instances of their own, so that
 // they add nothing to the plain ones).  Lit streets used to take the general
 // kernel, which folds every road strip's keys with 64-bit LDS atomics and
@@ -69,7 +94,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
     const SceneRec sc = uniform_scene(s.scenes[scene]);
     const int ego = ego_cam >> 2;
-    const Cam cam = make_cam(s, sc, ego, one_cam ? 0 : ego_cam & 3);
+    const Cam cam = make_cam<true>(s, sc, ego, one_cam ? 0 : ego_cam & 3);
     const int W = cam.W, H = cam.H;
 
     const int nbits = ((W * (H - L.hr0) + 63) >> 6) + 1;
@@ -80,7 +105,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
 
     // ---- A: road culling bins and boxes
     const int nbox = sc.n_agents + sc.n_static;
-    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
+    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass<true>(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
     __syncthreads();
 
     // ---- B: the road and box units (set-up and clipping of the faces into the
@@ -112,7 +137,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
             if (tid == 0) L.cnt[R_NSB] = L.cnt[R_RING] = L.cnt[R_JOB] = 0;
             __syncthreads();
             const int s1 = min(s0 + L.bins, sc.n_bins);
-            for (int b0 = s0 + 64 * wv; b0 < s1; b0 += B) cull_pass(s, sc, cam, ego, L, b0, s1, 0);
+            for (int b0 = s0 + 64 * wv; b0 < s1; b0 += B) cull_pass<false>(s, sc, cam, ego, L, b0, s1, 0);
             __syncthreads();
         }
         road_work(
@@ -152,6 +177,8 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     const uint32_t bg_rgb = s.bg_rgb;
     const uint32_t road_rgb = AP && s.shade ? shade_rgb(s.road_rgb, shade_level(s, 0.0f, 0.0f, 4)) : s.road_rgb;
     free_region(L, ovf ? L.bcap : nbt, W);
+    // every state this view needs is read, unless its boxes are streamed
+    const int arrived = ovf ? 0 : view_arrives(s, scene);
     const int mrows = max(1, mask_rows_fit(L.region, nbt, W, L.nmw));
     // the pattern table, and the masks of the first chunk of box rows, in
     // chunks of rows whose items fit; the rows without boxes go with the first
@@ -163,6 +190,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     if (masks)
         for (int p = tid; p < L.nmw * G * (c1 - kr0); p += B) L.work[p] = 0ull;
     __syncthreads();
+    if (!ovf) step_scene(s, sc, scene, arrived);
     write_rows(L, img, road_rgb, bg_rgb, W, 0, kr0);
     write_rows(L, img, road_rgb, bg_rgb, W, kr1, H);
     if (masks) {
@@ -178,7 +206,11 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
             __syncthreads();
         }
     }
-    if (ovf) key_band_rows<AP>(s, sc, cam, ego, L, img, road_rgb, bg_rgb, kr0, kr1, wv);
+    if (ovf) {
+        key_band_rows<AP>(s, sc, cam, ego, L, img, road_rgb, bg_rgb, kr0, kr1, wv);
+        __syncthreads();
+        step_scene(s, sc, scene, view_arrives(s, scene));
+    }
 }
 
 __device__ __forceinline__ void carve_rgb(unsigned char *smem, RgbLds &L, int W, int H, const RgbCfg &c)
@@ -247,6 +279,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5
     s.road_zmax = e->s.road_zmax;
     s.signals = e->s.signals;
     s.signal_color = e->s.signal_color;
+    s.act = e->s.act;
+    s.scene_done = e->s.scene_done;
+    s.halted = e->s.halted;
+    s.dt = e->s.dt;
+    s.n_agents = e->s.n_agents;
+    s.n_cams = e->s.n_cams;
     s.focal = e->s.focal;
     s.cam_height = e->s.cam_height;
     s.z_near = e->s.z_near;

@@ -48,7 +48,7 @@ int64_t n_bins_of(int32_t n_roads) { return 2 * ((n_roads + gp::kBinQuads - 1) /
 constexpr float kBinExtent = 32.0f;   // metres
 
 struct Layout {
-    int64_t halted, infr, actu, signals, signal_color;
+    int64_t halted, infr, actu, signals, signal_color, scene_done;
     int64_t scenes, views, state, cs, dims, agent_color, box_rgb, roads, road_index, road_color, bins, palette,
         queue, order, counter;
     int64_t upload_end;   // the sections above are uploaded at creation
@@ -166,6 +166,7 @@ Layout make_layout(const gp_config *cfg, const gp_scene_desc *sc, int32_t n)
     L.actu = take(16 * L.n_agents);
     L.signals = take(16 * L.n_signals);
     L.signal_color = take(L.n_signals);
+    L.scene_done = take(4 * (int64_t)gp::kDoneStride * n);
     L.queue = take(4 * L.n_views);
     L.order = take(4 * L.n_views);
     L.counter = take(4 * (gp::kQueues + 2) * gp::kCtrStride);
@@ -740,6 +741,7 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     D.road_color = base + L.road_color;
     D.bins = reinterpret_cast<const gp::RoadBin *>(base + L.bins);
     D.palette = base + L.palette;
+    D.scene_done = reinterpret_cast<uint32_t *>(base + L.scene_done);
     D.halted = base + L.halted;
     D.infr = base + L.infr;
     D.actu = reinterpret_cast<float4 *>(base + L.actu);
@@ -963,6 +965,16 @@ gp_status gp_sim_step_render_graph(gp_sim *sim, const float *d_actions, uint8_t 
         return fail(GP_EINVAL, "misaligned pointer");
     gp_launch l = sim->launch;
     l.sched = GP_SCHED_PERSISTENT;
+    if (split_ok(sim, l)) {
+        // the split rasteriser steps the agents itself: one direct launch
+        gp::DevSim d = sim->dev;
+        d.act = reinterpret_cast<const float2 *>(d_actions);
+        const gp::RenderOut o{d_rgb, nullptr, nullptr};
+        hipError_t e = gp::launch_render_rgb(d, o, rgb_cfg(sim, l, sim->lay.n_views), 1, 0, (int)sim->lay.n_views,
+                                             static_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return hip_fail(e, "render launch");
+        return GP_OK;
+    }
     if (sim->lay.n_views <= kGraphMinViews) {
         // a few views render in less time than a graph replay costs on the
         // host: the step and the render are launched directly
@@ -1106,6 +1118,7 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
     auto *act = reinterpret_cast<float *>(h + B.actions);
     int64_t a0 = 0, at[B_N];
     std::copy(g0, g0 + B_N, at);
+    bool step_kernel = false;     // some sim's agents are stepped by a kernel of their own
     bool lights = false;          // the general launch takes the instances with traffic lights
     for (int k = 0; k < n_sims; ++k) {
         const gp_sim *sim = sims[k];
@@ -1113,6 +1126,10 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
         e.s = sim->dev;
         e.o = gp::RenderOut{d_rgb[k], nullptr, nullptr};
         e.act = reinterpret_cast<const float2 *>(d + B.actions + 8 * a0);
+        // the split rasteriser steps the agents itself
+        const bool steps = group_of(sim) == B_SPLIT || group_of(sim) == B_APPEAR;
+        if (steps) e.s.act = e.act;
+        step_kernel = step_kernel || !steps;
         std::memcpy(&tab[k], &e, sizeof(e));
         std::memcpy(act + 2 * a0, h_actions[k], 8 * (size_t)sim->lay.n_agents);
         a0 += sim->lay.n_agents;
@@ -1130,8 +1147,10 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
     const auto *dtab = reinterpret_cast<const gp::SimEntry *>(d + B.table);
     const auto *ditems = reinterpret_cast<const int2 *>(d + B.items);
     auto *ctl = reinterpret_cast<uint32_t *>(d + B.ctl);
-    e = gp::launch_step_multi(dtab, n_sims, max_agents, hs);
-    if (e != hipSuccess) return hip_fail(e, "batch step launch");
+    if (step_kernel) {
+        e = gp::launch_step_multi(dtab, n_sims, max_agents, hs);
+        if (e != hipSuccess) return hip_fail(e, "batch step launch");
+    }
     for (int g = B_SPLIT; g <= B_APPEAR; ++g) {
         rc.appear = g == B_APPEAR;
         e = gp::launch_render_rgb_multi(dtab, ditems + g0[g], (int)gn[g], rc, W, H, hs);

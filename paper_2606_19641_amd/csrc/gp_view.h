@@ -503,15 +503,7 @@ __device__ __forceinline__ int box_reserve(const RgbLds &L, bool shared, int &nb
     return at;
 }
 
-// the colour of face f of box j, lit where the sim has a light
-template <bool AP>
-__device__ __forceinline__ uint32_t face_rgb(const DevSim &s, const SceneRec &sc, int j, int f)
-{
-    const uint32_t c = s.box_rgb[box_slot(sc, j)];
-    return AP && s.shade ? lit_face(s, sc, c, j, f) : c;
-}
-
-// the same from the box's record
+// the colour of face f of a box, lit where the sim has a light
 template <bool AP>
 __device__ __forceinline__ uint32_t rec_rgb(const DevSim &s, const SceneRec &sc, const BoxRec &b, int f)
 {
@@ -661,6 +653,7 @@ __device__ __forceinline__ void do_lights(const DevSim &s, const SceneRec &sc, c
 // view: the survivors join the view's bin list and box records (R_NSB and R_NSV
 // count them all, also those that the lists cannot hold).  The loads of both
 // are under way together.
+template <bool STEP>
 __device__ __forceinline__ void cull_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L, int b0,
                                           int n_bins, int nbox)
 {
@@ -672,9 +665,13 @@ __device__ __forceinline__ void cull_pass(const DevSim &s, const SceneRec &sc, c
     if (bin) bn = s.bins[sc.bin_base + b];
     if (box) {
         const int ga = box_slot(sc, b);
-        st = s.state[ga];
         dm = s.dims[ga];
-        cs = s.cs[ga];
+        if (STEP) {
+            box_pose(s, ga, dm, st, cs);
+        } else {
+            st = s.state[ga];
+            cs = s.cs[ga];
+        }
     }
     bool kbin = false, kbox = false;
     if (b0 < n_bins) {
@@ -1195,7 +1192,7 @@ __device__ __forceinline__ void resolve_full(const DevSim &s, lptr<const uint32_
 // hold: as many boxes at a time are culled as there are records, the first wavefront
 // lists the faces of as many as fit, every wavefront folds them (ends with a
 // barrier).
-template <bool AP>
+template <bool AP, bool STEP>
 __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
                                                lptr<unsigned long long> keys, int b0, int b1, int wv, int K)
 {
@@ -1203,7 +1200,7 @@ __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &
     for (int j0 = 0; j0 < nbox; j0 += L.nrec) {
         if (threadIdx.x == 0) L.cnt[R_NSV] = L.cnt[R_AT] = 0;
         __syncthreads();
-        if (wv == 0) cull_pass(s, sc, cam, ego, L, j0, 0, min(j0 + L.nrec, nbox));
+        if (wv == 0) cull_pass<STEP>(s, sc, cam, ego, L, j0, 0, min(j0 + L.nrec, nbox));
         __syncthreads();
         const int ns = L.cnt[R_NSV];
         for (int q = 0; q < ns;) {
@@ -1251,7 +1248,15 @@ __device__ __forceinline__ uint32_t streamed_rgb(const DevSim &s, const SceneRec
 {
     const int prim = (kMaxPrims - 1) - (int)((keylo >> 8) & (uint32_t)(kMaxPrims - 1));
     const int nbox = sc.n_agents + sc.n_static;
-    if (!AP || prim < 6 * nbox) return face_rgb<AP>(s, sc, prim / 6, prim % 6);
+    if (!AP || prim < 6 * nbox) {
+        const int slot = box_slot(sc, prim / 6);
+        const uint32_t c = s.box_rgb[slot];
+        if (!AP || !s.shade) return c;
+        float4 st;
+        float2 cs;
+        box_pose(s, slot, s.dims[slot], st, cs);
+        return lit_heading(s, c, cs, prim % 6);
+    }
     return signal_rgb(s, sc, prim - 6 * nbox - sc.n_roads);
 }
 
@@ -1269,7 +1274,7 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
         __syncthreads();
         for (int p = (int)threadIdx.x; p < (b1 - b0) * W; p += (int)blockDim.x) keys[p] = 0ull;
         __syncthreads();
-        stream_entries<AP>(s, sc, cam, ego, L, keys, b0, b1, wv, (int)blockDim.x >> 6);
+        stream_entries<AP, true>(s, sc, cam, ego, L, keys, b0, b1, wv, (int)blockDim.x >> 6);
         __syncthreads();
         resolve_band(
             L, W, [&](int j) { return fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C); },

@@ -197,3 +197,44 @@ def test_spans_beyond_the_fp64_range(z_near):
     from paper_2606_19641_amd import gp
     sim = gp.Sim([s], cam, pal)
     _check(sim, [s], cam, pal, [(0, a, k) for a in range(7) for k in range(3)], z_near)
+
+
+@pytest.mark.parametrize("case", ["one agent", "small scenes", "several cameras", "lists overflow", "lit, lists overflow"])
+def test_render_that_steps_the_agents(case):
+    """step_render_graph and a batch, where the raster steps the agents itself,
+    against a step and a render apart: images and states over several steps,
+    some agents halted, scenes of one to more than 64 agents."""
+    from paper_2606_19641_amd import gp
+    print(f"stepping render: {case}", flush=True)
+    scenes = {"one agent": lambda: [_crowd(1, 1)],
+              "small scenes": lambda: [_crowd(10 + k, 1 + k) for k in range(40)],
+              "several cameras": lambda: [_crowd(2, 63), _crowd(3, 64), _crowd(4, 65, radius=60.0), _crowd(5, 3)],
+              "lists overflow": lambda: [_crowd(6, 200, radius=12.0), _crowd(7, 2)],
+              "lit, lists overflow": lambda: [_street(8, 90, 100, 130), _street(9, 5, 2, 1)]}[case]()
+    cam = g.camera_for(48, cams=g.FRONT_AND_SIDES if case != "one agent" else g.FRONT)
+    pal = g.mixed_palette()
+    pal[6:9] = ((255, 32, 32), (255, 200, 0), (32, 224, 64))
+    a, b, c = (gp.Sim(scenes, cam, pal) for _ in range(3))
+    for s in (a, b, c):
+        s.set_launch(raster=1)
+        if case.startswith("lit"):
+            s.set_light((0.6, -0.48, 0.64, 0.25))
+        if case in ("several cameras", "lists overflow"):
+            s.check_infractions()                    # halts the agents that overlap others
+    nb = gp.batch_required_bytes([c])
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    st = torch.empty(nb, dtype=torch.uint8, pin_memory=True)
+    out, batch = b.new_rgb(), c.new_rgb()
+    n = sum(s.n_agents for s in scenes)
+    for k in range(4):
+        act = g.batch_actions(77, k, scenes)
+        dev = torch.from_numpy(act).cuda()
+        a.step(dev)
+        ref, _, _ = a.render()
+        b.step_render_graph(dev, out)
+        gp.batch_step_render([c], [act], [batch], ws, st)
+        torch.cuda.synchronize()
+        for s, img, how in ((b, out, "step_render_graph"), (c, batch, "batch")):
+            assert torch.equal(img, ref), (case, k, how)
+            assert torch.equal(s.get_state().view(torch.int32), a.get_state().view(torch.int32)), (case, k, how)
+    assert n == a.n_agents
