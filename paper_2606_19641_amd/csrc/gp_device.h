@@ -44,6 +44,24 @@ struct ViewRec {
     int32_t ego_cam;   // ego * 4 + cam
 };
 
+// All that a view's workgroup needs to start, in one cache line's half: read by
+// scalar loads it saves the two dependent loads of view and scene record.
+struct alignas(64) ViewInit {
+    int32_t view, scene, ego, cam;
+    SceneRec sc;
+    int32_t pad;
+};
+static_assert(sizeof(ViewInit) == 64, "ViewInit layout");
+
+// Camera constants of every view of a sim, computed once on the host with the
+// operations written at their fields (binary32, round to nearest).
+struct CamConst {
+    float cx, cy;                             // 0.5 W, 0.5 H
+    float F256, CX256, CY256, G;              // 256 f, 256 cx, 256 cy, 2^28 / F256
+    float t_left, t_right, t_top, t_bottom;   // cx / f, (W - cx) / f, cy / f, (H - cy) / f
+    float road_b;                             // -1 / (f (0 - cam_height)): the road plane's B; its A and C are zeros
+};
+
 // Road culling bin: bounding box of up to kBinQuads consecutive road slots.
 struct RoadBin {
     float xmin, ymin, xmax, ymax;
@@ -55,6 +73,9 @@ struct RoadBin {
 struct DevSim {
     const SceneRec *scenes;
     const ViewRec *views;
+    const ViewInit *vinit;    // [V] by view
+    const ViewInit *vorder;   // [V] in the order of order[]
+    CamConst camk;
     float4 *state;            // [A + S] x, y, psi, v: the A agents, then the S static obstacles (v = 0)
     float2 *cs;               // [A + S] cos psi, sin psi
     const float4 *dims;       // [A + S] L, W, H, 0

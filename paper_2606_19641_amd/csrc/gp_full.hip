@@ -70,18 +70,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     L.hr0 = first_road_row(H);
     lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
 
-    const int view = ordered ? s.order[blockIdx.x] : view_begin + (int)blockIdx.x;
-    const int scene = __builtin_amdgcn_readfirstlane(s.views[view].scene);
-    const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
-    const SceneRec sc = uniform_scene(s.scenes[scene]);
-    const int ego = ego_cam >> 2;
-    const Cam cam = make_cam(s, sc, ego, ego_cam & 3);
+    const ViewInit vi = view_init(ordered ? s.vorder + blockIdx.x : s.vinit + view_begin + (int)blockIdx.x);
+    const int view = vi.view, ego = vi.ego;
+    const SceneRec &sc = vi.sc;
+    const int nbox = sc.n_agents + sc.n_static;
+    CullIn in = cull_load<false>(s, sc, ego, 64 * wv, sc.n_bins, nbox);
+    const Cam cam = make_cam(s, sc, ego, vi.cam);
     for (int p = tid; p < 256; p += B)
         pal[p] = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) | ((uint32_t)s.palette[3 * p + 2] << 16);
     if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();
-    const int nbox = sc.n_agents + sc.n_static;
-    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass<false>(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
+    cull_all<false>(s, sc, cam, ego, L, in, wv, B);
     __syncthreads();
     const int nsb = L.cnt[R_NSB], nsv = L.cnt[R_NSV];
     const int ubox = box_unit(K);

@@ -106,7 +106,7 @@ __device__ __forceinline__ float uniform_f(float x)
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-// per-view camera constants (kCamFloats floats, then the image size)
+// per-view camera constants
 struct Cam {
     float px, py, fx, fy, h;
     float f, cx, cy, F256, CX256, CY256, G, zn, zf;
@@ -115,8 +115,6 @@ struct Cam {
     float road_zmax;                          // farthest road depth a sample row can see
     int W, H;
 };
-constexpr int kCamFloats = 22;
-static_assert(offsetof(Cam, W) == 4 * kCamFloats && sizeof(Cam) == 4 * (kCamFloats + 2), "Cam layout");
 
 __device__ __forceinline__ V3 to_cam(const Cam &c, float dx, float dy, float Z)
 {
@@ -176,31 +174,31 @@ __device__ __forceinline__ Cam make_cam(const DevSim &s, const SceneRec &sc, int
     c.W = s.width;
     c.H = s.height;
     c.f = s.focal;
-    c.cx = 0.5f * (float)s.width;
-    c.cy = 0.5f * (float)s.height;
-    c.F256 = 256.0f * c.f;
-    c.CX256 = 256.0f * c.cx;
-    c.CY256 = 256.0f * c.cy;
-    c.G = 268435456.0f / c.F256;
+    c.cx = s.camk.cx;
+    c.cy = s.camk.cy;
+    c.F256 = s.camk.F256;
+    c.CX256 = s.camk.CX256;
+    c.CY256 = s.camk.CY256;
+    c.G = s.camk.G;
     c.zn = s.z_near;
     c.zf = s.z_far;
-    c.t_right = ((float)s.width - c.cx) / c.f;
-    c.t_left = c.cx / c.f;
-    c.t_top = c.cy / c.f;
-    c.t_bottom = ((float)s.height - c.cy) / c.f;
+    c.t_right = s.camk.t_right;
+    c.t_left = s.camk.t_left;
+    c.t_top = s.camk.t_top;
+    c.t_bottom = s.camk.t_bottom;
     c.road_zmax = s.road_zmax;
-    // every road corner has camera y = -h, so d = n.p0 = -h for every strip
-    const V3 n = dir_to_cam(c, 0.0f, 0.0f, 1.0f);
-    V3 p0;
-    p0.x = 0.0f; p0.y = 0.0f - c.h; p0.z = 0.0f;
-    c.road = face_plane(c, n, plane_d(n, p0));
+    // Every road corner has camera y = -h and the cameras are level: the road
+    // plane's A and C are zeros (of a sign that depends on the heading and
+    // cannot matter: 1/z is only used where it is positive)
+    c.road.A = 0.0f;
+    c.road.B = s.camk.road_b;
+    c.road.C = 0.0f;
     // one view per workgroup: every field is wave-uniform; keep them in
     // scalar registers
-    float *f = &c.px;
-#pragma unroll
-    for (int q = 0; q < kCamFloats; ++q) f[q] = uniform_f(f[q]);
-    c.W = __builtin_amdgcn_readfirstlane(c.W);
-    c.H = __builtin_amdgcn_readfirstlane(c.H);
+    c.px = uniform_f(c.px);
+    c.py = uniform_f(c.py);
+    c.fx = uniform_f(c.fx);
+    c.fy = uniform_f(c.fy);
     return c;
 }
 

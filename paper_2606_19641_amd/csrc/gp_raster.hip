@@ -83,18 +83,18 @@ __device__ __forceinline__ void step_scene(const DevSim &s, const SceneRec &sc, 
 // they add nothing to the plain ones).  Lit streets used to take the general
 // kernel, which folds every road strip's keys with 64-bit LDS atomics and
 // writes single bytes: 2,048 views at 128 x 128 with 16 obstacles and 12 lights
-// a scene 326 us, here 77 us.  one_cam: the sim's record holds the
-// view's camera direction only (a batch's copy of it), as camera 0.
+// a scene 326 us, here 77 us.  cam_index: the view's camera in s.cam_dir (0 in a
+// batch's copy of the sim's record, which holds the view's direction only).
 template <bool AP>
-__device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, RgbLds L, int view, bool one_cam)
+__device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, RgbLds L, const ViewInit &vi, int cam_index)
 {
     const int B = (int)blockDim.x, K = B >> 6;
     const int tid = (int)threadIdx.x, wv = tid >> 6;
-    const int scene = __builtin_amdgcn_readfirstlane(s.views[view].scene);
-    const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
-    const SceneRec sc = uniform_scene(s.scenes[scene]);
-    const int ego = ego_cam >> 2;
-    const Cam cam = make_cam<true>(s, sc, ego, one_cam ? 0 : ego_cam & 3);
+    const int view = vi.view, scene = vi.scene, ego = vi.ego;
+    const SceneRec &sc = vi.sc;
+    const int nbox = sc.n_agents + sc.n_static;
+    CullIn in = cull_load<true>(s, sc, ego, 64 * wv, sc.n_bins, nbox);
+    const Cam cam = make_cam<true>(s, sc, ego, cam_index);
     const int W = cam.W, H = cam.H;
 
     const int nbits = ((W * (H - L.hr0) + 63) >> 6) + 1;
@@ -104,8 +104,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     __syncthreads();
 
     // ---- A: road culling bins and boxes
-    const int nbox = sc.n_agents + sc.n_static;
-    for (int b0 = 64 * wv; b0 < max(sc.n_bins, nbox); b0 += B) cull_pass<true>(s, sc, cam, ego, L, b0, sc.n_bins, nbox);
+    cull_all<true>(s, sc, cam, ego, L, in, wv, B);
     __syncthreads();
 
     // ---- B: the road and box units (set-up and clipping of the faces into the
@@ -137,7 +136,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
             if (tid == 0) L.cnt[R_NSB] = L.cnt[R_RING] = L.cnt[R_JOB] = 0;
             __syncthreads();
             const int s1 = min(s0 + L.bins, sc.n_bins);
-            for (int b0 = s0 + 64 * wv; b0 < s1; b0 += B) cull_pass<false>(s, sc, cam, ego, L, b0, s1, 0);
+            for (int b0 = s0 + 64 * wv; b0 < s1; b0 += B) cull_pass<false>(s, cam, L, cull_load<false>(s, sc, ego, b0, s1, 0), b0, s1, 0);
             __syncthreads();
         }
         road_work(
@@ -241,7 +240,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5
     extern __shared__ __align__(16) unsigned char smem[];
     RgbLds L;
     carve_rgb(smem, L, s.width, s.height, c);
-    render_view_rgb<AP>(s, o.rgb, L, ordered ? s.order[blockIdx.x] : view_begin + (int)blockIdx.x, false);
+    const ViewInit vi = view_init(ordered ? s.vorder + blockIdx.x : s.vinit + view_begin + (int)blockIdx.x);
+    render_view_rgb<AP>(s, o.rgb, L, vi, vi.cam);
 }
 
 // Batched render over several sims (serving): workgroup b renders item b, a
@@ -261,7 +261,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5
     ctab e = (ctab)tab + sim;
     DevSim s;
     s.scenes = e->s.scenes;
-    s.views = e->s.views;
+    s.camk.cx = e->s.camk.cx;
+    s.camk.cy = e->s.camk.cy;
+    s.camk.F256 = e->s.camk.F256;
+    s.camk.CX256 = e->s.camk.CX256;
+    s.camk.CY256 = e->s.camk.CY256;
+    s.camk.G = e->s.camk.G;
+    s.camk.t_left = e->s.camk.t_left;
+    s.camk.t_right = e->s.camk.t_right;
+    s.camk.t_top = e->s.camk.t_top;
+    s.camk.t_bottom = e->s.camk.t_bottom;
+    s.camk.road_b = e->s.camk.road_b;
     s.state = e->s.state;
     s.cs = e->s.cs;
     s.dims = e->s.dims;
@@ -292,12 +302,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5
 #pragma unroll
     for (int k = 0; k < 4; ++k) s.light[k] = e->s.light[k];
     s.shade = e->s.shade;
-    const int cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam) & 3;
-    s.cam_dir[0][0] = e->s.cam_dir[cam][0];
-    s.cam_dir[0][1] = e->s.cam_dir[cam][1];
+    const ViewInit vi = view_init(e->s.vinit + view);
+    s.cam_dir[0][0] = e->s.cam_dir[vi.cam][0];
+    s.cam_dir[0][1] = e->s.cam_dir[vi.cam][1];
     RgbLds L;
     carve_rgb(smem, L, s.width, s.height, c);
-    render_view_rgb<AP>(s, e->o.rgb, L, view, true);
+    render_view_rgb<AP>(s, e->o.rgb, L, vi, 0);
 }
 
 }  // namespace

@@ -760,12 +760,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     L.region = l.region;
     lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
 
-    const int view = s.order[view_begin + (int)blockIdx.x];
-    const int scene = __builtin_amdgcn_readfirstlane(s.views[view].scene);
-    const int ego_cam = __builtin_amdgcn_readfirstlane(s.views[view].ego_cam);
-    const SceneRec sc = uniform_scene(s.scenes[scene]);
-    const int ego = ego_cam >> 2;
-    const Cam cam = make_cam(s, sc, ego, ego_cam & 3);
+    const ViewInit vi = view_init(s.vorder + view_begin + (int)blockIdx.x);
+    const int view = vi.view, ego = vi.ego;
+    const SceneRec &sc = vi.sc;
+    const Cam cam = make_cam(s, sc, ego, vi.cam);
     const float s2 = uniform_f(rc_scale2(cam));
     const float hfs = uniform_f(cam.h * cam.f * s2);
 

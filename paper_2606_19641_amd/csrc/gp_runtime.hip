@@ -49,7 +49,7 @@ constexpr float kBinExtent = 32.0f;   // metres
 
 struct Layout {
     int64_t halted, infr, actu, signals, signal_color, scene_done;
-    int64_t scenes, views, state, cs, dims, agent_color, box_rgb, roads, road_index, road_color, bins, palette,
+    int64_t scenes, views, vinit, vorder, state, cs, dims, agent_color, box_rgb, roads, road_index, road_color, bins, palette,
         queue, order, counter;
     int64_t upload_end;   // the sections above are uploaded at creation
     // the chip-wide rgb raster's buffers (present when chip is true); ctl and
@@ -149,6 +149,8 @@ Layout make_layout(const gp_config *cfg, const gp_scene_desc *sc, int32_t n)
     auto take = [&](int64_t bytes) { int64_t at = o; o = align_up(o + std::max<int64_t>(bytes, 1)); return at; };
     L.scenes = take(sizeof(gp::SceneRec) * (int64_t)n);
     L.views = take(sizeof(gp::ViewRec) * L.n_views);
+    L.vinit = take(sizeof(gp::ViewInit) * L.n_views);
+    L.vorder = take(sizeof(gp::ViewInit) * L.n_views);
     // box arrays: the agents, then the static obstacles
     const int64_t n_box = L.n_agents + L.n_static;
     L.state = take(16 * n_box);
@@ -588,6 +590,8 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     auto at = [&](int64_t off) { return host.data() + off; };
     sim->scenes.resize(n_scenes);
     auto *views = reinterpret_cast<gp::ViewRec *>(at(L.views));
+    auto *vinit = reinterpret_cast<gp::ViewInit *>(at(L.vinit));
+    auto *vorder = reinterpret_cast<gp::ViewInit *>(at(L.vorder));
     auto *state = reinterpret_cast<float *>(at(L.state));
     auto *dims = reinterpret_cast<float *>(at(L.dims));
     auto *acol = at(L.agent_color);
@@ -710,6 +714,11 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
                     if (left(r) > left(q)) q = r;
             ord[b] = queue[next[q]++];
         }
+        for (int64_t v = 0; v < L.n_views; ++v) {
+            const int32_t sv = views[v].scene, ec = views[v].ego_cam;
+            vinit[v] = gp::ViewInit{(int32_t)v, sv, ec >> 2, ec & 3, sim->scenes[sv], 0};
+        }
+        for (int64_t b = 0; b < L.n_views; ++b) vorder[b] = vinit[ord[b]];
     }
 
     // the device (everything above is host work on the host image)
@@ -731,6 +740,8 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     gp::DevSim &D = sim->dev;
     D.scenes = reinterpret_cast<const gp::SceneRec *>(base + L.scenes);
     D.views = reinterpret_cast<const gp::ViewRec *>(base + L.views);
+    D.vinit = reinterpret_cast<const gp::ViewInit *>(base + L.vinit);
+    D.vorder = reinterpret_cast<const gp::ViewInit *>(base + L.vorder);
     D.state = reinterpret_cast<float4 *>(base + L.state);
     D.cs = reinterpret_cast<float2 *>(base + L.cs);
     D.dims = reinterpret_cast<const float4 *>(base + L.dims);
@@ -791,6 +802,21 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     D.z_near = cfg->z_near;
     D.z_far = cfg->z_far;
     D.dt = cfg->dt;
+    {
+        const float W = (float)cfg->width, H = (float)cfg->height, f = cfg->focal_px;
+        gp::CamConst &k = D.camk;
+        k.cx = 0.5f * W;
+        k.cy = 0.5f * H;
+        k.F256 = 256.0f * f;
+        k.CX256 = 256.0f * k.cx;
+        k.CY256 = 256.0f * k.cy;
+        k.G = 268435456.0f / k.F256;
+        k.t_right = (W - k.cx) / f;
+        k.t_left = k.cx / f;
+        k.t_top = k.cy / f;
+        k.t_bottom = (H - k.cy) / f;
+        k.road_b = -1.0f / (f * (0.0f - cfg->cam_height));
+    }
     // Road points project to row v = cy + h f / z.  Rows whose sample is below
     // the horizon and not more than 4 subpixels above the far line can show
     // road; the farthest depth they look at, plus 2% (>= 2.5 subpixels of

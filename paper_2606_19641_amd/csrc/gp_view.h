@@ -648,30 +648,59 @@ __device__ __forceinline__ void do_lights(const DevSim &s, const SceneRec &sc, c
     if (light_pass(s, sc, cam, L, 64 * k, true, nbt, bmin, bmax)) box_rows(L, bmin, bmax);
 }
 
-// Road culling bins [b0, min(b0 + 64, n_bins)) (frustum, road depth limit and
-// row-gap test) and boxes [b0, min(b0 + 64, nbox)) of the scene against the
-// view: the survivors join the view's bin list and box records (R_NSB and R_NSV
-// count them all, also those that the lists cannot hold).  The loads of both
-// are under way together.
+// A lane's bin and box of a culling pass: bin b of the scene's [0, n_bins), box
+// b of [0, nbox) but the ego.  The loads need no camera: the first pass's are
+// under way while the camera is computed.
+struct CullIn {
+    RoadBin bn;
+    float4 st, dm;
+    float2 cs, act;
+    int b;
+    bool bin, box, moved;
+};
+
 template <bool STEP>
-__device__ __forceinline__ void cull_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L, int b0,
-                                          int n_bins, int nbox)
+__device__ __forceinline__ CullIn cull_load(const DevSim &s, const SceneRec &sc, int ego, int b0, int n_bins, int nbox)
 {
-    const int b = b0 + (int)lane_id();
-    const bool bin = b < n_bins, box = b < nbox && b != ego;
-    RoadBin bn = {};
-    float4 st = make_float4(0.0f, 0.0f, 0.0f, 0.0f), dm = st;
-    float2 cs = make_float2(0.0f, 0.0f);
-    if (bin) bn = s.bins[sc.bin_base + b];
-    if (box) {
-        const int ga = box_slot(sc, b);
-        dm = s.dims[ga];
-        if (STEP) {
-            box_pose(s, ga, dm, st, cs);
-        } else {
-            st = s.state[ga];
-            cs = s.cs[ga];
+    CullIn c = {};
+    c.b = b0 + (int)lane_id();
+    c.bin = c.b < n_bins;
+    c.box = c.b < nbox && c.b != ego;
+    if (c.bin) c.bn = s.bins[sc.bin_base + c.b];
+    if (c.box) {
+        const int ga = box_slot(sc, c.b);
+        c.dm = s.dims[ga];
+        c.st = s.state[ga];
+        c.cs = s.cs[ga];
+        if (STEP && s.act && ga < s.n_agents) {
+            c.act = s.act[ga];
+            c.moved = s.halted[ga] == 0;
         }
+    }
+    return c;
+}
+
+// Bins (frustum, road depth limit and row-gap test) and boxes loaded from b0
+// on, against the view: the survivors join the view's bin list and box records
+// (R_NSB and R_NSV count them all, also those that the lists cannot hold).
+template <bool STEP>
+__device__ __forceinline__ void cull_pass(const DevSim &s, const Cam &cam, const RgbLds &L, const CullIn &c, int b0, int n_bins,
+                                          int nbox)
+{
+    const RoadBin &bn = c.bn;
+    const float4 dm = c.dm;
+    float4 st = c.st;
+    float2 cs = c.cs;
+    const bool bin = c.bin, box = c.box;
+    const int b = c.b;
+    if (STEP && s.act && b0 < nbox) {
+        float4 n;
+        float2 t;
+        (void)bicycle(s.dt, st, dm.x, c.act.x, c.act.y, n, t);
+        st.x = c.moved ? n.x : st.x;
+        st.y = c.moved ? n.y : st.y;
+        cs.x = c.moved ? t.x : cs.x;
+        cs.y = c.moved ? t.y : cs.y;
     }
     bool kbin = false, kbox = false;
     if (b0 < n_bins) {
@@ -694,6 +723,19 @@ __device__ __forceinline__ void cull_pass(const DevSim &s, const SceneRec &sc, c
     abox = __builtin_amdgcn_readlane(abox, 0) + lanes_below(mbox);
     if (kbin && abin < L.bins) L.sbins[abin] = bn.start * 128 + bn.count;
     if (kbox && abox < L.nrec) lds_store(L.recs + abox, BoxRec{st.x, st.y, cs.x, cs.y, dm.x, dm.y, dm.z, b});
+}
+
+// The culling of a whole scene, shared by the wavefronts; in holds the loads of
+// this wavefront's first pass.
+template <bool STEP>
+__device__ __forceinline__ void cull_all(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L, CullIn &in,
+                                         int wv, int B)
+{
+    const int nbox = sc.n_agents + sc.n_static, n = max(sc.n_bins, nbox);
+    for (int b0 = 64 * wv; b0 < n; b0 += B) {
+        if (b0 != 64 * wv) in = cull_load<STEP>(s, sc, ego, b0, sc.n_bins, nbox);
+        cull_pass<STEP>(s, cam, L, in, b0, sc.n_bins, nbox);
+    }
 }
 
 // records a box unit sets up: ten fill a pass's lanes with their six faces;
@@ -1200,7 +1242,10 @@ __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &
     for (int j0 = 0; j0 < nbox; j0 += L.nrec) {
         if (threadIdx.x == 0) L.cnt[R_NSV] = L.cnt[R_AT] = 0;
         __syncthreads();
-        if (wv == 0) cull_pass<STEP>(s, sc, cam, ego, L, j0, 0, min(j0 + L.nrec, nbox));
+        if (wv == 0) {
+            const int j1 = min(j0 + L.nrec, nbox);
+            cull_pass<STEP>(s, cam, L, cull_load<STEP>(s, sc, ego, j0, 0, j1), j0, 0, j1);
+        }
         __syncthreads();
         const int ns = L.cnt[R_NSV];
         for (int q = 0; q < ns;) {
@@ -1284,6 +1329,21 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
 }
 
 // ------------------------------------------------------------ per view
+
+// a view's start record by scalar loads (it never changes)
+__device__ __forceinline__ ViewInit view_init(const ViewInit *p)
+{
+    typedef const __attribute__((address_space(4))) int32_t *cint;
+    const cint q = (cint)(const int32_t *)p;
+    ViewInit v;
+    v.view = q[0];
+    v.scene = q[1];
+    v.ego = q[2];
+    v.cam = q[3];
+    v.sc = SceneRec{q[4], q[5], q[6], q[7], q[8], q[9], q[10], q[11], q[12], q[13], q[14]};
+    v.pad = 0;
+    return v;
+}
 
 // Issue priority of the view's wavefronts (0..3) against the other views'
 // on the same SIMDs.  Every view of a launch is resident at once, so the
