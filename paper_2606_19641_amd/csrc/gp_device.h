@@ -151,7 +151,7 @@ struct FullCfg {
     int bcap;         // box faces and lights one view's list holds: 64..256
     int recs;         // boxes one view's records hold: 1..64
     int bins_cap;     // culling bins of the largest scene
-    int band_rows;    // rows of the key band
+    int band_rows;    // rows of the band of road keys
 };
 
 // Settings of the ray caster (gp_raycast.hip).
@@ -159,7 +159,7 @@ struct RcCfg {
     int waves;        // wavefronts per view: 1..16
     int bcap;         // boxes and lights the LDS list holds, a multiple of 64
     int bins_cap;     // culling bins of the largest scene
-    int band_rows;    // rows of the key band (at least)
+    int band_rows;    // rows of the key band (cover: at least), else of the band of road keys
     int cover;        // 1: roads as coverage bits
 };
 

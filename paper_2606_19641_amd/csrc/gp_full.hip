@@ -6,16 +6,20 @@
 //
 // One workgroup per view, its work divided as in the wave-split rgb raster
 // (gp_view.h): bins, strips that pass the cheap test in a ring, set-up jobs, box
-// and light units into the view's list.  Here every fragment counts, so the
-// image goes in bands of rows whose 64-bit keys lie in LDS: per band the strips
-// that reach its rows are set up, their exact spans cut into pieces of 16
-// samples that fold the strip's key (its 1/z is the row's) with LDS atomic max,
-// then the list's entries likewise; a lane resolves four pixels and writes 12
-// bytes of colour, 16 of depth and 16 of ids.
+// and light units into the view's list.  Here it matters which strip a sample
+// shows, but every strip lies in one plane: in a row they all have the same 1/z,
+// and the largest 32-bit key word wins.  So the rows below the horizon go in bands
+// of road key words in LDS: per band the strips that reach its rows are set up,
+// their exact spans cut into pieces of 16 samples that fold the strip's word with
+// LDS atomic max.  Box rows then take the group masks and spans of the rgb raster
+// and fold 64-bit keys in registers, eight samples per lane; in the other rows a
+// lane resolves four pixels from the road words alone.  A lane writes 12 bytes of
+// colour, 16 of depth and 16 of ids per four pixels.
 //
-// Bound by the keys' folding and the three output streams.  One MI355X, 2,048
-// views at 128 x 128 with depth and ids: 180 us (the banded kernel, which sets up
-// every strip of a surviving bin and writes single bytes, 282 us).
+// Bound by the road words' folding and the three output streams.  One MI355X,
+// 2,048 views at 128 x 128 with depth and ids: 137 us (with 64-bit keys of every
+// fragment in bands half as high 171, in the banded kernel, which sets up every
+// strip of a surviving bin and writes single bytes, 282).
 #include "gp_view.h"
 
 namespace gp {
@@ -23,7 +27,7 @@ namespace gp {
 namespace {
 
 struct FullLayout {
-    size_t cnt, faces, recs, cq, pal, sbins, sring, waves, keys, total;
+    size_t cnt, recs, pal, sbins, faces, sring, waves, road, total;
 };
 
 __host__ __device__ inline FullLayout full_layout(int W, const FullCfg &c)
@@ -31,44 +35,108 @@ __host__ __device__ inline FullLayout full_layout(int W, const FullCfg &c)
     FullLayout l;
     size_t o = 0;
     l.cnt = o; o = align16(o + 4 * R_NCNT);
-    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
     l.recs = o; o = align16(o + sizeof(BoxRec) * (size_t)c.recs);
-    l.cq = o; o = align16(o + 4 * (size_t)kBoxClip);
     l.pal = o; o = align16(o + 4 * 256);
     l.sbins = o; o = align16(o + 4 * (size_t)c.bins_cap);
+    l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
+    const size_t least = align16(o + (size_t)resolve_bytes(W));
     l.sring = o; o = align16(o + 4 * (size_t)kSharedRing);
     l.waves = o; o = align16(o + (size_t)kWaveBytes * (size_t)c.waves);
-    l.keys = o; o = align16(o + 8 * (size_t)W * (size_t)c.band_rows);
+    o = o > least ? o : least;
+    l.road = o; o = align16(o + 4 * (size_t)W * (size_t)c.band_rows);
     l.total = o;
     return l;
 }
 
-// One workgroup per view: view view_begin + blockIdx.x (ordered 0), or
-// order[blockIdx.x].
+// Rows [c0, c1) from the road keys and the box faces' group masks and spans, as
+// in the rgb raster's resolve_masks, but eight samples per task: with sixteen
+// the keys and what is written of them do not fit the registers.
+template <class Color>
+__device__ __forceinline__ void resolve_box_rows(const DevSim &s, lptr<const uint32_t> pal, Color color, const RgbLds &L,
+                                                 const Cam &cam, lptr<const uint32_t> road, int band0, const RenderOut &o,
+                                                 int64_t view_px, int c0, int c1)
+{
+    const uint32_t q_road = road_shade(s);
+    const int W = cam.W, R = c1 - c0, G = (W + 15) >> 4, n = 2 * R * G, nmw = L.nmw;
+    lptr<const unsigned long long> M = (lptr<const unsigned long long>)L.work;
+    lptr<const int32_t> S = (lptr<const int32_t>)(M + nmw * G * R);
+    for (int task = (int)threadIdx.x; task < n; task += (int)blockDim.x) {
+        const int r = task / (2 * G), h = task - 2 * r * G, g = h >> 1, i = min(g << 4, W - 16) + 8 * (h & 1), j = c0 + r;
+        const float dv = ((float)j + 0.5f) - cam.cy;
+        // sample offsets ((float)(i + m) + 0.5f) - cx are small exact values: du0 + m
+        const float du0 = ((float)i + 0.5f) - cam.cx;
+        const unsigned long long rz = (unsigned long long)__float_as_uint(fmaf(cam.road.B, dv, cam.road.C)) << 32;
+        unsigned long long best[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const uint32_t w = j >= L.hr0 ? road[(j - band0) * W + i + m] : 0u;
+            best[m] = w != 0u ? rz | w : 0ull;
+        }
+        for (int w = 0; w < nmw; ++w) {
+            unsigned long long mk = M[nmw * (G * r + g) + w];
+            while (mk != 0ull) {
+                const int t = 64 * w + (__ffsll((long long)mk) - 1);
+                mk &= mk - 1ull;
+                const int sp = S[t * R + r];
+                const f4v pk = ((lptr<const f4v>)(L.faces + t))[2];   // A B C keylo
+                const int lo = max((sp & 0xFFFF) - i, 0), hi = min(((sp >> 16) & 0x7FFF) - i, 7);
+                if (lo > hi) continue;
+                const uint32_t in = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
+                const float bdv = fmaf(pk.y, dv, pk.z);
+                const uint32_t keylo = __float_as_uint(pk.w);
+                if (sp < 0) {
+                    // a light: few samples, each with its own sphere test
+#pragma unroll
+                    for (int m = 0; m < 8; ++m) {
+                        if (!((in >> m) & 1u)) continue;
+                        const float invz = light_invz(L, cam, t, du0 + (float)m, -dv);
+                        const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
+                        if (invz > 0.0f && key > best[m]) best[m] = key;
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int m = 0; m < 8; ++m) {
+                    const float invz = fmaf(pk.x, du0 + (float)m, bdv);
+                    const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
+                    const bool take = (((in >> m) & 1u) != 0u) & (invz > 0.0f) & (key > best[m]);
+                    best[m] = take ? key : best[m];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const unsigned long long k4[4] = {best[4 * q], best[4 * q + 1], best[4 * q + 2], best[4 * q + 3]};
+            show4(s, pal, q_road, color, o, k4, view_px + (int64_t)j * W + i + 4 * q, 4);
+        }
+    }
+}
+
+// One workgroup per view: view view_begin + blockIdx.x (ordered 0), or the
+// view of workgroup blockIdx.x.
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_render_full(DevSim s, RenderOut o, FullCfg c,
                                                                                              int ordered, int view_begin)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int B = (int)blockDim.x, K = B >> 6, tid = (int)threadIdx.x, wv = tid >> 6;
+    const int B = (int)blockDim.x, K = B >> 6, tid = (int)threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int W = s.width, H = s.height;
     const FullLayout l = full_layout(W, c);
     RgbLds L = {};
     L.cnt = (lptr<int32_t>)(smem + l.cnt);
-    L.faces = (lptr<FaceRec>)(smem + l.faces);
     L.recs = (lptr<BoxRec>)(smem + l.recs);
-    L.cq = (lptr<int32_t>)(smem + l.cq);
+    L.faces = (lptr<FaceRec>)(smem + l.faces);
     L.sbins = (lptr<int32_t>)(smem + l.sbins);
     L.sring = (lptr<int32_t>)(smem + l.sring);
     L.waves = (lptr<unsigned char>)(smem + l.waves);
-    L.work = (lptr<unsigned long long>)(smem + l.keys);
     L.bcap = c.bcap;
     L.batch = kBatch;
     L.ring = kSharedRing;
     L.bins = c.bins_cap;
     L.nrec = c.recs;
-    L.krows = c.band_rows;
+    L.tail = (int)(l.road - l.faces);
     L.hr0 = first_road_row(H);
-    lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
+    lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal), road = (lptr<uint32_t>)(smem + l.road);
 
     const ViewInit vi = view_init(ordered ? s.vorder + blockIdx.x : s.vinit + view_begin + (int)blockIdx.x);
     const int view = vi.view, ego = vi.ego;
@@ -86,43 +154,82 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int ubox = box_unit(K);
     const int nbu = nsv <= L.nrec ? (nsv + ubox - 1) / ubox : 0, nlu = (sc.n_signals + 63) / 64;
     WaveSt ws = wave_state(L, wv);
-    for (int b0 = 0; b0 < H; b0 += L.krows) {
-        const int b1 = min(b0 + L.krows, H);
-        const int r0 = max(b0, L.hr0), r1 = max(b1, L.hr0);        // rows that can show road
-        if (b0 > 0) __syncthreads();                               // the last band's keys are read
-        for (int p = tid; p < (b1 - b0) * W; p += B) L.work[p] = 0ull;
-        if (b0 > 0 && tid == 0) L.cnt[R_RING] = L.cnt[R_JOB] = 0;
+    const int64_t view_px = (int64_t)view * H * W;
+    int nbt = 0, kr0 = H, kr1 = H;               // listed entries, the rows that they reach
+    bool ovf = false;
+    auto color = [&](uint32_t keylo) -> uint32_t {
+        if (ovf) return streamed_rgb<true>(s, sc, keylo);
+        return ((lptr<const uint32_t>)(L.faces + (keylo & 0xFFu)))[14];
+    };
+    auto rz = [&](int j) { return fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C); };
+    // Bands of the rows below the horizon; the rows above go with the first
+    for (int b0 = L.hr0;; b0 += c.band_rows) {
+        const bool first = b0 == L.hr0;
+        const int b1 = min(b0 + c.band_rows, H);
+        if (!first) __syncthreads();                               // the last band's keys are read
+        for (int p = tid; p < (b1 - b0) * W; p += B) road[p] = 0u;
+        if (!first && tid == 0) L.cnt[R_RING] = L.cnt[R_JOB] = 0;
         __syncthreads();
         // the first band's road work lists the boxes and lights too
-        if (b0 == 0 || r0 < r1)
-            (void)road_work(
-                s, sc, L, r0 < r1 ? nsb : 0, b0 == 0 ? nbu + nlu : 0, false,
-                [&](bool live, const float4 &q0, const float4 &q1) -> bool {
-                    float x[4], z[4];
-                    ground_xz(cam, q0.x, q0.y, x[0], z[0]);
-                    ground_xz(cam, q0.z, q0.w, x[1], z[1]);
-                    ground_xz(cam, q1.x, q1.y, x[2], z[2]);
-                    ground_xz(cam, q1.z, q1.w, x[3], z[3]);
-                    return live && !road_culled<false>(cam, x, z, r0, r1);
-                },
-                [&](int u) {
-                    if (u >= nbu) do_lights(s, sc, cam, L, u - nbu);
-                    else do_boxes<true>(s, sc, cam, L, u, ubox, nsv, (lptr<int32_t>)ws.tris);   // the staging is free here
-                },
-                [&](int a, int n) {
-                    setup_job<true>(s, sc, cam, L, ws, a, n, [&](int t) { road_fold(L, cam, ws, t, r0, r1, b0); });
-                });
-        const bool ovf = L.cnt[R_BOVF] != 0 || nsv > L.nrec;
-        if (!ovf) box_band<true>(L, cam, L.work, L.cnt[R_NBT], b0, b1, wv, K);
-        else stream_entries<true, false>(s, sc, cam, ego, L, L.work, b0, b1, wv, K);
-        __syncthreads();
-        resolve_full(
-            s, (lptr<const uint32_t>)pal,
-            [&](uint32_t keylo) -> uint32_t {
-                if (ovf) return streamed_rgb<true>(s, sc, keylo);
-                return ((lptr<const uint32_t>)(L.faces + (keylo & 0xFFu)))[14];
+        road_work(
+            s, sc, L, b0 < b1 ? nsb : 0, first ? nbu + nlu : 0,
+            [&](bool live, const float4 &q0, const float4 &q1) -> bool {
+                float x[4], z[4];
+                ground_xz(cam, q0.x, q0.y, x[0], z[0]);
+                ground_xz(cam, q0.z, q0.w, x[1], z[1]);
+                ground_xz(cam, q1.x, q1.y, x[2], z[2]);
+                ground_xz(cam, q1.z, q1.w, x[3], z[3]);
+                return live && !road_culled<false>(cam, x, z, b0, b1);
             },
-            (lptr<const unsigned long long>)L.work, o, ((int64_t)view * H + b0) * W, (b1 - b0) * W);
+            [&](int u) {
+                if (u >= nbu) do_lights(s, sc, cam, L, u - nbu);
+                else do_boxes<true>(s, sc, cam, L, u, ubox, nsv, (lptr<int32_t>)ws.tris);   // the staging is free here
+            },
+            [&](int a, int n) {
+                setup_job<true>(s, sc, cam, L, ws, a, n, [&](int t) { road_fold(L, road, cam, ws, t, b0, b1, b0); });
+            });
+        if (first) {
+            nbt = L.cnt[R_NBT];
+            ovf = L.cnt[R_BOVF] != 0 || nsv > L.nrec;
+            if (ovf || (W < 16 && nbt > 0)) {
+                kr0 = 0;
+            } else if (nbt > 0) {
+                kr0 = L.cnt[R_BMIN];
+                kr1 = L.cnt[R_BMAX] + 1;
+            }
+            free_region(L, ovf ? L.bcap : nbt, W);
+        }
+        const int r0 = first ? 0 : b0;
+        const int k0 = min(max(kr0, r0), b1), k1 = min(max(kr1, k0), b1);      // this band's box rows
+        const lptr<const unsigned long long> none = (lptr<const unsigned long long>)nullptr;
+        resolve_rows(s, (lptr<const uint32_t>)pal, rz, color, W, L.hr0, (lptr<const uint32_t>)road, b0, none, o, view_px, r0, k0);
+        resolve_rows(s, (lptr<const uint32_t>)pal, rz, color, W, L.hr0, (lptr<const uint32_t>)road, b0, none, o, view_px, k1, b1);
+        if (ovf || W < 16) {
+            // box keys of a few rows at a time
+            for (int c0 = k0; c0 < k1; c0 += L.krows) {
+                const int c1 = min(c0 + L.krows, k1);
+                __syncthreads();
+                for (int p = tid; p < (c1 - c0) * W; p += B) L.work[p] = 0ull;
+                __syncthreads();
+                if (ovf) stream_entries<true, false>(s, sc, cam, ego, L, L.work, c0, c1, wv, K);
+                else box_band<true>(L, cam, L.work, nbt, c0, c1, wv, K);
+                __syncthreads();
+                resolve_rows(s, (lptr<const uint32_t>)pal, rz, color, W, L.hr0, (lptr<const uint32_t>)road, b0,
+                             (lptr<const unsigned long long>)L.work, o, view_px, c0, c1);
+            }
+        } else {
+            const int mrows = max(1, mask_rows_fit(L.region, nbt, W, L.nmw)), G = (W + 15) >> 4;
+            for (int c0 = k0; c0 < k1; c0 += mrows) {
+                const int c1 = min(c0 + mrows, k1);
+                __syncthreads();
+                for (int p = tid; p < L.nmw * G * (c1 - c0); p += B) L.work[p] = 0ull;
+                __syncthreads();
+                box_spans<true>(L, cam, nbt, c0, c1, wv, K);
+                __syncthreads();
+                resolve_box_rows(s, (lptr<const uint32_t>)pal, color, L, cam, (lptr<const uint32_t>)road, b0, o, view_px, c0, c1);
+            }
+        }
+        if (b1 >= H) break;
     }
 }
 

@@ -140,7 +140,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
             __syncthreads();
         }
         road_work(
-            s, sc, L, over ? L.cnt[R_NSB] : nsb, s0 == 0 ? nbu + nlu : 0, false,
+            s, sc, L, over ? L.cnt[R_NSB] : nsb, s0 == 0 ? nbu + nlu : 0,
             [&](bool live, const float4 &q0, const float4 &q1) -> bool {
                 float x[4], z[4];
                 ground_xz(cam, q0.x, q0.y, x[0], z[0]);

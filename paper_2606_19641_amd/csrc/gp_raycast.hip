@@ -33,15 +33,16 @@
 // One workgroup per view.  Strips are culled by bins and one by one into the
 // view's ring (gp_view.h).  In rgb-only renders of scenes with one road
 // colour (COV) strips leave coverage bits, the rows without boxes are written
-// like the raster's, and keys are kept for box rows only, in bands of LDS; in
-// the others every fragment folds its key into a band of keys (LDS atomic max)
-// and the road work is done again for each band.
+// like the raster's; in the others they leave 32-bit key words in bands of rows
+// (the strips of a row's sample have one depth: the largest word wins), and the
+// road work is done again for each band.  64-bit keys are kept for box rows only,
+// in bands of LDS.
 //
 // Bound by VALU issue.  One MI355X: 2,048 views at 128 x 128 (32 agents, 2,000
 // strips) 116 us (1,100 us with the tests dealt by pixel; 218 us before the
 // certain runs of boxes and strips were taken without the full test), 16 scenes
-// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 475 us
-// (2,400 us).
+// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 426 us
+// (474 us with 64-bit keys of strips too, 2,400 us by pixel).
 #include "gp_view.h"
 
 namespace gp {
@@ -54,16 +55,17 @@ constexpr int kRcNarrow = 12;             // items of fewer columns are tested w
 static_assert(kRcTests <= 16, "a piece's coverage bits fit the 32-bit pair below");
 
 struct RcLayout {
-    size_t cnt, bits, faces, sbins, sring, waves, pal, keys, total;
+    size_t cnt, bits, faces, sbins, sring, waves, pal, keys, road, total;
     int krows, region;
 };
 
-// LDS of one view: without COV the key band has its own memory (the ring is in
-// use beside it); with COV it takes the memory from sbins on, free by then,
-// behind the pattern table
+// LDS of one view: the band of 64-bit keys takes memory that is free by then, with
+// COV that from sbins on behind the pattern table, without it that of the ring and
+// the staging; the band of road keys (without COV) has its own
 __host__ __device__ inline RcLayout rc_layout(int W, int H, const RcCfg &c)
 {
     RcLayout l;
+    l.road = 0;
     size_t o = 0;
     l.cnt = o; o = align16(o + 4 * R_NCNT);
     l.faces = o; o = align16(o + sizeof(FaceRec) * (size_t)c.bcap);
@@ -81,8 +83,12 @@ __host__ __device__ inline RcLayout rc_layout(int W, int H, const RcCfg &c)
         o = o > least ? o : least;
         l.region = (int)(o - l.keys);
     } else {
-        l.keys = o; o = align16(o + band);
-        l.region = (int)band;
+        // box keys in the memory of the ring and the staging, road keys behind them
+        l.keys = l.sring;
+        const size_t least = align16(l.keys + 8 * (size_t)W);
+        o = o > least ? o : least;
+        l.region = (int)(o - l.keys);
+        l.road = o; o = align16(o + band / 2);
     }
     l.krows = l.region / (8 * W) > 0 ? l.region / (8 * W) : 1;
     l.total = o;
@@ -240,14 +246,15 @@ __device__ __forceinline__ void rc_inside(const Cam &c, const RcStrip &t, const 
 }
 
 // One set-up job: the n ring strips from a staged, their (strip, row) items on
-// rows [b0, b1) (of a key band that starts at row band0) dealt to the lanes by
-// a prefix over row counts, the items'
+// rows [b0, b1) dealt to the lanes by a prefix over row counts, the items'
 // columns cut into pieces of up to kRcPiece samples, dealt again, and the exact
-// test run per sample.
+// test run per sample.  Without COV the strips' key words are folded into the
+// band of road keys (from row band0): every strip lies in one plane, so the
+// largest key word of a row's sample names the strip it shows.
 template <bool COV>
 __device__ __forceinline__ void rc_strips(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L,
-                                          lptr<RcStrip> st, float hfs, float s2, int a, int n, int b0, int b1,
-                                          int band0)
+                                          lptr<RcStrip> st, lptr<uint32_t> road, float hfs, float s2, int a, int n, int b0,
+                                          int b1, int band0)
 {
     const int ln = (int)lane_id(), W = cam.W;
     wave_lds_order();
@@ -304,10 +311,9 @@ __device__ __forceinline__ void rc_strips(const DevSim &s, const SceneRec &sc, c
                 const int syl = __shfl(yl, o2), syr = __shfl(yr, o2), sj = __shfl(j, o2), so = __shfl(o, o2);
                 if (pi >= npt) continue;
                 const int i0 = syl + 16 * k, i1 = min(i0 + 15, syr);
-                const unsigned long long key = ((unsigned long long)__float_as_uint(1.0f / rc_row(cam, sj).z) << 32) |
-                                               ((lptr<const uint32_t>)(st + so))[9];
-                lptr<unsigned long long> kp = L.work + (sj - band0) * W;
-                for (int i = i0; i <= i1; ++i) lds_max64(kp + i, key);
+                const uint32_t key = ((lptr<const uint32_t>)(st + so))[9];
+                lptr<uint32_t> kp = road + (sj - band0) * W;
+                for (int i = i0; i <= i1; ++i) lds_max32(kp + i, key);
             }
         }
         const int nl = (yl - xl + kRcTests - 1) / kRcTests;
@@ -357,9 +363,8 @@ __device__ __forceinline__ void rc_strips(const DevSim &s, const SceneRec &sc, c
                 lds_or32(w, (uint32_t)m);
                 if ((uint32_t)(m >> 32)) lds_or32(w + 1, (uint32_t)(m >> 32));
             } else {
-                const unsigned long long key = ((unsigned long long)__float_as_uint(1.0f / row.z) << 32) | t.keylo;
-                lptr<unsigned long long> kp = L.work + (sj - band0) * W + i0;
-                for (; in != 0u; in &= in - 1u) lds_max64(kp + (__ffs((int)in) - 1), key);
+                lptr<uint32_t> kp = road + (sj - band0) * W + i0;
+                for (; in != 0u; in &= in - 1u) lds_max32(kp + (__ffs((int)in) - 1), t.keylo);
             }
         }
     }
@@ -758,7 +763,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     L.nrec = 0;
     L.nmw = 0;
     L.region = l.region;
-    lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal);
+    lptr<uint32_t> pal = (lptr<uint32_t>)(smem + l.pal), road = (lptr<uint32_t>)(smem + l.road);
 
     const ViewInit vi = view_init(s.vorder + view_begin + (int)blockIdx.x);
     const int view = vi.view, ego = vi.ego;
@@ -813,16 +818,16 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (u < nbu) rc_boxes(s, sc, cam, ego, L, s2, ub * u, ub);
         else rc_lights(s, sc, cam, L, 64 * (u - nbu));
     };
-    auto roads = [&](int jobs, bool reuse, int b0, int b1, int band0) -> bool {
-        return road_work(
-            s, sc, L, nsb, jobs, reuse,
+    auto roads = [&](int jobs, int b0, int b1) {
+        road_work(
+            s, sc, L, b0 < b1 ? nsb : 0, jobs,
             [&](bool live, const float4 &q0, const float4 &q1) -> bool {
                 float x[4], z[4], m;
                 int j0, j1;
                 rc_corners(cam, q0, q1, x, z);
-                return live && !rc_outside(cam, hfs, x, z, L.hr0, H, j0, j1, m);
+                return live && !rc_outside(cam, hfs, x, z, b0, b1, j0, j1, m);
             },
-            box_job, [&](int a, int n) { rc_strips<COV>(s, sc, cam, L, st, hfs, s2, a, n, b0, b1, band0); });
+            box_job, [&](int a, int n) { rc_strips<COV>(s, sc, cam, L, st, road, hfs, s2, a, n, b0, b1, b0); });
     };
     // the entries of rows [b0, b1) folded into the (cleared) key band; ends with a barrier
     auto boxes = [&](int b0, int b1) {
@@ -853,7 +858,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         for (int p = tid; p < npix; p += B) L.work[p] = 0ull;
     };
     if (COV) {
-        (void)roads(chunked ? 0 : nbu + nlu, false, L.hr0, H, 0);
+        roads(chunked ? 0 : nbu + nlu, L.hr0, H);
         uint8_t *img = o.rgb + 3 * ((int64_t)view * W * H);
         int kr0 = H, kr1 = H;
         if (chunked) {
@@ -887,25 +892,45 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         }
         return;
     }
-    bool first = true, whole = false;            // whole: the ring holds every strip of the view
-    for (int b0 = 0; b0 < H; b0 += L.krows) {
-        const int b1 = min(b0 + L.krows, H);
-        if (!first) __syncthreads();                 // the last band's keys are read
-        clear((b1 - b0) * W);
-        if (!first && tid == 0) {
-            L.cnt[R_JOB] = 0;
-            if (!whole) L.cnt[R_RING] = 0;
-        }
+    const int64_t view_px = (int64_t)view * H * W;
+    auto rz = [&](int j) {
+        const RcRow r = rc_row(cam, j);
+        return r.ok ? 1.0f / r.z : 0.0f;
+    };
+    auto color = [&](uint32_t keylo) { return rc_color(s, sc, L, chunked, keylo); };
+    const lptr<const uint32_t> cpal = (lptr<const uint32_t>)pal, croad = (lptr<const uint32_t>)road;
+    const lptr<const unsigned long long> none = (lptr<const unsigned long long>)nullptr;
+    int kr0 = H, kr1 = H;                        // rows that boxes and lights reach
+    // bands of the rows below the horizon; the rows above go with the first
+    for (int b0 = L.hr0;; b0 += c.band_rows) {
+        const bool first = b0 == L.hr0;
+        const int b1 = min(b0 + c.band_rows, H);
+        if (!first) __syncthreads();             // the last band's keys are read
+        for (int p = tid; p < (b1 - b0) * W; p += B) road[p] = 0u;
+        if (!first && tid == 0) L.cnt[R_RING] = L.cnt[R_JOB] = 0;
         __syncthreads();
-        // the first band's road work lists the boxes too, whether or not the band shows road
-        if (first || b1 > L.hr0)
-            whole = roads(first && !chunked ? nbu + nlu : 0, whole, max(b0, L.hr0), max(b1, L.hr0), b0) | whole;
-        first = false;
-        boxes(b0, b1);
-        resolve_full(s, (lptr<const uint32_t>)pal,
-                     [&](uint32_t keylo) { return rc_color(s, sc, L, chunked, keylo); },
-                     (lptr<const unsigned long long>)L.work, o,
-                     ((int64_t)view * H + b0) * W, (b1 - b0) * W);
+        roads(first && !chunked ? nbu + nlu : 0, b0, b1);
+        if (first) {
+            if (chunked) {
+                kr0 = 0;
+            } else if (L.cnt[R_NBT] > 0) {
+                kr0 = L.cnt[R_BMIN];
+                kr1 = L.cnt[R_BMAX] + 1;
+            }
+        }
+        const int r0 = first ? 0 : b0;
+        const int k0 = min(max(kr0, r0), b1), k1 = min(max(kr1, k0), b1);      // this band's box rows
+        resolve_rows(s, cpal, rz, color, W, L.hr0, croad, b0, none, o, view_px, r0, k0);
+        resolve_rows(s, cpal, rz, color, W, L.hr0, croad, b0, none, o, view_px, k1, b1);
+        for (int c0 = k0; c0 < k1; c0 += L.krows) {
+            const int c1 = min(c0 + L.krows, k1);
+            __syncthreads();
+            clear((c1 - c0) * W);
+            __syncthreads();
+            boxes(c0, c1);
+            resolve_rows(s, cpal, rz, color, W, L.hr0, croad, b0, (lptr<const unsigned long long>)L.work, o, view_px, c0, c1);
+        }
+        if (b1 >= H) break;
     }
 }
 

@@ -399,25 +399,26 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
     return c;
 }
 
-// Settings of the general raster: wavefronts per view and samples of the key
-// band.  A larger band leaves room for fewer workgroups in LDS, a smaller one
-// repeats the set-up of the strips that reach it more often.  Us by wavefronts
-// and samples, depth and ids (one MI355X): 2,048 views 128 x 128 4/2,048 180,
-// 4/1,024 265, 4/4,096 223, 8/4,096 199; 4,096 views 210 x 126 4/2,048 574, 8/4,096
-// 597, 4/4,096 681; 4,096 views 434 x 252 4/4,096 1,836, 8/4,096 2,037, 4/2,048
-// 2,361; 1,024 views 512 x 512 8/4,096 1,552, 4/4,096 1,805; 128 views 128 x 128
-// 8/4,096 48, 4/2,048 73.
+// Settings of the general raster: wavefronts per view (4, 8 from 60K pixels on)
+// and samples of the band of road keys (1,024 per wavefront, 8,192 at most).  A
+// larger band leaves room for fewer workgroups in LDS, a smaller one repeats the
+// set-up of the strips that reach it more often.  Us by wavefronts and samples,
+// depth and ids (one MI355X): 2,048 views 128 x 128 4/4,096 137, 4/8,192 194,
+// 8/4,096 181, 8/8,192 164; 4,096 views 210 x 126 4/4,096 396, 8/8,192 406, 4/8,192
+// 504; 2,048 views 434 x 252 8/8,192 707, 4/4,096 774, 8/16,384 957; 1,024 views 512 x
+// 512 8/8,192 956, 4/8,192 1,152, 8/16,384 1,217; 128 views 128 x 128 16/8,192 39,
+// 4/4,096 56.
 gp::FullCfg full_cfg(const gp_sim *sim)
 {
     const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
     gp::FullCfg c;
-    c.waves = px >= 200000 ? 8 : 4;
+    c.waves = px >= 60000 ? 8 : 4;
     while (c.waves < 16 && 2 * c.waves * sim->lay.n_views <= 16 * (int64_t)sim->n_cu) c.waves *= 2;
     c.bcap = full_box_faces(sim);
     c.recs = box_recs(sim);
     c.bins_cap = sim->bins_cap;
-    const int samples = std::max(512 * c.waves, px >= 60000 ? 4096 : 2048);
-    c.band_rows = std::min(sim->cfg.height, std::max(1, samples / sim->cfg.width));
+    const int samples = std::min(1024 * c.waves, 8192), rows = sim->cfg.height / 2;     // rows below the horizon
+    c.band_rows = std::max(1, std::min(rows, samples / sim->cfg.width));
     return c;
 }
 
@@ -425,14 +426,15 @@ gp::FullCfg full_cfg(const gp_sim *sim)
 // largest scene up to 256 (scenes with more are cast in chunks).  Wavefronts per
 // view: 4, with coverage bits 8 from 200K pixels on, without them (depth,
 // primitive ids, mixed road colours) 8 from 24K on; doubled while every view's
-// wavefronts fit the chip.  The key band holds 4,096 samples with coverage bits
-// and 512 per wavefront without: a larger band leaves room for fewer
-// workgroups, a smaller one repeats the road work more often.  Us by
-// wavefronts and samples (one MI355X): 2,048 views 128 x 128 rgb 4/4,096 116,
-// 4/2,048 124, 2/2,048 136, 8/4,096 129; with depth and ids 4/2,048 209, 8/4,096
-// 227, 4/4,096 259; 1,024 views 512 x 512 rgb 8/4,096 819, 4/4,096 1,054; 16
-// scenes, four cameras 210 x 126, depth and ids 8/4,096 475, 4/2,048 527; 128
-// views 128 x 128 rgb 8/4,096 45, 4/4,096 56.
+// wavefronts fit the chip.  With coverage bits the band of box keys holds 4,096
+// samples, without them the band of road keys 1,024 per wavefront, 8,192 at most: a
+// larger band leaves room for fewer workgroups, a smaller one repeats the work of
+// the primitives that reach it more often.  Us by wavefronts and samples (one
+// MI355X): 2,048 views 128 x 128 rgb 4/4,096 116, 4/2,048 124, 2/2,048 136, 8/4,096
+// 129; with depth and ids 4/4,096 209, 8/8,192 215, 4/8,192 287; 1,024 views 512 x 512
+// rgb 8/4,096 819, 4/4,096 1,054; 16 scenes, four cameras 210 x 126, depth and ids
+// 8/8,192 470, 4/4,096 549, 8/16,384 725; 2,048 views 434 x 252 with them 8/8,192 1,173,
+// 4/4,096 1,521; 128 views 128 x 128 rgb 8/4,096 45, 4/4,096 56.
 gp::RcCfg rc_cfg(const gp_sim *sim, bool rgb_only)
 {
     const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
@@ -442,7 +444,8 @@ gp::RcCfg rc_cfg(const gp_sim *sim, bool rgb_only)
     while (c.waves < 16 && 2 * c.waves * sim->lay.n_views <= 16 * (int64_t)sim->n_cu) c.waves *= 2;
     c.bcap = (int)std::min<int64_t>(256, ((int64_t)sim->boxes_cap + sim->signals_cap + 63) / 64 * 64);
     c.bins_cap = sim->bins_cap;
-    c.band_rows = std::min(sim->cfg.height, std::max(1, (c.cover ? 4096 : 512 * c.waves) / sim->cfg.width));
+    if (c.cover) c.band_rows = std::min(sim->cfg.height, std::max(1, 4096 / sim->cfg.width));
+    else c.band_rows = std::max(1, std::min(sim->cfg.height / 2, std::min(1024 * c.waves, 8192) / sim->cfg.width));
     return c;
 }
 

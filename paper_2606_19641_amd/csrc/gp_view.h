@@ -195,10 +195,12 @@ __device__ __forceinline__ void road_spans(const RgbLds &L, const Cam &cam, cons
 }
 
 // Fragments of the n staged road primitives in rows [b0, b1) folded into the
-// key band (first row band0): (primitive, row) items dealt to the lanes, their
-// exact spans cut into pieces of up to 16 samples, dealt again.  Every strip
-// lies in one plane, so 1/z is the row's.
-__device__ __forceinline__ void road_fold(const RgbLds &L, const Cam &cam, const WaveSt &ws, int n, int b0, int b1, int band0)
+// band of road keys (first row band0): (primitive, row) items dealt to the lanes,
+// their exact spans cut into pieces of up to 16 samples, dealt again.  Every
+// strip lies in one plane, so 1/z is the row's and the strip that a sample shows
+// is the one with the largest key word: the band holds key words only.
+__device__ __forceinline__ void road_fold(const RgbLds &L, lptr<uint32_t> road, const Cam &cam, const WaveSt &ws, int n, int b0,
+                                          int b1, int band0)
 {
     const int ln = (int)lane_id(), W = cam.W;
     wave_lds_order();
@@ -234,10 +236,8 @@ __device__ __forceinline__ void road_fold(const RgbLds &L, const Cam &cam, const
             const int sx = __shfl(x2, o2), sj = __shfl(j, o2), sk = __shfl(key, o2);
             if (pi >= npt) continue;
             const int i0 = (sx & 0xFFFF) + 16 * k, i1 = min(i0 + 15, sx >> 16);
-            const float rz = fmaf(cam.road.B, ((float)sj + 0.5f) - cam.cy, cam.road.C);
-            const unsigned long long kv = ((unsigned long long)__float_as_uint(rz) << 32) | (uint32_t)sk;
-            lptr<unsigned long long> row = L.work + (sj - band0) * W;
-            for (int i = i0; i <= i1; ++i) lds_max64(row + i, kv);
+            lptr<uint32_t> row = road + (sj - band0) * W;
+            for (int i = i0; i <= i1; ++i) lds_max32(row + i, (uint32_t)sk);
         }
     }
     wave_lds_order();
@@ -420,14 +420,12 @@ __device__ __forceinline__ bool load_unit(const DevSim &s, const SceneRec &sc, c
 // first round box(u) for u < box_jobs (their lists are needed only by the
 // resolve, so a long box unit overlaps the other wavefronts' road jobs), then
 // road(a, n) for up to batch ring strips at a time.  R_RING and R_JOB are zero
-// at the start (published by a barrier); ends with a barrier.  Returns whether
-// one round sufficed: the ring then still holds every strip, and a further call
-// with reuse set (R_JOB zero) only deals its jobs again.
+// at the start (published by a barrier); ends with a barrier.
 // (The units were dealt through LDS counters too, with ring entries reserved:
 // four dependent LDS operations before a unit's loads, and units cost the same.)
 template <class Test, class Box, class Road>
-__device__ __forceinline__ bool road_work(const DevSim &s, const SceneRec &sc, const RgbLds &L, int nsb, int box_jobs,
-                                          bool reuse, Test test, Box box, Road road)
+__device__ __forceinline__ void road_work(const DevSim &s, const SceneRec &sc, const RgbLds &L, int nsb, int box_jobs,
+                                          Test test, Box box, Road road)
 {
     const int ln = (int)lane_id(), K = (int)blockDim.x >> 6;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -435,22 +433,20 @@ __device__ __forceinline__ bool road_work(const DevSim &s, const SceneRec &sc, c
     for (int u0 = 0;; u0 += per) {
         // B1, the next unit's strips loaded while the current one is tested
         const int u1 = min(u0 + per, n_units);
-        if (!reuse) {
-            float4 q0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), q1 = q0;
-            int gq = 0;
-            bool live = u0 + wv < u1 && load_unit(s, sc, L, nsb, u0 + wv, gq, q0, q1);
-            for (int u = u0 + wv; u < u1; u += K) {
-                float4 n0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), n1 = n0;
-                int gn = 0;
-                const bool nlive = u + K < u1 && load_unit(s, sc, L, nsb, u + K, gn, n0, n1);
-                ring_append(L, test(live, q0, q1), gq);
-                q0 = n0;
-                q1 = n1;
-                gq = gn;
-                live = nlive;
-            }
-            __syncthreads();
+        float4 q0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), q1 = q0;
+        int gq = 0;
+        bool live = u0 + wv < u1 && load_unit(s, sc, L, nsb, u0 + wv, gq, q0, q1);
+        for (int u = u0 + wv; u < u1; u += K) {
+            float4 n0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), n1 = n0;
+            int gn = 0;
+            const bool nlive = u + K < u1 && load_unit(s, sc, L, nsb, u + K, gn, n0, n1);
+            ring_append(L, test(live, q0, q1), gq);
+            q0 = n0;
+            q1 = n1;
+            gq = gn;
+            live = nlive;
         }
+        __syncthreads();
         const int nring = L.cnt[R_RING];
         const bool more = u1 < n_units;
         // the ring cut into jobs of at most batch strips, as many as a
@@ -473,7 +469,7 @@ __device__ __forceinline__ bool road_work(const DevSim &s, const SceneRec &sc, c
         }
         __syncthreads();
         box_jobs = 0;
-        if (!more) return u0 == 0;
+        if (!more) return;
         if (threadIdx.x == 0) L.cnt[R_RING] = L.cnt[R_JOB] = 0;
         __syncthreads();
     }
@@ -1184,48 +1180,78 @@ __device__ __forceinline__ void resolve_band(const RgbLds &L, int W, Rz rz, Colo
     }
 }
 
-// Pixels [0, npix) of the key band into the images from pixel pix0 on: colour
-// and optional depth and primitive id.  Road keys hold their palette index in
-// the low byte; color(w) is the colour of a box or light key with low word w.
-// A lane takes four pixels and writes 12 bytes of colour, 16 of depth and 16 of
-// ids.
+// What four pixels from px on show by their keys: colour and optional depth and
+// primitive id.  Road keys hold their palette index in the low byte; color(w) is
+// the colour of a box or light key with low word w.  Writes 12 bytes of colour,
+// 16 of depth and 16 of ids (n < 4: the first n pixels).
 template <class Color>
-__device__ __forceinline__ void resolve_full(const DevSim &s, lptr<const uint32_t> pal, Color color,
-                                             lptr<const unsigned long long> keys, const RenderOut &o, int64_t pix0, int npix)
+__device__ __forceinline__ void show4(const DevSim &s, lptr<const uint32_t> pal, uint32_t q_road, Color color, const RenderOut &o,
+                                      const unsigned long long (&keys)[4], int64_t px, int n)
 {
     struct __attribute__((packed, aligned(1))) P3 { uint32_t x, y, z; };
     struct __attribute__((packed, aligned(4))) P4 { uint32_t x, y, z, w; };
-    const uint32_t q_road = s.shade ? shade_level(s, 0.0f, 0.0f, 4) : 255u;
+    uint32_t c[4], d[4], id[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const unsigned long long key = keys[k];
+        const int prim = (kMaxPrims - 1) - (int)(((uint32_t)key >> 8) & (uint32_t)(kMaxPrims - 1));
+        const bool box = ((uint32_t)key >> 31) != 0u;          // the class bit: boxes and lights
+        c[k] = pal[box ? 0u : ((uint32_t)key & 0xFFu)];        // (no key: entry 0, the background)
+        if (s.shade && key != 0ull) c[k] = shade_rgb(c[k], q_road);
+        if (box) c[k] = color((uint32_t)key);
+        id[k] = key != 0ull ? (uint32_t)prim : 0xFFFFFFFFu;
+        d[k] = 0x7F800000u;
+        if (o.depth && key != 0ull) d[k] = __float_as_uint(1.0f / __uint_as_float((uint32_t)(key >> 32)));
+    }
+    if (n == 4) {
+        *reinterpret_cast<P3 *>(o.rgb + 3 * px) = P3{(c[0] & 0xFFFFFFu) | (c[1] << 24), ((c[1] >> 8) & 0xFFFFu) | (c[2] << 16),
+                                                     ((c[2] >> 16) & 0xFFu) | (c[3] << 8)};
+        if (o.depth) *reinterpret_cast<P4 *>(o.depth + px) = P4{d[0], d[1], d[2], d[3]};
+        if (o.primid) *reinterpret_cast<P4 *>(o.primid + px) = P4{id[0], id[1], id[2], id[3]};
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (k >= n) continue;
+        for (int ch = 0; ch < 3; ++ch) o.rgb[3 * (px + k) + ch] = channel(c[k], ch);
+        if (o.depth) o.depth[px + k] = __uint_as_float(d[k]);
+        if (o.primid) o.primid[px + k] = (int32_t)id[k];
+    }
+}
+
+__device__ __forceinline__ uint32_t road_shade(const DevSim &s) { return s.shade ? shade_level(s, 0.0f, 0.0f, 4) : 255u; }
+
+// Rows [r0, r1) from the band of road keys (first row band0; only its rows
+// show road) and, where keys is set, the 64-bit box keys of the same rows; four
+// pixels per lane.  rz(j): the road's 1/z in row j.
+template <class Rz, class Color>
+__device__ __forceinline__ void resolve_rows(const DevSim &s, lptr<const uint32_t> pal, Rz rz, Color color, int W, int hr0,
+                                             lptr<const uint32_t> road, int band0, lptr<const unsigned long long> keys,
+                                             const RenderOut &o, int64_t view_px, int r0, int r1)
+{
+    const uint32_t q_road = road_shade(s);
+    const int npix = (r1 - r0) * W;
     for (int p = 4 * (int)threadIdx.x; p < npix; p += 4 * (int)blockDim.x) {
         const int n = min(4, npix - p);
-        uint32_t c[4], d[4], id[4];
+        int j = r0 + p / W, i = p - (j - r0) * W;
+        unsigned long long k4[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const unsigned long long key = k < n ? keys[p + k] : 0ull;
-            const int prim = (kMaxPrims - 1) - (int)(((uint32_t)key >> 8) & (uint32_t)(kMaxPrims - 1));
-            const bool box = ((uint32_t)key >> 31) != 0u;          // the class bit: boxes and lights
-            c[k] = pal[box ? 0u : ((uint32_t)key & 0xFFu)];        // (no key: entry 0, the background)
-            if (s.shade && key != 0ull) c[k] = shade_rgb(c[k], q_road);
-            if (box) c[k] = color((uint32_t)key);
-            id[k] = key != 0ull ? (uint32_t)prim : 0xFFFFFFFFu;
-            d[k] = 0x7F800000u;
-            if (o.depth && key != 0ull) d[k] = __float_as_uint(1.0f / __uint_as_float((uint32_t)(key >> 32)));
+            k4[k] = 0ull;
+            if (k < n) {
+                if (keys) k4[k] = keys[p + k];
+                if (j >= hr0) {
+                    const uint32_t w = road[(j - band0) * W + i];
+                    const unsigned long long rk = ((unsigned long long)__float_as_uint(rz(j)) << 32) | w;
+                    if (w != 0u && rk > k4[k]) k4[k] = rk;
+                }
+            }
+            if (++i == W) {
+                i = 0;
+                ++j;
+            }
         }
-        const int64_t px = pix0 + p;
-        if (n == 4) {
-            *reinterpret_cast<P3 *>(o.rgb + 3 * px) = P3{(c[0] & 0xFFFFFFu) | (c[1] << 24), ((c[1] >> 8) & 0xFFFFu) | (c[2] << 16),
-                                                         ((c[2] >> 16) & 0xFFu) | (c[3] << 8)};
-            if (o.depth) *reinterpret_cast<P4 *>(o.depth + px) = P4{d[0], d[1], d[2], d[3]};
-            if (o.primid) *reinterpret_cast<P4 *>(o.primid + px) = P4{id[0], id[1], id[2], id[3]};
-            continue;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k >= n) continue;
-            for (int ch = 0; ch < 3; ++ch) o.rgb[3 * (px + k) + ch] = channel(c[k], ch);
-            if (o.depth) o.depth[px + k] = __uint_as_float(d[k]);
-            if (o.primid) o.primid[px + k] = (int32_t)id[k];
-        }
+        show4(s, pal, q_road, color, o, k4, view_px + (int64_t)r0 * W + p, n);
     }
 }
 
