@@ -862,7 +862,7 @@ struct FaceRec {
     int16_t j0, j1;
     int16_t huge, nv;
     uint32_t rgb;
-    int32_t pad;
+    int32_t odd;          // plane_odd
 };
 static_assert(sizeof(FaceRec) == 64 && offsetof(FaceRec, A) == 32 && offsetof(FaceRec, j0) == 48, "FaceRec layout");
 
@@ -872,13 +872,19 @@ __device__ __forceinline__ void face_geo(FaceRec &f, const Prim &p)
     f.j0 = p.j0; f.j1 = p.j1; f.huge = p.huge; f.nv = p.nv;
 }
 
+// 1 for a plane whose 1/z may be no number somewhere (a coefficient is not finite)
+__device__ __forceinline__ int32_t plane_odd(float A, float B, float C)
+{
+    return !(fabsf(A) < INFINITY && fabsf(B) < INFINITY && fabsf(C) < INFINITY);
+}
+
 __device__ __forceinline__ FaceRec face_of(const TriRec &t, uint32_t rgb)
 {
     FaceRec f;
     face_geo(f, prim_of(t.g));
     f.A = t.A; f.B = t.B; f.C = t.C; f.keylo = t.keylo;
     f.rgb = rgb;
-    f.pad = 0;
+    f.odd = plane_odd(t.A, t.B, t.C);
     return f;
 }
 
@@ -980,8 +986,8 @@ __device__ __forceinline__ void fast_face(const Cam &cam, const Poly &P, uint32_
         const Plane pl = face_plane(cam, P.n, d);
         face_geo(f0, p0);
         face_geo(f1, p1);
-        f0.A = pl.A; f0.B = pl.B; f0.C = pl.C; f0.keylo = P.keylo; f0.rgb = rgb; f0.pad = 0;
-        f1.A = pl.A; f1.B = pl.B; f1.C = pl.C; f1.keylo = P.keylo; f1.rgb = rgb; f1.pad = 0;
+        f0.A = pl.A; f0.B = pl.B; f0.C = pl.C; f0.keylo = P.keylo; f0.rgb = rgb; f0.odd = plane_odd(pl.A, pl.B, pl.C);
+        f1.A = pl.A; f1.B = pl.B; f1.C = pl.C; f1.keylo = P.keylo; f1.rgb = rgb; f1.odd = f0.odd;
     }
 }
 
@@ -1118,6 +1124,24 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
     return v;
+}
+
+// OR over the wavefront, by the same steps
+__device__ __forceinline__ unsigned long long wave_or64(unsigned long long v)
+{
+    int lo = (int)v, hi = (int)(v >> 32);
+#define GP_OR_STEP(ctrl, rows)                                                   \
+    lo |= __builtin_amdgcn_update_dpp(0, lo, ctrl, rows, 0xf, false);            \
+    hi |= __builtin_amdgcn_update_dpp(0, hi, ctrl, rows, 0xf, false);
+    GP_OR_STEP(0x111, 0xf)
+    GP_OR_STEP(0x112, 0xf)
+    GP_OR_STEP(0x114, 0xf)
+    GP_OR_STEP(0x118, 0xf)
+    GP_OR_STEP(0x142, 0xa)
+    GP_OR_STEP(0x143, 0xc)
+#undef GP_OR_STEP
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(lo, 63) |
+           ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(hi, 63) << 32);
 }
 
 // number of lanes whose inclusive prefix (non-decreasing over the lanes) is

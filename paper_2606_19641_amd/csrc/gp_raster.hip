@@ -116,13 +116,16 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     const int prio_b = nsb >= 24 ? 2 : (nsb >= 16 ? 1 : 0);
     view_priority(prio_b);
     // a view that may list more faces (three a box) than its list holds gives it
-    // the memory of a smaller ring and smaller set-up jobs
-    if (3 * nsv + (AP ? sc.n_signals : 0) > L.bcap && nsv <= L.nrec) {
+    // the memory of a smaller ring, then of smaller set-up jobs too
+    const int most = 3 * nsv + (AP ? sc.n_signals : 0);
+    if (most > L.bcap && nsv <= L.nrec) {
         L.ring = kSmallRing;
-        L.batch = kSmallBatch;
-        const int tail = 4 * kSmallRing + K * wave_bytes(kSmallBatch);
-        const int cap = min(256, (L.tail - max(tail, resolve_bytes(W))) / (int)sizeof(FaceRec));
-        if (cap > L.bcap) L.bcap = cap;
+        int tail = 4 * kSmallRing + K * wave_bytes(kBatch);
+        if (most > (L.tail - tail) / (int)sizeof(FaceRec)) {
+            L.batch = kSmallBatch;
+            tail = 4 * kSmallRing + K * wave_bytes(kSmallBatch);
+        }
+        L.bcap = max(L.bcap, min(256, (L.tail - max(tail, resolve_bytes(W))) / (int)sizeof(FaceRec)));
         L.sring = (lptr<int32_t>)((lptr<unsigned char>)L.faces + L.tail - tail);
         L.waves = (lptr<unsigned char>)(L.sring + kSmallRing);
     }

@@ -151,44 +151,40 @@ __device__ __forceinline__ uint32_t bits_at(const RgbLds &L, int b)
     return __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
 }
 
-// Rasterise the n staged road triangles into the coverage bitmask.  Lane t
-// first takes the first row of triangle t; the further rows of triangles
-// that span several rows are then dealt to the lanes by a prefix over their
-// counts.  Per (triangle, row) the exact span of covered samples is OR-ed
-// into the row's coverage words.
+// Rasterise the n (<= 64) staged road primitives into the coverage bitmask.
+// Their (primitive, row) items are dealt to the lanes by a prefix over row
+// counts; per item the exact span of covered samples is OR-ed into the coverage
+// words.  Every primitive has a row, so the first items of the primitives that
+// start within a pass of 64 items are distinct: a bit for each, OR-ed over the
+// wavefront, tells a lane its item's primitive by counting (owner_of's search
+// takes about fifteen instructions and seven cross-lane reads more).
 __device__ __forceinline__ void road_spans(const RgbLds &L, const Cam &cam, const WaveSt &ws, int n)
 {
     const int ln = (int)lane_id();
     wave_lds_order();
-    for (int t0 = 0; t0 < n; t0 += 64) {
-        const int t = t0 + ln;
-        int c = 0;
-        if (t < n) {
-            const int32_t jj = ((lptr<const int32_t>)(ws.tris + t))[8];     // j0 | j1 << 16
-            c = (jj >> 16) - (int)(int16_t)(jj & 0xFFFF);
-        }
-        const int incl = wave_incl_scan(c);
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        const int excl = incl - c;
-        for (int g0 = -64; g0 < total; g0 += 64) {
-            // g0 < 0: lane t's own first row; then the dealt further rows
-            const int gi = g0 + ln;
-            int o = ln, extra = 0;
-            bool act = t < n;
-            if (g0 >= 0) {
-                o = owner_of(incl, gi);
-                extra = 1 + gi - __shfl(excl, o);
-                act = gi < total;
-            }
-            if (act) {
-                const Prim pr = lds_load(ws.tris + t0 + o);
-                const int j = pr.j0 + extra;
-                int xl, xr;
-                // (the row test holds for every row with road unless 1/z underflows)
-                const float rz = fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C);
-                const int b = (j - L.hr0) * cam.W;
-                if ((b >= 0) & (rz > 0.0f) & prim_span(pr, j, cam.W, xl, xr)) or_span(L.bits, b + xl, b + xr);
-            }
+    int c = 0;
+    if (ln < n) {
+        const int32_t jj = ((lptr<const int32_t>)(ws.tris + ln))[8];     // j0 | j1 << 16
+        c = (jj >> 16) - (int)(int16_t)(jj & 0xFFFF) + 1;
+    }
+    const int incl = wave_incl_scan(c);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int excl = incl - c;
+    for (int g0 = 0; g0 < total; g0 += 64) {
+        const int gi = g0 + ln, at = excl - g0;
+        const bool starts = (ln < n) & ((uint32_t)at < 64u);
+        const unsigned long long m = wave_or64(starts ? 1ull << (at & 63) : 0ull);
+        const int before = __popcll(__ballot((ln < n) & (at < 0)));
+        const int o = before + lanes_below(m) + (int)((m >> ln) & 1ull) - 1;
+        const int ex = __shfl(excl, o);
+        if (gi < total) {
+            const Prim pr = lds_load(ws.tris + o);
+            const int j = pr.j0 + (gi - ex);
+            int xl, xr;
+            // (the row test holds for every row with road unless 1/z underflows)
+            const float rz = fmaf(cam.road.B, ((float)j + 0.5f) - cam.cy, cam.road.C);
+            const int b = (j - L.hr0) * cam.W;
+            if ((b >= 0) & (rz > 0.0f) & prim_span(pr, j, cam.W, xl, xr)) or_span(L.bits, b + xl, b + xr);
         }
     }
     wave_lds_order();
@@ -766,6 +762,16 @@ __device__ __forceinline__ bool entry_span(const Prim &e, int j, int W, int &xl,
     return prim_span(e, j, W, xl, xr);
 }
 
+// Box keys as doubles: a key's high word, the bits of a positive 1/z, is below
+// 0x7ff00000, so keys order like the positive doubles of the same bits, and one
+// v_max_f64 keeps the larger of two.  (fmax would quiet its operands first.)
+__device__ __forceinline__ double key_max(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // 1/z of the light entry at t for the sample offsets a, b (0: not shown)
 __device__ __forceinline__ float light_invz(const RgbLds &L, const Cam &cam, int t, float a, float b)
 {
@@ -885,8 +891,8 @@ __device__ __forceinline__ void box_spans(const RgbLds &L, const Cam &cam, int n
                 const int j = max((int)pr.j0, c0) + (gi - ex);
                 int xl, xr;
                 if (entry_span<AP>(pr, j, cam.W, xl, xr)) {
-                    // bit 31 marks a light's columns
-                    S[tt * R + (j - c0)] = xl | (xr << 16) | (AP && pr.nv == 0 ? (int)0x80000000 : 0);
+                    // bit 31 marks a light's columns and faces of no finite plane
+                    S[tt * R + (j - c0)] = xl | (xr << 16) | (((AP && pr.nv == 0) || pr.pad1 != 0) ? (int)0x80000000 : 0);
                     lptr<unsigned long long> mrow = M + nmw * G * (j - c0) + (tt >> 6);
                     const unsigned long long bit = 1ull << (tt & 63);
                     const int gl = xr >= cam.W - 16 ? G - 1 : xr >> 4;
@@ -921,9 +927,9 @@ __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, u
         const uint32_t rzb = __float_as_uint(rz);
         // sample offsets ((float)(i + m) + 0.5f) - cx are small exact values: du0 + m
         const float du0 = ((float)i + 0.5f) - cam.cx;
-        unsigned long long best[16];
+        double best[16];
 #pragma unroll
-        for (int m = 0; m < 16; ++m) best[m] = 0ull;
+        for (int m = 0; m < 16; ++m) best[m] = 0.0;
         for (int w = 0; w < nmw; ++w) {
             unsigned long long mk = M[nmw * (G * r + g) + w];
             while (mk != 0ull) {
@@ -937,36 +943,36 @@ __device__ __forceinline__ void resolve_masks(const RgbLds &L, const Cam &cam, u
                 const uint32_t in = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
                 const float bdv = fmaf(pk.y, dv, pk.z);
                 const uint32_t keylo = __float_as_uint(pk.w);
-                if (AP && sp < 0) {
-                    // a light: few samples, each with its own sphere test
+                if (sp < 0) {
+                    // a light: few samples, each with its own sphere test; or a
+                    // face whose 1/z may be no number: with the test spelt out
+                    const bool light = AP && ((lptr<const int32_t>)(L.faces + t))[15] == 0;
 #pragma unroll
                     for (int m = 0; m < 16; ++m) {
                         if (!((in >> m) & 1u)) continue;
-                        const float invz = light_invz(L, cam, t, du0 + (float)m, -dv);
-                        const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
-                        if (invz > 0.0f && key > best[m]) best[m] = key;
+                        const float invz = light ? light_invz(L, cam, t, du0 + (float)m, -dv) : fmaf(pk.x, du0 + (float)m, bdv);
+                        if (invz > 0.0f) best[m] = key_max(best[m], __hiloint2double(__float_as_int(invz), (int)keylo));
                     }
                     continue;
                 }
-                // branch-free: the three tests combined bitwise, so that each
-                // sample is a select and not a branch around the compare
+                // outside the span the sign bit is set: such keys, like those of
+                // negative 1/z, lose to any other
+                const uint32_t out = ~in;
 #pragma unroll
                 for (int m = 0; m < 16; ++m) {
-                    const float invz = fmaf(pk.x, du0 + (float)m, bdv);
-                    const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
-                    const bool take = (((in >> m) & 1u) != 0u) & (invz > 0.0f) & (key > best[m]);
-                    best[m] = take ? key : best[m];
+                    const uint32_t hw = __float_as_uint(fmaf(pk.x, du0 + (float)m, bdv)) | ((out << (31 - m)) & 0x80000000u);
+                    best[m] = key_max(best[m], __hiloint2double((int)hw, (int)keylo));
                 }
             }
         }
         uint32_t c[16];
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
-            const unsigned long long kb = best[m];
+            const uint32_t kh = (uint32_t)__double2hiint(best[m]), kl = (uint32_t)__double2loint(best[m]);
             const bool road = (bits >> m) & 1u;
-            const bool box = (kb != 0ull) & (!road | ((uint32_t)(kb >> 32) >= rzb));
+            const bool box = (kh != 0u) & (!road | (kh >= rzb));          // (1/z of zero counts as no key)
             // the key's low byte names the list entry (entry 0 without a key: read, not used)
-            const uint32_t boxc = ((lptr<const uint32_t>)(L.faces + ((uint32_t)kb & 0xFFu)))[14];
+            const uint32_t boxc = ((lptr<const uint32_t>)(L.faces + (kl & 0xFFu)))[14];
             c[m] = box ? boxc : (road ? road_rgb : bg_rgb);
         }
         store16(img + 3 * ((int64_t)j * W + i), c);
