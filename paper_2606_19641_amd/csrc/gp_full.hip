@@ -17,7 +17,7 @@
 // colour, 16 of depth and 16 of ids per four pixels.
 //
 // Bound by the road words' folding and the three output streams.  One MI355X,
-// 2,048 views at 128 x 128 with depth and ids: 137 us (with 64-bit keys of every
+// 2,048 views at 128 x 128 with depth and ids: 119 us (with 64-bit keys of every
 // fragment in bands half as high 171, in the banded kernel, which sets up every
 // strip of a surviving bin and writes single bytes, 282).
 #include "gp_view.h"
@@ -56,7 +56,6 @@ __device__ __forceinline__ void resolve_box_rows(const DevSim &s, lptr<const uin
                                                  const Cam &cam, lptr<const uint32_t> road, int band0, const RenderOut &o,
                                                  int64_t view_px, int c0, int c1)
 {
-    const uint32_t q_road = road_shade(s);
     const int W = cam.W, R = c1 - c0, G = (W + 15) >> 4, n = 2 * R * G, nmw = L.nmw;
     lptr<const unsigned long long> M = (lptr<const unsigned long long>)L.work;
     lptr<const int32_t> S = (lptr<const int32_t>)(M + nmw * G * R);
@@ -65,12 +64,12 @@ __device__ __forceinline__ void resolve_box_rows(const DevSim &s, lptr<const uin
         const float dv = ((float)j + 0.5f) - cam.cy;
         // sample offsets ((float)(i + m) + 0.5f) - cx are small exact values: du0 + m
         const float du0 = ((float)i + 0.5f) - cam.cx;
-        const unsigned long long rz = (unsigned long long)__float_as_uint(fmaf(cam.road.B, dv, cam.road.C)) << 32;
-        unsigned long long best[8];
+        const int rzb = __float_as_int(fmaf(cam.road.B, dv, cam.road.C));
+        double best[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             const uint32_t w = j >= L.hr0 ? road[(j - band0) * W + i + m] : 0u;
-            best[m] = w != 0u ? rz | w : 0ull;
+            best[m] = __hiloint2double(w != 0u ? rzb : 0, (int)w);
         }
         for (int w = 0; w < nmw; ++w) {
             unsigned long long mk = M[nmw * (G * r + g) + w];
@@ -85,29 +84,32 @@ __device__ __forceinline__ void resolve_box_rows(const DevSim &s, lptr<const uin
                 const float bdv = fmaf(pk.y, dv, pk.z);
                 const uint32_t keylo = __float_as_uint(pk.w);
                 if (sp < 0) {
-                    // a light: few samples, each with its own sphere test
+                    const bool light = ((lptr<const int32_t>)(L.faces + t))[15] == 0;
 #pragma unroll
                     for (int m = 0; m < 8; ++m) {
                         if (!((in >> m) & 1u)) continue;
-                        const float invz = light_invz(L, cam, t, du0 + (float)m, -dv);
-                        const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
-                        if (invz > 0.0f && key > best[m]) best[m] = key;
+                        const float invz = light ? light_invz(L, cam, t, du0 + (float)m, -dv) : fmaf(pk.x, du0 + (float)m, bdv);
+                        if (invz > 0.0f) best[m] = key_max(best[m], __hiloint2double(__float_as_int(invz), (int)keylo));
                     }
                     continue;
                 }
+                const uint32_t out = ~in;
 #pragma unroll
                 for (int m = 0; m < 8; ++m) {
-                    const float invz = fmaf(pk.x, du0 + (float)m, bdv);
-                    const unsigned long long key = ((unsigned long long)__float_as_uint(invz) << 32) | keylo;
-                    const bool take = (((in >> m) & 1u) != 0u) & (invz > 0.0f) & (key > best[m]);
-                    best[m] = take ? key : best[m];
+                    const uint32_t hw = __float_as_uint(fmaf(pk.x, du0 + (float)m, bdv)) | ((out << (31 - m)) & 0x80000000u);
+                    best[m] = key_max(best[m], __hiloint2double((int)hw, (int)keylo));
                 }
             }
         }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const unsigned long long k4[4] = {best[4 * q], best[4 * q + 1], best[4 * q + 2], best[4 * q + 3]};
-            show4(s, pal, q_road, color, o, k4, view_px + (int64_t)j * W + i + 4 * q, 4);
+            unsigned long long k4[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                k4[k] = (unsigned long long)__double_as_longlong(best[4 * q + k]);
+                if (k4[k] >> 32 == 0ull) k4[k] = 0ull;               // 1/z of zero counts as no key
+            }
+            show4(s, pal, color, o, k4, view_px + (int64_t)j * W + i + 4 * q, 4);
         }
     }
 }
@@ -144,8 +146,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int nbox = sc.n_agents + sc.n_static;
     CullIn in = cull_load<false>(s, sc, ego, 64 * wv, sc.n_bins, nbox);
     const Cam cam = make_cam(s, sc, ego, vi.cam);
-    for (int p = tid; p < 256; p += B)
-        pal[p] = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) | ((uint32_t)s.palette[3 * p + 2] << 16);
+    road_palette(s, pal);
     if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();
     cull_all<false>(s, sc, cam, ego, L, in, wv, B);

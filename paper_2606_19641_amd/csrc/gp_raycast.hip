@@ -41,7 +41,7 @@
 // Bound by VALU issue.  One MI355X: 2,048 views at 128 x 128 (32 agents, 2,000
 // strips) 116 us (1,100 us with the tests dealt by pixel; 218 us before the
 // certain runs of boxes and strips were taken without the full test), 16 scenes
-// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 426 us
+// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 403 us
 // (474 us with 64-bit keys of strips too, 2,400 us by pixel).
 #include "gp_view.h"
 
@@ -776,9 +776,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         const int nbits = ((W * (H - L.hr0) + 63) >> 6) + 1;
         for (int p = tid; p < nbits; p += B) L.bits[p] = 0ull;
     } else {
-        for (int p = tid; p < 256; p += B)
-            pal[p] = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) |
-                     ((uint32_t)s.palette[3 * p + 2] << 16);
+        road_palette(s, pal);
     }
     if (tid < R_NCNT) L.cnt[tid] = tid == R_BMIN ? 0x7FFFFFFF : (tid == R_BMAX ? -1 : 0);
     __syncthreads();

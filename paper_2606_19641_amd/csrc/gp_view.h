@@ -1186,34 +1186,51 @@ __device__ __forceinline__ void resolve_band(const RgbLds &L, int W, Rz rz, Colo
     }
 }
 
+// the palette as the roads show it (lit where the sim has a light) into LDS
+__device__ __forceinline__ void road_palette(const DevSim &s, lptr<uint32_t> pal)
+{
+    const uint32_t q = s.shade ? shade_level(s, 0.0f, 0.0f, 4) : 255u;
+    for (int p = (int)threadIdx.x; p < 256; p += (int)blockDim.x) {
+        const uint32_t c = (uint32_t)s.palette[3 * p] | ((uint32_t)s.palette[3 * p + 1] << 8) | ((uint32_t)s.palette[3 * p + 2] << 16);
+        pal[p] = s.shade ? shade_rgb(c, q) : c;
+    }
+}
+
+// Four pixels from px on: colours c (byte 3 ignored), depths d, ids.
+__device__ __forceinline__ void store4(const RenderOut &o, int64_t px, const uint32_t (&c)[4], const uint32_t (&d)[4],
+                                       const uint32_t (&id)[4])
+{
+    struct __attribute__((packed, aligned(1))) P3 { uint32_t x, y, z; };
+    struct __attribute__((packed, aligned(4))) P4 { uint32_t x, y, z, w; };
+    *reinterpret_cast<P3 *>(o.rgb + 3 * px) = P3{(c[0] & 0xFFFFFFu) | (c[1] << 24), ((c[1] >> 8) & 0xFFFFu) | (c[2] << 16),
+                                                 ((c[2] >> 16) & 0xFFu) | (c[3] << 8)};
+    if (o.depth) *reinterpret_cast<P4 *>(o.depth + px) = P4{d[0], d[1], d[2], d[3]};
+    if (o.primid) *reinterpret_cast<P4 *>(o.primid + px) = P4{id[0], id[1], id[2], id[3]};
+}
+
 // What four pixels from px on show by their keys: colour and optional depth and
 // primitive id.  Road keys hold their palette index in the low byte; color(w) is
 // the colour of a box or light key with low word w.  Writes 12 bytes of colour,
 // 16 of depth and 16 of ids (n < 4: the first n pixels).
 template <class Color>
-__device__ __forceinline__ void show4(const DevSim &s, lptr<const uint32_t> pal, uint32_t q_road, Color color, const RenderOut &o,
+__device__ __forceinline__ void show4(const DevSim &s, lptr<const uint32_t> pal, Color color, const RenderOut &o,
                                       const unsigned long long (&keys)[4], int64_t px, int n)
 {
-    struct __attribute__((packed, aligned(1))) P3 { uint32_t x, y, z; };
-    struct __attribute__((packed, aligned(4))) P4 { uint32_t x, y, z, w; };
     uint32_t c[4], d[4], id[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const unsigned long long key = keys[k];
         const int prim = (kMaxPrims - 1) - (int)(((uint32_t)key >> 8) & (uint32_t)(kMaxPrims - 1));
         const bool box = ((uint32_t)key >> 31) != 0u;          // the class bit: boxes and lights
-        c[k] = pal[box ? 0u : ((uint32_t)key & 0xFFu)];        // (no key: entry 0, the background)
-        if (s.shade && key != 0ull) c[k] = shade_rgb(c[k], q_road);
+        c[k] = pal[box ? 0u : ((uint32_t)key & 0xFFu)];
+        if (key == 0ull) c[k] = s.bg_rgb;
         if (box) c[k] = color((uint32_t)key);
         id[k] = key != 0ull ? (uint32_t)prim : 0xFFFFFFFFu;
         d[k] = 0x7F800000u;
         if (o.depth && key != 0ull) d[k] = __float_as_uint(1.0f / __uint_as_float((uint32_t)(key >> 32)));
     }
     if (n == 4) {
-        *reinterpret_cast<P3 *>(o.rgb + 3 * px) = P3{(c[0] & 0xFFFFFFu) | (c[1] << 24), ((c[1] >> 8) & 0xFFFFu) | (c[2] << 16),
-                                                     ((c[2] >> 16) & 0xFFu) | (c[3] << 8)};
-        if (o.depth) *reinterpret_cast<P4 *>(o.depth + px) = P4{d[0], d[1], d[2], d[3]};
-        if (o.primid) *reinterpret_cast<P4 *>(o.primid + px) = P4{id[0], id[1], id[2], id[3]};
+        store4(o, px, c, d, id);
         return;
     }
 #pragma unroll
@@ -1225,7 +1242,45 @@ __device__ __forceinline__ void show4(const DevSim &s, lptr<const uint32_t> pal,
     }
 }
 
-__device__ __forceinline__ uint32_t road_shade(const DevSim &s) { return s.shade ? shade_level(s, 0.0f, 0.0f, 4) : 255u; }
+// Rows [r0, r1) that no box reaches, from the band of road keys (first row
+// band0); four pixels of one row per lane, the last four of a row sharing some
+// with those before them where W is no multiple of four (W >= 4).  rz(j): the
+// road's 1/z in row j.  Most rows of a view: a lane's pixels take one division
+// and no choice between boxes (2,048 views at 128 x 128 with depth and ids 119 us;
+// 135 with a 64-bit key resolved per pixel).
+template <class Rz>
+__device__ __forceinline__ void resolve_roads(const DevSim &s, lptr<const uint32_t> pal, Rz rz, int W, int hr0,
+                                              lptr<const uint32_t> road, int band0, const RenderOut &o, int64_t view_px, int r0,
+                                              int r1)
+{
+    const int G = (W + 3) >> 2, B = (int)blockDim.x, dr = B / G, dg = B - dr * G;
+    int r = r0 + (int)threadIdx.x / G, g = (int)threadIdx.x % G;
+    while (r < r1) {
+        const int i = min(4 * g, W - 4);
+        uint32_t c[4], d[4], id[4], w[4] = {0u, 0u, 0u, 0u};
+        uint32_t depth = 0x7F800000u;
+        if (r >= hr0) {
+            lptr<const uint32_t> p = road + (r - band0) * W + i;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] = p[k];
+            if (o.depth) depth = __float_as_uint(1.0f / rz(r));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool has = w[k] != 0u;
+            c[k] = has ? pal[w[k] & 0xFFu] : s.bg_rgb;
+            d[k] = has ? depth : 0x7F800000u;
+            id[k] = has ? (uint32_t)(kMaxPrims - 1) - ((w[k] >> 8) & (uint32_t)(kMaxPrims - 1)) : 0xFFFFFFFFu;
+        }
+        store4(o, view_px + (int64_t)r * W + i, c, d, id);
+        r += dr;
+        g += dg;
+        if (g >= G) {
+            g -= G;
+            ++r;
+        }
+    }
+}
 
 // Rows [r0, r1) from the band of road keys (first row band0; only its rows
 // show road) and, where keys is set, the 64-bit box keys of the same rows; four
@@ -1235,7 +1290,10 @@ __device__ __forceinline__ void resolve_rows(const DevSim &s, lptr<const uint32_
                                              lptr<const uint32_t> road, int band0, lptr<const unsigned long long> keys,
                                              const RenderOut &o, int64_t view_px, int r0, int r1)
 {
-    const uint32_t q_road = road_shade(s);
+    if (!keys && W >= 4) {
+        resolve_roads(s, pal, rz, W, hr0, road, band0, o, view_px, r0, r1);
+        return;
+    }
     const int npix = (r1 - r0) * W;
     for (int p = 4 * (int)threadIdx.x; p < npix; p += 4 * (int)blockDim.x) {
         const int n = min(4, npix - p);
@@ -1257,7 +1315,7 @@ __device__ __forceinline__ void resolve_rows(const DevSim &s, lptr<const uint32_
                 ++j;
             }
         }
-        show4(s, pal, q_road, color, o, k4, view_px + (int64_t)r0 * W + p, n);
+        show4(s, pal, color, o, k4, view_px + (int64_t)r0 * W + p, n);
     }
 }
 
