@@ -368,22 +368,24 @@ int full_box_faces(const gp_sim *sim)
 int box_recs(const gp_sim *sim) { return (int)std::min<int64_t>(64, sim->boxes_cap); }
 
 // Wavefronts per view in the split rasteriser: the launch's view_waves, times
-// 2 from 32K pixels on and 4 from 200K on (a view's rows are a serial loop of
+// 2 from 32K pixels on and 4 from 105K on (a view's rows are a serial loop of
 // its workgroup, and larger images leave room for fewer workgroups in LDS),
 // doubled while all wavefronts together still fit the chip at four per SIMD.
-// Render us by wavefronts per view, 2 / 4 / 8 / 16 (one MI355X):
-//   2,048 views 128 x 128 (32 agents, 2,000 strips)   54.2 /  65.7 / 102 / 167
-//   8,192 views 210 x 126                              214 /   257 / 411 / 687
-//   8,192 views 434 x 252                              762 /   563 / 659 / 953
-//   4,096 views 512 x 512 (64 agents, 4,000 strips)    886 /   742 / 687 / 822
-//   1,024 views 128 x 128                             49.8 /  40.4 / 58.4 / 82.2
-//     256 views 128 x 128                             38.4 /  31.7 / 28.6 / 27.7
-//       8 views  64 x 64  (8 agents, 200 strips)      26.9 /  22.2 / 18.4 / 19.0
-//      64 views 512 x 512                              256 /   143 / 94.2 / 72.4
+// Step + render us by wavefronts per view, 2 / 4 / 8 / 16 (one MI355X):
+//   2,048 views 128 x 128 (32 agents, 2,000 strips)   46.1 /  53.2 /  84 / 132
+//   2,048 views 192 x 192                             70.8 /  71.9 /  97
+//   2,048 views 256 x 256                              119 /   112 / 125
+//   2,048 views 320 x 320                              207 /   160 / 161
+//   2,048 views 384 x 384                              274 /   221 / 210
+//   8,192 views 210 x 126                              181 /   193 / 328 / 529
+//   8,192 views 434 x 252                              625 /   572 / 555 / 785
+//   4,096 views 512 x 512 (64 agents, 4,000 strips)    775 /   695 / 649 / 685
+//     520 views 128 x 128 (a batch of eight sims)     79.6 /  67.6 / 69.5 / 80.7
+//       8 views  64 x 64  (8 agents, 200 strips)      22.7 /  20.2 / 17.9 / 18.3
 int split_waves(const gp_sim *sim, const gp_launch &l, int64_t n_views)
 {
     const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
-    int k = l.view_waves * (px >= 200000 ? 4 : (px >= 32768 ? 2 : 1));
+    int k = l.view_waves * (px >= 105000 ? 4 : (px >= 32768 ? 2 : 1));
     while (k < 16 && 2 * k * n_views <= 16 * (int64_t)sim->n_cu) k *= 2;
     return std::min(k, 16);
 }

@@ -725,8 +725,11 @@ __device__ __forceinline__ void cull_all(const DevSim &s, const SceneRec &sc, co
 {
     const int nbox = sc.n_agents + sc.n_static, n = max(sc.n_bins, nbox);
     for (int b0 = 64 * wv; b0 < n; b0 += B) {
-        if (b0 != 64 * wv) in = cull_load<STEP>(s, sc, ego, b0, sc.n_bins, nbox);
+        // the next pass's loads are under way while this one is tested
+        CullIn next = {};
+        if (b0 + B < n) next = cull_load<STEP>(s, sc, ego, b0 + B, sc.n_bins, nbox);
         cull_pass<STEP>(s, cam, L, in, b0, sc.n_bins, nbox);
+        in = next;
     }
 }
 
