@@ -593,9 +593,9 @@ __device__ __forceinline__ void rc_certain(const Cam &cam, const FaceRec &f, flo
 // The (entry, row) items are dealt to the lanes; an item's columns are the
 // certain runs above and what is left between them, cut into pieces that are
 // dealt again: certain pieces take one division a sample for the hit, the
-// others the full test.  Many items are shared out over the wavefronts by
-// passes of 64; few are set up by every wavefront, which then share the pieces
-// (one box near the camera can hold most of a view's samples).
+// others the full test.  Passes of 64 items are shared out over the wavefronts;
+// where there are fewer passes than wavefronts, several set up the same pass and
+// share its pieces (one box near the camera can hold most of a view's samples).
 __device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, int b0, int b1, int wv, int nwv)
 {
     const int ln = (int)lane_id(), W = cam.W;
@@ -611,9 +611,10 @@ __device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, 
         const int incl = wave_incl_scan(c);
         const int total = __builtin_amdgcn_readlane(incl, 63);
         const int excl = incl - c;
-        const bool split = total <= 128 * nwv;              // pieces shared out, not passes
+        // a pass of 64 items goes to one of the groups of gsz wavefronts
+        const int gsz = max(1, nwv / max(1, (total + 63) >> 6)), groups = nwv / gsz, mine = wv / gsz, wi = wv - mine * gsz;
         for (int g0 = 0; g0 < total; g0 += 64, ++pass) {
-            if (!split && pass % nwv != wv) continue;
+            if (pass % groups != mine) continue;
             const int gi = g0 + ln;
             const int o = owner_of(incl, gi);
             const int j = __shfl(first, o) + (gi - __shfl(excl, o));
@@ -642,7 +643,7 @@ __device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, 
                 const int inc2 = wave_incl_scan(nq);
                 const int npt = __builtin_amdgcn_readlane(inc2, 63);
                 const int ex2 = inc2 - nq;
-                for (int p0 = split ? 64 * wv : 0; p0 < npt; p0 += split ? 64 * nwv : 64) {
+                for (int p0 = 64 * wi; p0 < npt; p0 += 64 * gsz) {
                     const int pi = p0 + ln;
                     const int o2 = owner_of(inc2, pi);
                     int k = pi - __shfl(ex2, o2);
@@ -689,7 +690,7 @@ __device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, 
             const int inc2 = wave_incl_scan(nu);
             const int npt = __builtin_amdgcn_readlane(inc2, 63);
             const int ex2 = inc2 - nu;
-            for (int p0 = split ? 64 * wv : 0; p0 < npt; p0 += split ? 64 * nwv : 64) {
+            for (int p0 = 64 * wi; p0 < npt; p0 += 64 * gsz) {
                 const int pi = p0 + ln;
                 const int o2 = owner_of(inc2, pi);
                 int k = pi - __shfl(ex2, o2);
