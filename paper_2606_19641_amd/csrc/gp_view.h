@@ -447,7 +447,7 @@ __device__ __forceinline__ void road_work(const DevSim &s, const SceneRec &sc, c
         const bool more = u1 < n_units;
         // the ring cut into jobs of at most batch strips, as many as a
         // multiple of the wavefronts, of equal size: a job's set-up takes about
-        // the same time for any number of strips up to a wavefront's width
+        // the same time for any number of strips up to a wavefront's width.
         const int njobs = (max(K, (nring + L.batch - 1) / L.batch) + K - 1) / K * K;
         const int jsz = (nring + njobs - 1) / njobs;
         // B2
