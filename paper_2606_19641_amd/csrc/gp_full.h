@@ -20,6 +20,8 @@
 // 2,048 views at 128 x 128 with depth and ids: 119 us (with 64-bit keys of every
 // fragment in bands half as high 171, in the banded kernel, which sets up every
 // strip of a surviving bin and writes single bytes, 282).
+#pragma once
+
 #include "gp_view.h"
 
 namespace gp {

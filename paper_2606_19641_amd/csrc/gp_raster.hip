@@ -48,6 +48,7 @@
 // file is compiled with -ffp-contract=off, correctly rounded division and
 // IEEE denormals.
 
+#include "gp_full.h"      // the general raster, compiled here too
 #include "gp_view.h"
 
 namespace gp {
