@@ -145,7 +145,7 @@ struct RgbCfg {
     int appear;       // 1: the instances with the directional light and traffic lights
 };
 
-// Settings of the general raster (gp_full.hip).
+// Settings of the general raster (gp_full.h).
 struct FullCfg {
     int waves;        // wavefronts per view: 1..16
     int bcap;         // box faces and lights one view's list holds: 64..256
@@ -189,6 +189,10 @@ hipError_t step_graph_node(hipGraph_t g, hipGraphExec_t exec, hipGraphNode_t *no
                            const float *actions);
 // clear_halted = 1 also clears the halted flags and the jerk actuators
 hipError_t launch_cs(const DevSim &s, int clear_halted, hipStream_t st);
+// agent states from device memory src [A][4] (4-byte aligned), a new episode
+hipError_t launch_set_state(const DevSim &s, const float *src, hipStream_t st);
+// dst's dynamic state from src's (same scenes, same device)
+hipError_t launch_fork(const DevSim &dst, const DevSim &src, int n_signals, hipStream_t st);
 // jerk-actuated step of every agent; actions [A] uint8 indices 0..11
 hipError_t launch_step_jerk(const DevSim &s, const uint8_t *actions, hipStream_t st);
 // infraction check of every agent; flags_out (optional) [A] gets bit 0
@@ -204,7 +208,7 @@ size_t render_lds_bytes(int width, int height, const LaunchCfg &c, int fast);
 // view_begin + n_views); c.cover: rgb only, one road colour, width >= 16
 hipError_t launch_raycast(const DevSim &s, const RenderOut &o, const RcCfg &c, int view_begin, int n_views, hipStream_t st);
 size_t raycast_lds_bytes(int width, int height, const RcCfg &c);
-// general raster (gp_full.hip): any outputs, road colours, light and traffic
+// general raster (gp_full.h): any outputs, road colours, light and traffic
 // lights; workgroup b renders view order[b] (ordered) or view_begin + b
 hipError_t launch_render_full(const DevSim &s, const RenderOut &o, const FullCfg &c, int ordered, int view_begin, int grid,
                               hipStream_t st);

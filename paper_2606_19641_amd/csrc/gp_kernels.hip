@@ -42,6 +42,8 @@
 #include "gp_device.h"
 #include "gp_geom.h"
 
+#include <algorithm>
+
 namespace gp {
 
 // ------------------------------------------------------------ agent step
@@ -137,6 +139,37 @@ __global__ void k_cs(DevSim s, int clear_halted)
     float sp, cp;
     dev_sincos(s.state[i].z, sp, cp);
     s.cs[i] = make_float2(cp, sp);
+}
+
+// A new episode's agent states from src [A][4], their heading cosines, and halted
+// flags and jerk actuators cleared.  (A copy and a kernel of its own behind it
+// cost 10 us at 2,048 agents, this 5: launches.)
+struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };     // any tensor's row
+__global__ void k_set_state(DevSim s, const Float4u *__restrict__ src)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= s.n_agents) return;
+    const Float4u q = src[i];
+    float sp, cp;
+    dev_sincos(q.z, sp, cp);
+    s.state[i] = make_float4(q.x, q.y, q.z, q.w);
+    s.cs[i] = make_float2(cp, sp);
+    s.halted[i] = 0;
+    s.actu[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+// dst's dynamic state from src's, sims of the same scenes: one launch instead of
+// four or five copies.
+__global__ void k_fork(DevSim dst, DevSim src, int n_signals)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < src.n_agents) {
+        dst.state[i] = src.state[i];
+        dst.cs[i] = src.cs[i];
+        dst.halted[i] = src.halted[i];
+        dst.actu[i] = src.actu[i];
+    }
+    if (i < n_signals) dst.signal_color[i] = src.signal_color[i];
 }
 
 // ------------------------------------------------------------ infractions
@@ -1275,6 +1308,22 @@ hipError_t launch_cs(const DevSim &s, int clear_halted, hipStream_t st)
 {
     const int B = 256;
     hipLaunchKernelGGL(k_cs, dim3((s.n_boxes + B - 1) / B), dim3(B), 0, st, s, clear_halted);
+    return hipGetLastError();
+}
+
+hipError_t launch_set_state(const DevSim &s, const float *src, hipStream_t st)
+{
+    if (s.n_agents <= 0) return hipSuccess;
+    const int B = 256;
+    hipLaunchKernelGGL(k_set_state, dim3((s.n_agents + B - 1) / B), dim3(B), 0, st, s, reinterpret_cast<const Float4u *>(src));
+    return hipGetLastError();
+}
+
+hipError_t launch_fork(const DevSim &dst, const DevSim &src, int n_signals, hipStream_t st)
+{
+    const int B = 256, n = std::max(src.n_agents, n_signals);
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fork, dim3((n + B - 1) / B), dim3(B), 0, st, dst, src, n_signals);
     return hipGetLastError();
 }
 

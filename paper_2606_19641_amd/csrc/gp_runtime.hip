@@ -1206,12 +1206,29 @@ gp_status gp_sim_get_state(gp_sim *sim, float *d_dst, void *stream)
     return e == hipSuccess ? GP_OK : hip_fail(e, "get_state copy");
 }
 
+// is p memory of the sim's device, so that a kernel may read it, at float alignment?
+static bool device_memory_of(const gp_sim *sim, const void *p)
+{
+    hipPointerAttribute_t a{};
+    if (reinterpret_cast<uintptr_t>(p) % 4 != 0) return false;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == sim->device;
+}
+
 gp_status gp_sim_set_state(gp_sim *sim, const float *d_src, void *stream)
 {
     if (!sim || !d_src) return fail(GP_EINVAL, "NULL argument");
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = hipMemcpyAsync(sim->dev.state, d_src, 16 * (size_t)sim->lay.n_agents,
-                                  hipMemcpyDeviceToDevice, hs);
+    hipError_t e;
+    if (device_memory_of(sim, d_src)) {
+        e = gp::launch_set_state(sim->dev, d_src, hs);
+        return e == hipSuccess ? GP_OK : hip_fail(e, "set_state");
+    }
+    // any other memory is copied by the runtime
+    e = hipMemcpyAsync(sim->dev.state, d_src, 16 * (size_t)sim->lay.n_agents, hipMemcpyDeviceToDevice, hs);
     if (e != hipSuccess) return hip_fail(e, "set_state copy");
     e = gp::launch_cs(sim->dev, 1, hs);
     return e == hipSuccess ? GP_OK : hip_fail(e, "heading cosines");
@@ -1293,7 +1310,12 @@ gp_status gp_sim_fork(gp_sim *dst, const gp_sim *src, void *stream)
             return fail(GP_EINVAL, "fork needs sims over the same scenes (scene %d differs)", k);
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const size_t n = (size_t)src->lay.n_agents;
-    hipError_t e = hipMemcpyAsync(dst->dev.state, src->dev.state, 16 * n, hipMemcpyDeviceToDevice, hs);
+    hipError_t e;
+    if (dst->device == src->device) {
+        e = gp::launch_fork(dst->dev, src->dev, (int)src->lay.n_signals, hs);
+        return e == hipSuccess ? GP_OK : hip_fail(e, "fork");
+    }
+    e = hipMemcpyAsync(dst->dev.state, src->dev.state, 16 * n, hipMemcpyDeviceToDevice, hs);
     if (e == hipSuccess) e = hipMemcpyAsync(dst->dev.cs, src->dev.cs, 8 * n, hipMemcpyDeviceToDevice, hs);
     if (e == hipSuccess) e = hipMemcpyAsync(dst->dev.halted, src->dev.halted, n, hipMemcpyDeviceToDevice, hs);
     if (e == hipSuccess) e = hipMemcpyAsync(dst->dev.actu, src->dev.actu, 16 * n, hipMemcpyDeviceToDevice, hs);
