@@ -222,6 +222,7 @@ hipError_t launch_render_rgb(const DevSim &s, const RenderOut &o, const RgbCfg &
 hipError_t launch_render_rgb_multi(const SimEntry *tab, const int2 *items, int n_items, const RgbCfg &c, int width,
                                    int height, hipStream_t st);
 size_t rgb_lds_bytes(int width, int height, const RgbCfg &c);
+constexpr int kFaceBytes = 64;            // LDS of one list entry
 // chip-wide rgb raster (gp_chip.hip), same conditions as the wave-split one
 // plus 64 <= width <= 1024: the setup pass over views [view_begin,
 // view_begin + n_views) (mode 0) or every view in order[] (mode 1), the road

@@ -864,7 +864,7 @@ struct FaceRec {
     uint32_t rgb;
     int32_t odd;          // plane_odd
 };
-static_assert(sizeof(FaceRec) == 64 && offsetof(FaceRec, A) == 32 && offsetof(FaceRec, j0) == 48, "FaceRec layout");
+static_assert(sizeof(FaceRec) == kFaceBytes && offsetof(FaceRec, A) == 32 && offsetof(FaceRec, j0) == 48, "FaceRec layout");
 
 __device__ __forceinline__ void face_geo(FaceRec &f, const Prim &p)
 {

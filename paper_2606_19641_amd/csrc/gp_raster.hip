@@ -247,7 +247,7 @@ __device__ __forceinline__ void carve_rgb(unsigned char *smem, RgbLds &L, int W,
 // One workgroup per view: view view_begin + blockIdx.x (ordered 0), or
 // order[blockIdx.x].
 template <bool AP>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5))) void k_render_rgb(DevSim s, RenderOut o, RgbCfg c,
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_render_rgb(DevSim s, RenderOut o, RgbCfg c,
                                                                                             int ordered, int view_begin)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5
 // scenes of 8..128 agents at 128 x 128: 62 us per batch, 142 us in the banded
 // queue kernel.
 template <bool AP>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(AP ? 4 : 5))) void k_render_rgb_multi(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_render_rgb_multi(
     const SimEntry *__restrict__ tab, const int2 *__restrict__ items, RgbCfg c)
 {
     extern __shared__ __align__(16) unsigned char smem[];

@@ -347,14 +347,23 @@ gp_status check_lds(const gp_sim *sim, const gp_launch &l)
     return GP_OK;
 }
 
-// Box faces (and traffic lights) one view's list holds in the split rasteriser.
-// A view of the largest scenes lists about twenty; one that may list more than
-// 64 takes memory of its road work for them (LDS of 27 KB instead, a list for
-// 3/2 of 128 boxes, left five workgroups to a CU: 64 scenes of 4..128 agents
-// with three cameras at 128 x 128 428 us per step, here 310).  A view that
-// overflows its list all the same is rendered by the streaming pass, several
-// times slower.
-constexpr int kListFaces = 64;
+// Box faces (and traffic lights) one view's list holds in the split rasteriser:
+// what fits a workgroup's share of LDS when sixteen wavefronts reside on a CU
+// (10 KB per wavefront; the registers allow no more), 64 at least, three per box
+// and one per light at most.  A view that may list more takes memory of its road
+// work for them; one that overflows its list all the same is rendered by the
+// streaming pass, several times slower.  (LDS of 27 KB, a list for 3/2 of 128
+// boxes, left five workgroups of two wavefronts to a CU: 64 scenes of 4..128 agents
+// with three cameras at 128 x 128 428 us per step, here 270.)
+void size_list(gp::RgbCfg &c, int width, int height, int64_t entries)
+{
+    c.bcap = 64;
+    const int64_t spare = 10240LL * c.waves - (int64_t)gp::rgb_lds_bytes(width, height, c);
+    const int64_t fit = 64 + std::max<int64_t>(0, spare) / (int64_t)gp::kFaceBytes;
+    c.bcap = (int)std::max<int64_t>(64, std::min<int64_t>(256, std::min(fit, entries)));
+}
+
+int64_t list_entries(const gp_sim *sim) { return 3LL * sim->boxes_cap + sim->signals_cap; }
 
 // The same in the general raster: a box shows at most three faces, one entry
 // each, and a view sees about a quarter of its scene's boxes.
@@ -394,9 +403,9 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
 {
     gp::RgbCfg c;
     c.waves = split_waves(sim, l, n_views);
-    c.bcap = kListFaces;
     c.recs = box_recs(sim);
     c.bins_cap = std::min(sim->bins_cap, 256);
+    size_list(c, sim->cfg.width, sim->cfg.height, list_entries(sim));
     c.appear = (sim->dev.shade || sim->lay.n_signals > 0) ? 1 : 0;
     return c;
 }
@@ -1122,10 +1131,13 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
     const gp::LaunchCfg c = launch_cfg(l);
     const int W = sims[0]->cfg.width, H = sims[0]->cfg.height;
     gp::RgbCfg rc = rgb_cfg(sims[0], l, n_views);
+    int64_t entries = list_entries(sims[0]);
     for (int k = 1; k < n_sims; ++k) {
+        entries = std::max(entries, list_entries(sims[k]));
         rc.recs = std::max(rc.recs, box_recs(sims[k]));
         rc.bins_cap = std::max(rc.bins_cap, std::min(sims[k]->bins_cap, 256));
     }
+    size_list(rc, W, H, entries);
     const bool split = l.raster == GP_RASTER_SPLIT && W >= 16 && gp::rgb_lds_bytes(W, H, rc) <= sims[0]->max_lds;
     enum { B_SPLIT = 0, B_APPEAR, B_FAST, B_GENERAL, B_N };
     auto group_of = [&](const gp_sim *sim) {
