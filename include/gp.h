@@ -139,7 +139,7 @@ typedef struct {
     int32_t blocks_per_cu;    /* persistent grid = blocks_per_cu * CUs (1..16)         */
     int32_t raster;           /* gp_raster                                            */
     int32_t view_waves;       /* split: wavefronts per view: 1, 2 or 4 (times 2 from 32K and 4
-                                 from 200K pixels, and doubled, up to 16, while every view's
+                                 from 105K pixels, and doubled, up to 16, while every view's
                                  wavefronts fit the chip at once)                       */
     int32_t road_wgs_per_cu;  /* chip: road-pass workgroups (4 wavefronts) per CU, 1..16 */
 } gp_launch;

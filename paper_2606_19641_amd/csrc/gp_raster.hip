@@ -36,13 +36,15 @@
 //              samples, each lane folding the 64-bit keys of its 16 samples in
 //              registers and writing 48 bytes.
 //
-// What bounds it: an image is a write stream, but the launch lasts as long as
-// its instruction issue and its slowest views, not its stores.  Measured on one
-// MI355X, render alone: 2,048 views at 128 x 128 54 us (1.9 TB/s; 60 us with
-// padded coverage rows and 48-byte stores), 8,192 views at 210 x 126 205 us
-// (3.2 TB/s; 464 us in the banded kernel, which took every width that is no
-// multiple of 16), at 434 x 252 563 us (4.8 TB/s; 1,478 us), 4,096 views at
-// 512 x 512 687 us (4.7 TB/s; 2,104 us in the chip-wide passes).
+// What bounds it: an image is a write stream, but at 128 x 128 the launch lasts as
+// long as its views' chains of loads and LDS round trips (a wavefront waits for
+// half of its time) and its slowest views; scenes of up to 128 agents are bound by
+// VALU issue (73% busy), images from 434 x 252 on mostly by their stores.  Step +
+// render on one MI355X, before the wave-split raster took a size / now: 2,048 views
+// at 128 x 128 74 / 45 us (2.2 TB/s), 8,192 views at 210 x 126 480 / 177 us (3.7
+// TB/s), at 434 x 252 1,505 / 553 us (4.9 TB/s), 4,096 views at 512 x 512 2,140 / 655
+// us (4.9 TB/s), 64 scenes of 4..128 agents with three cameras at 128 x 128 2,730 /
+// 265 us.
 //
 // Every float operation is written out (fmaf for fused operations) and the
 // file is compiled with -ffp-contract=off, correctly rounded division and
@@ -61,8 +63,8 @@ namespace {
 // themselves in once their reads are done (the barrier before has every
 // wavefront past them), and the one that completes the count steps the scene's
 // agents and clears it.  A step kernel of its own before the render costs 5 us
-// of start and drain: step + render of 2,048 views at 128 x 128 60.0 us, here
-// 52.3 us.
+// of start and drain: step + render of 2,048 views at 128 x 128 60.0 us, so 52.3
+// us when this was built.
 __device__ __forceinline__ int view_arrives(const DevSim &s, int scene)
 {
     int n = 0;
@@ -84,7 +86,7 @@ __device__ __forceinline__ void step_scene(const DevSim &s, const SceneRec &sc, 
 // they add nothing to the plain ones).  Lit streets used to take the general
 // kernel, which folds every road strip's keys with 64-bit LDS atomics and
 // writes single bytes: 2,048 views at 128 x 128 with 16 obstacles and 12 lights
-// a scene 326 us, here 77 us.  cam_index: the view's camera in s.cam_dir (0 in a
+// a scene 326 us, here 56 us.  cam_index: the view's camera in s.cam_dir (0 in a
 // batch's copy of the sim's record, which holds the view's direction only).
 template <bool AP>
 __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, RgbLds L, const ViewInit &vi, int cam_index)
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
 // (sim, view) pair.  The sim's record is copied out of the table with its
 // view's camera only: a copy indexed by camera would live in scratch memory,
 // and a record read in place would be loaded again after every store.  Eight
-// scenes of 8..128 agents at 128 x 128: 62 us per batch, 142 us in the banded
+// scenes of 8..128 agents at 128 x 128: 60 us per batch, 142 us in the banded
 // queue kernel.
 template <bool AP>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_render_rgb_multi(
