@@ -355,10 +355,10 @@ gp_status check_lds(const gp_sim *sim, const gp_launch &l)
 // streaming pass, several times slower.  (LDS of 27 KB, a list for 3/2 of 128
 // boxes, left five workgroups of two wavefronts to a CU: 64 scenes of 4..128 agents
 // with three cameras at 128 x 128 428 us per step, here 270.)
-void size_list(gp::RgbCfg &c, int width, int height, int64_t entries)
+void size_list(gp::RgbCfg &c, int width, int height, int64_t entries, size_t max_lds)
 {
     c.bcap = 64;
-    const int64_t spare = 10240LL * c.waves - (int64_t)gp::rgb_lds_bytes(width, height, c);
+    const int64_t spare = std::min<int64_t>(10240LL * c.waves, (int64_t)max_lds) - (int64_t)gp::rgb_lds_bytes(width, height, c);
     const int64_t fit = 64 + std::max<int64_t>(0, spare) / (int64_t)gp::kFaceBytes;
     c.bcap = (int)std::max<int64_t>(64, std::min<int64_t>(256, std::min(fit, entries)));
 }
@@ -405,7 +405,7 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
     c.waves = split_waves(sim, l, n_views);
     c.recs = box_recs(sim);
     c.bins_cap = std::min(sim->bins_cap, 256);
-    size_list(c, sim->cfg.width, sim->cfg.height, list_entries(sim));
+    size_list(c, sim->cfg.width, sim->cfg.height, list_entries(sim), sim->max_lds);
     c.appear = (sim->dev.shade || sim->lay.n_signals > 0) ? 1 : 0;
     return c;
 }
@@ -1137,7 +1137,7 @@ gp_status gp_batch_step_render(gp_sim *const *sims, int32_t n_sims, const float 
         rc.recs = std::max(rc.recs, box_recs(sims[k]));
         rc.bins_cap = std::max(rc.bins_cap, std::min(sims[k]->bins_cap, 256));
     }
-    size_list(rc, W, H, entries);
+    size_list(rc, W, H, entries, sims[0]->max_lds);
     const bool split = l.raster == GP_RASTER_SPLIT && W >= 16 && gp::rgb_lds_bytes(W, H, rc) <= sims[0]->max_lds;
     enum { B_SPLIT = 0, B_APPEAR, B_FAST, B_GENERAL, B_N };
     auto group_of = [&](const gp_sim *sim) {
