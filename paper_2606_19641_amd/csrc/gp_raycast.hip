@@ -39,9 +39,9 @@
 // in bands of LDS.
 //
 // Bound by VALU issue.  One MI355X: 2,048 views at 128 x 128 (32 agents, 2,000
-// strips) 116 us (1,100 us with the tests dealt by pixel; 218 us before the
+// strips) 110 us (1,100 us with the tests dealt by pixel; 218 us before the
 // certain runs of boxes and strips were taken without the full test), 16 scenes
-// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 403 us
+// of 8..64 agents, four cameras at 210 x 126, lit, with depth and ids 390 us
 // (474 us with 64-bit keys of strips too, 2,400 us by pixel).
 #include "gp_view.h"
 

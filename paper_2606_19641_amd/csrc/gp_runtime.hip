@@ -410,6 +410,18 @@ gp::RgbCfg rgb_cfg(const gp_sim *sim, const gp_launch &l, int64_t n_views)
     return c;
 }
 
+// A key band some rows smaller where that lets sixteen wavefronts reside on a CU
+// (10 KB of LDS per wavefront; the registers allow no more): up to a quarter of
+// its rows, sixteen left at least, below that the further bands cost more (the ray
+// caster at 333 x 200, ten rows instead of twelve: 362 -> 386 us).  The ray caster's
+// 32 rows of 128 samples made 41,024 bytes for four wavefronts, three workgroups to
+// a CU: 2,048 views 127 us, with 31 rows 110; with 128 agents a scene 399, 381.
+void trim_band(int &rows, int row_bytes, int64_t lds, int waves)
+{
+    const int64_t cut = (lds - 10240LL * waves + row_bytes - 1) / row_bytes;
+    if (cut > 0 && cut <= rows / 4 && rows - cut >= 16) rows -= (int)cut;
+}
+
 // Settings of the general raster: wavefronts per view (4, 8 from 60K pixels on)
 // and samples of the band of road keys (1,024 per wavefront, 8,192 at most).  A
 // larger band leaves room for fewer workgroups in LDS, a smaller one repeats the
@@ -430,6 +442,7 @@ gp::FullCfg full_cfg(const gp_sim *sim)
     c.bins_cap = sim->bins_cap;
     const int samples = std::min(1024 * c.waves, 8192), rows = sim->cfg.height / 2;     // rows below the horizon
     c.band_rows = std::max(1, std::min(rows, samples / sim->cfg.width));
+    trim_band(c.band_rows, 4 * sim->cfg.width, (int64_t)gp::full_lds_bytes(sim->cfg.width, c), c.waves);
     return c;
 }
 
@@ -457,6 +470,8 @@ gp::RcCfg rc_cfg(const gp_sim *sim, bool rgb_only)
     c.bins_cap = sim->bins_cap;
     if (c.cover) c.band_rows = std::min(sim->cfg.height, std::max(1, 4096 / sim->cfg.width));
     else c.band_rows = std::max(1, std::min(sim->cfg.height / 2, std::min(1024 * c.waves, 8192) / sim->cfg.width));
+    trim_band(c.band_rows, (c.cover ? 8 : 4) * sim->cfg.width, (int64_t)gp::raycast_lds_bytes(sim->cfg.width, sim->cfg.height, c),
+              c.waves);
     return c;
 }
 
