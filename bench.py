@@ -4,7 +4,7 @@ One step = the kinematic step of every agent + the render of every view
 (rgb, uint8) of one batch of synthetic scenes already resident in HBM.
 Default workload: 64 scenes x 32 agents, 2,000 road quads each, one forward
 camera at 128x128.  The batched form (one persistent-kernel render plus the
-step, replayed as one hipGraph) is timed, and the plain form (per-scene
+step: one launch, or one hipGraph replay) is timed, and the plain form (per-scene
 launches of the same kernels) is timed beside it on the same GPU.
 
 Prints ONE JSON line.  With --gpus N > 1 it exits with a message: the path
@@ -486,7 +486,7 @@ def main():
                                 if launch.get("raster") == 1 else
                                 "three chip-wide passes" if launch.get("raster") == 2 else
                                 "persistent work queue (one workgroup per view when the views fit the resident grid)")
-                               + " + hipGraph (step + render)",
+                               + ("; one launch steps and renders" if launch.get("raster") == 1 else " + hipGraph (step + render)"),
                    "launch": launch},
         "plain_value": plain,
         "batched_over_plain": (batched / plain) if plain else None,
