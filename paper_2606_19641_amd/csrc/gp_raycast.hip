@@ -437,11 +437,24 @@ __device__ __forceinline__ void rc_boxes(const DevSim &s, const SceneRec &sc, co
             if ((z[k] >= zc) != (z[k1] >= zc)) point(fmaf((zc - z[k]) / (z[k1] - z[k]), x[k1] - x[k], x[k]), zc);
         }
         const float Wf = (float)cam.W, Hf = (float)cam.H;
-        const int i0 = max(0, (int)fminf(fmaxf(floorf(umin - 0.5f) - 1.0f, -1.0f), Wf));
-        const int i1 = min(cam.W - 1, (int)fminf(fmaxf(ceilf(umax - 0.5f) + 1.0f, -1.0f), Wf));
-        const int j0 = max(0, (int)fminf(fmaxf(floorf(vmin - 0.5f) - 1.0f, -1.0f), Hf));
-        const int j1 = min(cam.H - 1, (int)fminf(fmaxf(ceilf(vmax - 0.5f) + 1.0f, -1.0f), Hf));
+        int i0 = max(0, (int)fminf(fmaxf(floorf(umin - 0.5f) - 1.0f, -1.0f), Wf));
+        int i1 = min(cam.W - 1, (int)fminf(fmaxf(ceilf(umax - 0.5f) + 1.0f, -1.0f), Wf));
+        int j0 = max(0, (int)fminf(fmaxf(floorf(vmin - 0.5f) - 1.0f, -1.0f), Hf));
+        int j1 = min(cam.H - 1, (int)fminf(fmaxf(ceilf(vmax - 0.5f) + 1.0f, -1.0f), Hf));
         keep = (umin <= umax) & !(zmin > 1.01f * (cam.zf * s2)) & (i0 <= i1) & (j0 <= j1);
+        // A negative size turns a box inside out (its exit comes before its entry:
+        // no hit), and where a corner is 100 km off or no number at all neither a
+        // crossing of the near plane nor the runs of rc_certain are to be relied on:
+        // such boxes take the slab test of every sample, of the whole image where
+        // they reach behind the near plane
+        const float far = fabsf(ox) + fabsf(oy) + fabsf(ax) + fabsf(ay) + fabsf(bx) + fabsf(by);
+        const bool plain = (dm.x >= 0.0f) & (dm.y >= 0.0f) & (dm.z >= 0.0f) & (dm.z < 1e5f) & (far < 1e5f);
+        if (!plain & (zmin < zc)) {
+            i0 = j0 = 0;
+            i1 = cam.W - 1;
+            j1 = cam.H - 1;
+            keep = true;
+        }
         f.X0 = __float_as_int(st.x); f.Y0 = __float_as_int(st.y);
         f.X1 = __float_as_int(cs.x); f.Y1 = __float_as_int(cs.y);
         f.X2 = __float_as_int(0.5f * dm.x); f.Y2 = __float_as_int(0.5f * dm.y);
@@ -458,6 +471,7 @@ __device__ __forceinline__ void rc_boxes(const DevSim &s, const SceneRec &sc, co
         f.keylo = key_low(1u, 6 * u, 0u);
         f.j0 = (int16_t)j0; f.j1 = (int16_t)j1;
         f.nv = 1;
+        f.huge = !plain;
     }
     const unsigned long long bm = __ballot(keep);
     int nbt = 0;
@@ -539,7 +553,8 @@ __device__ __forceinline__ unsigned long long rc_box_key(const Cam &cam, const f
 // two slabs, and within [z_near, z_far], where seven affine functions of a are
 // positive.  The margin (2^-16 of the distances in play) dominates the rounding
 // of the exact test, so on these columns that test takes this side and
-// accepts the hit: only its division is left to do.
+// accepts the hit: only its division is left to do.  (Boxes of finite sizes that
+// are not negative: else the runs need be neither right nor disjoint.)
 __device__ __forceinline__ void rc_certain(const Cam &cam, const FaceRec &f, float b, int xl, int xr, int *segs)
 {
     const float cb = __int_as_float(f.X1), sb = __int_as_float(f.Y1);
@@ -626,7 +641,7 @@ __device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, 
                 const FaceRec f = lds_load(L.faces + t0 + o);
                 xl = f.X3;
                 xr = f.Y3;
-                if (f.nv != 0) rc_certain(cam, f, cam.cy - ((float)j + 0.5f), xl, xr, segs);
+                if (f.nv != 0 && f.huge == 0) rc_certain(cam, f, cam.cy - ((float)j + 0.5f), xl, xr, segs);
                 int at = xl;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {

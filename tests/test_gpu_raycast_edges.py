@@ -92,3 +92,39 @@ def test_odd_strips_and_far_maps(shift):
                             agent_state=(s.agent_state + np.array([shift, shift, 0, 0])).astype(np.float32))
     cam = g.camera_for(72, 56, g.STUDENT_RIG)
     _check([s], cam, [(0, a, k) for a in range(6) for k in range(4)], shift)
+
+
+@pytest.mark.parametrize("kind", ["inside_out", "endless", "far_wall"])
+def test_boxes_of_odd_sizes(kind):
+    """Boxes whose hits no bound short of the slab test itself may decide: a
+    negative length, width or height (never hit), infinite sizes, and thin walls
+    thousands of kilometres long that pass the camera within a metre."""
+    print(f"raycast odd boxes: {kind}", flush=True)
+    s = g.crowded_scene(21, n_agents=12, n_roads=60, radius=15.0)
+    dims = s.agent_dims.copy()
+    if kind == "inside_out":
+        for a, d in ((3, (0,)), (4, (1,)), (5, (2,)), (6, (0, 1, 2)), (9, (0, 2)), (10, (1, 2))):
+            dims[a, list(d)] *= -1.0
+        dims[7, 0] = dims[8, 2] = 0.0
+    elif kind == "endless":
+        # headings in the camera's quadrant: every corner's depth is an infinity, not a NaN
+        s.agent_state[:, 2] = 0.2 + 0.1 * np.arange(12)
+        for a, d in ((1, 0), (2, 0), (5, 2), (8, 2)):
+            dims[a, d] = np.inf
+    else:
+        rng = np.random.default_rng(4)
+        th, off = rng.uniform(-0.3, 0.3, 40), rng.uniform(-0.6, 0.6, 40)
+        along = rng.uniform(-0.4, 0.4, 40) * 4e6
+        s.agent_state[0] = 0.0
+        s.static_xyp = np.stack([np.cos(th) * along - np.sin(th) * off, np.sin(th) * along + np.cos(th) * off, th],
+                                1).astype(np.float32)
+        s.static_dims = np.tile(np.array([4e6, 0.001, 2.5], np.float32), (40, 1))
+        s.static_color = (2 + np.arange(40) % 3).astype(np.uint8)
+    s = dataclasses.replace(s, agent_dims=dims)
+    cam = g.Camera(width=150, height=60, focal_px=75.0, cam_dirs=g.FRONT)
+    _check([s], cam, [(0, a, 0) for a in range(12)], kind)
+    if kind == "far_wall":                       # one wall at a time: nothing hides a missed column
+        for k in range(0, 40, 2):
+            one = dataclasses.replace(s, static_xyp=s.static_xyp[k:k + 1], static_dims=s.static_dims[k:k + 1],
+                                      static_color=s.static_color[k:k + 1])
+            _check([one], g.Camera(width=300, height=8, focal_px=150.0, cam_dirs=g.FRONT), [(0, 0, 0)], (kind, k))
