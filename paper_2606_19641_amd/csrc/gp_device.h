@@ -158,9 +158,10 @@ struct FullCfg {
 struct RcCfg {
     int waves;        // wavefronts per view: 1..16
     int bcap;         // boxes and lights the LDS list holds, a multiple of 64
-    int bins_cap;     // culling bins of the largest scene
+    int bins_cap;     // surviving culling bins one view's list holds: every bin of the largest scene, or (seg) fewer
     int band_rows;    // rows of the key band (cover: at least), else of the band of road keys
     int cover;        // 1: roads as coverage bits
+    int seg;          // 1: the scene's bins are taken in segments where more survive than the list holds
 };
 
 // Buffers of the chip-wide rgb raster (gp_chip.hip), all inside the

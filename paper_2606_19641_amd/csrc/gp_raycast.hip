@@ -752,7 +752,36 @@ __device__ __forceinline__ void rc_band(const RgbLds &L, const Cam &cam, int n, 
     }
 }
 
-template <bool COV>
+// Bins [s0, s1) of the scene whose strips some row below the horizon can see, into
+// the view's list (R_NSB counts them all, also those that it cannot hold).
+__device__ __forceinline__ void rc_cull(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, float hfs, int H,
+                                        int s0, int s1, int wv, int B)
+{
+    for (int b0 = s0 + 64 * wv; b0 < s1; b0 += B) {
+        const int b = b0 + (int)lane_id();
+        bool keep = false;
+        int rec = 0;
+        if (b < s1) {
+            const RoadBin bn = s.bins[sc.bin_base + b];
+            float x[4], z[4], m;
+            int j0, j1;
+            rc_corners(cam, make_float4(bn.xmin, bn.ymin, bn.xmax, bn.ymin), make_float4(bn.xmax, bn.ymax, bn.xmin, bn.ymax),
+                       x, z);
+            keep = !rc_outside(cam, hfs, x, z, L.hr0, H, j0, j1, m);
+            rec = bn.start * 128 + bn.count;
+        }
+        const unsigned long long bm = __ballot(keep);
+        if (bm == 0ull) continue;
+        int at = 0;
+        if (lane_id() == 0) at = lds_add(L.cnt + R_NSB, __popcll(bm));
+        at = __builtin_amdgcn_readlane(at, 0) + lanes_below(bm);
+        if (keep && at < L.bins) L.sbins[at] = rec;
+    }
+}
+
+// SEG: the scene may have more bins than the list holds (instances of their own:
+// the segments' state spills 35 scalar registers more, 3% of a render of the others)
+template <bool COV, bool SEG>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_raycast(DevSim s, RenderOut o, RcCfg c,
                                                                                          int view_begin)
 {
@@ -798,7 +827,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     __syncthreads();
 
     // ---- bins of the scene whose strips some row can see
-    for (int b0 = 64 * wv; b0 < sc.n_bins; b0 += B) {
+    // (with segments: below; called through rc_cull this loop costs a few spilled
+    // registers more, 1.5% of a render with labels)
+    for (int b0 = 64 * wv; !SEG && b0 < sc.n_bins; b0 += B) {
         const int b = b0 + (int)lane_id();
         bool keep = false;
         int rec = 0;
@@ -832,16 +863,42 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (u < nbu) rc_boxes(s, sc, cam, ego, L, s2, ub * u, ub);
         else rc_lights(s, sc, cam, L, 64 * (u - nbu));
     };
+    // the strips on rows [b0, b1) and the jobs before them; SEG: where more bins
+    // survive than the list holds, the scene's bins in segments that it does hold
+    // (what strips leave is OR-ed or folded, so their order is free).  Ends with a
+    // barrier.
+    bool listed = false, over = false;           // (SEG) the list holds the survivors; there are more
     auto roads = [&](int jobs, int b0, int b1) {
-        road_work(
-            s, sc, L, b0 < b1 ? nsb : 0, jobs,
-            [&](bool live, const float4 &q0, const float4 &q1) -> bool {
-                float x[4], z[4], m;
-                int j0, j1;
-                rc_corners(cam, q0, q1, x, z);
-                return live && !rc_outside(cam, hfs, x, z, b0, b1, j0, j1, m);
-            },
-            box_job, [&](int a, int n) { rc_strips<COV>(s, sc, cam, L, st, road, hfs, s2, a, n, b0, b1, b0); });
+        auto test = [&](bool live, const float4 &q0, const float4 &q1) -> bool {
+            float x[4], z[4], m;
+            int j0, j1;
+            rc_corners(cam, q0, q1, x, z);
+            return live && !rc_outside(cam, hfs, x, z, b0, b1, j0, j1, m);
+        };
+        auto strips = [&](int a, int n) { rc_strips<COV>(s, sc, cam, L, st, road, hfs, s2, a, n, b0, b1, b0); };
+        if constexpr (!SEG) {
+            road_work(s, sc, L, b0 < b1 ? nsb : 0, jobs, test, box_job, strips);
+        } else {
+            for (int s0 = 0;;) {
+                if (!listed) {
+                    __syncthreads();             // the counters are read
+                    if (tid == 0) L.cnt[R_NSB] = L.cnt[R_RING] = L.cnt[R_JOB] = 0;
+                    __syncthreads();
+                    rc_cull(s, sc, cam, L, hfs, H, s0, over ? min(s0 + L.bins, sc.n_bins) : sc.n_bins, wv, B);
+                    __syncthreads();
+                    const bool fits = L.cnt[R_NSB] <= L.bins;
+                    listed = fits & !over;
+                    if (!fits) {
+                        over = true;
+                        continue;
+                    }
+                }
+                road_work(s, sc, L, b0 < b1 ? L.cnt[R_NSB] : 0, jobs, test, box_job, strips);
+                jobs = 0;
+                s0 += L.bins;
+                if (!over || s0 >= sc.n_bins) return;
+            }
+        }
     };
     // the entries of rows [b0, b1) folded into the (cleared) key band; ends with a barrier
     auto boxes = [&](int b0, int b1) {
@@ -959,8 +1016,9 @@ hipError_t launch_raycast(const DevSim &s, const RenderOut &o, const RcCfg &c, i
         return hipErrorInvalidValue;
     const size_t lds = raycast_lds_bytes(s.width, s.height, c);
     const dim3 block(64 * c.waves);
-    if (c.cover) hipLaunchKernelGGL(k_raycast<true>, dim3(n_views), block, lds, st, s, o, c, view_begin);
-    else hipLaunchKernelGGL(k_raycast<false>, dim3(n_views), block, lds, st, s, o, c, view_begin);
+    const auto kernel = c.cover ? (c.seg ? k_raycast<true, true> : k_raycast<true, false>)
+                                : (c.seg ? k_raycast<false, true> : k_raycast<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(n_views), block, lds, st, s, o, c, view_begin);
     return hipGetLastError();
 }
 

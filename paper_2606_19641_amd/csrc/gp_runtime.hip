@@ -468,8 +468,16 @@ gp::RcCfg rc_cfg(const gp_sim *sim, bool rgb_only)
     while (c.waves < 16 && 2 * c.waves * sim->lay.n_views <= 16 * (int64_t)sim->n_cu) c.waves *= 2;
     c.bcap = (int)std::min<int64_t>(256, ((int64_t)sim->boxes_cap + sim->signals_cap + 63) / 64 * 64);
     c.bins_cap = sim->bins_cap;
+    c.seg = 0;
     if (c.cover) c.band_rows = std::min(sim->cfg.height, std::max(1, 4096 / sim->cfg.width));
     else c.band_rows = std::max(1, std::min(sim->cfg.height / 2, std::min(1024 * c.waves, 8192) / sim->cfg.width));
+    // A list of every bin is the faster one as long as it fits (32 views 434 x 252,
+    // rgb: 130K strips 424 us, 448 with segments of 1,024 bins, 445 of 4,096; 200K 508,
+    // 544, 540; with labels 603, 729, 593 and 855, 1,043, 844): segments only beyond
+    if ((int64_t)gp::raycast_lds_bytes(sim->cfg.width, sim->cfg.height, c) > (int64_t)sim->max_lds) {
+        c.bins_cap = std::min(sim->bins_cap, 4096);
+        c.seg = 1;
+    }
     trim_band(c.band_rows, (c.cover ? 8 : 4) * sim->cfg.width, (int64_t)gp::raycast_lds_bytes(sim->cfg.width, sim->cfg.height, c),
               c.waves);
     return c;

@@ -128,3 +128,50 @@ def test_boxes_of_odd_sizes(kind):
             one = dataclasses.replace(s, static_xyp=s.static_xyp[k:k + 1], static_dims=s.static_dims[k:k + 1],
                                       static_color=s.static_color[k:k + 1])
             _check([one], g.Camera(width=300, height=8, focal_px=150.0, cam_dirs=g.FRONT), [(0, 0, 0)], (kind, k))
+
+
+def _dense_map(seed, n_agents, n_near, n_far):
+    """n_near short strips within 60 m of the agents (thousands of culling bins in
+    a view) and n_far scattered over 60 km (a bin of their own each)."""
+    s = _one_colour(g.crowded_scene(seed, n_agents=n_agents, n_roads=8, radius=15.0))
+    rng = np.random.default_rng(seed)
+    c = np.concatenate([rng.uniform(-60, 60, (n_near, 1, 2)), rng.uniform(-3e4, 3e4, (n_far, 1, 2))])
+    q = np.array([[-1, -0.4], [1, -0.4], [1, 0.4], [-1, 0.4]]) * rng.uniform(0.2, 0.9, (len(c), 1, 1))
+    roads = np.concatenate([s.road_xy.astype(np.float64), c + q])
+    return dataclasses.replace(s, road_xy=roads.astype(np.float32), road_color=np.full(len(roads), 1, np.uint8))
+
+
+@pytest.mark.parametrize("n_near,n_far", [(4000, 0), (30000, 0), (450000, 0), (3000, 400000)])
+@pytest.mark.parametrize("size", [(40, 30), (12, 10)])
+def test_more_bins_than_the_list_holds(n_near, n_far, size):
+    """Scenes up to more culling bins than LDS holds, most of them out of sight or
+    more in one view than its list holds; few views and many."""
+    print(f"raycast bins: {n_near} near, {n_far} far strips at {size}", flush=True)
+    cam = g.Camera(width=size[0], height=size[1], focal_px=size[0] / 2.0, cam_dirs=g.FRONT_AND_SIDES)
+    some = n_near + n_far < 100000
+    many = [_dense_map(5, 90 if some else 3, n_near, n_far)]
+    if some:
+        many = many * 4 + [_dense_map(6, 2, 50, 0)]
+    _check(many, cam, [(0, a, k) for a in (0, 2) for k in range(3)] + ([(4, 1, 0)] if some else []), (n_near, size))
+    two = dataclasses.replace(many[0], road_color=(1 + 4 * (np.arange(len(many[0].road_color)) % 2)).astype(np.uint8))
+    _check([two], cam, [(0, 1, k) for k in range(3)], (n_near, size, "two colours"))
+
+
+def test_largest_image_of_a_large_map():
+    """1024 x 600, where the coverage bits alone take 38 KB of LDS: rgb-only equal
+    to the render with labels (no coverage bits), and the 8 rows about the horizon
+    equal to the oracle's image of those rows alone (the same rays)."""
+    from paper_2606_19641_amd import gp
+    print("raycast 1024 x 600, 165,000 strips", flush=True)
+    s = _dense_map(7, 2, 5000, 160000)
+    big, band = (g.Camera(width=1024, height=h, focal_px=512.0, cam_dirs=g.FRONT) for h in (600, 8))
+    pal = g.mixed_palette()
+    sim = gp.Sim([s], big, pal)
+    only, _, _ = sim.render_raycast()
+    rgb, d, p = sim.render_raycast(depth=True, primid=True)
+    torch.cuda.synchronize()
+    assert torch.equal(only, rgb)
+    ref = oracle.render_scene_view(s, band, pal, 1, 0, backend="raycast")
+    assert np.array_equal(rgb[1, 296:304].cpu().numpy(), ref.rgb)
+    assert np.array_equal(p[1, 296:304].cpu().numpy(), ref.primid)
+    assert np.array_equal(d[1, 296:304].cpu().numpy().view(np.uint32), ref.depth.view(np.uint32))
