@@ -156,6 +156,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int nsb = L.cnt[R_NSB], nsv = L.cnt[R_NSV];
     const int ubox = box_unit(K);
     const int nbu = nsv <= L.nrec ? (nsv + ubox - 1) / ubox : 0, nlu = (sc.n_signals + 63) / 64;
+    const int most = 3 * nsv + sc.n_signals;
+    if (most > L.bcap && nsv <= L.nrec) grow_list(L, most, K, W);
     WaveSt ws = wave_state(L, wv);
     const int64_t view_px = (int64_t)view * H * W;
     int nbt = 0, kr0 = H, kr1 = H;               // listed entries, the rows that they reach
@@ -200,6 +202,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
                 kr0 = L.cnt[R_BMIN];
                 kr1 = L.cnt[R_BMAX] + 1;
             }
+            // streamed entries: a shorter list leaves more rows to a band of keys (300
+            // crowded boxes 2,080 us; with 192 entries 1,755, with 128 1,583)
+            if (ovf) L.bcap = min(L.bcap, 128);
             free_region(L, ovf ? L.bcap : nbt, W);
         }
         const int r0 = first ? 0 : b0;

@@ -118,29 +118,8 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     // road work ahead grows with the surviving bins (a mean view keeps about a dozen)
     const int prio_b = nsb >= 24 ? 2 : (nsb >= 16 ? 1 : 0);
     view_priority(prio_b);
-    // a view that may list more faces (three a box) than its list holds gives it
-    // memory of its ring, as much as it needs down to kSmallRing, then of the
-    // staging; with four to seven wavefronts of the staging first: their jobs are
-    // small, and a small ring means more rounds (a batch of eight rollouts of
-    // 8..128 agents 67 us per step, 64 so)
     const int most = 3 * nsv + (AP ? sc.n_signals : 0);
-    if (most > L.bcap && nsv <= L.nrec) {
-        const int half = K * (wave_bytes(kBatch) - wave_bytes(kSmallBatch));
-        int lack = (min(most, 256) - L.bcap) * (int)sizeof(FaceRec);
-        if (K >= 4 && K < 8) {
-            L.batch = kSmallBatch;
-            lack -= half;
-        }
-        if (lack > 0) {
-            L.ring = max(kSmallRing, kSharedRing - 64 * ((lack + 255) >> 8));
-            lack -= 4 * (kSharedRing - L.ring);
-        }
-        if (lack > 0) L.batch = kSmallBatch;
-        const int tail = 4 * L.ring + K * wave_bytes(L.batch);
-        L.bcap = max(L.bcap, min(256, (L.tail - max(tail, resolve_bytes(W))) / (int)sizeof(FaceRec)));
-        L.sring = (lptr<int32_t>)((lptr<unsigned char>)L.faces + L.tail - tail);
-        L.waves = (lptr<unsigned char>)(L.sring + L.ring);
-    }
+    if (most > L.bcap && nsv <= L.nrec) grow_list(L, most, K, W);
     WaveSt ws = wave_state(L, wv);
     // more surviving bins than the list holds: the scene's bins in segments that
     // it does hold

@@ -118,6 +118,30 @@ __device__ __forceinline__ WaveSt wave_state(const RgbLds &L, int wv)
     return ws;
 }
 
+// A view that may list more faces (three a box) than its list holds gives it
+// memory of its ring, as much as it needs down to kSmallRing, then of the
+// staging; with four to seven wavefronts of the staging first: their jobs are
+// small, and a small ring means more rounds (a batch of eight rollouts of
+// 8..128 agents 67 us per step, 64 so).  Before the first wave_state.
+__device__ __forceinline__ void grow_list(RgbLds &L, int most, int K, int W)
+{
+    const int half = K * (wave_bytes(kBatch) - wave_bytes(kSmallBatch));
+    int lack = (min(most, 256) - L.bcap) * (int)sizeof(FaceRec);
+    if (K >= 4 && K < 8) {
+        L.batch = kSmallBatch;
+        lack -= half;
+    }
+    if (lack > 0) {
+        L.ring = max(kSmallRing, kSharedRing - 64 * ((lack + 255) >> 8));
+        lack -= 4 * (kSharedRing - L.ring);
+    }
+    if (lack > 0) L.batch = kSmallBatch;
+    const int tail = 4 * L.ring + K * wave_bytes(L.batch);
+    L.bcap = max(L.bcap, min(256, (L.tail - max(tail, resolve_bytes(W))) / (int)sizeof(FaceRec)));
+    L.sring = (lptr<int32_t>)((lptr<unsigned char>)L.faces + L.tail - tail);
+    L.waves = (lptr<unsigned char>)(L.sring + L.ring);
+}
+
 // The memory behind the list's n faces for the resolve (the ring and the
 // wavefronts' staging are idle by then); after the pattern table's use its
 // place holds the streaming pass's clip queue.
@@ -554,14 +578,15 @@ __device__ __forceinline__ void rec_face(const Cam &cam, const BoxRec &b, int f,
 }
 
 // One setup pass over the faces of box records [r0, r0 + n) (n <= 10): fast
-// faces and the triangles of clipped faces (clip queue cq) are appended to the
-// box list (box_reserve), the low byte of each key word naming the entry;
-// returns false as soon as they would not fit (the list is then incomplete).
+// faces and the triangles of clipped faces (clip queue cq) that have a sample row
+// in [y0, y1) are appended to the box list (box_reserve), the low byte of each key
+// word naming the entry; returns false as soon as they would not fit (the list is
+// then incomplete).
 // One record never overflows a private list of 64 (its six faces have at most
 // 10 triangles each).
 template <bool AP>
 __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, const Cam &cam, const RgbLds &L, int r0, int n,
-                                         lptr<int32_t> cq, bool shared, int &nbt, int &bmin, int &bmax)
+                                         int y0, int y1, lptr<int32_t> cq, bool shared, int &nbt, int &bmin, int &bmax)
 {
     const int ln = (int)lane_id();
     const bool live = ln < 6 * n;
@@ -572,7 +597,7 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
     if (live) {
         const BoxRec b = lds_load(L.recs + r);
         rec_face(cam, b, f, Pf);
-        fast_face(cam, Pf, rec_rgb<AP>(s, sc, b, f), 0, cam.H, f0, v0, f1, v1, clip);
+        fast_face(cam, Pf, rec_rgb<AP>(s, sc, b, f), y0, y1, f0, v0, f1, v1, clip);
     }
     const unsigned long long b0 = __ballot(v0), b1 = __ballot(v1), bc = __ballot(clip);
     const int n0 = __popcll(b0), nf = n0 + __popcll(b1), ncl = __popcll(bc);
@@ -607,7 +632,7 @@ __device__ __forceinline__ bool box_pass(const DevSim &s, const SceneRec &sc, co
             rgb = rec_rgb<AP>(s, sc, b, code & 7);
         }
         TriRec t;
-        const bool ok = clip_seg<true>(cam, Q, lv, 0, cam.H, t);
+        const bool ok = clip_seg<true>(cam, Q, lv, y0, y1, t);
         const unsigned long long bo = __ballot(ok);
         const int ato = box_reserve(L, shared, nbt, __popcll(bo));
         if (ato < 0) return false;
@@ -746,7 +771,7 @@ __device__ __forceinline__ void do_boxes(const DevSim &s, const SceneRec &sc, co
                                          int n_recs, lptr<int32_t> scr)
 {
     int nbt = 0, bmin = 0x7FFFFFFF, bmax = -1;
-    if (box_pass<AP>(s, sc, cam, L, unit * k, min(unit, n_recs - unit * k), scr, true, nbt, bmin, bmax))
+    if (box_pass<AP>(s, sc, cam, L, unit * k, min(unit, n_recs - unit * k), 0, cam.H, scr, true, nbt, bmin, bmax))
         box_rows(L, bmin, bmax);
 }
 
@@ -1324,16 +1349,20 @@ __device__ __forceinline__ void resolve_rows(const DevSim &s, lptr<const uint32_
 
 // The fragments of every box and light in rows [b0, b1) folded into the key
 // band, for views with more boxes than the records or entries than the list
-// hold: as many boxes at a time are culled as there are records, the first wavefront
-// lists the faces of as many as fit, every wavefront folds them (ends with a
-// barrier).
+// hold: as many boxes at a time are culled as there are records, the wavefronts
+// (twelve clip queues fit the idle pattern table) list their faces in these rows,
+// every wavefront folds them; records whose faces overflow the list are listed by
+// the first wavefront, as many at a time as fit (ends with a barrier).  With the
+// first wavefront listing everything, all rows of it in every band, depth and ids of
+// 2,160 views 128 x 128 among 90 crowded boxes took 820 us, now 553, of 1,800 among
+// 300 3,120, now 1,585 (the banded kernel 691 and 2,037).
 template <bool AP, bool STEP>
 __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &sc, const Cam &cam, int ego, const RgbLds &L,
                                                lptr<unsigned long long> keys, int b0, int b1, int wv, int K)
 {
     const int nbox = sc.n_agents + sc.n_static;
     for (int j0 = 0; j0 < nbox; j0 += L.nrec) {
-        if (threadIdx.x == 0) L.cnt[R_NSV] = L.cnt[R_AT] = 0;
+        if (threadIdx.x == 0) L.cnt[R_NSV] = L.cnt[R_AT] = L.cnt[R_NBT] = L.cnt[R_BOVF] = 0;
         __syncthreads();
         if (wv == 0) {
             const int j1 = min(j0 + L.nrec, nbox);
@@ -1341,13 +1370,23 @@ __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &
         }
         __syncthreads();
         const int ns = L.cnt[R_NSV];
+        // all of them at once by all wavefronts
+        const int kw = min(K, kPatBytes / (4 * kBoxClip)), unit = min(10, (ns + kw - 1) / kw);
+        bool shared = true;
         for (int q = 0; q < ns;) {
-            if (wv == 0) {
-                int n = 0, bmn = 0, bmx = 0, step = 10;
+            int bmn = 0, bmx = 0;
+            if (shared) {
+                for (int r = unit * wv; wv < kw && r < ns; r += unit * kw) {
+                    int n = 0;
+                    wave_lds_order();
+                    if (!box_pass<AP>(s, sc, cam, L, r, min(unit, ns - r), b0, b1, L.cq + kBoxClip * wv, true, n, bmn, bmx)) break;
+                }
+            } else if (wv == 0) {
+                int n = 0, step = 10;
                 while (q < ns) {
                     int m = n;
                     wave_lds_order();
-                    if (box_pass<AP>(s, sc, cam, L, q, min(step, ns - q), L.cq, false, m, bmn, bmx)) {
+                    if (box_pass<AP>(s, sc, cam, L, q, min(step, ns - q), b0, b1, L.cq, false, m, bmn, bmx)) {
                         n = m;
                         q += min(step, ns - q);
                     } else if (n > 0 || step == 1) {
@@ -1362,7 +1401,12 @@ __device__ __forceinline__ void stream_entries(const DevSim &s, const SceneRec &
                 }
             }
             __syncthreads();
-            q = L.cnt[R_AT];
+            if (shared && L.cnt[R_BOVF] != 0) {
+                shared = false;
+                __syncthreads();       // the list is read by none
+                continue;
+            }
+            q = shared ? ns : L.cnt[R_AT];
             box_band<AP>(L, cam, keys, L.cnt[R_NBT], b0, b1, wv, K);
             __syncthreads();
         }

@@ -100,3 +100,58 @@ def test_odd_strips_and_far_maps(shift, colours):
                             agent_state=(s.agent_state + np.array([shift, shift, 0, 0])).astype(np.float32))
     cam = g.camera_for(72, 56, g.STUDENT_RIG)
     _check([s], cam, [(0, a, k) for a in range(6) for k in range(4)], shift)
+
+
+def _check_split(scenes, cam, picks, label, light=None):
+    """The general raster asked for by name, against the banded kernels on every
+    view and the oracle on the picked ones."""
+    from paper_2606_19641_amd import gp
+    pal = g.mixed_palette()
+    pal[0], pal[1] = (9, 70, 201), (150, 31, 4)
+    pal[6:9] = g.default_palette()[6:9]
+    sim = gp.Sim(scenes, cam, pal)
+    sim.set_light(light)
+    sim.set_launch(raster=1)
+    only, _, _ = sim.render()
+    rgb, d, p = sim.render(depth=True, primid=True)
+    sim.set_launch(raster=0)
+    ref = sim.render(depth=True, primid=True)
+    torch.cuda.synchronize()
+    assert torch.equal(only, rgb), (label, "rgb only")
+    assert torch.equal(rgb, ref[0]) and torch.equal(p, ref[2]), (label, "banded")
+    assert torch.equal(d.view(torch.int32), ref[1].view(torch.int32)), (label, "banded depth")
+    n_cams = len(cam.cam_dirs)
+    base = np.cumsum([0] + [s.n_agents for s in scenes])
+    rgb, d, p = rgb.cpu().numpy(), d.cpu().numpy(), p.cpu().numpy()
+    for si, a, k in picks:
+        ref = oracle.render_scene_view(scenes[si], cam, pal, a, k, light=light)
+        v = (base[si] + a) * n_cams + k
+        assert np.array_equal(rgb[v], ref.rgb), (label, si, a, k)
+        assert np.array_equal(p[v], ref.primid), (label, si, a, k)
+        assert np.array_equal(d[v].view(np.uint32), ref.depth.view(np.uint32)), (label, si, a, k)
+
+
+@pytest.mark.parametrize("n_agents,radius,scenes,size", [
+    (40, 10.0, 8, (64, 48)),       # lists that grow into the ring and the staging
+    (64, 6.0, 1, (48, 48)),        # as many boxes as records, in sixteen wavefronts
+    (65, 12.0, 1, (130, 40)),      # one more
+    (90, 14.0, 1, (17, 61)),
+    (110, 8.0, 1, (300, 210)),     # streamed by eight wavefronts
+    (150, 5.0, 2, (64, 64)),       # streamed by four, more faces at once than the list holds
+])
+@pytest.mark.parametrize("lights", [0, 130])
+@pytest.mark.parametrize("colours", [1, 2])
+def test_crowds_through_the_split_division(n_agents, radius, scenes, size, lights, colours):
+    print(f"general raster crowd: {scenes} x {n_agents} agents at {size}, {lights} lights, {colours} colours", flush=True)
+    sc = [g.crowded_scene(700 + n_agents + k, n_agents=n_agents, n_roads=50, radius=radius) for k in range(scenes)]
+    rng = np.random.default_rng(n_agents)
+    for s in sc:
+        if colours == 1:
+            s.road_color[:] = 1
+        if lights:
+            s.signal_xyzr = np.stack([rng.uniform(-12, 12, lights), rng.uniform(-12, 12, lights),
+                                      rng.uniform(0.5, 4, lights), rng.uniform(0.1, 1.2, lights)], 1).astype(np.float32)
+            s.signal_color = rng.integers(6, 9, lights).astype(np.uint8)
+    cam = g.Camera(width=size[0], height=size[1], focal_px=size[0] / 2.0, cam_dirs=g.FRONT_AND_SIDES)
+    light = (0.6, -0.48, 0.64, 0.25) if lights else None
+    _check_split(sc, cam, [(scenes - 1, a, k) for a in (0, n_agents // 2) for k in (0, 2)], (n_agents, size), light)
