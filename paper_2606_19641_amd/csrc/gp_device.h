@@ -210,7 +210,7 @@ size_t render_lds_bytes(int width, int height, const LaunchCfg &c, int fast);
 hipError_t launch_raycast(const DevSim &s, const RenderOut &o, const RcCfg &c, int view_begin, int n_views, hipStream_t st);
 size_t raycast_lds_bytes(int width, int height, const RcCfg &c);
 // general raster (gp_full.h): any outputs, road colours, light and traffic
-// lights; workgroup b renders view order[b] (ordered) or view_begin + b
+// lights, width >= 16; workgroup b renders view order[b] (ordered) or view_begin + b
 hipError_t launch_render_full(const DevSim &s, const RenderOut &o, const FullCfg &c, int ordered, int view_begin, int grid,
                               hipStream_t st);
 size_t full_lds_bytes(int width, const FullCfg &c);

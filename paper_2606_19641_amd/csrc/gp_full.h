@@ -196,7 +196,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (first) {
             nbt = L.cnt[R_NBT];
             ovf = L.cnt[R_BOVF] != 0 || nsv > L.nrec;
-            if (ovf || (W < 16 && nbt > 0)) {
+            if (ovf) {
                 kr0 = 0;
             } else if (nbt > 0) {
                 kr0 = L.cnt[R_BMIN];
@@ -212,15 +212,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         const lptr<const unsigned long long> none = (lptr<const unsigned long long>)nullptr;
         resolve_rows(s, (lptr<const uint32_t>)pal, rz, color, W, L.hr0, (lptr<const uint32_t>)road, b0, none, o, view_px, r0, k0);
         resolve_rows(s, (lptr<const uint32_t>)pal, rz, color, W, L.hr0, (lptr<const uint32_t>)road, b0, none, o, view_px, k1, b1);
-        if (ovf || W < 16) {
+        if (ovf) {
             // box keys of a few rows at a time
             for (int c0 = k0; c0 < k1; c0 += L.krows) {
                 const int c1 = min(c0 + L.krows, k1);
                 __syncthreads();
                 for (int p = tid; p < (c1 - c0) * W; p += B) L.work[p] = 0ull;
                 __syncthreads();
-                if (ovf) stream_entries<true, false>(s, sc, cam, ego, L, L.work, c0, c1, wv, K);
-                else box_band<true>(L, cam, L.work, nbt, c0, c1, wv, K);
+                stream_entries<true, false>(s, sc, cam, ego, L, L.work, c0, c1, wv, K);
                 __syncthreads();
                 resolve_rows(s, (lptr<const uint32_t>)pal, rz, color, W, L.hr0, (lptr<const uint32_t>)road, b0,
                              (lptr<const unsigned long long>)L.work, o, view_px, c0, c1);
@@ -249,7 +248,7 @@ hipError_t launch_render_full(const DevSim &s, const RenderOut &o, const FullCfg
                               hipStream_t st)
 {
     if (grid <= 0) return hipSuccess;
-    if (c.waves < 1 || c.waves > 16 || c.band_rows < 1 || c.bcap < 64 || c.bcap > 256 || c.recs < 1 || c.recs > 64 || c.bins_cap < 1)
+    if (c.waves < 1 || c.waves > 16 || s.width < 16 || c.band_rows < 1 || c.bcap < 64 || c.bcap > 256 || c.recs < 1 || c.recs > 64 || c.bins_cap < 1)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_render_full, dim3(grid), dim3(64 * c.waves), full_lds_bytes(s.width, c), st, s, o, c, ordered,
                        view_begin);

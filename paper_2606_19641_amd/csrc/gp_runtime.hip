@@ -509,8 +509,9 @@ gp_status render_impl(gp_sim *sim, const gp::RenderOut &o, const gp_launch &l, h
     const gp::RgbCfg rc = rgb_cfg(sim, l, sim->lay.n_views);
     const gp::FullCfg fc = full_cfg(sim);
     // renders that take neither rgb-only rasteriser: the general raster, or the
-    // banded kernels where they are asked for
-    const bool full = !split && (kind != 1) && l.raster != GP_RASTER_BANDED &&
+    // banded kernels where they are asked for, below 16 samples a row or where the
+    // general raster's LDS does not fit
+    const bool full = !split && (kind != 1) && l.raster != GP_RASTER_BANDED && sim->cfg.width >= 16 &&
                       gp::full_lds_bytes(sim->cfg.width, fc) <= sim->max_lds;
     hipError_t e;
     if (chip_ok(sim, o, l, kind)) {
@@ -881,21 +882,16 @@ gp_status gp_sim_create(const gp_config *cfg, const gp_scene_desc *scenes, int32
     l.batch_tris = 256;
     l.block_threads = 256;
     l.blocks_per_cu = 3;
-    // rgb renders take the split rasteriser where its LDS fits, else the
-    // chip-wide passes where the image size allows them
-    l.raster = GP_RASTER_BANDED;
+    // the wave-split work division from 16 samples a row on, whatever the road
+    // colours (render_impl gives a render to the rgb or the general raster, and to
+    // the banded kernels where their LDS does not fit).  512 views of mixed colours,
+    // banded / general raster, us: 1 x 1 14 / 19, 8 x 8 19 / 23, 15 x 15 22 / 24;
+    // 2,048 views 48 x 48 110 / 54, 128 x 128 265 / 103, 210 x 126 400 / 164, 434 x
+    // 252 2,825 / 510
+    l.raster = cfg->width >= 16 ? GP_RASTER_SPLIT : GP_RASTER_BANDED;
     l.view_waves = 2;
     l.road_wgs_per_cu = 8;
-    {
-        gp_launch t = l;
-        t.raster = GP_RASTER_SPLIT;
-        if (split_ok(sim, t)) {
-            l.raster = GP_RASTER_SPLIT;
-            if (cfg->width % 16 == 0 && (int64_t)cfg->width * cfg->height <= 128 * 128) l.blocks_per_cu = 8;
-        } else if (L.chip && cfg->cam_height > 0.0f) {
-            l.raster = GP_RASTER_CHIP;
-        }
-    }
+    if (split_ok(sim, l) && cfg->width % 16 == 0 && (int64_t)cfg->width * cfg->height <= 128 * 128) l.blocks_per_cu = 8;
     sim->launch = l;
     if (check_lds(sim, l) != GP_OK) { delete sim; return GP_EINVAL; }
     e = hipStreamCreateWithFlags(&sim->capture_stream, hipStreamNonBlocking);

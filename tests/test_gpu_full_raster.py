@@ -155,3 +155,54 @@ def test_crowds_through_the_split_division(n_agents, radius, scenes, size, light
     cam = g.Camera(width=size[0], height=size[1], focal_px=size[0] / 2.0, cam_dirs=g.FRONT_AND_SIDES)
     light = (0.6, -0.48, 0.64, 0.25) if lights else None
     _check_split(sc, cam, [(scenes - 1, a, k) for a in (0, n_agents // 2) for k in (0, 2)], (n_agents, size), light)
+
+
+@pytest.mark.parametrize("size,raster", [((16, 16), 1), (g.STUDENT_RESOLUTIONS[0], 1), ((48, 48), 1), ((333, 41), 1),
+                                         ((128, 128), 1), ((15, 15), 0), ((1, 9), 0)])
+@pytest.mark.parametrize("colours", [1, 2])
+def test_default_work_division(size, raster, colours):
+    """Nobody asked for the banded kernels: from 16 samples a row on, sims of any
+    road colours divide a view's work over its wavefronts, at ragged widths too; below,
+    that division runs in no launch setting."""
+    from paper_2606_19641_amd import gp
+    print(f"default launch at {size}, {colours} colours", flush=True)
+    s = g.crowded_scene(31, n_agents=7, n_roads=90, radius=15.0)
+    if colours == 1:
+        s.road_color[:] = 1
+    cam = g.Camera(width=size[0], height=size[1], focal_px=max(size[0] / 2.0, 4.0), cam_dirs=g.FRONT_AND_SIDES)
+    sim = gp.Sim([s], cam, g.mixed_palette())
+    assert sim.get_launch()["raster"] == raster
+    _check([s], cam, [(0, a, k) for a in (0, 4) for k in range(3)], (size, colours))
+    _check_split([s], cam, [], (size, colours, "asked for"))
+
+
+@pytest.mark.parametrize("first", [0, 1, 2])
+def test_batch_of_mixed_and_single_colours(first):
+    """A batch whose first sim has mixed road colours: the others take the split
+    raster, and every sim gets what it gets alone."""
+    from paper_2606_19641_amd import gp
+    print(f"batch of mixed colours, sim {first} first", flush=True)
+    scenes = [g.crowded_scene(41 + k, n_agents=6 + 5 * k, n_roads=60) for k in range(3)]
+    scenes[1].road_color[:] = 1
+    scenes[2].road_color[:] = 1
+    scenes[2].signal_xyzr = np.array([[6.0, 1.0, 3.0, 0.5]], np.float32)
+    scenes[2].signal_color = np.array([6], np.uint8)
+    scenes = scenes[first:] + scenes[:first]
+    cam, pal = g.camera_for(80, 50), g.default_palette()
+    sims, alone = ([gp.Sim([s], cam, pal) for s in scenes] for _ in range(2))
+    nb = gp.batch_required_bytes(sims)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    staging = torch.empty(nb, dtype=torch.uint8, pin_memory=True)
+    rgbs = [x.new_rgb() for x in sims]
+    for step in range(2):
+        acts = [g.actions(5, step, np.full(s.n_agents, i), np.arange(s.n_agents)) for i, s in enumerate(scenes)]
+        gp.batch_step_render(sims, acts, rgbs, ws, staging)
+        torch.cuda.synchronize()
+        for x, a, r, y in zip(alone, acts, rgbs, sims):
+            x.step(torch.from_numpy(a).cuda())
+            ref, _, _ = x.render()
+            x.set_launch(raster=0)
+            banded, _, _ = x.render()
+            x.set_launch(raster=1)
+            torch.cuda.synchronize()
+            assert torch.equal(r, ref) and torch.equal(r, banded) and torch.equal(x.get_state(), y.get_state()), step
