@@ -157,7 +157,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int ubox = box_unit(K);
     const int nbu = nsv <= L.nrec ? (nsv + ubox - 1) / ubox : 0, nlu = (sc.n_signals + 63) / 64;
     const int most = 3 * nsv + sc.n_signals;
-    if (most > L.bcap && nsv <= L.nrec) grow_list(L, most, K, W);
+    if (most > L.bcap && nsv <= L.nrec) grow_list<true>(L, most, K, W);
     WaveSt ws = wave_state(L, wv);
     const int64_t view_px = (int64_t)view * H * W;
     int nbt = 0, kr0 = H, kr1 = H;               // listed entries, the rows that they reach

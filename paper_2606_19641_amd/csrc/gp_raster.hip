@@ -119,7 +119,7 @@ __device__ __forceinline__ void render_view_rgb(const DevSim &s, uint8_t *rgb, R
     const int prio_b = nsb >= 24 ? 2 : (nsb >= 16 ? 1 : 0);
     view_priority(prio_b);
     const int most = 3 * nsv + (AP ? sc.n_signals : 0);
-    if (most > L.bcap && nsv <= L.nrec) grow_list(L, most, K, W);
+    if (most > L.bcap && nsv <= L.nrec) grow_list<false>(L, most, K, W);
     WaveSt ws = wave_state(L, wv);
     // more surviving bins than the list holds: the scene's bins in segments that
     // it does hold

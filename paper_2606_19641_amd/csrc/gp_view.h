@@ -119,17 +119,20 @@ __device__ __forceinline__ WaveSt wave_state(const RgbLds &L, int wv)
 }
 
 // A view that may list more faces (three a box) than its list holds gives it
-// memory of its ring, as much as it needs down to kSmallRing, then of the
-// staging; with four to seven wavefronts of the staging first: their jobs are
-// small, and a small ring means more rounds (a batch of eight rollouts of
-// 8..128 agents 67 us per step, 64 so).  Before the first wave_state.
+// memory of its ring, as much as it needs down to kSmallRing, and of the staging.
+// STAGING: of the staging first, in the general raster, whose bands set up their
+// strips in small jobs anyway (depth and ids of crowds of 50 boxes, ring / staging
+// first, us: four wavefronts 205 / 184, eight 138 / 137 and at 352 x 352 1,230 /
+// 1,200, sixteen 99 / 92).  The rgb raster's rounds are larger: ring first (two to
+// four wavefronts 234 / 234, 96 / 96, a batch of eight rollouts 86.5 / 87, eight 72.5
+// / 73, at 352 x 352 364 / 373).  Before the first wave_state.
+template <bool STAGING>
 __device__ __forceinline__ void grow_list(RgbLds &L, int most, int K, int W)
 {
-    const int half = K * (wave_bytes(kBatch) - wave_bytes(kSmallBatch));
     int lack = (min(most, 256) - L.bcap) * (int)sizeof(FaceRec);
-    if (K >= 4 && K < 8) {
+    if (STAGING) {
         L.batch = kSmallBatch;
-        lack -= half;
+        lack -= K * (wave_bytes(kBatch) - wave_bytes(kSmallBatch));
     }
     if (lack > 0) {
         L.ring = max(kSmallRing, kSharedRing - 64 * ((lack + 255) >> 8));
