@@ -115,7 +115,9 @@ typedef enum {
 /* Rasteriser of rgb-only renders (no depth / primitive id) of sims whose road
  * strips share one colour (the chip-wide one without traffic lights or
  * shading).  Other renders take the general raster, which divides a view's work
- * as the split one does, or the banded one where that is asked for. */
+ * as the split one does, or the banded one where that is asked for, below 16
+ * samples a row or where the general raster's LDS does not fit.  The default is
+ * GP_RASTER_SPLIT from 16 samples a row on, else GP_RASTER_BANDED. */
 typedef enum {
     GP_RASTER_BANDED = 0,     /* one workgroup of block_threads per view; LDS key bands of
                                  band_rows rows; triangle lists of batch_tris             */
@@ -274,7 +276,8 @@ gp_status gp_sim_set_state(gp_sim *sim, const float *d_src, void *stream);
  * gp_batch_step_render: for each sims[k], one kinematic step with the host
  * actions h_actions[k] (float [n_agents_k][2]) followed by an rgb render of
  * every view into d_rgb[k] (device uint8 [n_views_k][H][W][3], 4-byte
- * aligned), all sims in one step launch and at most three render launches.
+ * aligned), in at most three render launches; the wave-split raster steps its
+ * sims in the render itself, the others are stepped by one launch before it.
  * Each sim's result is bit-identical to gp_sim_step + gp_sim_render on that
  * sim alone.  Every sim must have the same image size; a sim may appear once.
  * The library packs the batch into h_staging (host memory, pinned for an

@@ -8,7 +8,8 @@
 // fill rule and winner order, only organised for throughput.
 //
 // One workgroup of K wavefronts (1..16) renders one view of any size from 16
-// samples a row on, with about 16 KB of LDS at 128 x 128 and two wavefronts:
+// samples a row on, with up to 10 KB of LDS per wavefront where the image leaves
+// room for it (about 19 KB at 128 x 128 and two wavefronts):
 //   A  cull    the scene's road culling bins are tested against the view
 //              (frustum, road depth limit and the row-gap test below) and its
 //              boxes against the frustum; the surviving bins are listed in
@@ -39,7 +40,7 @@
 // What bounds it: an image is a write stream, but at 128 x 128 the launch lasts as
 // long as its views' chains of loads and LDS round trips (a wavefront waits for
 // half of its time) and its slowest views; scenes of up to 128 agents are bound by
-// VALU issue (73% busy), images from 434 x 252 on mostly by their stores.  Step +
+// VALU issue (84% busy), images from 434 x 252 on mostly by their stores.  Step +
 // render on one MI355X, before the wave-split raster took a size / now: 2,048 views
 // at 128 x 128 74 / 45 us (2.2 TB/s), 8,192 views at 210 x 126 480 / 177 us (3.7
 // TB/s), at 434 x 252 1,505 / 553 us (4.9 TB/s), 4,096 views at 512 x 512 2,140 / 655

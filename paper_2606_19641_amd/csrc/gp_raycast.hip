@@ -247,8 +247,8 @@ __device__ __forceinline__ void rc_inside(const Cam &c, const RcStrip &t, const 
 
 // One set-up job: the n ring strips from a staged, their (strip, row) items on
 // rows [b0, b1) dealt to the lanes by a prefix over row counts, the items'
-// columns cut into pieces of up to kRcPiece samples, dealt again, and the exact
-// test run per sample.  Without COV the strips' key words are folded into the
+// columns cut into pieces, dealt again: without COV the certain ones of up to 16
+// samples, the others of up to kRcTests, with the exact test run per sample.  Without COV the strips' key words are folded into the
 // band of road keys (from row band0): every strip lies in one plane, so the
 // largest key word of a row's sample names the strip it shows.
 template <bool COV>
@@ -853,8 +853,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int nsb = L.cnt[R_NSB];
     lptr<RcStrip> st = (lptr<RcStrip>)(L.waves + (size_t)wv * kWaveBytes);
 
-    // The list holds every box and light of the scene, or (c.chunk) is filled
-    // and folded in chunks of candidates per band.
+    // The list holds every box and light of the scene, or (chunked) is filled and
+    // folded in chunks of candidates per band.
     const int nbox = sc.n_agents + sc.n_static, ncand = nbox + sc.n_signals;
     const bool chunked = ncand > c.bcap;
     const int ub = K >= 8 ? 16 : 64;

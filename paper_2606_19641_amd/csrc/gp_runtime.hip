@@ -366,7 +366,8 @@ void size_list(gp::RgbCfg &c, int width, int height, int64_t entries, size_t max
 int64_t list_entries(const gp_sim *sim) { return 3LL * sim->boxes_cap + sim->signals_cap; }
 
 // The same in the general raster: a box shows at most three faces, one entry
-// each, and a view sees about a quarter of its scene's boxes.
+// each, and a view sees about a quarter of its scene's boxes (one that sees more
+// takes memory of its staging and ring too).
 int full_box_faces(const gp_sim *sim)
 {
     return (int)std::min<int64_t>(256, (sim->boxes_cap * 3LL / 2 + sim->signals_cap / 2 + 63) / 64 * 64);
@@ -430,7 +431,9 @@ void trim_band(int &rows, int row_bytes, int64_t lds, int waves)
 // 8/4,096 181, 8/8,192 164; 4,096 views 210 x 126 4/4,096 396, 8/8,192 406, 4/8,192
 // 504; 2,048 views 434 x 252 8/8,192 707, 4/4,096 774, 8/16,384 957; 1,024 views 512 x
 // 512 8/8,192 956, 4/8,192 1,152, 8/16,384 1,217; 128 views 128 x 128 16/8,192 39,
-// 4/4,096 56.
+// 4/4,096 56.  Where the line lies: 2,048 views 176 x 176 4 / 8 wavefronts 207 / 221,
+// 200 x 200 263 / 272, 224 x 224 324 / 326, 245 x 245 415 / 385, 272 x 272 473 / 433 (640
+// views, half of the chip: 8 from 176 x 176 on).
 gp::FullCfg full_cfg(const gp_sim *sim)
 {
     const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
@@ -458,7 +461,10 @@ gp::FullCfg full_cfg(const gp_sim *sim)
 // 129; with depth and ids 4/4,096 209, 8/8,192 215, 4/8,192 287; 1,024 views 512 x 512
 // rgb 8/4,096 819, 4/4,096 1,054; 16 scenes, four cameras 210 x 126, depth and ids
 // 8/8,192 470, 4/4,096 549, 8/16,384 725; 2,048 views 434 x 252 with them 8/8,192 1,173,
-// 4/4,096 1,521; 128 views 128 x 128 rgb 8/4,096 45, 4/4,096 56.
+// 4/4,096 1,521; 128 views 128 x 128 rgb 8/4,096 45, 4/4,096 56.  Where the lines
+// lie: 2,048 views with depth and ids 144 x 144 4 / 8 wavefronts 241 / 254, 155 x 155 266
+// / 276, 176 x 176 349 / 306, 200 x 200 412 / 400; rgb 245 x 245 283 / 288, 300 x 300 395 /
+// 392, 400 x 400 638 / 629, 448 x 448 786 / 754, 480 x 480 920 / 887.
 gp::RcCfg rc_cfg(const gp_sim *sim, bool rgb_only)
 {
     const int64_t px = (int64_t)sim->cfg.width * sim->cfg.height;
@@ -1279,7 +1285,7 @@ gp_status gp_sim_set_light(gp_sim *sim, const float *h_light)
     drop_graph(sim);            // a captured graph holds the old kernel arguments
     sim->dev.shade = h_light ? 1 : 0;
     for (int k = 0; k < 4; ++k) sim->dev.light[k] = h_light ? h_light[k] : 0.0f;
-    // lit frames are resolved by the general kernel
+    // the banded and chip-wide rgb kernels serve unlit frames without traffic lights
     sim->dev.road_color_uniform = (sim->road_uniform && !h_light && sim->lay.n_signals == 0) ? 1 : 0;
     return GP_OK;
 }
